@@ -285,8 +285,9 @@ typedef struct {
  * at by itself.  Default (0):
  *   - steps 7 and 8 (FFN up-projection and GELU) as one kernel where ibert_gemm_i8_gelu can do so; the workspace
  *     region f1 is then left untouched;
- *   - steps 2, 3 and 4 as one kernel where ibert_attention_i can do so; the workspace regions scores and probs are then
- *     left untouched (profile records: one, numbered 2);
+ *   - steps 2, 3 and 4 as one kernel where ibert_attention_i can do so (profile records: one, numbered 2); the workspace
+ *     regions scores and probs are then left untouched, except that a single-layer call with a workspace stores them for
+ *     every seq that is not a multiple of 128;
  *   - r1 / r2, which are clamped to 16 bits by definition, stored as int16 [T, hidden] (IBERT_I16) at the start of their
  *     workspace regions and read by ibert_layernorm_i16: the two kernels move half the bytes. */
 enum {
@@ -404,10 +405,11 @@ int ibert_layer_quant_from_scales(const ibert_layer_scales* scales, int32_t seq,
  *     ctx    = ibert_gemm_i8_requant(probs, V_h as [K,N]; ctx_dy, INT8, clamp 127), written into [T, hidden]
  * qkv: device int8 [batch*seq, 3*hidden] (Q | K | V, the heads of each side by side); ctx: device int8
  * [batch*seq, hidden].  softmax->out_dtype must be IBERT_I8.
- * With seq in {128, 256, 384, 512} and hidden/heads = 64 (qkv 16-byte aligned, ctx 4-byte aligned) the three steps
+ * With seq <= 512 and hidden/heads = 64 (qkv 16-byte aligned, ctx 4-byte aligned) the three steps
  * run as one kernel and scores/probs are never stored.  Any other shape takes the
- * three-kernel route through `scratch` (device, 256-byte aligned, ibert_attention_scratch_bytes() bytes;
- * IBERT_ERR_WORKSPACE if it is NULL, small or misaligned).  scratch may always be passed.
+ * three-kernel route through `scratch` (device, 256-byte aligned, ibert_attention_scratch_bytes() bytes), which is asked
+ * for unless seq is one of 128, 256, 384, 512 and hidden/heads = 64 (IBERT_ERR_WORKSPACE if it is NULL, small or
+ * misaligned), whether or not the shape needs it.  scratch may always be passed.
  * ---------------------------------------------------------------------------------------------- */
 size_t ibert_attention_scratch_bytes(int32_t batch, int32_t seq, int32_t heads);
 int ibert_attention_i(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq, int32_t hidden, int32_t heads,

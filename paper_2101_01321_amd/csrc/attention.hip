@@ -3,18 +3,21 @@
 // Sec. 4.1), bit-identical to running them one after the other.  The INT32 scores and the INT8
 // probabilities never leave the CU.
 //
-// Shape: head width 64, sequence length L = 128, 256, 384 or 512 (a whole score row, L/4 values per lane, stays in
-// registers; the integer exponent cannot be rescaled exactly, so the row maximum must be known before the first
-// exponent is taken).  One workgroup of four wavefronts owns 64 queries of one (batch, head); a wavefront owns 16.
-//   * K_h (L x 64) and the 64 Q_h rows go to LDS row-major (64-byte rows, chunk index swizzled by the row);
-//     V_h goes to LDS transposed, one L-byte row per output channel, with the keys of a row ordered so that a
-//     lane's MFMA operand (16 keys) is one 16-byte read -- see `vt_offset`.
-//   * Scores: L/16 MFMAs (16x16x64) per wavefront; lane l then holds, for query l%16, the L/4 keys
+// Shape: head width 64, any sequence length up to 512 (a whole score row, L/4 values per lane, stays in registers; the
+// integer exponent cannot be rescaled exactly, so the row maximum must be known before the first exponent is taken).
+// One workgroup of four wavefronts owns 64 queries of one (batch, head); a wavefront owns 16.  The kernel is instantiated
+// per number of 64-key blocks; rows past the end of the sequence are read from its last row, their keys are masked and
+// their queries not stored.
+//   * Everything goes from global memory straight into LDS (global_load_lds, 1 KB = 16 rows of 64 bytes per request), in
+//     row-major order with the 16-byte chunks of a row swizzled by the row: the wavefront's queries, K_h and V_h.
+//   * K_h rows are MFMA operands as they stand (one 16-byte read per lane).  V_h is needed transposed: ds_read_b64_tr_b8 hands
+//     a lane 8 keys of one channel, from rows that the lanes of a 16-lane group choose freely (see `context` below).
+//   * Scores: one MFMA (16x16x64) per wavefront and 16 keys; lane l then holds, for query l%16, the keys
 //     {16 i + 4 (l/16) + r}.  Row maximum and row sum finish with two cross-lane steps over the four lanes
 //     that share a query.
 //   * The probabilities are packed four to a dword as they are produced; the four dwords i = 4kb..4kb+3 are
 //     exactly the lane's MFMA operand for key block kb under the key order above, so P never moves.
-//   * Context: L/16 MFMAs per wavefront, requantized and stored as 4 bytes per lane.
+//   * Context: requantized and stored as 4 bytes per lane.
 //   * Padded sequences: the keys from key_lens[b] on take the logit INT32_MIN before the row maximum is taken (the
 //     paper does not treat padding; this is the integer form of adding minus infinity to a masked logit).
 #include "common.h"
@@ -27,217 +30,327 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 struct AttentionArgs {
     const int8_t* qkv;     // [batch*seq, 3*hidden]: Q | K | V, heads side by side
     int8_t* ctx;           // [batch*seq, hidden]
-    int32_t heads;
-    int32_t xcd_chunk;     // workgroups per XCD when the grid divides by 8, else 0
-    int64_t ld_qkv, ld_ctx;
+    int32_t heads, seq, qblks;
+    uint32_t qblks_magic, heads_magic;   // floor(2^32 / d) + 1: see udiv
+    int32_t xcd_q, xcd_r;  // workgroups per XCD and the remainder, see the kernel
+    int32_t ld_qkv, ld_ctx;
     int32_t s_m, s_s;      // scores requantization
     int32_t c_m, c_s;      // context requantization
     SoftmaxConst sm;
+    int32_t z_m, z_c, z_s; // FORM 1, 2: floor(d / q_ln2) = (z_c - z_m u) >> z_s for u = q_b - d
     const int32_t* key_lens;   // optional [batch]: sequence b attends to its first key_lens[b] keys only
+    int32_t* scores;       // FORM 0 only, optional: the INT32 scores [batch*heads, seq, seq] and
+    int8_t* probs;         // the INT8 probabilities are also stored
 };
 
 constexpr int ATT_DH = 64, ATT_QB = 64, ATT_THREADS = 256;
 
-// LDS byte offset inside the transposed V tile of (channel c, key n): row c (L bytes), 16-byte chunk
-// (n/64)*4 + (n%16)/4 swizzled by c, byte 4*((n%64)/16) + n%4 inside the chunk.
-template <int L>
-__device__ __forceinline__ int vt_offset(int c, int n)
+// floor(n / d) for 0 <= n < 2^31: the reciprocal multiply gives the quotient or one more.  (A division by a run-time
+// divisor is some thirty dependent scalar instructions at the head of every workgroup.)
+__device__ __forceinline__ int32_t udiv(int32_t n, int32_t d, uint32_t magic)
 {
-    const int kb = n >> 6, ip = (n >> 4) & 3, q = (n >> 2) & 3, r = n & 3;
-    return c * L + ((((kb << 2) | q) ^ (c & 7)) << 4) + (ip << 2) + r;
+    if (magic == 0) return n;                              // d == 1
+    const int32_t q = (int32_t)__umulhi((uint32_t)n, magic);
+    return n - q * d < 0 ? q - 1 : q;
 }
 
-__device__ __forceinline__ int swz64(int row) { return (row >> 1) & 3; }      // chunk swizzle of 64-byte rows
+// LDS chunk swizzles of 64-byte rows: four rows share a 256-byte bank cycle.  K and Q: a lane group reads one chunk of 16
+// consecutive rows.  V: a transposing read takes one chunk of rows 16 apart and of 16 consecutive ones.
+__device__ __forceinline__ int swz_k(int row) { return (row >> 1) & 3; }
+__device__ __forceinline__ int swz_v(int row) { return (row >> 2) & 3; }
 
 // DY(x; m, s) for |x| < 2^b when b <= s <= 62 (b <= 23): x m + 2^(s-1) fits 63 bits and the result fits 32 (it is
 // below 2^(b+31-s)), so the floor-division by 2^s is bits [s, s+32) of the 64-bit sum: the high dword shifted by
-// s - 32, or for s < 32 a funnel shift of the two dwords.  rnd = 2^(s-1).
-// FORM 1: the shift is known to be at least 32 (a scale ratio below 1/2), FORM 2: known to be below 32 -- only that
-// form is computed, two instructions a value; FORM 0: both and a select.
-template <int FORM>
-__device__ __forceinline__ int32_t dyadic_hi(int32_t x, int32_t m, int64_t rnd, int32_t sh)
+// s - 32 (HIGH: s >= 32), or for s < 32 a funnel shift of the two dwords.  add = 2^(s-1), or that plus a multiple of 2^s.
+template <bool HIGH>
+__device__ __forceinline__ int32_t dyadic_hi(int32_t x, int32_t m, int64_t add, int32_t sh)
 {
-    const int64_t p = (int64_t)x * m + rnd;
+    const int64_t p = (int64_t)x * m + add;
     const int32_t hi = (int32_t)(p >> 32);
-    const int32_t a = hi >> ((sh - 32) & 31);
-    if (FORM == 1) return a;
-    const int32_t b = (int32_t)__builtin_amdgcn_alignbit((uint32_t)hi, (uint32_t)p, (uint32_t)(sh & 31));
-    if (FORM == 2) return b;
-    return sh >= 32 ? a : b;
+    return HIGH ? hi >> ((sh - 32) & 31) : (int32_t)__builtin_amdgcn_alignbit((uint32_t)hi, (uint32_t)p, (uint32_t)(sh & 31));
 }
 
-// FAST: the 24-bit Softmax forms apply.  RQ: the scores shift is in [21, 62] and the context shift in [23, 62]
-// (accumulators: 64 products of INT8 pairs, below 2^21; up to 512 products of a probability and an INT8 value,
-// below 2^23), so dyadic_hi applies; |scores| then stays below 2^31 and needs no clamp.  RQ = 2 .. 5 say in addition on
-// which side of 32 each shift lies: RQ - 2 = (scores shift >= 32) + 2 (context shift >= 32).
-template <int NKB, bool FAST, int RQ>                     // NKB: key blocks of 64 (L = 64 NKB)
+// A copy of a uniform value that the compiler does not relate to the original.  The tests of the block loops below then stay
+// scalar compares where they stand; related, they are evaluated once and carried as lane masks, which costs two vector
+// instructions and a register pair for each test.
+__device__ __forceinline__ int32_t opaque(int32_t v)
+{
+    asm volatile("" : "+s"(v));
+    return v;
+}
+
+// NKB: key blocks of 64.  FORM 0: any constants, and the only form that stores scores and probabilities.  FORM 1, 2: the
+// 24-bit Softmax forms apply (softmax_fast_ok), the scores multiplier is positive and its shift in [32, 45] / [21, 31],
+// the context shift in [23, 62].  There, whole blocks of masked keys are skipped (their probabilities are exactly zero:
+// |scores| < 2^30, so the distance to INT32_MIN is far beyond 31 q_ln2).  The loops over key blocks are unrolled (the values
+// live in registers) but each block stands behind a uniform test against the run-time block count, also where there is no
+// mask: without those tests the scheduler interleaves all blocks and doubles the registers (NKB = 8: 303 instead of 150).
+//
+// Bound: vector ALU issue (L = 128, 256 x 16 heads: ALU slots full, 18 instructions a score with everything around it).
+// So what a score costs is what counts.  FORM 1, 2: the requantization is monotone, so the
+// row maximum is taken on the raw accumulators; with mx its requantized value, u = q_b - d = q_b - mx + score comes out
+// of the same 64-bit multiply-add as the score itself (an integer added behind the rounding shift is that integer times 2^s
+// added before it), so neither a subtraction nor q_b - d costs an instruction of its own: 2 (multiply-add, half rate) + shift
+// + cap, then z (2), q_b - r, the polynomial, its shift, half an add and half a maximum.
+template <int NKB, int FORM>
 __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
 {
-    constexpr int ATT_L = 64 * NKB, QBLKS = ATT_L / ATT_QB, NI = ATT_L / 16;
-    constexpr int S_FORM = RQ < 2 ? 0 : (((RQ - 2) & 1) ? 1 : 2), C_FORM = RQ < 2 ? 0 : (((RQ - 2) & 2) ? 1 : 2);
+    constexpr int NI = 4 * NKB;
     extern __shared__ __attribute__((aligned(16))) int8_t att_lds[];
-    int8_t* const ks = att_lds;                                               // K_h, row-major [L][64]
-    int8_t* const qs = att_lds + ATT_L * ATT_DH;                              // the block's queries [64][64]
-    int8_t* const vt = qs + ATT_QB * ATT_DH;                                  // V_h transposed [64][L]
+    int8_t* const qs = att_lds;                                               // queries [64][64]
+    int8_t* const ks = qs + ATT_QB * ATT_DH;                                  // K_h [64 NKB][64]
+    int8_t* const vs = ks + 64 * NKB * ATT_DH;                                // V_h [64 NKB][64]
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // Workgroups are dealt round-robin to the 8 XCDs.  The two halves of a head's queries read the same K and V,
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // Workgroups are dealt round-robin to the 8 XCDs.  The query blocks of a head read the same K and V,
     // and neighbouring heads share 128-byte lines of the packed QKV rows: give each XCD a contiguous run of
-    // (batch, head, half) so that those re-reads hit its own L2.
-    int bid = blockIdx.x;
-    if (a.xcd_chunk > 0) bid = (bid & 7) * a.xcd_chunk + (bid >> 3);
-    const int qblk = bid % QBLKS;                          // which 64 of the queries
-    const int bh = bid / QBLKS;
-    const int b = bh / a.heads, h = bh - b * a.heads;
-    const int hidden = a.heads * ATT_DH;
-    const int8_t* base = a.qkv + (int64_t)b * ATT_L * a.ld_qkv + h * ATT_DH;
+    // (batch, head, query block) -- xcd_q of them, one more for the first xcd_r XCDs -- so that those re-reads hit its own L2.
+    const int xcd = blockIdx.x & 7;
+    const int bid = xcd * a.xcd_q + (xcd < a.xcd_r ? xcd : a.xcd_r) + (int)(blockIdx.x >> 3);
+    const int bh = udiv(bid, a.qblks, a.qblks_magic);
+    const int qblk = bid - bh * a.qblks;                   // which 64 of the queries
+    const int b = udiv(bh, a.heads, a.heads_magic), h = bh - b * a.heads;
+    const int L = a.seq, hidden = a.heads * ATT_DH;
+    const int8_t* base = a.qkv + (int64_t)b * L * a.ld_qkv + h * ATT_DH;
+    int nk = L;                                            // keys that are not masked
+    if (a.key_lens) {
+        nk = a.key_lens[b];
+        nk = nk < 1 ? 1 : (nk > L ? L : nk);
+    }
+    const int nkb = ((FORM == 0 ? L : nk) + 63) >> 6;      // key blocks worked on
 
     // ---- global -> LDS -------------------------------------------------------------------------
+    const int frow = lane & 15, fch = lane >> 4;
+    const int qrow0 = qblk * ATT_QB + wave * 16;           // the wavefront's first query
     {
-        const int row = tid >> 2, ch = tid & 3;            // 64 rows x 4 chunks of 16 bytes per pass
-        const v4i q0 = *reinterpret_cast<const v4i*>(base + (int64_t)(qblk * ATT_QB + row) * a.ld_qkv + ch * 16);
-        v4i kk[NKB];
+        // lane l of a request brings, for row l / 4 of its 16, the chunk that the swizzle puts at byte 16 l
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)att_lds + (uint32_t)wave * 1024u;
+        const int r16 = lane >> 2;
+        const uint32_t ck = (uint32_t)(((lane & 3) ^ swz_k(r16)) << 4), cv = (uint32_t)(((lane & 3) ^ swz_v(r16)) << 4);
+        auto request = [&](const int8_t* src, int row0, uint32_t chunk, uint32_t dst) {
+            int row = row0 + r16;
+            row = row < L ? row : L - 1;
+            const uint32_t voff = (uint32_t)row * (uint32_t)a.ld_qkv + chunk;
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         :: "s"(dst), "v"(voff), "s"(src) : "memory", "m0");
+        };
+        request(base, qrow0, ck, lds0);
+        const int n = opaque(nkb);
 #pragma unroll
         for (int p = 0; p < NKB; ++p)
-            kk[p] = *reinterpret_cast<const v4i*>(base + hidden + (int64_t)(row + 64 * p) * a.ld_qkv + ch * 16);
-        *reinterpret_cast<v4i*>(qs + row * 64 + ((ch ^ swz64(row)) << 4)) = q0;
+            if (p < n) request(base + hidden, 64 * p + 16 * wave, ck, lds0 + (uint32_t)(ATT_QB * ATT_DH + p * 4096));
 #pragma unroll
         for (int p = 0; p < NKB; ++p)
-            *reinterpret_cast<v4i*>(ks + (row + 64 * p) * 64 + ((ch ^ swz64(row + 64 * p)) << 4)) = kk[p];
-        // V: 4 keys x 4 channels per item, 4 L items, L/64 per lane (two at a time); item t: key group t/16, channel quad t%16
-#pragma unroll
-        for (int u0 = 0; u0 < NKB; u0 += 2) {
-            uint32_t vv[2][4];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int t = (u0 + u) * ATT_THREADS + tid;
-                const int g = t >> 4, cq = t & 15;
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    vv[u][r] = *reinterpret_cast<const uint32_t*>(base + 2 * hidden + (int64_t)(4 * g + r) * a.ld_qkv + 4 * cq);
-            }
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int t = (u0 + u) * ATT_THREADS + tid;
-                const int g = t >> 4, cq = t & 15;
-                // 4x4 byte transpose: x01/y01 interleave rows 0,1; x23/y23 rows 2,3; tt[e] = bytes (r = 0..3) of channel e
-                const uint32_t x01 = __builtin_amdgcn_perm(vv[u][1], vv[u][0], 0x05010400u);
-                const uint32_t y01 = __builtin_amdgcn_perm(vv[u][1], vv[u][0], 0x07030602u);
-                const uint32_t x23 = __builtin_amdgcn_perm(vv[u][3], vv[u][2], 0x05010400u);
-                const uint32_t y23 = __builtin_amdgcn_perm(vv[u][3], vv[u][2], 0x07030602u);
-                uint32_t tt[4];
-                tt[0] = __builtin_amdgcn_perm(x23, x01, 0x05040100u);
-                tt[1] = __builtin_amdgcn_perm(x23, x01, 0x07060302u);
-                tt[2] = __builtin_amdgcn_perm(y23, y01, 0x05040100u);
-                tt[3] = __builtin_amdgcn_perm(y23, y01, 0x07060302u);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    *reinterpret_cast<uint32_t*>(vt + vt_offset<ATT_L>(4 * cq + e, 4 * g)) = tt[e];
-            }
-        }
+            if (p < n) request(base + 2 * hidden, 64 * p + 16 * wave, cv, lds0 + (uint32_t)(ATT_QB * ATT_DH + NKB * 4096 + p * 4096));
+        // the queries and K have landed (V may still be on its way: it is not needed before the context)
+        if (n == NKB) __builtin_amdgcn_s_waitcnt(0x0f70 | NKB);
+        else __builtin_amdgcn_s_waitcnt(0x0f70);
+        asm volatile("s_barrier" ::: "memory");
     }
-    __syncthreads();
 
     // ---- scores --------------------------------------------------------------------------------
-    const int frow = lane & 15, fch = lane >> 4;
-    const int qrow = wave * 16 + frow;                     // query row inside the block
-    const v4i qf = *reinterpret_cast<const v4i*>(qs + qrow * 64 + ((fch ^ swz64(qrow)) << 4));
+    const int qrow = qrow0 + frow;                         // the lane's query
+    const v4i qf = *reinterpret_cast<const v4i*>(qs + (16 * wave + frow) * 64 + ((fch ^ swz_k(frow)) << 4));
     const int64_t s_rnd = (int64_t)1 << ((a.s_s - 1) & 63), c_rnd = (int64_t)1 << ((a.c_s - 1) & 63);
-    int32_t sc[NI][4];                                     // sc[i][r]: key 16 i + 4 fch + r
+    v4i sc[NI];                                            // sc[i][r]: key 16 i + 4 fch + r
+    const int n0 = opaque(nkb);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        const int krow = 16 * i + frow;
-        const v4i kf = *reinterpret_cast<const v4i*>(ks + krow * 64 + ((fch ^ swz64(krow)) << 4));
-        const v4i acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf, qf, v4i{0, 0, 0, 0}, 0, 0, 0);
+    for (int kb = 0; kb < NKB; ++kb) {
+        if (kb >= n0) continue;
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            sc[i][r] = RQ ? dyadic_hi<S_FORM>(acc[r], a.s_m, s_rnd, a.s_s) : clamp_i64_to_i32(dyadic64(acc[r], a.s_m, a.s_s), 2147483647);
+        for (int i = 4 * kb; i < 4 * kb + 4; ++i) {
+            const int krow = 16 * i + frow;
+            const v4i kf = *reinterpret_cast<const v4i*>(ks + krow * 64 + ((fch ^ swz_k(krow)) << 4));
+            sc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf, qf, v4i{0, 0, 0, 0}, 0, 0, 0);
+        }
     }
-    if (a.key_lens) {                                      // uniform over the workgroup
-        int32_t nk = a.key_lens[b];
-        nk = nk < 1 ? 1 : nk;
-        if (nk < ATT_L) {
+    if constexpr (FORM == 0) {
 #pragma unroll
-            for (int i = 0; i < NI; ++i)
+        for (int kb = 0; kb < NKB; ++kb) {
+            if (kb >= n0) continue;
+#pragma unroll
+            for (int i = 4 * kb; i < 4 * kb + 4; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int key = 16 * i + 4 * fch + r;
+                    sc[i][r] = clamp_i64_to_i32(dyadic64(sc[i][r], a.s_m, a.s_s), 2147483647);
+                    if (a.scores && qrow < L && key < L) a.scores[((int64_t)bh * L + qrow) * L + key] = sc[i][r];
+                }
+        }
+    }
+    // masked keys, and rows past the end of the sequence (only a block that the end cuts has any; FORM 0: every block may)
+    const int n1 = opaque(nkb);
+#pragma unroll
+    for (int kb = 0; kb < NKB; ++kb)
+        if (kb < n1 && nk < 64 * (kb + 1)) {
+#pragma unroll
+            for (int i = 4 * kb; i < 4 * kb + 4; ++i)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) sc[i][r] = 16 * i + 4 * fch + r < nk ? sc[i][r] : INT32_MIN;
         }
-    }
 
-    // ---- softmax over the L keys of the lane's query (four lanes share a query) ---------------
-    int32_t mx = sc[0][0];
+    // ---- softmax over the keys of the lane's query (four lanes share a query) ------------------
+    int32_t mx = INT32_MIN;
+    const int n2 = opaque(nkb);
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
+    for (int kb = 0; kb < NKB; ++kb) {
+        if (kb >= n2) continue;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) mx = sc[i][r] > mx ? sc[i][r] : mx;
+        for (int i = 4 * kb; i < 4 * kb + 4; ++i) {
+            const int32_t m01 = sc[i][0] > sc[i][1] ? sc[i][0] : sc[i][1], m23 = sc[i][2] > sc[i][3] ? sc[i][2] : sc[i][3];
+            mx = mx > m01 ? mx : m01;
+            mx = mx > m23 ? mx : m23;
+        }
+    }
     {
         const int32_t o1 = __shfl_xor(mx, 16, 64);
         mx = o1 > mx ? o1 : mx;
         const int32_t o2 = __shfl_xor(mx, 32, 64);
         mx = o2 > mx ? o2 : mx;
     }
-    uint32_t ex[NI][4];
     uint32_t sum = 0;
+    if constexpr (FORM == 0) {
 #pragma unroll
-    for (int i = 0; i < NI; ++i)
+        for (int kb = 0; kb < NKB; ++kb) {
+            if (kb >= n2) continue;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const uint32_t d = (uint32_t)mx - (uint32_t)sc[i][r];
-            ex[i][r] = FAST ? iexp_from_diff_fast(d, a.sm) : iexp_from_diff(d, a.sm);
-            sum += ex[i][r];
+            for (int i = 4 * kb; i < 4 * kb + 4; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    // (a masked key may keep a share of a row at the bottom of the INT32 range; a row past the end none)
+                    const uint32_t e = iexp_from_diff((uint32_t)mx - (uint32_t)sc[i][r], a.sm);
+                    sc[i][r] = 16 * i + 4 * fch + r < L ? (int32_t)e : 0;
+                    sum += (uint32_t)sc[i][r];
+                }
         }
+    } else {
+        const int64_t mxq = ((int64_t)mx * a.s_m + s_rnd) >> a.s_s;                  // the row maximum, |.| < 2^30
+        const int64_t row_c = s_rnd + (((int64_t)a.sm.q_b - mxq) << a.s_s);          // |.| < 2^59
+        const int32_t u_lo = (int32_t)a.sm.q_b - (int32_t)a.sm.d_cap;
+        const int nx = opaque(nkb);
+#pragma unroll
+        for (int kb = 0; kb < NKB; ++kb) {
+            if (kb >= nx) continue;
+#pragma unroll
+            for (int i = 4 * kb; i < 4 * kb + 4; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int32_t u = dyadic_hi<FORM == 1>(sc[i][r], a.s_m, row_c, a.s_s);
+                    sc[i][r] = u > u_lo ? u : u_lo;
+                }
+            if (nk < 64 * (kb + 1)) {
+#pragma unroll
+                for (int i = 4 * kb; i < 4 * kb + 4; ++i)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) sc[i][r] = 16 * i + 4 * fch + r < nk ? sc[i][r] : u_lo;
+            }
+#pragma unroll
+            for (int i = 4 * kb; i < 4 * kb + 4; ++i) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int32_t u = sc[i][r];
+                    const uint32_t z = (uint32_t)smad24(u, a.z_m, a.z_c) >> a.z_s;             // floor(d / q_ln2) <= 31
+                    const uint32_t v = umad24(z, a.sm.q_ln2, (uint32_t)u);                    // q_b - r, in (0, q_b]
+                    sc[i][r] = (int32_t)(umad24(v, v, a.sm.q_c) >> z);                        // I-Poly, Alg. 1
+                }
+                sum += (uint32_t)sc[i][0] + (uint32_t)sc[i][1];
+                sum += (uint32_t)sc[i][2] + (uint32_t)sc[i][3];
+            }
+        }
+    }
     sum += (uint32_t)__shfl_xor((int32_t)sum, 16, 64);
     sum += (uint32_t)__shfl_xor((int32_t)sum, 32, 64);
     const uint32_t Fz = 0x80000000u / sum;                 // sum >= q_b^2 + q_c >= 1 (the maximum itself)
 
     v4i pf[NKB];                                           // probabilities as MFMA operands, one per key block
+    const int n3 = opaque(nkb);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-        uint32_t o[4];
+    for (int kb = 0; kb < NKB; ++kb) {
+        if (kb >= n3) continue;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            // FAST: e < 2^24 and Fz <= 2^23 (sum >= q_b^2 + q_c >= 2^8), so the 24-bit multiply is exact
-            o[r] = FAST ? umad24(ex[i][r], Fz, 1u << (30 - a.sm.k)) >> (31 - a.sm.k) : normalise(ex[i][r], Fz, a.sm.k);
-            o[r] = o[r] > 127u ? 127u : o[r];
+        for (int i = 4 * kb; i < 4 * kb + 4; ++i) {
+            uint32_t o[4];
+            if constexpr (FORM == 0) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    o[r] = normalise((uint32_t)sc[i][r], Fz, a.sm.k);
+                    o[r] = o[r] > 127u ? 127u : o[r];
+                    const int key = 16 * i + 4 * fch + r;
+                    if (a.probs && qrow < L && key < L) a.probs[((int64_t)bh * L + qrow) * L + key] = (int8_t)o[r];
+                }
+                pf[kb][i & 3] = (int32_t)(o[0] | (o[1] << 8) | (o[2] << 16) | (o[3] << 24));
+            } else {
+                // e < 2^24 and Fz <= 2^23 (sum >= q_b^2 + q_c >= 2^8), so the 24-bit multiply is exact.  For k = 7 (a byte
+                // boundary: bits 24 to 31) the value is the top byte, 0 .. 128, and four of them are packed by permutes; 128
+                // becomes the cap 127 by subtracting bit 7 from each byte.  A smaller k shifts first (and cannot reach 128).
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[r] = umad24((uint32_t)sc[i][r], Fz, 1u << (30 - a.sm.k));
+                if (a.sm.k != 7) {
+                    asm volatile("");                      // (a branch: as selects this would cost every value two instructions)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) o[r] >>= 7 - a.sm.k;
+                }
+                const uint32_t lo = __builtin_amdgcn_perm(o[1], o[0], 0x0c0c0703u), hi = __builtin_amdgcn_perm(o[3], o[2], 0x0c0c0703u);
+                const uint32_t pk = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+                pf[kb][i & 3] = (int32_t)(pk - ((pk >> 7) & 0x01010101u));
+            }
         }
-        pf[i >> 2][i & 3] = (int32_t)(o[0] | (o[1] << 8) | (o[2] << 16) | (o[3] << 24));
     }
 
     // ---- context -------------------------------------------------------------------------------
-    int8_t* out = a.ctx + (int64_t)(b * ATT_L + qblk * ATT_QB + qrow) * a.ld_ctx + h * ATT_DH + 4 * fch;
+    // Operand of the transposed V for channels 16 cb .. +15: lane (frow, fch) needs channel 16 cb + frow of the keys
+    // 64 kb + 16 i + 4 fch + r, i and r = 0 .. 3, in this order.  ds_read_b64_tr_b8: in each group of 16 lanes the pair of
+    // lanes 2j, 2j + 1 points at the two 8-byte halves of 16 channels of a row j, and lane x receives channel x of the rows
+    // j = 0 .. 7; so the group's rows are the keys i = 0, 1 (i = 2, 3 in the second read), r = 0 .. 3.
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    asm volatile("s_barrier" ::: "memory");                // V has landed for every wavefront
+    typedef int v2i __attribute__((ext_vector_type(2)));
+    typedef __attribute__((address_space(3))) v2i* lds_v2i;
+    const int vrow = 16 * (frow >> 3) + 4 * fch + ((frow >> 1) & 3);
+    int8_t* out = a.ctx + (int64_t)(b * L + qrow) * a.ld_ctx + h * ATT_DH + 4 * fch;
+    v4i acc[4] = {};
+    const int nc = opaque(nkb);
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) {
-        const int c = 16 * cb + frow;
-        v4i acc = {0, 0, 0, 0};
+    for (int kb = 0; kb < NKB; ++kb) {
+        if (kb >= nc) continue;
 #pragma unroll
-        for (int kb = 0; kb < NKB; ++kb) {
-            const v4i vf = *reinterpret_cast<const v4i*>(vt + c * ATT_L + ((((kb << 2) | fch) ^ (c & 7)) << 4));
-            acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(vf, pf[kb], acc, 0, 0, 0);
+        for (int cb = 0; cb < 4; ++cb) {
+            int8_t* const p = vs + vrow * 64 + ((cb ^ swz_v(vrow)) << 4) + 8 * (frow & 1) + kb * 4096;
+            const v2i lo = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i)p);
+            const v2i hi = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_v2i)(p + 2048));
+            acc[cb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(v4i{lo.x, lo.y, hi.x, hi.y}, pf[kb], acc[cb], 0, 0, 0);
         }
-        int32_t o[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            o[r] = RQ ? med3_i32(dyadic_hi<C_FORM>(acc[r], a.c_m, c_rnd, a.c_s), -127, 127) : clamp_i64_to_i32(dyadic64(acc[r], a.c_m, a.c_s), 127);
-        *reinterpret_cast<uint32_t*>(out + 16 * cb) = pack4_i8(o[0], o[1], o[2], o[3]);
     }
+    auto store = [&](auto one) {
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            const uint32_t pk = pack4_perm(one(acc[cb][0]), one(acc[cb][1]), one(acc[cb][2]), one(acc[cb][3]));
+            if (qrow < L) *reinterpret_cast<uint32_t*>(out + 16 * cb) = pk;
+        }
+    };
+    if (FORM == 0) store([&](int32_t v) { return clamp_i64_to_i32(dyadic64(v, a.c_m, a.c_s), 127); });
+    else if (a.c_s >= 32) store([&](int32_t v) { return med3_const<-127, 127>(dyadic_hi<true>(v, a.c_m, c_rnd, a.c_s)); });
+    else store([&](int32_t v) { return med3_const<-127, 127>(dyadic_hi<false>(v, a.c_m, c_rnd, a.c_s)); });
 }
 
 // Is the one-kernel form available for this shape and these pointers?
 bool attention_fused_ok(const int8_t* qkv, const int8_t* ctx, int32_t seq, int32_t hidden, int32_t heads)
 {
-    return (seq == 128 || seq == 256 || seq == 384 || seq == 512) && heads >= 1 && hidden == heads * ATT_DH &&
-           aligned(qkv, 16) && aligned(ctx, 4);
+    return seq >= 1 && seq <= 512 && heads >= 1 && hidden == heads * ATT_DH && hidden < (1 << 20) && aligned(qkv, 16) && aligned(ctx, 4);
 }
 
+// The lengths for which the one-kernel form was always used: callers may pass no scratch for them, and the workspace
+// regions scores and probs are documented as untouched.
+bool attention_whole_blocks(int32_t seq) { return seq % 128 == 0 && seq <= 512; }
+
 template <int NKB>
-static int launch_attention_l(const AttentionArgs& a, int64_t blocks, bool fast, int rq, hipStream_t stream)
+static int launch_attention_l(const AttentionArgs& a, int64_t blocks, int form, hipStream_t stream)
 {
-    constexpr int L = 64 * NKB;
-    constexpr size_t lds_bytes = (size_t)L * ATT_DH + ATT_QB * ATT_DH + (size_t)ATT_DH * L;
+    constexpr size_t lds_bytes = (size_t)(ATT_QB + 2 * 64 * NKB) * ATT_DH;
     const dim3 grid((unsigned)blocks), block(ATT_THREADS);
-#define IBERT_ATT_LAUNCH(F_, R_)                                                                                  \
+#define IBERT_ATT_LAUNCH(F_)                                                                                      \
     do {                                                                                                          \
-        auto kern = attention_kernel<NKB, F_, R_>;                                                                \
+        auto kern = attention_kernel<NKB, F_>;                                                                    \
         static bool attr_done = false;                                                                            \
         if (!attr_done && lds_bytes > 65536) {                                                                    \
             IBERT_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                              \
@@ -246,16 +359,10 @@ static int launch_attention_l(const AttentionArgs& a, int64_t blocks, bool fast,
         }                                                                                                         \
         hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, a);                                              \
     } while (0)
-    if (fast) {
-        switch (rq) {
-            case 0: IBERT_ATT_LAUNCH(true, 0); break;
-            case 2: IBERT_ATT_LAUNCH(true, 2); break;
-            case 3: IBERT_ATT_LAUNCH(true, 3); break;
-            case 4: IBERT_ATT_LAUNCH(true, 4); break;
-            default: IBERT_ATT_LAUNCH(true, 5); break;
-        }
-    } else {
-        if (rq) IBERT_ATT_LAUNCH(false, 1); else IBERT_ATT_LAUNCH(false, 0);      // (the general Softmax forms dominate there)
+    switch (form) {
+        case 0: IBERT_ATT_LAUNCH(0); break;
+        case 1: IBERT_ATT_LAUNCH(1); break;
+        default: IBERT_ATT_LAUNCH(2); break;
     }
 #undef IBERT_ATT_LAUNCH
     return IBERT_OK;
@@ -263,28 +370,42 @@ static int launch_attention_l(const AttentionArgs& a, int64_t blocks, bool fast,
 
 int launch_attention(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq, int32_t hidden, int32_t heads,
                      ibert_dyadic scores_dy, const ibert_softmax_params& sp, ibert_dyadic ctx_dy, hipStream_t stream,
-                     const int32_t* key_lens)
+                     const int32_t* key_lens, int32_t* scores, int8_t* probs)
 {
     if (!attention_fused_ok(qkv, ctx, seq, hidden, heads)) return IBERT_ERR_NOT_IMPLEMENTED;
-    const int64_t blocks = (int64_t)batch * heads * (seq / ATT_QB);
+    AttentionArgs a;
+    a.qblks = (seq + ATT_QB - 1) / ATT_QB;
+    const int64_t blocks = (int64_t)batch * heads * a.qblks;
     if (blocks == 0) return IBERT_OK;
     if (blocks > 0x7fffffffLL) return IBERT_ERR_SHAPE;
-    AttentionArgs a;
-    a.qkv = qkv; a.ctx = ctx; a.heads = heads;
-    a.xcd_chunk = blocks % 8 == 0 ? (int32_t)(blocks / 8) : 0;
-    a.ld_qkv = 3 * (int64_t)hidden; a.ld_ctx = hidden;
+    a.qkv = qkv; a.ctx = ctx; a.heads = heads; a.seq = seq;
+    auto magic = [](int32_t d) { return d == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)d) + 1u; };
+    a.qblks_magic = magic(a.qblks); a.heads_magic = magic(heads);
+    a.xcd_q = (int32_t)(blocks / 8); a.xcd_r = (int32_t)(blocks % 8);
+    a.ld_qkv = 3 * hidden; a.ld_ctx = hidden;
     a.s_m = scores_dy.m; a.s_s = scores_dy.s; a.c_m = ctx_dy.m; a.c_s = ctx_dy.s;
     a.sm = softmax_const(sp);
+    // z = floor(d / q_ln2) = (d M) >> z_s with M = floor(2^z_s / q_ln2) + 1 (exact for d <= 31 q_ln2 while
+    // 31 q_ln2^2 < 2^z_s); z_s = 26 keeps M inside 23 bits for the smallest q_ln2
+    a.z_s = sp.q_ln2 >= 17 ? 27 : 26;
+    const uint32_t M = (1u << a.z_s) / (uint32_t)(sp.q_ln2 > 0 ? sp.q_ln2 : 1) + 1u;
+    a.z_m = -(int32_t)M;
+    a.z_c = (int32_t)(M * (uint32_t)sp.q_b);
     a.key_lens = key_lens;
-    // register-only requantization: accumulators are below 64*127^2 (scores) and L*127*127 (context) < 2^23
-    const int rq = (a.s_s >= 21 && a.s_s <= 62 && a.c_s >= 23 && a.c_s <= 62) ? 2 + (a.s_s >= 32 ? 1 : 0) + (a.c_s >= 32 ? 2 : 0) : 0;
-    const bool fast = softmax_fast_ok(sp);
+    a.scores = scores; a.probs = probs;
+    // FORM 1, 2 (see the kernel): accumulators are at most 64*128^2 = 2^20 (scores) and 512*127*128 < 2^23 (context)
+    const bool fast = softmax_fast_ok(sp) && a.s_m > 0 && a.s_s >= 21 && a.s_s <= 45 && a.c_s >= 23 && a.c_s <= 62 && !scores && !probs;
+    const int form = !fast ? 0 : (a.s_s >= 32 ? 1 : 2);
     int rc;
-    switch (seq) {
-        case 128: rc = launch_attention_l<2>(a, blocks, fast, rq, stream); break;
-        case 256: rc = launch_attention_l<4>(a, blocks, fast, rq, stream); break;
-        case 384: rc = launch_attention_l<6>(a, blocks, fast, rq, stream); break;
-        default: rc = launch_attention_l<8>(a, blocks, fast, rq, stream); break;
+    switch ((seq + 63) / 64) {
+        case 1: rc = launch_attention_l<1>(a, blocks, form, stream); break;
+        case 2: rc = launch_attention_l<2>(a, blocks, form, stream); break;
+        case 3: rc = launch_attention_l<3>(a, blocks, form, stream); break;
+        case 4: rc = launch_attention_l<4>(a, blocks, form, stream); break;
+        case 5: rc = launch_attention_l<5>(a, blocks, form, stream); break;
+        case 6: rc = launch_attention_l<6>(a, blocks, form, stream); break;
+        case 7: rc = launch_attention_l<7>(a, blocks, form, stream); break;
+        default: rc = launch_attention_l<8>(a, blocks, form, stream); break;
     }
     if (rc) return rc;
     IBERT_LAUNCH_CHECK("attention_kernel");

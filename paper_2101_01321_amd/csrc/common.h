@@ -57,7 +57,13 @@ __device__ __forceinline__ uint32_t pack4_i8(int32_t a, int32_t b, int32_t c, in
            ((uint32_t)(d & 0xff) << 24);
 }
 
-// clamp(v, lo, hi) for lo <= hi in one instruction.
+// clamp(v, lo, hi) for lo <= hi in one instruction (constant bounds: the compiler finds it by itself).
+template <int LO, int HI>
+__device__ __forceinline__ int32_t med3_const(int32_t v)
+{
+    v = v < LO ? LO : v;
+    return v > HI ? HI : v;
+}
 __device__ __forceinline__ int32_t med3_i32(int32_t v, int32_t lo, int32_t hi)
 {
     int32_t r;
@@ -65,23 +71,18 @@ __device__ __forceinline__ int32_t med3_i32(int32_t v, int32_t lo, int32_t hi)
     return r;
 }
 
-// Full-rate 24-bit multiplies (low 32 bits of the product of the operands' low 24 bits), with explicit types.
-__device__ __forceinline__ uint32_t umul24(uint32_t a, uint32_t b) { return (uint32_t)__umul24(a, b); }
-__device__ __forceinline__ int32_t smul24(int32_t a, int32_t b) { return (int32_t)__mul24(a, b); }
-
-// a*b + c with 24-bit operands in one full-rate instruction (the compiler otherwise tends to pick a 64-bit
-// multiply-add for this pattern).
-__device__ __forceinline__ uint32_t umad24(uint32_t a, uint32_t b, uint32_t c)
-{
-    uint32_t r;
-    asm("v_mad_u32_u24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
+// Full-rate 24-bit multiplies (low 32 bits of the product of the operands' low 24 bits) and multiply-adds.  The LLVM
+// intrinsics are declared by name: an add of their result is selected as one v_mad_*24 (from the C expression the compiler
+// tends to pick a 64-bit multiply-add), and, unlike inline assembly, the scheduler can move them -- behind an asm block it
+// also has to put an s_nop in front of the next reader of the result (softmax row: a fifth of the instructions).
+__device__ uint32_t llvm_mul_u24(uint32_t a, uint32_t b) __asm("llvm.amdgcn.mul.u24.i32");
+__device__ int32_t llvm_mul_i24(int32_t a, int32_t b) __asm("llvm.amdgcn.mul.i24.i32");
+__device__ __forceinline__ uint32_t umul24(uint32_t a, uint32_t b) { return llvm_mul_u24(a, b); }
+__device__ __forceinline__ int32_t smul24(int32_t a, int32_t b) { return llvm_mul_i24(a, b); }
+__device__ __forceinline__ uint32_t umad24(uint32_t a, uint32_t b, uint32_t c) { return llvm_mul_u24(a, b) + c; }
 __device__ __forceinline__ int32_t smad24(int32_t a, int32_t b, int32_t c)
 {
-    int32_t r;
-    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
+    return (int32_t)((uint32_t)llvm_mul_i24(a, b) + (uint32_t)c);
 }
 
 // Four values already inside [-128,127] -> one dword, three byte permutes.
@@ -124,9 +125,11 @@ int launch_gemm_gelu(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W,
                      const int32_t* mult, const int32_t* shift, const ibert_gelu_params& gelu, int8_t* C,
                      int32_t* scratch, hipStream_t stream);
 bool attention_fused_ok(const int8_t* qkv, const int8_t* ctx, int32_t seq, int32_t hidden, int32_t heads);
+bool attention_whole_blocks(int32_t seq);
+// scores, probs (optional): where the one-kernel form also stores those two tensors
 int launch_attention(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq, int32_t hidden, int32_t heads,
                      ibert_dyadic scores_dy, const ibert_softmax_params& sp, ibert_dyadic ctx_dy, hipStream_t stream,
-                     const int32_t* key_lens = nullptr);
+                     const int32_t* key_lens = nullptr, int32_t* scores = nullptr, int8_t* probs = nullptr);
 // key_lens (device, optional): row r keeps its first key_lens[r / rows_per_len] columns
 int launch_softmax(const int32_t* x, void* y, int64_t rows, int32_t cols, int64_t ldx, int64_t ldy,
                    const ibert_softmax_params& p, hipStream_t stream, const int32_t* key_lens = nullptr,

@@ -39,7 +39,7 @@ __device__ __forceinline__ int32_t gelu_one_fast(int32_t q, const GeluConst& a, 
     const int32_t sg = q >> 31;
     const int32_t erf = (poly ^ sg) - sg;             // -poly for q < 0
     const int32_t t = smul24(q, erf + a.q_1);
-    return med3_i32((__mulhi(t, a.m) + rnd) >> sh, -127, 127);
+    return med3_const<-127, 127>((__mulhi(t, a.m) + rnd) >> sh);
 }
 
 // Host: do the parameters allow gelu_one_fast?
@@ -79,7 +79,7 @@ __device__ __forceinline__ int32_t hgelu_one_fast(int32_t q, const HGeluConst& a
     const int32_t g = (int32_t)__builtin_amdgcn_alignbit((uint32_t)(p >> 32), (uint32_t)p, (uint32_t)(a.slope_s & 31));
     const int32_t u = med3_i32(g + a.q_3, 0, a.q_6);
     const int32_t t = smul24(q, u);
-    return med3_i32((__mulhi(t, a.m) + rnd) >> sh, -127, 127);
+    return med3_const<-127, 127>((__mulhi(t, a.m) + rnd) >> sh);
 }
 
 inline bool hgelu_fast_ok(const ibert_hgelu_params& p)

@@ -140,15 +140,17 @@ static int run_attention_unfused(const int8_t* qkv, int32_t* scores, int8_t* pro
 #undef RUN_GEMM
 }
 
-// Steps 2-4: one kernel where the shape allows it (and `fused` asks for it), else the three-kernel route.
+// Steps 2-4: one kernel where the shape allows it (and `fused` asks for it), else the three-kernel route.  `keep`: the
+// caller may look at scores and probs afterwards, so that lengths whose workspace holds them have them stored.
 static int run_attention(const int8_t* qkv, int32_t* scores, int8_t* probs, int8_t* ctx, int64_t B, int64_t L, int64_t H,
                          int64_t nh, const ibert_dyadic& scores_dy, const ibert_softmax_params& softmax,
-                         const ibert_dyadic& ctx_dy, const int32_t* key_lens, bool fused, hipStream_t stream)
+                         const ibert_dyadic& ctx_dy, const int32_t* key_lens, bool fused, bool keep, hipStream_t stream)
 {
     if (fused && attention_fused_ok(qkv, ctx, (int32_t)L, (int32_t)H, (int32_t)nh)) {
+        const bool store = keep && !attention_whole_blocks((int32_t)L);
         prof_before(stream);
         const int rc = launch_attention(qkv, ctx, (int32_t)B, (int32_t)L, (int32_t)H, (int32_t)nh, scores_dy, softmax,
-                                        ctx_dy, stream, key_lens);
+                                        ctx_dy, stream, key_lens, store ? scores : nullptr, store ? probs : nullptr);
         if (rc) return rc;
         // both MatMuls; bytes: Q, K, V read once, the context written once
         prof_after(stream, 2, 4.0 * B * nh * L * L * (H / nh), 4.0 * B * L * H);
@@ -160,7 +162,7 @@ static int run_attention(const int8_t* qkv, int32_t* scores, int8_t* probs, int8
 
 static int run_layer(const ibert_layer_weights& w, const ibert_layer_quant& q, const int8_t* x, int8_t* y,
                      int32_t batch, int32_t seq, int32_t hidden, int32_t heads, int32_t ffn, const int32_t* key_lens,
-                     char* ws, const ibert_layer_workspace_layout& lo, hipStream_t stream)
+                     char* ws, const ibert_layer_workspace_layout& lo, bool keep, hipStream_t stream)
 {
     const int64_t B = batch, L = seq, H = hidden, nh = heads, F = ffn, T = B * L, dh = H / nh;
     int8_t* qkv = reinterpret_cast<int8_t*>(ws + lo.qkv);
@@ -213,7 +215,7 @@ static int run_layer(const ibert_layer_weights& w, const ibert_layer_quant& q, c
 
     // 2-4: attention scores, Softmax, context
     rc = run_attention(qkv, scores, probs, ctx, B, L, H, nh, q.scores_dy, q.softmax, q.ctx_dy, key_lens,
-                       fuse_attention, stream);
+                       fuse_attention, keep, stream);
     if (rc) return rc;
 
     // 5: output projection + residual x, INT32 at the LayerNorm input scale
@@ -327,8 +329,10 @@ int ibert_attention_masked_i(const int8_t* qkv, int8_t* ctx, int32_t batch, int3
         scores = static_cast<int32_t*>(scratch);
         probs = static_cast<int8_t*>(scratch) + align_up(n * 4);
     }
+    // (scratch is asked for wherever it ever was needed, whether or not this shape still uses it)
+    if (!scratch && !(attention_fused_ok(qkv, ctx, seq, hidden, heads) && attention_whole_blocks(seq))) return IBERT_ERR_WORKSPACE;
     return run_attention(qkv, scores, probs, ctx, batch, seq, hidden, heads, *scores_dy, *softmax, *ctx_dy, key_lens,
-                         true, (hipStream_t)stream);
+                         true, false, (hipStream_t)stream);
 }
 
 int ibert_profile_begin(int32_t capacity)
@@ -429,7 +433,7 @@ int ibert_encoder_layer_masked_i(const ibert_layer_weights* weights, const ibert
     if (workspace_bytes < lo.total || !ibert::aligned(workspace, 256)) return IBERT_ERR_WORKSPACE;
     rc = ibert::check_layer(*weights, *quant, seq, hidden);
     if (rc) return rc;
-    return ibert::run_layer(*weights, *quant, x, y, batch, seq, hidden, heads, ffn, key_lens, (char*)workspace, lo,
+    return ibert::run_layer(*weights, *quant, x, y, batch, seq, hidden, heads, ffn, key_lens, (char*)workspace, lo, true,
                             (hipStream_t)stream);
 }
 
@@ -458,7 +462,7 @@ int ibert_encoder_layer_static_i(const ibert_layer_weights* weights, const ibert
     if (rc) return rc;
     // every region of the workspace is written by the step that produces it before any step reads it, so nothing of
     // the previous call's contents has to be cleared
-    return ibert::run_layer(*weights, *quant, x, y, batch, seq, hidden, heads, ffn, key_lens, (char*)ws, lo,
+    return ibert::run_layer(*weights, *quant, x, y, batch, seq, hidden, heads, ffn, key_lens, (char*)ws, lo, false,
                             (hipStream_t)stream);
 }
 
@@ -491,7 +495,7 @@ int ibert_encoder_masked_i(const ibert_layer_weights* weights, const ibert_layer
     const int8_t* in = x;
     for (int32_t l = 0; l < n_layers; ++l) {
         int8_t* out = (l == n_layers - 1) ? y : pp[l & 1];
-        rc = ibert::run_layer(weights[l], quant[l], in, out, batch, seq, hidden, heads, ffn, key_lens, ws, lo,
+        rc = ibert::run_layer(weights[l], quant[l], in, out, batch, seq, hidden, heads, ffn, key_lens, ws, lo, false,
                               (hipStream_t)stream);
         if (rc) return rc;
         in = out;

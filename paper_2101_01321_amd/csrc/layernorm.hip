@@ -160,7 +160,7 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_rows_kernel(LayerNormArg
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int32_t keep = (FULL || (ALIGNED ? col < C : col + e < C)) ? -1 : 0;
-            v[c][e] = med3_i32(v[c][e], -32767, 32767) & keep;
+            v[c][e] = med3_const<-32767, 32767>(v[c][e]) & keep;
             sum += v[c][e];                            // |sum| <= 1024 * 32767 < 2^25
             sq += (uint32_t)smul24(v[c][e], v[c][e]);  // |v| < 2^15: a 24-bit multiply; the total is below 2^40
         }
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_rows_kernel(LayerNormArg
             const int32_t d = v[c][e] - mu;                                        // |d| < 2^17
             const int32_t n = (f24 ? smul24(d, f) : d * f) >> 14;                  // |d*f| < 2^30; |n| < 2^16
             const int32_t acc = smad24(n, gm[c][e], bt[c][e]);                     // |gamma_q| < 2^14: 24-bit multiply
-            o[e] = med3_i32(acc >> a.shift, -127, 127);
+            o[e] = med3_const<-127, 127>(acc >> a.shift);
         }
         if (WIDE) {
             const uint32_t pk = pack4_perm(o[0], o[1], o[2], o[3]);
