@@ -1,7 +1,7 @@
 // INT8 x INT8 -> INT32 MatMul with bias, dyadic requantization, optional residual and clamp (Sec. 1 third contribution,
 // App. C.1): argument checks, the choice of a tile configuration, the generic kernel for unaligned operands, and the
 // C entry points.  The MFMA kernel is in gemm_kernel.h; its tile configurations are compiled in gemm_inst_*.hip.
-#include "gemm_kernel.h"
+#include "gemm_stream.h"
 
 namespace ibert {
 
@@ -13,6 +13,10 @@ namespace ibert {
 #include "gemm_instances_e.inc"
 #include "gemm_instances_f.inc"
 #undef IBERT_GEMM_INSTANCE
+extern template int launch_stream<256, 256, 8, false>(GemmArgs&, bool, hipStream_t);
+extern template int launch_stream<256, 256, 8, true>(GemmArgs&, bool, hipStream_t);
+extern template int launch_stream<256, 192, 8, false>(GemmArgs&, bool, hipStream_t);
+extern template int launch_stream<256, 192, 8, true>(GemmArgs&, bool, hipStream_t);
 
 // ---------------------------------------------------------------------------------------------
 // Generic kernel: one output element per lane (lanes run along n), any layout and alignment.
@@ -102,6 +106,8 @@ static const GemmConfig kConfigs[] = {      // index = configuration number of i
     {128, 96, 128, 3, true},        // with eight wavefronts (four rows of two)
     {128, 96, 128, 3, true},        // the same with four more wavefronts that only request tiles
     {128, 128, 128, 3, true},       // eight wavefronts and four that only request tiles
+    {256, 256, 128, 2, true},       // persistent (gemm_stream.h)
+    {256, 192, 128, 2, true},       // persistent
 };
 constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
 static int g_config_override = -1;
@@ -262,6 +268,8 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
                 case 10: if (dma_ok(d, 256, 128)) return launch_mfma<256, 128, 128, 2, false, true, true>(g, i8, stream); break;
                 case 13: if (dma_ok(d, 256, 192)) return launch_mfma<256, 192, 128, 2, false, true, true, 8>(g, i8, stream); break;
                 case 14: if (dma_ok(d, 256, 128)) return launch_mfma<256, 128, 128, 2, false, true, true, 8>(g, i8, stream); break;
+                case 23: return launch_stream<256, 256, 8, true>(g, i8, stream);
+                case 24: return launch_stream<256, 192, 8, true>(g, i8, stream);
                 default: break;
             }
             return IBERT_ERR_NOT_IMPLEMENTED;
@@ -290,6 +298,8 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
             case 20: if (dma_ok(d, 128, 96)) return launch_mfma<128, 96, 128, 3, false, true, false, 8>(g, i8, stream); break;
             case 21: if (dma_ok(d, 128, 96)) return launch_mfma<128, 96, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
             case 22: if (dma_ok(d, 128, 128)) return launch_mfma<128, 128, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
+            case 23: if (launch_stream<256, 256, 8, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
+            case 24: if (launch_stream<256, 192, 8, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
             default: break;
         }
         return launch_mfma<128, 128, 64, 2>(g, i8, stream);

@@ -1,0 +1,606 @@
+// INT8 MatMul for many tokens: persistent workgroups that stream K steps through LDS without stopping at tile boundaries.
+// Arithmetic and epilogue are those of gemm_kernel.h (W as [N,K], bias, dyadic requantization, optional residual or
+// GELU, clamp); what differs is how the work is laid out in time.
+//
+//   * One workgroup of eight wavefronts (2 x 4) per CU owns a BM x BN tile at a time and walks over several tiles.
+//   * A K step is 128 bytes (whole cache lines: requests of 64-byte row pieces run at half the rate, 17 against 28-32 TB/s
+//     measured chip-wide).  LDS holds two steps.  A step is four phases, one per quadrant of the wavefront's tile, over its whole K:
+//         1: A top x W first   (reads W second)      3: A bottom x W first   (reads A top of the next step)
+//         2: A top x W second  (reads A bottom)      4: A bottom x W second  (reads W first of the next step)
+//     so that no operand needs a second set of registers (96 in all), and the LDS regions fall free one after the other: A top
+//     and W first of a step have been read by everybody at the barrier that ends the step before, W second and A bottom at the barrier
+//     after phase 2.  Their refills -- for the step after next -- are requested in the half step after that, and are not
+//     needed for two half steps more: the requests are spread evenly over all wavefronts and all of the time (32 B/clk of the
+//     50 the path does), each has some 2000 cycles to arrive, and there are two barriers per step.
+//     (With a step as one unit all its requests fall into the half after the barrier and take longer than the MFMAs.)
+//   * The stream of steps runs on into the next tile: while the epilogue of a tile runs, the first two steps of the next
+//     one arrive.  The GELU table is built once per workgroup.
+//   * What bounds it: a 256x256 step takes about 2900 cycles for 2048 of MFMA (the rest is address work, barriers and the clock
+//     that the matrix cores' power draw brings down: 2.7-2.85 POP/s in the loop, 3.7-3.85 for MFMA alone on random data), an
+//     epilogue 6000 (INT8), 9000 (GELU) or 13000 (INT16 + residual).  Measured against one workgroup per tile, us, W cold:
+//     [32768,4096] x K 1024 with GELU 212 -> 142, [15311,3072] x K 768 with GELU 115 -> 45 (any M: tiles may be ragged),
+//     [32768,1024] x K 1024 + residual 62 -> 44, [32768,768] x K 768 at 512 tokens 38.5 -> 34; K 3072, N 768 loses 3 %.
+//   * Everything must fit the registers: with one spill the loop takes 1.6 times as long, even where no scratch is touched.
+//   * Rows past M (any M is allowed) are read from the last row, computed like it and stored onto it: the same bytes again.
+#pragma once
+#include "gemm_kernel.h"
+
+namespace ibert {
+
+struct StreamArgs {
+    const int8_t* A;
+    const int8_t* W;
+    const int32_t* bias;
+    const int32_t* mult;
+    const int32_t* shift;
+    const int8_t* R;
+    void* C;
+    int32_t M, nk;             // nk: K steps (K / 128)
+    int32_t lda, ldw, ldc, ldr;
+    int32_t tiles_m, bn;       // tile rows; tile columns of an XCD's share
+    uint32_t bn_magic;         // see udiv_fix
+    int32_t xs, gs;            // log2 of the shares side by side (columns) and above each other (rows): xs + gs = 3
+    int32_t per_xcd;           // workgroups per XCD
+    int32_t per_channel, dy_m, dy_s;
+    int32_t out_clamp;
+    int32_t res_m, res_s, res_fast;
+    int64_t res_rnd;
+    int32_t k_fast;            // K * 127^2 < 2^30
+    int32_t gelu_fast, gelu_lut_lo, gelu_lut_n;
+    GeluConst gelu;
+    uint32_t* path_word;
+};
+
+// floor(n / d) for 0 <= n < 2^31 with magic = floor(2^32 / d) + 1 (0 for d == 1): the estimate is the quotient or one more.
+__device__ __forceinline__ int32_t udiv_fix(int32_t n, int32_t d, uint32_t magic)
+{
+    if (magic == 0) return n;
+    const int32_t q = (int32_t)__umulhi((uint32_t)n, magic);
+    return n - q * d < 0 ? q - 1 : q;
+}
+
+template <int BM, int BN, int NW, bool OUT_I8, bool GELU>
+struct StreamLayout {
+    static constexpr int STAGE = (BM + BN) * 128;
+    static constexpr int PAR = 2 * STAGE;                          // two buffers of 3 x BN constants
+    static constexpr int LUT = PAR + 2 * 3 * BN * 4;
+    static constexpr int ROOM = 163840 - LUT;                      // for the GELU table
+};
+
+// OUT_I8: INT8 output (no residual), with GELU if GELU; else INT16 output with or without residual.
+template <int BM, int BN, int NW, bool OUT_I8, bool GELU>
+__global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
+{
+    using SL = StreamLayout<BM, BN, NW, OUT_I8, GELU>;
+    static_assert(!GELU || OUT_I8, "the GELU epilogue writes INT8");
+    constexpr int NT = 64 * NW, WC = NW / 2;                       // wavefronts in two rows of WC
+    constexpr int WM = BM / 2, WN = BN / WC, FM = WM / 16, FN = WN / 16;
+    constexpr int FMH = FM / 2, FN0 = (FN + 1) / 2, FN1 = FN / 2;  // MFMA blocks: A top and A bottom, W first and W second
+    // 1 KB requests (8 rows x 128 bytes) per wavefront and region: A top, A bottom, W first, W second
+    constexpr int QA = FMH * 2 * 2 / NW, QW0 = FN0 * 2 * WC / NW, QW1 = FN1 * 2 * WC / NW;
+    constexpr int N0 = QA + QW0, N1 = QW1 + QA;                    // requested together: group 0 (A top, W first), group 1
+    static_assert(FM % 2 == 0 && FN >= 2 && FN <= 4 && FMH * 4 % NW == 0 && FN0 * 2 * WC % NW == 0 && FN1 * 2 * WC % NW == 0, "tile shape");
+    extern __shared__ __attribute__((aligned(16))) int8_t lds[];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
+    const int frow = lane & 15, fch = lane >> 4;
+
+    // ---- the workgroup's tiles ------------------------------------------------------------------
+    // Workgroups are dealt round-robin to the 8 XCDs.  XCD x works on the tile columns of share x % 2^xs and, of those tiles in
+    // row-major order, on the (x >> xs)-th of 2^gs runs; its workgroups take the tiles of the run in turn.
+    const int x = blockIdx.x & 7;
+    const int nb = (x & ((1 << g.xs) - 1)) * g.bn, group = g.tiles_m * g.bn, xm = x >> g.xs;
+    const int t0 = (int)(((int64_t)xm * group) >> g.gs), count = (int)(((int64_t)(xm + 1) * group) >> g.gs) - t0;
+    int lt = blockIdx.x >> 3;                                      // index inside the run
+    if (lt >= count) return;
+    auto tile_at = [&](int l, int& m0, int& n0) {
+        const int t = t0 + l, tm = udiv_fix(t, g.bn, g.bn_magic);
+        m0 = tm * BM;
+        n0 = (nb + t - tm * g.bn) * BN;
+    };
+
+    // ---- requests -------------------------------------------------------------------------------
+    // lane l of a request brings, for row l / 8 of its 8, the chunk that the swizzle (row / 2 mod 8) puts at byte 16 l.  Request k
+    // of a wavefront in a region whose wavefront tiles have nb blocks of 8 rows there: block (wave + NW k) % nb of tile
+    // (wave + NW k) / nb -- its parity is the wavefront's, so the lane's chunk is the same in all of them.
+    const int r8 = lane >> 3;
+    const uint32_t chunk = (uint32_t)(((lane & 7) ^ (((wave & 1) << 2) | (r8 >> 1))) << 4);
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)lds;
+    auto block_row = [&](int k, int nb, int rows, int first) { const int q = wave + NW * k; return q / nb * rows + first + q % nb * 8; };
+    const int8_t *ra, *rw;                                         // request stream: operand rows of its tile, at its step
+    const uint32_t va = (uint32_t)r8 * (uint32_t)g.lda, vw = (uint32_t)r8 * (uint32_t)g.ldw + chunk;
+    int rlast = 0;                                                 // last row of A, counted from the tile's first
+    int rlt = lt, rk = 0;
+    uint32_t rstage = lds0;
+    bool rlive = true;
+    auto request_tile = [&](int l) {
+        int m0, n0;
+        tile_at(l, m0, n0);
+        ra = g.A + (int64_t)m0 * g.lda;
+        rw = g.W + (int64_t)n0 * g.ldw;
+        rlast = g.M - 1 - m0;
+    };
+    // request q of group h (0 or 1): the A rows first
+    auto request_one = [&](int h, int q) {
+        const bool is_a = q < QA;
+        const int row = is_a ? block_row(q, FMH * 2, WM, h * (WM / 2))
+                             : (h == 0 ? block_row(q - QA, FN0 * 2, WN, 0) : block_row(q - QA, FN1 * 2, WN, FN0 * 16));
+        const uint32_t la = rstage + (uint32_t)((is_a ? 0 : BM * 128) + row * 128);
+        const int first = is_a ? (row < rlast ? row : rlast) : row;
+        const int8_t* sb = is_a ? ra + (int64_t)first * g.lda : rw + (int64_t)first * g.ldw;
+        const uint32_t most = (uint32_t)(rlast - first) * (uint32_t)g.lda;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :: "s"(la), "v"(is_a ? (va < most ? va : most) + chunk : vw), "s"(sb) : "memory", "m0");
+    };
+    auto request_advance = [&]() {
+        if (!rlive) return;
+        ra += 128;
+        rw += 128;
+        rstage = 2 * lds0 + (uint32_t)SL::STAGE - rstage;
+        if (++rk == g.nk) {
+            rk = 0;
+            rlt += g.per_xcd;
+            rlive = rlt < count;
+            if (rlive) request_tile(rlt);
+        }
+    };
+    // Constants of a tile's columns (bias, mult, shift: 3 x BN dwords) by DMA, 64 dwords per request, dealt round the
+    // wavefronts; missing arrays are filled in by hand.
+    int par_n0 = -1, par_buf = 1;
+    auto request_constants = [&](int n0) {
+        if (n0 == par_n0) return;
+        par_n0 = n0;
+        par_buf ^= 1;
+        constexpr int CPA = BN / 64;
+        static_assert(BN % 64 == 0, "whole requests of constants");
+        const uint32_t base = lds0 + (uint32_t)(SL::PAR + par_buf * 3 * BN * 4);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const int32_t* src = a == 0 ? g.bias : (a == 1 ? g.mult : g.shift);
+            if (a == 0 ? g.bias != nullptr : g.per_channel != 0) {
+#pragma unroll
+                for (int c = 0; c < CPA; ++c)
+                    if ((a * CPA + c) % NW == wave) {
+                        const int32_t* sb = src + n0 + c * 64;
+                        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+                                     :: "s"(base + (uint32_t)((a * BN + c * 64) * 4)), "v"((uint32_t)lane * 4u), "s"(sb) : "memory", "m0");
+                    }
+            } else {
+                int32_t* p = reinterpret_cast<int32_t*>(lds + SL::PAR + par_buf * 3 * BN * 4) + a * BN;
+                const int32_t fill = a == 0 ? 0 : (a == 1 ? g.dy_m : g.dy_s);
+                for (int c = tid; c < BN; c += NT) p[c] = fill;
+            }
+        }
+    };
+    constexpr auto vm = [](int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); };
+
+    v4i acc[FN][FM];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < FN; ++i)
+#pragma unroll
+            for (int j = 0; j < FM; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+    };
+    // operand reads: block rows are multiples of 16, so the swizzle depends on frow only; slice sl of the step
+    // (the second slice is four chunks on: the address with bit 6 flipped)
+    const int rd0 = frow * 128 + ((fch ^ ((frow >> 1) & 7)) << 4);
+    auto operand = [&](int sl, int off) { return *reinterpret_cast<const v4i*>(lds + off + (sl ? rd0 ^ 64 : rd0)); };
+    v4i at[FMH][2], ab[FMH][2], w0[FN0][2], w1[FN1][2];
+    int stage = 0;                                                 // LDS offset of the step being computed
+    auto read_a = [&](v4i (&d)[FMH][2], int st, int h, int q) {    // q: block q / 2, slice q % 2
+        d[q >> 1][q & 1] = operand(q & 1, st + (wm0 + (h * FMH + (q >> 1)) * 16) * 128);
+    };
+    auto read_w0 = [&](int st, int q) { w0[q >> 1][q & 1] = operand(q & 1, st + BM * 128 + (wn0 + (q >> 1) * 16) * 128); };
+    auto read_w1 = [&](int st, int q) { w1[q >> 1][q & 1] = operand(q & 1, st + BM * 128 + (wn0 + (FN0 + (q >> 1)) * 16) * 128); };
+
+    // ---- prologue -------------------------------------------------------------------------------
+    int m0, n0;
+    tile_at(lt, m0, n0);
+    request_constants(n0);
+    request_tile(lt);
+    int left = ((count - lt + g.per_xcd - 1) / g.per_xcd) * g.nk;  // steps not yet computed
+    auto request_two_steps = [&]() {
+#pragma unroll 1
+        for (int st = 0; st < 2 && rlive; ++st) {
+#pragma unroll
+            for (int q = 0; q < N0; ++q) request_one(0, q);
+#pragma unroll
+            for (int q = 0; q < N1; ++q) request_one(1, q);
+            request_advance();
+        }
+    };
+    request_two_steps();
+    if constexpr (GELU) {
+        int8_t* lut = lds + SL::LUT;
+        const int32_t rnd = 1 << ((g.gelu.s - 33) & 31), sh = (g.gelu.s - 32) & 31;
+        for (int e = tid; e < g.gelu_lut_n; e += NT) {
+            const int32_t q = g.gelu_lut_lo + e;
+            lut[e] = (int8_t)(g.gelu_fast ? gelu_one_fast(q, g.gelu, rnd, sh) : gelu_one(q, g.gelu));
+        }
+    }
+    if (left >= 2) __builtin_amdgcn_s_waitcnt(vm(N0 + N1));
+    else __builtin_amdgcn_s_waitcnt(vm(0));
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+    // The MFMAs of one quadrant: W blocks i0 .. i0 + NI - 1 (operands xw) by A blocks j0 .. j0 + FMH - 1 (operands xa), slice by
+    // slice; `between(idx)` issues what goes in front of MFMA idx (`sched_barrier` pins that order).
+    auto quadrant = [&](auto& xw, auto ni_tag, int i0, v4i (&xa)[FMH][2], int j0, auto&& between) {
+        constexpr int NI = decltype(ni_tag)::value;
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+            for (int i = 0; i < NI; ++i)
+#pragma unroll
+                for (int j = 0; j < FMH; ++j) {
+                    between((sl * NI + i) * FMH + j);
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[i0 + i][j0 + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xw[i][sl], xa[j][sl], acc[i0 + i][j0 + j], 0, 0, 0);
+                }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    using NI0 = std::integral_constant<int, FN0>;
+    using NI1 = std::integral_constant<int, FN1>;
+    constexpr int M0 = 2 * FN0 * FMH, M1 = 2 * FN1 * FMH;          // MFMAs of the two kinds of quadrant
+    static_assert(2 * FN1 <= M0 && 2 * FMH <= M1 && 2 * FMH <= M0 && 2 * FN0 <= M1, "one operand read per MFMA at most");
+    // One K step.  REQ 1: each half requests its group for the step after next.  REQ 2: nothing in the first half (a wavefront may
+    // still be in the epilogue of the last tile, with the first operands of this step to read), both groups in the second.
+    // wait: whether the next step has to be waited for.
+    auto step = [&](auto req_tag, bool wait) {
+        constexpr int REQ = decltype(req_tag)::value;
+        const int nst = SL::STAGE - stage;
+        // request r of n over the MFMAs [0, M0 + M1) of a half step
+        auto ask = [&](int h, int n, int idx) {
+#pragma unroll
+            for (int r = 0; r < N0 + N1; ++r)
+                if (r < n && idx == (2 * r + 1) * (M0 + M1) / (2 * n) && rlive) request_one(REQ == 2 ? (r < N0 ? 0 : 1) : h, REQ == 2 && r >= N0 ? r - N0 : r);
+        };
+        quadrant(w0, NI0{}, 0, at, 0, [&](int idx) {
+            if (idx < 2 * FN1) read_w1(stage, idx);
+            if (REQ == 1) ask(0, N0, idx);
+        });
+        quadrant(w1, NI1{}, FN0, at, 0, [&](int idx) {
+            if (idx < 2 * FMH) read_a(ab, stage, 1, idx);
+            if (REQ == 1) ask(0, N0, M0 + idx);
+        });
+        if (wait) {
+            // group 0 of the next step has landed when only younger requests are outstanding: group 1 of that step and (made in
+            // this half) group 0 of the one after
+            if (REQ == 1 && left >= 3) __builtin_amdgcn_s_waitcnt(vm(N1 + N0));
+            else if (left >= 2) __builtin_amdgcn_s_waitcnt(vm(N1));
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        quadrant(w0, NI0{}, 0, ab, FMH, [&](int idx) {
+            if (idx < 2 * FMH) read_a(at, nst, 0, idx);
+            ask(1, REQ == 2 ? N0 + N1 : N1, idx);
+        });
+        quadrant(w1, NI1{}, FN0, ab, FMH, [&](int idx) {
+            if (idx < 2 * FN0) read_w0(nst, idx);
+            ask(1, REQ == 2 ? N0 + N1 : N1, M0 + idx);
+        });
+        request_advance();
+        if (wait) {
+            if (left >= 3) __builtin_amdgcn_s_waitcnt(vm(N0 + N1));    // the same for its group 1
+            else __builtin_amdgcn_s_waitcnt(vm(0));
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        stage = nst;
+        --left;
+    };
+
+    bool first = true;
+    const int8_t* const lut = lds + SL::LUT;
+    const uint32_t lut_lds = lds0 + (uint32_t)SL::LUT;
+    using R1 = std::integral_constant<int, 1>;
+    using R2 = std::integral_constant<int, 2>;
+    for (;;) {
+        if (!first) request_constants(n0);
+        clear();
+#pragma unroll
+        for (int q = 0; q < 2 * FMH; ++q) read_a(at, stage, 0, q);
+#pragma unroll
+        for (int q = 0; q < 2 * FN0; ++q) read_w0(stage, q);
+        // (the first two steps of a tile that follows another were waited for before that one's stores, see below)
+        step(R2{}, first);
+        for (int kt = 1; kt < g.nk; ++kt) step(R1{}, true);
+
+        // ---- epilogue ---------------------------------------------------------------------------
+        // acc[i][j][e] = C[m0 + wm0 + 16 j + frow][n0 + wn0 + 16 i + 4 fch + e]
+        const int32_t* par = reinterpret_cast<const int32_t*>(lds + SL::PAR + par_buf * 3 * BN * 4);
+        // (what only the epilogue needs of the arguments is fetched here: kept in scalar registers through the loop it
+        // would spill them)
+        typedef const __attribute__((address_space(4))) StreamArgs* kernel_args;
+#if defined(__HIP_DEVICE_COMPILE__)
+        kernel_args ga = (kernel_args)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(ga));
+#else
+        kernel_args ga = nullptr;
+#endif
+        const int last = ga->M - 1 - m0;
+        auto row_of = [&](int j) {                                 // row of the tile, clamped to the last one
+            const int row = wm0 + 16 * j + frow;
+            return (uint32_t)(row < last ? row : last);
+        };
+        // Residual: 16 bytes of a row per lane, then the same transposition as for the stores (an involution) hands
+        // every lane the four channels it holds accumulators of.
+        typedef unsigned v2u __attribute__((ext_vector_type(2)));
+        auto transpose4 = [](uint32_t& r0, uint32_t& r1, uint32_t& r2, uint32_t& r3) {
+            v2u t = __builtin_amdgcn_permlane32_swap(r0, r2, false, false); r0 = t.x; r2 = t.y;
+            t = __builtin_amdgcn_permlane32_swap(r1, r3, false, false); r1 = t.x; r3 = t.y;
+            t = __builtin_amdgcn_permlane16_swap(r0, r1, false, false); r0 = t.x; r1 = t.y;
+            t = __builtin_amdgcn_permlane16_swap(r2, r3, false, false); r2 = t.x; r3 = t.y;
+        };
+        const bool has_res = !OUT_I8 && ga->R != nullptr;
+        constexpr int JH = OUT_I8 ? FM : FM / 2;                   // rows finished together, see below
+        v4i rt[2][OUT_I8 ? 1 : JH];
+        auto load_residual = [&](auto half_tag) {
+            constexpr int H = decltype(half_tag)::value;
+#pragma unroll
+            for (int j = 0; j < (OUT_I8 ? 1 : JH); ++j) rt[H][j] = v4i{0, 0, 0, 0};
+            if (!OUT_I8 && has_res) {
+                const int8_t* rb = ga->R + (int64_t)m0 * ga->ldr + n0 + wn0;
+#pragma unroll
+                for (int j = 0; j < JH; ++j)
+                    rt[H][j] = *reinterpret_cast<const v4i*>(rb + row_of(H * JH + j) * (uint32_t)ga->ldr + (uint32_t)((fch < FN ? fch : 0) * 16));
+            }
+        };
+        // Fast form: every shift in [33, 62], every |bias| and K * 127^2 below 2^30, the residual shift in [8, 62] (see gemm_kernel.h),
+        // and a GELU table.
+        bool fast, fold;
+        {
+            int badc = 0, bigs = 0;
+#pragma unroll
+            for (int c = 0; c < BN; c += 64) {
+                const int32_t pb = par[c + lane], ps = par[2 * BN + c + lane];
+                const int32_t ab = pb < 0 ? -pb : pb;
+                badc |= (ps < 33 || ps > 62 || ab < 0 || ab >= (1 << 30)) ? 1 : 0;
+                bigs |= ps > 43 ? 1 : 0;
+            }
+            fast = __builtin_amdgcn_ballot_w64(badc != 0) == 0 && ga->res_fast && ga->k_fast && (!GELU || ga->gelu_lut_n > 0);
+            fold = __builtin_amdgcn_ballot_w64(bigs != 0) == 0;
+        }
+        const int32_t lut_hi = ga->gelu_lut_n - 1;
+        const int32_t clamp_lo = -ga->out_clamp, clamp_hi = ga->out_clamp;
+        constexpr uint32_t ES = OUT_I8 ? 1 : 2;
+        char* const cb = reinterpret_cast<char*>(ga->C) + ((int64_t)m0 * ga->ldc + n0 + wn0) * ES;
+        if (ga->path_word && m0 == 0 && n0 == 0 && tid == 0)
+            *ga->path_word = !fast ? IBERT_EPILOGUE_STAGED : (GELU ? IBERT_EPILOGUE_DIRECT_GELU_TABLE : IBERT_EPILOGUE_DIRECT);
+        // INT16: the rows of the wavefront in two halves, which keeps the packed results (two dwords a group) and the residual
+        // within the registers that the operands have left; the second half's residual is asked for in the middle of the first.
+        auto finish_rows = [&](auto jh_tag) {
+            constexpr int jh = decltype(jh_tag)::value;
+            uint32_t pq[OUT_I8 ? 1 : 2][JH][4];                    // packed results by block column i
+#pragma unroll
+            for (int h = 0; h < (OUT_I8 ? 1 : 2); ++h)
+#pragma unroll
+                for (int j = 0; j < JH; ++j)
+#pragma unroll
+                    for (int i = FN; i < 4; ++i) pq[h][j][i] = 0u;
+            uint32_t rr[OUT_I8 ? 1 : JH][4];
+            if constexpr (!OUT_I8) {
+#pragma unroll
+                for (int j = 0; j < JH; ++j) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) rr[j][e] = (uint32_t)rt[jh / JH][j][e];
+                    transpose4(rr[j][0], rr[j][1], rr[j][2], rr[j][3]);
+                }
+            }
+            auto put = [&](int i, int j, const int32_t (&o)[4]) {
+                if constexpr (OUT_I8) {
+                    pq[0][j][i] = pack4_perm(o[0], o[1], o[2], o[3]);
+                } else {
+                    pq[0][j][i] = __builtin_amdgcn_perm((uint32_t)o[1], (uint32_t)o[0], 0x05040100u);
+                    pq[OUT_I8 ? 0 : 1][j][i] = __builtin_amdgcn_perm((uint32_t)o[3], (uint32_t)o[2], 0x05040100u);
+                }
+            };
+            // RES: with residual; LUT: GELU from the table; FOLD: its address folded into the requantization constant (gemm_kernel.h)
+            auto finish_fast = [&](auto res_tag, auto lut_tag, auto fold_tag) {
+                constexpr bool RES = decltype(res_tag)::value, LUT = decltype(lut_tag)::value, FOLD = decltype(fold_tag)::value;
+#pragma unroll
+                for (int i = 0; i < FN; ++i) {
+                    const int cl = wn0 + 16 * i + 4 * fch;
+                    const v4i bb = *reinterpret_cast<const v4i*>(par + cl);
+                    const v4i mm = *reinterpret_cast<const v4i*>(par + BN + cl);
+                    const v4i ss = *reinterpret_cast<const v4i*>(par + 2 * BN + cl);
+                    int64_t cc[4];
+                    int32_t sh[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        cc[e] = (int64_t)bb[e] * mm[e] + ((int64_t)1 << ((ss[e] - 1) & 63));
+                        if (FOLD) cc[e] -= (int64_t)(ga->gelu_lut_lo - (int32_t)lut_lds) << (ss[e] & 63);
+                        sh[e] = (ss[e] - 32) & 31;
+                    }
+#pragma unroll
+                    for (int j = 0; j < JH; ++j) {
+                        int32_t o[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const int64_t p = (int64_t)acc[i][jh + j][e] * mm[e] + cc[e];
+                            int32_t v = (int32_t)(p >> 32) >> sh[e];
+                            if (RES) {
+                                const int32_t r8 = (int32_t)(int8_t)(rr[OUT_I8 ? 0 : j][i] >> (8 * e));
+                                v += (int32_t)(((int64_t)r8 * ga->res_m + ga->res_rnd) >> ga->res_s);
+                            }
+                            if (FOLD) {
+                                typedef const __attribute__((address_space(3))) uint8_t* lds_bytes;
+                                o[e] = *(lds_bytes)(uintptr_t)(uint32_t)med3_i32(v, (int32_t)lut_lds, (int32_t)lut_lds + lut_hi);
+                            } else if (LUT) {
+                                o[e] = lut[med3_i32(v - ga->gelu_lut_lo, 0, lut_hi)];
+                            } else {
+                                o[e] = med3_i32(v, clamp_lo, clamp_hi);
+                            }
+                        }
+                        put(i, j, o);
+                        // (two rows at a time, table reads a block column at a time: bounds the live registers)
+                        if (j % 2 == 1 && !LUT) __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (RES && jh == 0 && i == FN / 2) load_residual(std::integral_constant<int, 1>{});
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            using T = std::true_type;
+            using F = std::false_type;
+            if constexpr (GELU) {
+                if (fold) finish_fast(F{}, T{}, T{}); else finish_fast(F{}, T{}, F{});
+            } else if constexpr (OUT_I8) {
+                finish_fast(F{}, F{}, F{});
+            } else {
+                finish_fast(T{}, F{}, F{});                        // (no residual: zeros)
+            }
+            // A lane holds 4 channels of one token per block column and the four lanes that share the token (16 apart) 16 consecutive
+            // ones; transposing the 4 x 4 arrangement (lane group x block column) gives lane group b the 16 channels of block
+            // column b: one 16-byte store per token (INT8; INT16: below), 16 rows of 64 consecutive bytes per instruction.
+            // Before the first store this wavefront's requests have all landed (they are at least half a step old), so that the
+            // waits of the next tile's first step, which would count stores among the loads, can be left out.
+            if (jh == 0) __builtin_amdgcn_s_waitcnt(vm(0));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < JH; ++j) {
+                const uint32_t off = (row_of(jh + j) * (uint32_t)ga->ldc + (uint32_t)(16 / ES * fch)) * ES;
+                if constexpr (OUT_I8) {
+                    transpose4(pq[0][j][0], pq[0][j][1], pq[0][j][2], pq[0][j][3]);
+                    if (fch < FN) *reinterpret_cast<v4i*>(cb + off) = v4i{(int)pq[0][j][0], (int)pq[0][j][1], (int)pq[0][j][2], (int)pq[0][j][3]};
+                } else {
+                    // two block columns are 64 bytes of a row: lane group u takes bytes 16 u .. +15, which are the dword pairs of
+                    // column u / 2 from the groups 2 (u % 2) and the next -- the same two swaps
+                    constexpr int H = OUT_I8 ? 0 : 1;
+#pragma unroll
+                    for (int p = 0; p < FN; p += 2) {
+                        v2u t = __builtin_amdgcn_permlane32_swap(pq[0][j][p], pq[0][j][p + 1], false, false);
+                        t = __builtin_amdgcn_permlane16_swap(t.x, t.y, false, false);
+                        v2u u = __builtin_amdgcn_permlane32_swap(pq[H][j][p], pq[H][j][p + 1], false, false);
+                        u = __builtin_amdgcn_permlane16_swap(u.x, u.y, false, false);
+                        if (p + 1 < FN || fch < 2)
+                            *reinterpret_cast<v4i*>(cb + off + 32 * p) = v4i{(int)t.x, (int)u.x, (int)t.y, (int)u.y};
+                    }
+                }
+            }
+        };
+        if (fast) {
+            load_residual(std::integral_constant<int, 0>{});
+            finish_rows(std::integral_constant<int, 0>{});
+            if constexpr (JH < FM) finish_rows(std::integral_constant<int, JH>{});
+        } else {
+            // Any constants: 64-bit arithmetic in a rolled loop, 16 rows of each row of wavefronts at a time through LDS, where the
+            // next tile's first steps had arrived -- they are requested again afterwards.  (Unrolled over the accumulators like
+            // the fast form this costs so many registers that the kernel needs scratch memory, and then its main loop takes
+            // half as long again even where no scratch is touched: 25.8 k -> 39 k cycles for 8 steps.)
+            constexpr int SP = BN + 4, G4 = BN / 4;
+            int32_t* const st = reinterpret_cast<int32_t*>(lds);
+            __builtin_amdgcn_s_waitcnt(vm(0));
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll 1
+            for (int j = 0; j < FM; ++j) {
+#pragma unroll
+                for (int k = 0; k < FM; ++k)
+                    if (k == j) {
+#pragma unroll
+                        for (int i = 0; i < FN; ++i)
+                            *reinterpret_cast<v4i*>(st + ((wave & 1) * 16 + frow) * SP + wn0 + 16 * i + 4 * fch) = acc[i][k];
+                    }
+                __syncthreads();
+#pragma unroll 1
+                for (int q = tid; q < 32 * G4; q += NT) {
+                    const int r = q / G4, c = (q - r * G4) * 4, row = (r >> 4) * WM + 16 * j + (r & 15);
+                    if (row > last) continue;
+                    const v4i a4 = *reinterpret_cast<const v4i*>(st + r * SP + c);
+                    uint32_t r4 = 0;
+                    if (has_res) r4 = *reinterpret_cast<const uint32_t*>(ga->R + (int64_t)(m0 + row) * ga->ldr + n0 + c);
+                    int32_t o[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        int64_t v = dyadic64((int32_t)((uint32_t)a4[e] + (uint32_t)par[c + e]), par[BN + c + e], par[2 * BN + c + e] & 63);
+                        if (has_res) v += dyadic64((int32_t)(int8_t)(r4 >> (8 * e)), ga->res_m, ga->res_s);
+                        o[e] = clamp_i64_to_i32(v, ga->out_clamp);
+                        if constexpr (GELU) o[e] = gelu_one(o[e], GeluConst{ga->gelu.q_b, ga->gelu.q_c, ga->gelu.q_1, ga->gelu.q_max, ga->gelu.m, ga->gelu.s});
+                    }
+                    char* const cp = reinterpret_cast<char*>(ga->C) + ((int64_t)(m0 + row) * ga->ldc + n0 + c) * ES;
+                    if constexpr (OUT_I8) *reinterpret_cast<uint32_t*>(cp) = pack4_i8(o[0], o[1], o[2], o[3]);
+                    else *reinterpret_cast<uint2*>(cp) = uint2{__builtin_amdgcn_perm((uint32_t)o[1], (uint32_t)o[0], 0x05040100u),
+                                                               __builtin_amdgcn_perm((uint32_t)o[3], (uint32_t)o[2], 0x05040100u)};
+                }
+                __syncthreads();
+            }
+            rlt = lt + g.per_xcd;
+            rlive = rlt < count;
+            if (rlive) {
+                rk = 0;
+                rstage = lds0 + (uint32_t)stage;
+                request_tile(rlt);
+                request_two_steps();
+                __builtin_amdgcn_s_waitcnt(vm(0));
+                asm volatile("s_barrier" ::: "memory");
+            }
+        }
+        lt += g.per_xcd;
+        if (lt >= count) break;
+        tile_at(lt, m0, n0);
+        first = false;
+    }
+}
+
+// Does the kernel serve this problem (g as filled by launch_gemm)?
+template <int BM, int BN, int NW>
+bool stream_ok(const GemmArgs& g, bool i8)
+{
+    const bool c_ok = i8 ? g.c_vec16 : (g.c16 && aligned(g.C, 16) && g.ldc % 8 == 0);
+    return g.nbatch == 1 && g.M >= 1 && g.N % BN == 0 && g.K % 128 == 0 && g.lda < (1 << 20) && g.ldw < (1 << 20) && g.ldc < (1 << 20) &&
+           c_ok && (i8 ? !g.R : (!g.R || (g.r_vec && g.ldr < (1 << 20)))) && (int64_t)((g.M + BM - 1) / BM) * (g.N / BN) < (1 << 26);
+}
+
+template <int BM, int BN, int NW, bool GELU>
+int launch_stream(GemmArgs& g, bool i8, hipStream_t stream)
+{
+    if (!stream_ok<BM, BN, NW>(g, i8) || (GELU && !i8)) return IBERT_ERR_NOT_IMPLEMENTED;
+    StreamArgs s;
+    s.A = g.A; s.W = g.W; s.bias = g.bias; s.mult = g.mult; s.shift = g.shift; s.R = g.R; s.C = g.C;
+    s.M = g.M; s.nk = g.K / 128;
+    s.lda = (int32_t)g.lda; s.ldw = (int32_t)g.ldw; s.ldc = (int32_t)g.ldc; s.ldr = (int32_t)g.ldr;
+    s.tiles_m = (g.M + BM - 1) / BM;
+    const int tiles_n = g.N / BN;
+    // An XCD reads its share of W again for every round of tiles: shares side by side until one is at most half of its 4 MB
+    // L2 (each further one doubles the reads of A).
+    s.xs = 0;
+    while (s.xs < 2 && tiles_n % (2 << s.xs) == 0 && (((int64_t)g.N * g.K) >> s.xs) > (2 << 20) && s.tiles_m >= (8 >> s.xs)) ++s.xs;
+    s.gs = 3 - s.xs;
+    s.bn = tiles_n >> s.xs;
+    s.bn_magic = s.bn == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)s.bn) + 1u;
+    const int64_t run = ((int64_t)s.tiles_m * s.bn + (1 << s.gs) - 1) >> s.gs;      // the longest run of an XCD
+    s.per_xcd = (int32_t)(run < 32 ? run : 32);                    // one workgroup per CU
+    s.per_channel = g.per_channel; s.dy_m = g.dy_m; s.dy_s = g.dy_s; s.out_clamp = g.out_clamp;
+    s.res_m = g.res_m; s.res_s = g.res_s; s.res_fast = g.res_fast; s.res_rnd = g.res_rnd;
+    s.k_fast = (int64_t)g.K * 16129 < (1 << 30);
+    s.gelu_fast = g.gelu_fast; s.gelu_lut_lo = g.gelu_lut_lo; s.gelu_lut_n = 0; s.gelu = g.gelu;
+    s.path_word = g.path_word;
+    const dim3 grid(8u * (unsigned)s.per_xcd), block(64 * NW);
+#define IBERT_STREAM_LAUNCH(I8_)                                                                                    \
+    do {                                                                                                            \
+        using SL = StreamLayout<BM, BN, NW, I8_, GELU && I8_>;                                                      \
+        size_t lds_bytes = SL::LUT;                                                                                 \
+        if (GELU && g.gelu_lut_n <= SL::ROOM) {                                                                     \
+            s.gelu_lut_n = g.gelu_lut_n;                                                                            \
+            lds_bytes += (size_t)g.gelu_lut_n;                                                                      \
+        }                                                                                                           \
+        auto kern = gemm_stream_kernel<BM, BN, NW, I8_, GELU && I8_>;                                               \
+        static bool attr_done = false;                                                                              \
+        if (!attr_done) {                                                                                           \
+            IBERT_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                                \
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, 163840));               \
+            attr_done = true;                                                                                       \
+        }                                                                                                           \
+        hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, s);                                                \
+    } while (0)
+    if constexpr (GELU) IBERT_STREAM_LAUNCH(true);
+    else if (i8) IBERT_STREAM_LAUNCH(true);
+    else IBERT_STREAM_LAUNCH(false);
+#undef IBERT_STREAM_LAUNCH
+    IBERT_LAUNCH_CHECK("gemm_stream_kernel");
+    static char label[2][96];
+    char* l = label[i8 ? 1 : 0];
+    if (!l[0])
+        std::snprintf(l, sizeof label[0], "gemm_stream_kernel<%d, %d, %d, %s, %s>", BM, BN, NW, i8 ? "true" : "false", GELU ? "true" : "false");
+    g_last_kernel = l;
+    return IBERT_OK;
+}
+
+}  // namespace ibert

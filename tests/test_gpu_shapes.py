@@ -59,3 +59,52 @@ def test_layer_of_any_length_keeps_scores_and_probabilities(G):
     # a single layer call leaves every intermediate in the workspace for lengths that are no multiple of 128
     for seq in (33, 100, 131):
         _layer_case(G, synth.EncoderConfig("len%d" % seq, 192, 3, 320, seq, 2, 1))
+
+
+# ------------------------------------------------------------------------------------------- persistent MatMul
+def _stream_case(G, cfg, M, N, K, kind, shift, seed, form=True):
+    """One MatMul through tile configuration cfg; shift 40: every tile takes the fast epilogue, 30: the 64-bit one."""
+    import torch
+    from paper_2101_01321_amd import binding as B
+    rng = np.random.default_rng(seed)
+    A = rng.integers(-127, 128, size=(M, K), dtype=np.int8)
+    W = rng.integers(-127, 128, size=(N, K), dtype=np.int8)
+    bias = rng.integers(-50000, 50000, size=N, dtype=np.int32)
+    mult = rng.integers(2 ** 29, 2 ** 30, size=N, dtype=np.int64).astype(np.int32)
+    shifts = np.full(N, {"i8": shift, "i16": shift, "i16res": shift, "gelu": min(shift, 40)}[kind], np.int32)
+    R = rng.integers(-127, 128, size=(M, N), dtype=np.int8) if kind == "i16res" else None
+    res_dy = (1717986918, 23)
+    word = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    B.lib().ibert_gemm_config_override(cfg)
+    B.ibert_gemm_epilogue_record(word)
+    try:
+        G.say("persistent gemm cfg %d M=%d N=%d K=%d %s shift=%d" % (cfg, M, N, K, kind, shift))
+        kw = dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K, ldw=K, ldc=N, ldr=N, per_channel=1, residual_dy=res_dy)
+        if kind == "gelu":
+            gp, op = B.ibert_gelu_params_from_scale(2.0 ** -6, 0.7), P.gelu_params(2.0 ** -6, 0.7)
+            got, scratch = G.gemm_gelu(dict(kw, out_dtype=I8, out_clamp=5), A, W, bias, mult, shifts, gp, M * N)
+            assert np.all(scratch == -5)
+        else:
+            clamp = 127 if kind == "i8" else 32767
+            got = G.gemm(dict(kw, out_dtype=I8 if kind == "i8" else I16, out_clamp=clamp), A, W, bias, mult, shifts, R, out_elems=M * N)
+    finally:
+        B.ibert_gemm_epilogue_record(None)
+        B.lib().ibert_gemm_config_override(-1)
+    want_form = B.EPILOGUE_STAGED if shift < 33 else (B.EPILOGUE_DIRECT_GELU_TABLE if kind == "gelu" else B.EPILOGUE_DIRECT)
+    assert not form or int(word.item()) == want_form, (int(word.item()), want_form)
+    spec = GemmSpec(M, N, K, per_channel=1, dy=(1, 0), out_dtype=I8 if kind == "i8" else I32,
+                    out_clamp={"i8": 127, "gelu": gp.q_max if kind == "gelu" else 0}.get(kind, 32767), res_dy=res_dy)
+    want = oracle.gemm_requant(spec, A, W, bias, mult, shifts, R).reshape(-1)
+    if kind == "gelu":
+        want = oracle.gelu(want, op)
+    _eq(got.astype(np.int64), want.astype(np.int64), "persistent gemm")
+
+
+@pytest.mark.parametrize("cfg,bn", [(23, 256), (24, 192)])
+@pytest.mark.parametrize("kind", ["i8", "i16", "i16res", "gelu"])
+def test_gemm_persistent_tiles(G, cfg, bn, kind):
+    # K down to one pair of slices; M at, one past and far off a tile edge; more tiles than workgroups (several tiles each,
+    # with and without a change of tile column); shares of the XCDs that are empty
+    for M, N, K, shift in [(1, bn, 128, 40), (255, bn, 128, 40), (256, 2 * bn, 256, 40), (257, bn, 384, 40), (300, bn, 256, 30),
+                           (1000, 3 * bn, 640, 40), (256 * 90 + 17, 3 * bn, 128, 40), (256 * 130 + 1, 2 * bn, 256, 40)]:
+        _stream_case(G, cfg, M, N, K, kind, shift, seed=M + N + K)
