@@ -80,7 +80,7 @@ int check_gemm(const ibert_gemm_desc& d, const void* A, const void* W, const voi
 // Tile configurations of the MFMA kernel.
 struct GemmConfig {
     int bm, bn, bk, ring;
-    bool direct;          // direct-to-LDS loader (whole tiles only; ring = LDS stages) or register ring
+    bool direct;          // direct-to-LDS loader (N and K in whole tiles; ring = LDS stages) or register ring
 };
 static const GemmConfig kConfigs[] = {      // index = configuration number of ibert_gemm_config_override
     {256, 192, 128, 2, false},
@@ -151,10 +151,11 @@ static void gelu_table_range(const ibert_gelu_params& p, int32_t* lo, int32_t* n
     *n = (int32_t)count;
 }
 
-// The direct-to-LDS loader handles whole tiles only, with row offsets that fit its 32-bit lane offsets.
-static bool dma_ok(const ibert_gemm_desc& d, int bm, int bn)
+// The direct-to-LDS loader handles whole tile columns and K steps (any number of rows), with row offsets that fit its
+// 32-bit lane offsets.
+static bool dma_ok(const ibert_gemm_desc& d, int bn)
 {
-    return d.M % bm == 0 && d.N % bn == 0 && d.K % 128 == 0 && d.lda < (1 << 28) && d.ldw < (1 << 28);
+    return d.N % bn == 0 && d.K % 128 == 0 && d.lda < (1 << 23) && d.ldw < (1 << 23);
 }
 
 // Tile choice, measured on MI355X at RoBERTa-Base/Large shapes (256 CUs).
@@ -167,7 +168,7 @@ static bool dma_ok(const ibert_gemm_desc& d, int bm, int bn)
 static int choose_config(const ibert_gemm_desc& d, int64_t nb, bool gelu)
 {
     if (g_config_override >= 0 && g_config_override < kNumConfigs) return g_config_override;
-    auto tiles = [&](int bm, int bn) -> int64_t { return dma_ok(d, bm, bn) ? (int64_t)(d.M / bm) * (d.N / bn) * nb : 0; };
+    auto tiles = [&](int bm, int bn) -> int64_t { return dma_ok(d, bn) ? (int64_t)(d.M / bm) * (d.N / bn) * nb : 0; };
     // (256x256 pays only when K is long enough to amortise its 256-value-per-lane epilogue, and never with GELU in it)
     // (with eight wavefronts for 16- and 32-bit outputs from two rounds of tiles on: [32768,1024] x K 4096 154 -> 131 us,
     //  2.1 POP/s; K 1024 67.8 -> 65.2 us)
@@ -262,12 +263,12 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
             switch (cfg) {
                 case 3: return launch_mfma<64, 64, 128, 3, false, false, true>(g, i8, stream);
                 case 15: return launch_mfma<32, 32, 128, 4, false, false, true>(g, i8, stream);
-                case 6: if (dma_ok(d, 256, 192)) return launch_mfma<256, 192, 128, 2, false, true, true>(g, i8, stream); break;
-                case 7: if (dma_ok(d, 128, 128)) return launch_mfma<128, 128, 128, 2, false, true, true>(g, i8, stream); break;
-                case 9: if (dma_ok(d, 128, 96)) return launch_mfma<128, 96, 128, 2, false, true, true>(g, i8, stream); break;
-                case 10: if (dma_ok(d, 256, 128)) return launch_mfma<256, 128, 128, 2, false, true, true>(g, i8, stream); break;
-                case 13: if (dma_ok(d, 256, 192)) return launch_mfma<256, 192, 128, 2, false, true, true, 8>(g, i8, stream); break;
-                case 14: if (dma_ok(d, 256, 128)) return launch_mfma<256, 128, 128, 2, false, true, true, 8>(g, i8, stream); break;
+                case 6: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true, true>(g, i8, stream); break;
+                case 7: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 2, false, true, true>(g, i8, stream); break;
+                case 9: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 2, false, true, true>(g, i8, stream); break;
+                case 10: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true, true>(g, i8, stream); break;
+                case 13: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true, true, 8>(g, i8, stream); break;
+                case 14: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true, true, 8>(g, i8, stream); break;
                 case 23: return launch_stream<256, 256, 8, true>(g, i8, stream);
                 case 24: return launch_stream<256, 192, 8, true>(g, i8, stream);
                 default: break;
@@ -281,23 +282,23 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
             case 3: return launch_mfma<64, 64, 128, 3>(g, i8, stream);
             case 4: return launch_mfma<64, 128, 64, 3>(g, i8, stream);
             case 5: return launch_mfma<128, 96, 128, 2>(g, i8, stream);
-            case 6: if (dma_ok(d, 256, 192)) return launch_mfma<256, 192, 128, 2, false, true>(g, i8, stream); break;
-            case 7: if (dma_ok(d, 128, 128)) return launch_mfma<128, 128, 128, 2, false, true>(g, i8, stream); break;
-            case 8: if (dma_ok(d, 256, 256)) return launch_mfma<256, 256, 128, 2, false, true>(g, i8, stream); break;
-            case 9: if (dma_ok(d, 128, 96)) return launch_mfma<128, 96, 128, 2, false, true>(g, i8, stream); break;
-            case 10: if (dma_ok(d, 256, 128)) return launch_mfma<256, 128, 128, 2, false, true>(g, i8, stream); break;
-            case 11: if (dma_ok(d, 128, 96)) return launch_mfma<128, 96, 128, 3, false, true>(g, i8, stream); break;
-            case 12: if (dma_ok(d, 128, 128)) return launch_mfma<128, 128, 128, 3, false, true>(g, i8, stream); break;
-            case 13: if (dma_ok(d, 256, 192)) return launch_mfma<256, 192, 128, 2, false, true, false, 8>(g, i8, stream); break;
-            case 14: if (dma_ok(d, 256, 128)) return launch_mfma<256, 128, 128, 2, false, true, false, 8>(g, i8, stream); break;
+            case 6: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true>(g, i8, stream); break;
+            case 7: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 2, false, true>(g, i8, stream); break;
+            case 8: if (dma_ok(d, 256)) return launch_mfma<256, 256, 128, 2, false, true>(g, i8, stream); break;
+            case 9: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 2, false, true>(g, i8, stream); break;
+            case 10: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true>(g, i8, stream); break;
+            case 11: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 3, false, true>(g, i8, stream); break;
+            case 12: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 3, false, true>(g, i8, stream); break;
+            case 13: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true, false, 8>(g, i8, stream); break;
+            case 14: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true, false, 8>(g, i8, stream); break;
             case 15: return launch_mfma<32, 32, 128, 4>(g, i8, stream);
-            case 16: if (dma_ok(d, 256, 256)) return launch_mfma<256, 256, 128, 2, false, true, false, 8>(g, i8, stream); break;
-            case 17: if (dma_ok(d, 64, 96)) return launch_mfma<64, 96, 128, 3, false, true>(g, i8, stream); break;
-            case 18: if (dma_ok(d, 64, 96)) return launch_mfma<64, 96, 128, 2, false, true>(g, i8, stream); break;
-            case 19: if (dma_ok(d, 64, 128)) return launch_mfma<64, 128, 128, 2, false, true>(g, i8, stream); break;
-            case 20: if (dma_ok(d, 128, 96)) return launch_mfma<128, 96, 128, 3, false, true, false, 8>(g, i8, stream); break;
-            case 21: if (dma_ok(d, 128, 96)) return launch_mfma<128, 96, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
-            case 22: if (dma_ok(d, 128, 128)) return launch_mfma<128, 128, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
+            case 16: if (dma_ok(d, 256)) return launch_mfma<256, 256, 128, 2, false, true, false, 8>(g, i8, stream); break;
+            case 17: if (dma_ok(d, 96)) return launch_mfma<64, 96, 128, 3, false, true>(g, i8, stream); break;
+            case 18: if (dma_ok(d, 96)) return launch_mfma<64, 96, 128, 2, false, true>(g, i8, stream); break;
+            case 19: if (dma_ok(d, 128)) return launch_mfma<64, 128, 128, 2, false, true>(g, i8, stream); break;
+            case 20: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 3, false, true, false, 8>(g, i8, stream); break;
+            case 21: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
+            case 22: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
             case 23: if (launch_stream<256, 256, 8, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
             case 24: if (launch_stream<256, 192, 8, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
             default: break;

@@ -326,7 +326,11 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
     using EL = EpiLayout<BM, BN, BK, (DMA ? RING : 2)>;
     const int64_t c_off = zo * g.sC_o + zi * g.sC_i;
     const int8_t* R = g.R ? g.R + zo * g.sR_o + zi * g.sR_i : nullptr;
-    const bool interior = m0 + BM <= g.M && n0 + BN <= g.N && g.c_vec && (!R || g.r_vec) && g.ldc < (1 << 22);
+    // Direct-to-LDS kernels take any M: rows past the last one are read from it (operand and residual), computed like it and
+    // stored onto it -- the same bytes again --, so that an edge tile costs a minimum per address and is otherwise like any other.
+    const int rlast = g.M - 1 - m0;                                // the last row, counted from the tile's first
+    auto row_in = [&](int row) { return !DMA || row < rlast ? row : rlast; };
+    const bool interior = (DMA || m0 + BM <= g.M) && n0 + BN <= g.N && g.c_vec && (!R || g.r_vec) && g.ldc < (1 << 22);
 
     // Per-channel constants of this tile's BN columns, one or two columns per lane; used after the main loop.
     // (register-ring kernels; the direct-to-LDS kernels fetch them straight into LDS, see below)
@@ -359,7 +363,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             const int q = u * NT + tid;
             const int qq = q < RCH ? q : 0;
             const int row = qq / (BN / 16), c16 = qq - row * (BN / 16);
-            rpre[u] = *reinterpret_cast<const v4i*>(R + (int64_t)(m0 + row) * g.ldr + n0 + c16 * 16);
+            rpre[u] = *reinterpret_cast<const v4i*>(R + (int64_t)(m0 + row_in(row)) * g.ldr + n0 + c16 * 16);
         }
     }
     // (direct-to-LDS kernels: the constants live in LDS behind the stages, requested before the loop starts, see below)
@@ -389,9 +393,10 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         // swz<8> of the lane's row: the row is RG i + 8 wave + lr8 with RG a multiple of 32, so (row >> 1) & 7 depends on
         // the wavefront's parity and the lane only
         const int lsw = ((wv & 1) << 2) | (lr8 >> 1);
-        const uint32_t voff_a = (uint32_t)lr8 * (uint32_t)g.lda + (uint32_t)((lp ^ lsw) << 4);
-        const uint32_t voff_w = (uint32_t)lr8 * (uint32_t)g.ldw + (uint32_t)((lp ^ lsw) << 4);
-        const int8_t* ga = A + (int64_t)(m0 + wv * 8) * g.lda;
+        const uint32_t chunk = (uint32_t)((lp ^ lsw) << 4);
+        const uint32_t voff_a = (uint32_t)lr8 * (uint32_t)g.lda;
+        const uint32_t voff_w = (uint32_t)lr8 * (uint32_t)g.ldw + chunk;
+        const int8_t* ga = A + (int64_t)m0 * g.lda;
         const int8_t* gw = W + (int64_t)(n0 + wv * 8) * g.ldw;
         const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)lds + (uint32_t)wv * 1024u;
 
@@ -399,10 +404,12 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         auto dma_one = [&](int q, int kt, int buf) {
             const bool is_a = q < NLA;
             const int i = is_a ? q : q - NLA;
-            const int8_t* sb = (is_a ? ga + (int64_t)i * RG * g.lda : gw + (int64_t)i * RG * g.ldw) + (int64_t)kt * BK;
+            const int first = row_in(i * RG + wv * 8);              // (A: the block's first row, and how far its rows may reach)
+            const uint32_t most = (uint32_t)(rlast - first) * (uint32_t)g.lda;
+            const int8_t* sb = (is_a ? ga + (int64_t)first * g.lda : gw + (int64_t)i * RG * g.ldw) + (int64_t)kt * BK;
             const uint32_t la = lds0 + (uint32_t)(buf * STAGE + (is_a ? 0 : BM * BK) + i * (RG * BK));
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         :: "s"(la), "v"(is_a ? voff_a : voff_w), "s"(sb) : "memory", "m0");
+                         :: "s"(la), "v"(is_a ? (voff_a < most ? voff_a : most) + chunk : voff_w), "s"(sb) : "memory", "m0");
         };
         auto read_one = [&](int q, int buf, int s, v4i (&xa)[FM], v4i (&wb)[FN]) {
             const int8_t* base = lds + buf * STAGE + (((s * 4 + fch) ^ rd_swz) << 4);
@@ -673,7 +680,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
                 const int q = q0 + u * NT + tid;
                 const int qq = q < CH ? q : 0;
                 const int row = qq / (BN / 16), c16 = qq - row * (BN / 16);
-                t[u] = *reinterpret_cast<const v4i*>(R + (int64_t)(m0 + row) * g.ldr + n0 + c16 * 16);
+                t[u] = *reinterpret_cast<const v4i*>(R + (int64_t)(m0 + row_in(row)) * g.ldr + n0 + c16 * 16);
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -772,7 +779,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
                     res[2] = (int8_t)((pk[u] >> 16) & 0xff); res[3] = (int8_t)(pk[u] >> 24);
                     int32_t o[4];
                     requant4(a4[u], res, R != nullptr, fast_tag, o);
-                    char* cp = c_lane + (uint32_t)tr[u] * c_pitch;
+                    char* cp = c_lane + (uint32_t)row_in(tr[u]) * c_pitch;
                     if (OUT_I8) *reinterpret_cast<uint32_t*>(cp) = pack4_i8(o[0], o[1], o[2], o[3]);
                     else if (g.c16) *reinterpret_cast<uint2*>(cp) = uint2{pack2_i16(o[0], o[1]), pack2_i16(o[2], o[3])};
                     else *reinterpret_cast<v4i*>(cp) = v4i{o[0], o[1], o[2], o[3]};
@@ -846,8 +853,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         static_assert(SM == 0 || ES != 1 || OST_PAD || OST_SWZ, "the INT8 staging tile fits in front of the constants");
         static_assert(SM == 0 || ES != 4, "INT32 outputs are stored by the lanes themselves");
         int8_t* const ostage = lds;
-        char* const c_base = reinterpret_cast<char*>(g.C) +
-                             (c_off + (int64_t)(m0 + wm0 + frow) * g.ldc + n0 + wn0 + 4 * fch) * (int64_t)ES;
+        char* const c_base = reinterpret_cast<char*>(g.C) + (c_off + (int64_t)m0 * g.ldc + n0 + wn0 + 4 * fch) * (int64_t)ES;
         const uint32_t pitch = (uint32_t)g.ldc * ES;
         const uint32_t* const r_base = resl + (wm0 + frow) * G4 + (wn0 >> 2) + fch;
         static_assert(SM != 2 || (ES == 1 && FN <= 4), "lane-transposed stores: INT8, at most four block columns a wavefront");
@@ -890,7 +896,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
 #pragma unroll
                 for (int j = 0; j < FM; ++j) {
                     const uint32_t pk4 = (by[j][0] | (by[j][1] << 8)) | ((by[j][2] | (by[j][3] << 8)) << 16);
-                    char* cp = c_base + ((uint32_t)(j * 16) * pitch + (uint32_t)(i * 16) * ES);
+                    char* cp = c_base + ((uint32_t)row_in(wm0 + 16 * j + frow) * pitch + (uint32_t)(i * 16) * ES);
                     const int row = wm0 + 16 * j + frow, colb = wn0 + 16 * i + 4 * fch;
                     if (SM == 2) pq[i < 4 ? i : 0][j] = pk4;
                     else if (SM == 1) *reinterpret_cast<uint32_t*>(ostage + ost_at(row, colb)) = pk4;
@@ -930,7 +936,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             }
 #pragma unroll
             for (int j = 0; j < FM; ++j) {
-                char* cp = c_base + ((uint32_t)(j * 16) * pitch + (uint32_t)(i * 16) * ES);
+                char* cp = c_base + ((uint32_t)row_in(wm0 + 16 * j + frow) * pitch + (uint32_t)(i * 16) * ES);
                 const int row = wm0 + 16 * j + frow, colb = wn0 + 16 * i + 4 * fch;
                 if (ES == 1) {
                     const uint32_t pk4 = pack4_i8(o[j][0], o[j][1], o[j][2], o[j][3]);
@@ -953,7 +959,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             // block column b, which leave as one 16-byte store -- 16 tokens x 16 FN bytes per instruction, no trip
             // through LDS and no barrier.
             typedef unsigned v2u __attribute__((ext_vector_type(2)));
-            char* const c16 = reinterpret_cast<char*>(g.C) + c_off + (int64_t)(m0 + wm0 + frow) * g.ldc + n0 + wn0 + 16 * fch;
+            char* const c16 = reinterpret_cast<char*>(g.C) + c_off + (int64_t)m0 * g.ldc + n0 + wn0 + 16 * fch;
 #pragma unroll
             for (int j = 0; j < FM; ++j) {
                 uint32_t r0 = pq[0][j], r1 = pq[SM == 2 ? 1 : 0][j], r2 = pq[SM == 2 ? 2 : 0][j], r3 = pq[SM == 2 ? 3 : 0][j];
@@ -962,7 +968,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
                 t = __builtin_amdgcn_permlane16_swap(r0, r1, false, false); r0 = t.x; r1 = t.y;
                 t = __builtin_amdgcn_permlane16_swap(r2, r3, false, false); r2 = t.x; r3 = t.y;
                 if (fch < FN) {
-                    *reinterpret_cast<v4i*>(c16 + (uint32_t)(j * 16) * pitch) = v4i{(int)r0, (int)r1, (int)r2, (int)r3};
+                    *reinterpret_cast<v4i*>(c16 + (uint32_t)row_in(wm0 + 16 * j + frow) * pitch) = v4i{(int)r0, (int)r1, (int)r2, (int)r3};
                 }
             }
         }
@@ -975,7 +981,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
                 const int q = q0 + tid;
                 if (CH % NT == 0 || q < CH) {
                     const int row = q / P8, c8 = q - row * P8;
-                    *reinterpret_cast<uint2*>(ct + (uint32_t)row * pitch + c8 * 8) =
+                    *reinterpret_cast<uint2*>(ct + (uint32_t)row_in(row) * pitch + c8 * 8) =
                         *reinterpret_cast<const uint2*>(ostage + row * SPH + c8 * 8);
                 }
             }
@@ -989,7 +995,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
                 const int q = q0 + tid;
                 if (CH % NT == 0 || q < CH) {
                     const int row = q / C16, c16 = q - row * C16;
-                    *reinterpret_cast<v4i*>(ct + (uint32_t)row * pitch + c16 * 16) =
+                    *reinterpret_cast<v4i*>(ct + (uint32_t)row_in(row) * pitch + c16 * 16) =
                         *reinterpret_cast<const v4i*>(ostage + ost_at(row, c16 * 16));
                 }
             }

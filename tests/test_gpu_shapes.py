@@ -108,3 +108,14 @@ def test_gemm_persistent_tiles(G, cfg, bn, kind):
     for M, N, K, shift in [(1, bn, 128, 40), (255, bn, 128, 40), (256, 2 * bn, 256, 40), (257, bn, 384, 40), (300, bn, 256, 30),
                            (1000, 3 * bn, 640, 40), (256 * 90 + 17, 3 * bn, 128, 40), (256 * 130 + 1, 2 * bn, 256, 40)]:
         _stream_case(G, cfg, M, N, K, kind, shift, seed=M + N + K)
+
+
+@pytest.mark.parametrize("cfg,bm,bn", [(6, 256, 192), (7, 128, 128), (8, 256, 256), (9, 128, 96), (10, 256, 128), (11, 128, 96),
+                                       (12, 128, 128), (13, 256, 192), (14, 256, 128), (16, 256, 256), (17, 64, 96), (18, 64, 96),
+                                       (19, 64, 128), (20, 128, 96), (21, 128, 96), (22, 128, 128)])
+def test_gemm_direct_to_lds_ragged_rows(G, cfg, bm, bn):
+    # direct-to-LDS tiles whose last tile row is not whole: one row, one less and one more than a tile, several tiles and some
+    kinds = ["i8", "i16res"] + (["gelu"] if cfg in (6, 7, 9, 10, 13, 14) else [])
+    for M, N, K in [(1, bn, 128), (bm - 1, 2 * bn, 256), (bm + 1, bn, 512), (3 * bm + 37, 2 * bn, 384)]:
+        for kind in kinds:
+            _stream_case(G, cfg, M, N, K, kind, 40, seed=M + N + K, form=False)
