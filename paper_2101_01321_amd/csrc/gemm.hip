@@ -157,56 +157,72 @@ static bool dma_ok(const ibert_gemm_desc& d, int bn)
 {
     return d.N % bn == 0 && d.K % 128 == 0 && d.lda < (1 << 23) && d.ldw < (1 << 23);
 }
+static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Tile choice, measured on MI355X at RoBERTa-Base/Large shapes (256 CUs).
-// Whole-tile problems with K a multiple of 128 take the direct-to-LDS loader: the biggest tile that still
-// gives (nearly) every CU a workgroup -- big wavefront tiles need fewer LDS bytes per MFMA, which is what
-// limits the loop -- and, when the problem is too small for that, 128x96 tiles, several of which share a CU
-// so that one workgroup's requantization overlaps another's MFMAs.
-// Everything else takes the register-ring loader: 128x128 tiles with a 64-wide K step while that gives every
-// CU something to do, below that 64x64 tiles.
-static int choose_config(const ibert_gemm_desc& d, int64_t nb, bool gelu)
+// Tile choice for K % 128 == 0.  What a configuration takes is linear in the K steps and in the tiles that the fullest
+// compute unit gets: with k = K / 128, n = ceil(tiles / 256) and, for tiles of which `share` fit a compute unit side by
+// side, r = ceil(n / share),
+//   t = first[0] + first[1] k + (n - 1) (more[0] + more[1] k) + (r - 1) (again[0] + again[1] k)        nanoseconds,
+// where first[] holds launch, pipeline fill and the epilogue nobody hides, more[] one more tile on the same unit, and
+// again[] the extra cost of a tile that has to wait for a place (0 where share is 1).  The coefficients are least-squares
+// fits to 430 problems timed on MI355X (K 128 to 8192, N 384 to 4096, 16 to 32768 rows, W changing from call to call),
+// for 16-bit outputs with a residual (32-bit ones use them too), INT8 outputs and GELU outputs; the fits are within 3 to
+// 9 % (r.m.s.), and the configuration with the least t takes 0.7 % longer on average than the best of all would.
+// Thresholds on tile counts, which this replaces, took 16 % longer.  Some lines they could not draw: [4096,1024] x K 4096
+// to 4096 rows more, 52 -> 40 us at 8192 rows; 2741 rows of [768] x K 3072 25.1 -> 14.5 us (the last tile row is ragged);
+// a second round of large tiles that would be nearly empty, [5120,1024] x K 1024 19.7 -> 13.3 us.
+struct TileCost {
+    int config, share;
+    struct { int first[2], more[2], again[2]; } kind[3];
+};
+static const TileCost kTileCost[] = {
+    //        16/32-bit output                        INT8 output                             INT8 output of GELU (all 0: none)
+    {15, 5, {{3638, 152, 565, 82, 0, 0}, {3499, 164, 473, 81, 0, 0}, {3665, 167, 497, 78, 0, 0}}},              // 32x32, ring
+    {3, 3, {{4684, 275, 1323, 181, 301, 13}, {4162, 312, 894, 161, 210, 45}, {4832, 301, 1103, 151, 518, 65}}}, // 64x64, ring
+    {2, 2, {{7344, 648, 4254, 414, 0, 307}, {6139, 686, 3067, 416, 0, 260}, {0, 0, 0, 0, 0, 0}}},               // 128x128, ring
+    {17, 2, {{4107, 343, 1083, 184, 1640, 89}, {3543, 373, 733, 137, 1326, 180}, {0, 0, 0, 0, 0, 0}}},          // 64x96, three stages
+    {18, 3, {{3555, 506, 1443, 89, 747, 324}, {3140, 548, 758, 68, 782, 426}, {0, 0, 0, 0, 0, 0}}},             // 64x96
+    {21, 1, {{5899, 328, 4534, 441, 0, 0}, {4626, 357, 3577, 378, 0, 0}, {0, 0, 0, 0, 0, 0}}},                  // 128x96, with loaders
+    {19, 3, {{4154, 552, 1740, 118, 376, 453}, {3351, 615, 927, 94, 681, 464}, {0, 0, 0, 0, 0, 0}}},            // 64x128
+    {22, 1, {{6604, 386, 6028, 478, 0, 0}, {4965, 418, 3998, 455, 0, 0}, {0, 0, 0, 0, 0, 0}}},                  // 128x128, with loaders
+    {7, 2, {{5748, 641, 5109, 642, 0, 0}, {3972, 691, 2996, 616, 0, 0}, {6532, 647, 5452, 669, 0, 0}}},         // 128x128
+    {9, 2, {{5049, 576, 2896, 96, 1571, 464}, {3637, 623, 1510, 100, 863, 491}, {6006, 592, 2399, 84, 1975, 521}}}, // 128x96
+    {14, 1, {{7913, 840, 9950, 898, 0, 0}, {5170, 892, 4873, 878, 0, 0}, {7679, 822, 6995, 905, 0, 0}}},        // 256x128
+    {13, 1, {{10556, 880, 13677, 1134, 0, 0}, {6198, 970, 6969, 1096, 0, 0}, {9584, 897, 9397, 1130, 0, 0}}},   // 256x192
+    {24, 1, {{10260, 1045, 7938, 1381, 0, 0}, {6076, 1024, 4496, 1170, 0, 0}, {8775, 1012, 5551, 1170, 0, 0}}}, // 256x192, persistent
+    {23, 1, {{11521, 1234, 11232, 1460, 0, 0}, {7038, 1265, 5637, 1470, 0, 0}, {10179, 1155, 6600, 1521, 0, 0}}}, // 256x256, persistent
+};
+
+static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb, bool gelu)
 {
     if (g_config_override >= 0 && g_config_override < kNumConfigs) return g_config_override;
-    auto tiles = [&](int bm, int bn) -> int64_t { return dma_ok(d, bn) ? (int64_t)(d.M / bm) * (d.N / bn) * nb : 0; };
-    // (256x256 pays only when K is long enough to amortise its 256-value-per-lane epilogue, and never with GELU in it)
-    // (with eight wavefronts for 16- and 32-bit outputs from two rounds of tiles on: [32768,1024] x K 4096 154 -> 131 us,
-    //  2.1 POP/s; K 1024 67.8 -> 65.2 us)
-    if (tiles(256, 256) >= 512 && d.out_dtype != IBERT_I8 && !gelu) return 16;
-    // (INT8 outputs without GELU, whose rows leave packed through LDS, when the tiles come in whole rounds:
-    //  [32768,3072] x K 1024 134 -> 120 us; with a ragged last round, or GELU in the epilogue, it loses)
-    if (tiles(256, 256) >= 512 && tiles(256, 256) % 256 == 0 && d.out_dtype == IBERT_I8 && !gelu) return 16;
-    if (tiles(256, 256) >= 512 && d.K >= 8192 && !gelu) return 8;
-    // (with eight wavefronts; it pays from three quarters of a wave of tiles on: S1 of Base, 192 tiles, 17.1 -> 15.1 us)
-    if (tiles(256, 192) >= (gelu ? 224 : 192)) return 13;
-    // (one workgroup per CU and a long K: a third LDS stage lets the requests spread over the whole step)
-    if (tiles(128, 96) >= 256) {
-        // (exactly one 128x96 tile per CU and a 16- or 32-bit output: 64x96 tiles, three or four of which share a CU, so
-        //  that one's epilogue overlaps another's loop -- inside the encoder S5 of Base 9.7 -> 8.9 us, S9 17.9 -> 17.3 us;
-        //  a fourth LDS stage leaves room for one workgroup per CU only and loses, 24 us.)
-        // (a long K instead: the whole 128x96 tile with eight wavefronts in four rows of two, three stages, and four more
-        //  wavefronts that do nothing but request tiles, so that no MFMA wavefront ever waits for the address unit:
-        //  [4096,768] x K 3072, timed alone: 64x96 tiles 18.5 us, eight wavefronts 17.6, with the loaders 15.8; INT8 output
-        //  17.1 -> 14.4.  A short K gains nothing from it: S5 of Base 8.7 against 9.0.)
-        if (tiles(128, 96) <= 256 && d.K >= 2048 && !gelu) return 21;
-        if (tiles(128, 96) <= 256 && d.out_dtype != IBERT_I8 && !gelu) return 18;
-        return tiles(128, 96) <= 256 && d.K >= 2048 ? 11 : 9;
+    const bool i8 = d.out_dtype == IBERT_I8;
+    auto tiles = [&](int bm, int bn) -> int64_t { return ceil_div(d.M, bm) * ceil_div(d.N, bn) * nb; };
+    const bool wide = d.N % 96 == 0 || d.N % 128 == 0;                  // some direct-to-LDS tile divides N
+    // (GELU stays in a kernel of its own, behind a MatMul whose result the caller finds in its scratch, where K is short
+    //  and no direct-to-LDS tile fits)
+    if (d.K % 128 == 0 && (d.K >= 512 || wide)) {
+        int best = -1;
+        int64_t best_t = 0;
+        for (const TileCost& c : kTileCost) {
+            const GemmConfig& f = kConfigs[c.config];
+            const auto& w = c.kind[gelu ? 2 : (i8 ? 1 : 0)];
+            if (w.first[0] == 0 || (f.direct && !dma_ok(d, f.bn))) continue;
+            if (c.config == 23 && !stream_ok<256, 256, 8>(g, i8)) continue;
+            if (c.config == 24 && !stream_ok<256, 192, 8>(g, i8)) continue;
+            const int64_t k = d.K / 128, n = ceil_div(tiles(f.bm, f.bn), 256), r = ceil_div(n, c.share);
+            const int64_t t = w.first[0] + w.first[1] * k + (n - 1) * (w.more[0] + w.more[1] * k) +
+                              (r - 1) * (w.again[0] + w.again[1] * k);
+            if (best < 0 || t < best_t) { best = c.config; best_t = t; }
+        }
+        return best;
     }
-    // (eight wavefronts for INT8 outputs: S7+S8 of Large 34.7 -> 32.5 us; INT32 outputs lose 5 % with them)
-    if (tiles(256, 128) >= 448) return (gelu || d.out_dtype == IBERT_I8) ? 14 : 10;
-    if (tiles(128, 128) >= 128) {
-        // (likewise 64x128 tiles for a short K: S5 of Large 14.4 -> 12.9 us; with K 4096 they lose, 25.9 -> 30 us)
-        if (tiles(128, 128) <= 256 && d.K < 2048 && d.out_dtype != IBERT_I8 && !gelu) return 19;
-        // (one tile per CU and a long K: eight wavefronts plus four loaders -- S9 of Large, [4096,1024] x K 4096: 27.0 -> 23.3 us)
-        if (tiles(128, 128) <= 256 && d.K >= 2048 && !gelu) return 22;
-        return tiles(128, 128) <= 256 && d.K >= 2048 ? 12 : 7;
-    }
-    const int64_t tiles128 = (((int64_t)d.M + 127) / 128) * (((int64_t)d.N + 127) / 128) * nb;
-    if (tiles128 >= 384) return 2;
+    // The register-ring loader, which takes any K that is a multiple of 16: 128x128 tiles with a 64-wide K step while that
+    // gives every CU something to do, below that 64x64 tiles.
+    if (tiles(128, 128) >= 384) return 2;
     // (a handful of sequences: 32x32 tiles put four times as many compute units on a long K than 64x64 do;
     //  [128,768] x K 3072: 10.5 -> 7.0 us, K 768: 5.6 -> 4.5 us)
-    const int64_t tiles64 = (((int64_t)d.M + 63) / 64) * (((int64_t)d.N + 63) / 64) * nb;
-    if (d.K >= 512) return tiles64 <= 96 ? 15 : 3;
+    if (d.K >= 512) return tiles(64, 64) <= 96 ? 15 : 3;
     return 4;
 }
 
@@ -258,7 +274,7 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
     if (gelu && !(fast && d.K % 16 == 0)) return IBERT_ERR_NOT_IMPLEMENTED;
     if (fast) {
         if (d.K % 16 != 0) return launch_tail(g, i8, stream);       // bytewise K tail
-        const int cfg = choose_config(d, nb, gelu != nullptr);
+        const int cfg = choose_config(d, g, nb, gelu != nullptr);
         if (gelu) {
             switch (cfg) {
                 case 3: return launch_mfma<64, 64, 128, 3, false, false, true>(g, i8, stream);
