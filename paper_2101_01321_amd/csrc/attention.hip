@@ -101,6 +101,10 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
     int8_t* const ks = qs + ATT_QB * ATT_DH;                                  // K_h [64 NKB][64]
     int8_t* const vs = ks + 64 * NKB * ATT_DH;                                // V_h [64 NKB][64]
 
+    // every argument is in registers from here on: one trip to memory, not one at each first use
+    asm volatile("" :: "s"(a.qkv), "s"(a.ctx), "s"(a.heads), "s"(a.seq), "s"(a.qblks), "s"(a.qblks_magic), "s"(a.heads_magic),
+                 "s"(a.xcd_q), "s"(a.xcd_r), "s"(a.ld_qkv), "s"(a.ld_ctx), "s"(a.s_m), "s"(a.s_s), "s"(a.c_m), "s"(a.c_s),
+                 "s"(a.sm.q_b), "s"(a.sm.q_c), "s"(a.sm.q_ln2), "s"(a.sm.k), "s"(a.z_m), "s"(a.z_c), "s"(a.z_s), "s"(a.key_lens));
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroups are dealt round-robin to the 8 XCDs.  The query blocks of a head read the same K and V,
     // and neighbouring heads share 128-byte lines of the packed QKV rows: give each XCD a contiguous run of
@@ -203,10 +207,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
         }
     }
     {
-        const int32_t o1 = __shfl_xor(mx, 16, 64);
-        mx = o1 > mx ? o1 : mx;
-        const int32_t o2 = __shfl_xor(mx, 32, 64);
-        mx = o2 > mx ? o2 : mx;
+        const auto larger = [](int32_t x, int32_t y) { return x > y ? x : y; };
+        mx = combine_rows32(combine_rows16(mx, larger), larger);
     }
     uint32_t sum = 0;
     if constexpr (FORM == 0) {
@@ -258,8 +260,8 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
             }
         }
     }
-    sum += (uint32_t)__shfl_xor((int32_t)sum, 16, 64);
-    sum += (uint32_t)__shfl_xor((int32_t)sum, 32, 64);
+    const auto add = [](int32_t x, int32_t y) { return (int32_t)((uint32_t)x + (uint32_t)y); };
+    sum = (uint32_t)combine_rows32(combine_rows16((int32_t)sum, add), add);
     const uint32_t Fz = 0x80000000u / sum;                 // sum >= q_b^2 + q_c >= 1 (the maximum itself)
 
     v4i pf[NKB];                                           // probabilities as MFMA operands, one per key block

@@ -101,6 +101,21 @@ __device__ __forceinline__ int32_t dpp_mov(int32_t v)
     return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
 }
 
+// op of a value and its partner 16 or 32 lanes away, in every lane: swapping rows of lanes between two copies of a register
+// leaves the two operands in two registers, without the trip through LDS that a lane permute takes.
+template <typename Op>
+__device__ __forceinline__ int32_t combine_rows16(int32_t v, Op op)
+{
+    const auto t = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+    return op((int32_t)t[0], (int32_t)t[1]);
+}
+template <typename Op>
+__device__ __forceinline__ int32_t combine_rows32(int32_t v, Op op)
+{
+    const auto t = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+    return op((int32_t)t[0], (int32_t)t[1]);
+}
+
 // All-reduce over groups of LPR consecutive lanes (LPR = 16, 32 or 64; groups are aligned).
 template <int LPR, typename Op>
 __device__ __forceinline__ int32_t group_allreduce(int32_t v, Op op)
@@ -109,8 +124,8 @@ __device__ __forceinline__ int32_t group_allreduce(int32_t v, Op op)
     v = op(v, dpp_mov<0x4E>(v));
     v = op(v, dpp_mov<0x141>(v));
     v = op(v, dpp_mov<0x140>(v));
-    if (LPR > 16) v = op(v, __shfl_xor(v, 16, 64));
-    if (LPR > 32) v = op(v, __shfl_xor(v, 32, 64));
+    if (LPR > 16) v = combine_rows16(v, op);
+    if (LPR > 32) v = combine_rows32(v, op);
     return v;
 }
 

@@ -8,6 +8,8 @@
 // The same kernel also serves the INT8 embedding (Sec. 1, contribution 3; App. C.1): there the row is not read from
 // an INT32 buffer but made on the fly from one row of the INT8 token table and one of the INT8 position table, each
 // rescaled by a dyadic number to the common INT32 scale of the sum, and then normalized as above.
+#include <type_traits>
+
 #include "common.h"
 #include "layernorm_math.h"
 
@@ -40,17 +42,6 @@ __device__ __forceinline__ int32_t group_sum_i32(int32_t v)
     return group_allreduce<LPR>(v, [](int32_t a, int32_t b) { return a + b; });
 }
 
-// 64-bit all-reduce built from 32-bit ones.
-template <int LPR>
-__device__ __forceinline__ uint64_t group_sum_u64(uint64_t v)
-{
-    // every lane value is below 2^35 here (at most 32 squares below 2^30); split at bit 19 so that both parts,
-    // summed over 64 lanes, stay below 2^25 and plain 32-bit all-reduces are exact
-    const int32_t l0 = (int32_t)(v & 0x7ffff), l1 = (int32_t)(v >> 19);
-    const uint64_t s0 = (uint32_t)group_sum_i32<LPR>(l0), s1 = (uint32_t)group_sum_i32<LPR>(l1);
-    return s0 + (s1 << 19);
-}
-
 constexpr int LN_THREADS = 256;
 
 // ALIGNED: rows 16-byte (x) / 4-byte (y) aligned, C % 4 == 0, gamma/beta 16-byte aligned: every 4-element
@@ -71,6 +62,9 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_rows_kernel(LayerNormArg
     const int64_t row = (int64_t)blockIdx.x * ROWS_PER_BLOCK + threadIdx.x / LPR;
     const bool live = row < a.rows;
     const int32_t C = a.C;
+    // every argument is in registers from here on: one trip to memory, not one at each first use
+    asm volatile("" :: "s"(a.x), "s"(a.y), "s"(a.rows), "s"(a.C), "s"(a.ldx), "s"(a.ldy), "s"(a.gamma_q), "s"(a.beta_q), "s"(a.shift),
+                 "s"(a.magic_c));
     const int32_t* xr = (EMB || X16) ? nullptr : a.x + (live ? row : 0) * a.ldx;
     const int16_t* xh = X16 ? reinterpret_cast<const int16_t*>(a.x) + (live ? row : 0) * a.ldx : nullptr;
     const int8_t *tr = nullptr, *pr = nullptr;
@@ -153,20 +147,25 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_rows_kernel(LayerNormArg
 
     // clamp on load; the sum and the sum of squares in one sweep, so that their reductions overlap
     int32_t sum = 0;
-    uint64_t sq = 0;
+    int32_t sq_lo = 0, sq_hi = 0;                      // the sum of squares in two parts, sq_hi * 2^16 + sq_lo
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         const int col = col_of(c);
+        uint32_t sq4 = 0;                              // four squares of at most 32767^2: below 2^32
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int32_t keep = (FULL || (ALIGNED ? col < C : col + e < C)) ? -1 : 0;
             v[c][e] = med3_const<-32767, 32767>(v[c][e]) & keep;
             sum += v[c][e];                            // |sum| <= 1024 * 32767 < 2^25
-            sq += (uint32_t)smul24(v[c][e], v[c][e]);  // |v| < 2^15: a 24-bit multiply; the total is below 2^40
+            sq4 = (uint32_t)smul24(v[c][e], v[c][e]) + sq4;
         }
+        sq_lo += (int32_t)(sq4 & 0xffffu);             // below 2^16 NCH in a lane, 2^25 in a row
+        sq_hi += (int32_t)(sq4 >> 16);
     }
     sum = group_sum_i32<LPR>(sum);
-    sq = group_sum_u64<LPR>(sq);
+    sq_lo = group_sum_i32<LPR>(sq_lo);
+    sq_hi = group_sum_i32<LPR>(sq_hi);
+    const uint64_t sq = (uint64_t)(uint32_t)sq_lo + ((uint64_t)(uint32_t)sq_hi << 16);   // below 2^40
 
     // mu = floor((sum + floor(C/2)) / C), computed on the non-negative number sum + C/2 + 32768 C
     const uint32_t Cu = (uint32_t)C;
@@ -183,31 +182,35 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_rows_kernel(LayerNormArg
     const bool f24 = __builtin_amdgcn_ballot_w64(f >= (1 << 23)) == 0;
 
     int8_t* yr = a.y + row * a.ldy;
-    uint32_t even_pack = 0;                                    // WIDE: the packed bytes of the pair's first chunk
+    auto finish = [&](auto f24_tag) {
+        uint32_t even_pack = 0;                                // WIDE: the packed bytes of the pair's first chunk
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-        const int col = col_of(c);
-        if (!FULL && col >= C) continue;
-        int32_t o[4];
+        for (int c = 0; c < NCH; ++c) {
+            const int col = col_of(c);
+            if (!FULL && col >= C) continue;
+            int32_t o[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int32_t d = v[c][e] - mu;                                        // |d| < 2^17
-            const int32_t n = (f24 ? smul24(d, f) : d * f) >> 14;                  // |d*f| < 2^30; |n| < 2^16
-            const int32_t acc = smad24(n, gm[c][e], bt[c][e]);                     // |gamma_q| < 2^14: 24-bit multiply
-            o[e] = med3_const<-127, 127>(acc >> a.shift);
+            for (int e = 0; e < 4; ++e) {
+                const int32_t d = v[c][e] - mu;                                    // |d| < 2^17
+                const int32_t n = (decltype(f24_tag)::value ? smul24(d, f) : d * f) >> 14;   // |d*f| < 2^30; |n| < 2^16
+                const int32_t acc = smad24(n, gm[c][e], bt[c][e]);                 // |gamma_q| < 2^14: 24-bit multiply
+                o[e] = med3_const<-127, 127>(acc >> a.shift);
+            }
+            if (WIDE) {
+                const uint32_t pk = pack4_perm(o[0], o[1], o[2], o[3]);
+                if ((c & 1) == 0) even_pack = pk;
+                else *reinterpret_cast<uint2*>(yr + col - 4) = uint2{even_pack, pk};
+            } else if (ALIGNED) {
+                *reinterpret_cast<uint32_t*>(yr + col) = pack4_perm(o[0], o[1], o[2], o[3]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < C) yr[col + e] = (int8_t)o[e];
+            }
         }
-        if (WIDE) {
-            const uint32_t pk = pack4_perm(o[0], o[1], o[2], o[3]);
-            if ((c & 1) == 0) even_pack = pk;
-            else *reinterpret_cast<uint2*>(yr + col - 4) = uint2{even_pack, pk};
-        } else if (ALIGNED) {
-            *reinterpret_cast<uint32_t*>(yr + col) = pack4_perm(o[0], o[1], o[2], o[3]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (col + e < C) yr[col + e] = (int8_t)o[e];
-        }
-    }
+    };
+    if (f24) finish(std::true_type{});
+    else finish(std::false_type{});
 }
 
 // Alg. 4's integer square root on its own.  METHOD 0: a value per lane.  METHOD 1-3: the LPR = 64, 32, 16 lanes of a
