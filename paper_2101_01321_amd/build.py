@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libibert.so")
-GEMM_UNITS = ["gemm_inst_%s.hip" % u for u in "abcdefgh"]      # the MFMA kernel's tile configurations, one group per unit
+GEMM_UNITS = ["gemm_inst_%s.hip" % u for u in "abcdefghi"]      # the MFMA kernel's tile configurations, one group per unit
 SOURCES = GEMM_UNITS + ["gemm.hip", "attention.hip", "host.cpp", "layer.cpp", "gelu.hip", "softmax.hip", "layernorm.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed-FP32 instruction forms are switched off for all device code

@@ -1,6 +1,9 @@
 // INT8 x INT8 -> INT32 MatMul with bias, dyadic requantization, optional residual and clamp (Sec. 1 third contribution,
 // App. C.1): argument checks, the choice of a tile configuration, the generic kernel for unaligned operands, and the
 // C entry points.  The MFMA kernel is in gemm_kernel.h; its tile configurations are compiled in gemm_inst_*.hip.
+#include <algorithm>
+
+#include "gemm_few.h"
 #include "gemm_stream.h"
 
 namespace ibert {
@@ -13,6 +16,18 @@ namespace ibert {
 #include "gemm_instances_e.inc"
 #include "gemm_instances_f.inc"
 #undef IBERT_GEMM_INSTANCE
+extern template int launch_few<1, 1, false>(const GemmArgs&, bool, hipStream_t);
+extern template int launch_few<1, 1, true>(const GemmArgs&, bool, hipStream_t);
+extern template int launch_few<1, 2, false>(const GemmArgs&, bool, hipStream_t);
+extern template int launch_few<1, 2, true>(const GemmArgs&, bool, hipStream_t);
+extern template int launch_few<2, 2, false>(const GemmArgs&, bool, hipStream_t);
+extern template int launch_few<2, 2, true>(const GemmArgs&, bool, hipStream_t);
+extern template int launch_few<2, 4, false>(const GemmArgs&, bool, hipStream_t);
+extern template int launch_few<2, 4, true>(const GemmArgs&, bool, hipStream_t);
+extern template int launch_few<2, 6, false>(const GemmArgs&, bool, hipStream_t);
+extern template int launch_few<2, 6, true>(const GemmArgs&, bool, hipStream_t);
+extern template int launch_few<4, 4, false>(const GemmArgs&, bool, hipStream_t);
+extern template int launch_few<4, 4, true>(const GemmArgs&, bool, hipStream_t);
 extern template int launch_stream<256, 256, 8, false>(GemmArgs&, bool, hipStream_t);
 extern template int launch_stream<256, 256, 8, true>(GemmArgs&, bool, hipStream_t);
 extern template int launch_stream<256, 192, 8, false>(GemmArgs&, bool, hipStream_t);
@@ -108,6 +123,12 @@ static const GemmConfig kConfigs[] = {      // index = configuration number of i
     {128, 128, 128, 3, true},       // eight wavefronts and four that only request tiles
     {256, 256, 128, 2, true},       // persistent (gemm_stream.h)
     {256, 192, 128, 2, true},       // persistent
+    {16, 16, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
+    {16, 32, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
+    {32, 32, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
+    {32, 64, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
+    {32, 96, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
+    {64, 64, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
 };
 constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
 static int g_config_override = -1;
@@ -164,33 +185,40 @@ static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // side, r = ceil(n / share),
 //   t = first[0] + first[1] k + (n - 1) (more[0] + more[1] k) + (r - 1) (again[0] + again[1] k)        nanoseconds,
 // where first[] holds launch, pipeline fill and the epilogue nobody hides, more[] one more tile on the same unit, and
-// again[] the extra cost of a tile that has to wait for a place (0 where share is 1).  The coefficients are least-squares
-// fits to 430 problems timed on MI355X (K 128 to 8192, N 384 to 4096, 16 to 32768 rows, W changing from call to call),
-// for 16-bit outputs with a residual (32-bit ones use them too), INT8 outputs and GELU outputs; the fits are within 3 to
-// 9 % (r.m.s.), and the configuration with the least t takes 0.7 % longer on average than the best of all would.
-// Thresholds on tile counts, which this replaces, took 16 % longer.  Some lines they could not draw: [4096,1024] x K 4096
-// to 4096 rows more, 52 -> 40 us at 8192 rows; 2741 rows of [768] x K 3072 25.1 -> 14.5 us (the last tile row is ragged);
-// a second round of large tiles that would be nearly empty, [5120,1024] x K 1024 19.7 -> 13.3 us.
+// again[] the extra cost of a tile that has to wait for a place (0 where share is 1).  (Tiles of gemm_few.h: n from its own
+// dealing of tiles to XCDs, and a share that depends on K.)  The coefficients are least-squares fits to 640 problems timed
+// on MI355X (K 128 to 8192, N 128 to 4096, 1 to 32768 rows, W changing from call to call), for 16-bit outputs with a
+// residual (32-bit ones use them too), INT8 outputs and GELU outputs; the fits are within 4 to 13 % (r.m.s.), and the
+// configuration with the least t takes 0.5 % longer on average than the best of all would, at worst 22 %.  Thresholds on tile
+// counts, which this replaces, took 16 % longer with the same configurations.  Some lines they could not draw: [4096,1024] x
+// K 4096 to 4096 rows more, 52 -> 40 us at 8192 rows; 2741 rows of [768] x K 3072 25.1 -> 14.5 us (the last tile row is
+// ragged); a second round of large tiles that would be nearly empty, [5120,1024] x K 1024 19.7 -> 13.3 us.
 struct TileCost {
-    int config, share;
+    int config, share;                      // share 0: gemm_few.h
     struct { int first[2], more[2], again[2]; } kind[3];
 };
 static const TileCost kTileCost[] = {
     //        16/32-bit output                        INT8 output                             INT8 output of GELU (all 0: none)
-    {15, 5, {{3638, 152, 565, 82, 0, 0}, {3499, 164, 473, 81, 0, 0}, {3665, 167, 497, 78, 0, 0}}},              // 32x32, ring
-    {3, 3, {{4684, 275, 1323, 181, 301, 13}, {4162, 312, 894, 161, 210, 45}, {4832, 301, 1103, 151, 518, 65}}}, // 64x64, ring
-    {2, 2, {{7344, 648, 4254, 414, 0, 307}, {6139, 686, 3067, 416, 0, 260}, {0, 0, 0, 0, 0, 0}}},               // 128x128, ring
-    {17, 2, {{4107, 343, 1083, 184, 1640, 89}, {3543, 373, 733, 137, 1326, 180}, {0, 0, 0, 0, 0, 0}}},          // 64x96, three stages
-    {18, 3, {{3555, 506, 1443, 89, 747, 324}, {3140, 548, 758, 68, 782, 426}, {0, 0, 0, 0, 0, 0}}},             // 64x96
-    {21, 1, {{5899, 328, 4534, 441, 0, 0}, {4626, 357, 3577, 378, 0, 0}, {0, 0, 0, 0, 0, 0}}},                  // 128x96, with loaders
-    {19, 3, {{4154, 552, 1740, 118, 376, 453}, {3351, 615, 927, 94, 681, 464}, {0, 0, 0, 0, 0, 0}}},            // 64x128
-    {22, 1, {{6604, 386, 6028, 478, 0, 0}, {4965, 418, 3998, 455, 0, 0}, {0, 0, 0, 0, 0, 0}}},                  // 128x128, with loaders
-    {7, 2, {{5748, 641, 5109, 642, 0, 0}, {3972, 691, 2996, 616, 0, 0}, {6532, 647, 5452, 669, 0, 0}}},         // 128x128
-    {9, 2, {{5049, 576, 2896, 96, 1571, 464}, {3637, 623, 1510, 100, 863, 491}, {6006, 592, 2399, 84, 1975, 521}}}, // 128x96
-    {14, 1, {{7913, 840, 9950, 898, 0, 0}, {5170, 892, 4873, 878, 0, 0}, {7679, 822, 6995, 905, 0, 0}}},        // 256x128
-    {13, 1, {{10556, 880, 13677, 1134, 0, 0}, {6198, 970, 6969, 1096, 0, 0}, {9584, 897, 9397, 1130, 0, 0}}},   // 256x192
-    {24, 1, {{10260, 1045, 7938, 1381, 0, 0}, {6076, 1024, 4496, 1170, 0, 0}, {8775, 1012, 5551, 1170, 0, 0}}}, // 256x192, persistent
-    {23, 1, {{11521, 1234, 11232, 1460, 0, 0}, {7038, 1265, 5637, 1470, 0, 0}, {10179, 1155, 6600, 1521, 0, 0}}}, // 256x256, persistent
+    {25, 0, {{2406, 71, 56, 48, 581, 25}, {2372, 87, 116, 37, 320, 41}, {2664, 85, 83, 47, 480, 44}}},              // 16x16, K split
+    {26, 0, {{2463, 92, 33, 69, 1126, 10}, {2376, 109, 88, 58, 766, 27}, {2665, 107, 51, 70, 1077, 18}}},           // 16x32, K split
+    {27, 0, {{2631, 104, 34, 120, 1206, 0}, {2502, 125, 144, 86, 1002, 17}, {2749, 131, 150, 92, 1299, 1}}},        // 32x32, K split
+    {28, 0, {{2876, 148, 1793, 151, 0, 0}, {2698, 175, 1546, 142, 0, 0}, {2997, 172, 1869, 126, 0, 0}}},            // 32x64, K split
+    {29, 0, {{3691, 191, 2714, 219, 0, 0}, {3347, 212, 2371, 190, 0, 0}, {3723, 220, 3034, 166, 0, 0}}},            // 32x96, K split
+    {30, 0, {{3905, 198, 3034, 266, 0, 0}, {3439, 230, 2564, 224, 0, 0}, {3956, 232, 3184, 229, 0, 0}}},            // 64x64, K split
+    {15, 5, {{3500, 159, 581, 77, 0, 0}, {3500, 169, 497, 75, 0, 0}, {3673, 170, 549, 69, 0, 0}}},                  // 32x32, ring
+    {3, 3, {{4609, 277, 1390, 160, 0, 34}, {4205, 304, 914, 147, 0, 75}, {4819, 285, 1060, 137, 749, 68}}},         // 64x64, ring
+    {2, 2, {{7472, 628, 4126, 395, 0, 310}, {6288, 662, 2788, 409, 0, 256}, {0, 0, 0, 0, 0, 0}}},                   // 128x128, ring
+    {17, 2, {{4020, 347, 1212, 163, 1459, 70}, {3501, 377, 823, 116, 1047, 203}, {0, 0, 0, 0, 0, 0}}},              // 64x96, three stages
+    {18, 3, {{3525, 511, 1447, 72, 682, 329}, {3070, 557, 758, 56, 683, 435}, {0, 0, 0, 0, 0, 0}}},                 // 64x96
+    {21, 1, {{5825, 320, 4836, 333, 0, 0}, {4587, 353, 3465, 353, 0, 0}, {0, 0, 0, 0, 0, 0}}},                      // 128x96, with loaders
+    {19, 3, {{3722, 557, 1848, 109, 0, 409}, {3329, 618, 916, 82, 254, 483}, {0, 0, 0, 0, 0, 0}}},                  // 64x128
+    {22, 1, {{6537, 376, 5539, 420, 0, 0}, {4967, 408, 3662, 420, 0, 0}, {0, 0, 0, 0, 0, 0}}},                      // 128x128, with loaders
+    {7, 2, {{5451, 645, 5215, 637, 0, 0}, {3978, 690, 2886, 617, 0, 0}, {6445, 655, 5733, 630, 0, 0}}},             // 128x128
+    {9, 2, {{4894, 572, 2930, 70, 1293, 436}, {3579, 626, 1375, 102, 650, 459}, {5662, 625, 2550, 55, 1694, 526}}}, // 128x96
+    {14, 1, {{7647, 840, 9487, 865, 0, 0}, {5131, 882, 4119, 883, 0, 0}, {7561, 833, 6938, 815, 0, 0}}},            // 256x128
+    {13, 1, {{10461, 862, 13760, 999, 0, 0}, {6109, 963, 5826, 1068, 0, 0}, {9129, 952, 8517, 1062, 0, 0}}},        // 256x192
+    {24, 1, {{10329, 1000, 8312, 1109, 0, 0}, {6078, 997, 3462, 1137, 0, 0}, {8740, 1000, 4486, 1135, 0, 0}}},      // 256x192, persistent
+    {23, 1, {{11503, 1183, 9054, 1420, 0, 0}, {7019, 1225, 3640, 1465, 0, 0}, {9724, 1177, 5830, 1324, 0, 0}}},     // 256x256, persistent
 };
 
 static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb, bool gelu)
@@ -210,7 +238,17 @@ static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb
             if (w.first[0] == 0 || (f.direct && !dma_ok(d, f.bn))) continue;
             if (c.config == 23 && !stream_ok<256, 256, 8>(g, i8)) continue;
             if (c.config == 24 && !stream_ok<256, 192, 8>(g, i8)) continue;
-            const int64_t k = d.K / 128, n = ceil_div(tiles(f.bm, f.bn), 256), r = ceil_div(n, c.share);
+            const int64_t k = d.K / 128;
+            int64_t n, share = c.share;
+            if (share == 0) {
+                if (!few_ok(g, f.bn, i8)) continue;
+                const FewShape s = few_shape(f.bm, f.bn, (int32_t)k);
+                n = ceil_div(few_grid((int32_t)ceil_div(d.M, f.bm), d.N / f.bn).per_xcd, 32);
+                share = std::min<int64_t>(163840 / (int64_t)s.lds, 32 >> s.nwl);
+            } else {
+                n = ceil_div(tiles(f.bm, f.bn), 256);
+            }
+            const int64_t r = ceil_div(n, share);
             const int64_t t = w.first[0] + w.first[1] * k + (n - 1) * (w.more[0] + w.more[1] * k) +
                               (r - 1) * (w.again[0] + w.again[1] * k);
             if (best < 0 || t < best_t) { best = c.config; best_t = t; }
@@ -287,6 +325,12 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
                 case 14: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true, true, 8>(g, i8, stream); break;
                 case 23: return launch_stream<256, 256, 8, true>(g, i8, stream);
                 case 24: return launch_stream<256, 192, 8, true>(g, i8, stream);
+                case 25: return launch_few<1, 1, true>(g, i8, stream);
+                case 26: return launch_few<1, 2, true>(g, i8, stream);
+                case 27: return launch_few<2, 2, true>(g, i8, stream);
+                case 28: return launch_few<2, 4, true>(g, i8, stream);
+                case 29: return launch_few<2, 6, true>(g, i8, stream);
+                case 30: return launch_few<4, 4, true>(g, i8, stream);
                 default: break;
             }
             return IBERT_ERR_NOT_IMPLEMENTED;
@@ -317,6 +361,12 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
             case 22: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
             case 23: if (launch_stream<256, 256, 8, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
             case 24: if (launch_stream<256, 192, 8, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
+            case 25: if (launch_few<1, 1, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
+            case 26: if (launch_few<1, 2, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
+            case 27: if (launch_few<2, 2, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
+            case 28: if (launch_few<2, 4, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
+            case 29: if (launch_few<2, 6, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
+            case 30: if (launch_few<4, 4, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
             default: break;
         }
         return launch_mfma<128, 128, 64, 2>(g, i8, stream);

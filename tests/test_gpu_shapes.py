@@ -119,3 +119,13 @@ def test_gemm_direct_to_lds_ragged_rows(G, cfg, bm, bn):
     for M, N, K in [(1, bn, 128), (bm - 1, 2 * bn, 256), (bm + 1, bn, 512), (3 * bm + 37, 2 * bn, 384)]:
         for kind in kinds:
             _stream_case(G, cfg, M, N, K, kind, 40, seed=M + N + K, form=False)
+
+
+@pytest.mark.parametrize("cfg,bm,bn", [(25, 16, 16), (26, 16, 32), (27, 32, 32), (28, 32, 64), (29, 32, 96), (30, 64, 64)])
+@pytest.mark.parametrize("kind", ["i8", "i16", "i16res", "gelu"])
+def test_gemm_few_rows(G, cfg, bm, bn, kind):
+    # K from one step (fewer than wavefronts) to more steps than are in flight at once, where a stage is used again; rows at, one
+    # past and off a tile edge; tile columns that do and do not divide by the XCDs; both epilogue forms
+    for M, N, K, shift in [(1, bn, 128, 40), (bm, 8 * bn, 640, 40), (bm + 1, 3 * bn, 1024, 40), (3 * bm + 7, 12 * bn, 1152, 40),
+                           (2 * bm - 1, 2 * bn, 5248, 40), (bm + 3, 5 * bn, 256, 30), (17 * bm, 9 * bn, 384, 40)]:
+        _stream_case(G, cfg, M, N, K, kind, shift, seed=M + N + K, form=False)
