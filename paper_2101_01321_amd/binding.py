@@ -173,10 +173,23 @@ def _dp(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+_raw_stream = None
+
+
 def _stream(stream=None) -> int:
-    import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    """Handle of `stream`, or of torch's current stream on the current device.  The latter is asked for by its handle:
+    torch.cuda.current_stream() makes a Stream object of it first, 3 us a call, more than a launch costs."""
+    global _raw_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        import torch
+        first = torch.cuda.current_stream().cuda_stream          # (initializes the device)
+        get, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if get is None or device is None:
+            return first
+        _raw_stream = lambda: get(device())
+    return _raw_stream()
 
 
 # ------------------------------------------------------------------------- host helpers
