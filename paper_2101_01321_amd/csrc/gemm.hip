@@ -9,7 +9,6 @@
 namespace ibert {
 
 #define IBERT_GEMM_INSTANCE(...) extern template int launch_mfma<__VA_ARGS__>(GemmArgs&, bool, hipStream_t);
-#include "gemm_instances_a.inc"
 #include "gemm_instances_b.inc"
 #include "gemm_instances_c.inc"
 #include "gemm_instances_d.inc"
@@ -97,38 +96,40 @@ struct GemmConfig {
     int bm, bn, bk, ring;
     bool direct;          // direct-to-LDS loader (N and K in whole tiles; ring = LDS stages) or register ring
 };
+// (0, 1, 5, 6, 8, 10, 11, 12, 16 and 20 were tiles that the rule below never takes any more, as another kernel with the same
+//  tile is faster for every problem; their numbers stand for that one.)
 static const GemmConfig kConfigs[] = {      // index = configuration number of ibert_gemm_config_override
-    {256, 192, 128, 2, false},
-    {128, 128, 128, 2, false},
+    {256, 192, 128, 2, true},       // = 13
+    {128, 128, 128, 2, true},       // = 7
     {128, 128, 64, 2, false},
     {64, 64, 128, 3, false},
     {64, 128, 64, 3, false},
-    {128, 96, 128, 2, false},
-    {256, 192, 128, 2, true},
+    {128, 96, 128, 2, true},        // = 9
+    {256, 192, 128, 2, true},       // = 13
     {128, 128, 128, 2, true},
-    {256, 256, 128, 2, true},
+    {256, 256, 128, 2, true},       // = 23
     {128, 96, 128, 2, true},
-    {256, 128, 128, 2, true},
-    {128, 96, 128, 3, true},
-    {128, 128, 128, 3, true},
-    {256, 192, 128, 2, true},       // with eight wavefronts
-    {256, 128, 128, 2, true},       // with eight wavefronts
+    {256, 128, 128, 2, true},       // = 14
+    {128, 96, 128, 3, true},        // = 21
+    {128, 128, 128, 3, true},       // = 22
+    {256, 192, 128, 2, true},       // eight wavefronts
+    {256, 128, 128, 2, true},       // eight wavefronts
     {32, 32, 128, 4, false},
-    {256, 256, 128, 2, true},       // with eight wavefronts
+    {256, 256, 128, 2, true},       // = 23
     {64, 96, 128, 3, true},
     {64, 96, 128, 2, true},
     {64, 128, 128, 2, true},
-    {128, 96, 128, 3, true},        // with eight wavefronts (four rows of two)
-    {128, 96, 128, 3, true},        // the same with four more wavefronts that only request tiles
-    {128, 128, 128, 3, true},       // eight wavefronts and four that only request tiles
+    {128, 96, 128, 3, true},        // = 21
+    {128, 96, 128, 3, true},        // eight wavefronts in four rows of two and four that only request tiles
+    {128, 128, 128, 3, true},       // the same
     {256, 256, 128, 2, true},       // persistent (gemm_stream.h)
     {256, 192, 128, 2, true},       // persistent
-    {16, 16, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
-    {16, 32, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
-    {32, 32, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
-    {32, 64, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
-    {32, 96, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
-    {64, 64, 128, 4, true},       // K split over the wavefronts (gemm_few.h)
+    {16, 16, 128, 4, true},         // K split over the wavefronts (gemm_few.h)
+    {16, 32, 128, 4, true},
+    {32, 32, 128, 4, true},
+    {32, 64, 128, 4, true},
+    {32, 96, 128, 4, true},
+    {64, 64, 128, 4, true},
 };
 constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
 static int g_config_override = -1;
@@ -317,12 +318,10 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
             switch (cfg) {
                 case 3: return launch_mfma<64, 64, 128, 3, false, false, true>(g, i8, stream);
                 case 15: return launch_mfma<32, 32, 128, 4, false, false, true>(g, i8, stream);
-                case 6: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true, true>(g, i8, stream); break;
                 case 7: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 2, false, true, true>(g, i8, stream); break;
                 case 9: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 2, false, true, true>(g, i8, stream); break;
-                case 10: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true, true>(g, i8, stream); break;
-                case 13: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true, true, 8>(g, i8, stream); break;
-                case 14: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true, true, 8>(g, i8, stream); break;
+                case 6: case 13: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true, true, 8>(g, i8, stream); break;
+                case 10: case 14: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true, true, 8>(g, i8, stream); break;
                 case 23: return launch_stream<256, 256, 8, true>(g, i8, stream);
                 case 24: return launch_stream<256, 192, 8, true>(g, i8, stream);
                 case 25: return launch_few<1, 1, true>(g, i8, stream);
@@ -336,30 +335,20 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
             return IBERT_ERR_NOT_IMPLEMENTED;
         }
         switch (cfg) {
-            case 0: return launch_mfma<256, 192, 128, 2>(g, i8, stream);
-            case 1: return launch_mfma<128, 128, 128, 2>(g, i8, stream);
             case 2: return launch_mfma<128, 128, 64, 2>(g, i8, stream);
             case 3: return launch_mfma<64, 64, 128, 3>(g, i8, stream);
             case 4: return launch_mfma<64, 128, 64, 3>(g, i8, stream);
-            case 5: return launch_mfma<128, 96, 128, 2>(g, i8, stream);
-            case 6: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true>(g, i8, stream); break;
-            case 7: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 2, false, true>(g, i8, stream); break;
-            case 8: if (dma_ok(d, 256)) return launch_mfma<256, 256, 128, 2, false, true>(g, i8, stream); break;
-            case 9: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 2, false, true>(g, i8, stream); break;
-            case 10: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true>(g, i8, stream); break;
-            case 11: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 3, false, true>(g, i8, stream); break;
-            case 12: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 3, false, true>(g, i8, stream); break;
-            case 13: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true, false, 8>(g, i8, stream); break;
-            case 14: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true, false, 8>(g, i8, stream); break;
+            case 1: case 7: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 2, false, true>(g, i8, stream); break;
+            case 5: case 9: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 2, false, true>(g, i8, stream); break;
+            case 0: case 6: case 13: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true, false, 8>(g, i8, stream); break;
+            case 10: case 14: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true, false, 8>(g, i8, stream); break;
             case 15: return launch_mfma<32, 32, 128, 4>(g, i8, stream);
-            case 16: if (dma_ok(d, 256)) return launch_mfma<256, 256, 128, 2, false, true, false, 8>(g, i8, stream); break;
             case 17: if (dma_ok(d, 96)) return launch_mfma<64, 96, 128, 3, false, true>(g, i8, stream); break;
             case 18: if (dma_ok(d, 96)) return launch_mfma<64, 96, 128, 2, false, true>(g, i8, stream); break;
             case 19: if (dma_ok(d, 128)) return launch_mfma<64, 128, 128, 2, false, true>(g, i8, stream); break;
-            case 20: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 3, false, true, false, 8>(g, i8, stream); break;
-            case 21: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
-            case 22: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
-            case 23: if (launch_stream<256, 256, 8, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
+            case 11: case 20: case 21: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
+            case 12: case 22: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
+            case 8: case 16: case 23: if (launch_stream<256, 256, 8, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
             case 24: if (launch_stream<256, 192, 8, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
             case 25: if (launch_few<1, 1, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
             case 26: if (launch_few<1, 2, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;

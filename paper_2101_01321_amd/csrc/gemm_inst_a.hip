@@ -1,11 +1,7 @@
-// Instantiations of the MFMA MatMul kernel (gemm_kernel.h) for the tile configurations of gemm_instances_a.inc.
+// The MFMA MatMul kernel (gemm_kernel.h) with the bytewise tail loader.
 #include "gemm_kernel.h"
 
 namespace ibert {
-
-#define IBERT_GEMM_INSTANCE(...) template int launch_mfma<__VA_ARGS__>(GemmArgs&, bool, hipStream_t);
-#include "gemm_instances_a.inc"
-#undef IBERT_GEMM_INSTANCE
 
 // K not a multiple of 16 (rows still 16-byte aligned): one configuration with the bytewise tail loader.
 int launch_tail(GemmArgs& g, bool i8, hipStream_t stream)
