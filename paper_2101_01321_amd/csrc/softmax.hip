@@ -44,9 +44,19 @@ __device__ __forceinline__ uint32_t group_sum(uint32_t v)
 
 constexpr int SM_THREADS = 256;
 
-// LPR lanes per row, NCH chunks of 4 elements per lane.  ALIGNED: rows start 16-byte aligned (x) and
-// 4-byte aligned (int8 y) / 16-byte aligned (int32 y), so full chunks move as vectors.
-template <int LPR, int NCH, bool ALIGNED, bool OUT_I8, bool FAST>
+// VECTORS: the chunks of 4 elements move as vectors whatever the alignment of the rows (attention logits of text have as many
+// columns as the longest sentence has tokens).  Global memory takes vectors at any element's address, and the last chunk of a
+// row, when it is not full, is moved back to end with the row: its lane reads and writes up to three columns a second time (the
+// same bytes) but leaves them out of the sum, so no chunk takes a branch per element.  Otherwise (fewer than 4 columns):
+// element by element.
+// Measured against vectors for aligned rows only and single elements elsewhere, us, inputs from memory: [49152,125] 12.5 -> 8.5,
+// [64256,251] 27.3 -> 17.0, [98112,511] 74.2 -> 46.3 (5.4 TB/s); aligned rows gain from the missing branch too: [49152,128]
+// 9.0 -> 8.6, [98304,512] 45.6 -> 44.3 (5.7 TB/s).
+typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
+
+// LPR lanes per row, NCH chunks of 4 elements per lane.
+template <int LPR, int NCH, bool VECTORS, bool OUT_I8, bool FAST>
 __global__ __launch_bounds__(SM_THREADS) void softmax_rows_kernel(SoftmaxArgs a)
 {
     constexpr int ROWS_PER_BLOCK = SM_THREADS / LPR;
@@ -55,16 +65,20 @@ __global__ __launch_bounds__(SM_THREADS) void softmax_rows_kernel(SoftmaxArgs a)
     const bool live = row < a.rows;
     const int32_t* xr = a.x + (live ? row : 0) * a.ldx;
     const int32_t nk = live_cols(a, live ? row : 0);
+    // first column of the lane's chunk c, and the first of them that is the lane's own
+    auto own_of = [&](int c) { return (c * LPR + lane) * 4; };
+    auto col_of = [&](int c) { const int col = own_of(c); return VECTORS && col > a.cols - 4 ? a.cols - 4 : col; };
 
     int32_t q[NCH][4];
     int32_t mx = INT32_MIN;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-        const int col = (c * LPR + lane) * 4;
-        if (ALIGNED && live && col + 3 < a.cols) {
-            const int4 v = *reinterpret_cast<const int4*>(xr + col);
-            q[c][0] = col < nk ? v.x : INT32_MIN; q[c][1] = col + 1 < nk ? v.y : INT32_MIN;
-            q[c][2] = col + 2 < nk ? v.z : INT32_MIN; q[c][3] = col + 3 < nk ? v.w : INT32_MIN;
+        const int col = col_of(c);
+        if (VECTORS) {
+            i32x4_any v = {INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN};
+            if (own_of(c) < a.cols) v = *reinterpret_cast<const i32x4_any*>(xr + col);       // (row 0 where there is no row)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) q[c][e] = col + e < nk ? v[e] : INT32_MIN;
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e) q[c][e] = (live && col + e < nk) ? xr[col + e] : INT32_MIN;
@@ -80,13 +94,18 @@ __global__ __launch_bounds__(SM_THREADS) void softmax_rows_kernel(SoftmaxArgs a)
     uint32_t sum = 0;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-        const int col = (c * LPR + lane) * 4;
+        const int col = col_of(c), own = own_of(c);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const uint32_t d = (uint32_t)mx - (uint32_t)q[c][e];
             const uint32_t v = FAST ? iexp_from_diff_fast(d, a.c) : iexp_from_diff(d, a.c);
-            ex[c][e] = (col + e < a.cols) ? v : 0u;
-            sum += ex[c][e];
+            if (VECTORS) {
+                ex[c][e] = v;
+                sum += (col + e >= own && own < a.cols) ? v : 0u;
+            } else {
+                ex[c][e] = (col + e < a.cols) ? v : 0u;
+                sum += ex[c][e];
+            }
         }
     }
     sum = group_sum<LPR>(sum);
@@ -95,7 +114,7 @@ __global__ __launch_bounds__(SM_THREADS) void softmax_rows_kernel(SoftmaxArgs a)
 
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-        const int col = (c * LPR + lane) * 4;
+        const int col = col_of(c);
         uint32_t o[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -105,8 +124,9 @@ __global__ __launch_bounds__(SM_THREADS) void softmax_rows_kernel(SoftmaxArgs a)
         }
         if (OUT_I8) {
             int8_t* yr = reinterpret_cast<int8_t*>(a.y) + row * a.ldy;
-            if (ALIGNED && col + 3 < a.cols) {
-                *reinterpret_cast<uint32_t*>(yr + col) = o[0] | (o[1] << 8) | (o[2] << 16) | (o[3] << 24);
+            if (VECTORS) {
+                if (own_of(c) < a.cols)
+                    *reinterpret_cast<u32_any*>(yr + col) = o[0] | (o[1] << 8) | (o[2] << 16) | (o[3] << 24);
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -114,8 +134,9 @@ __global__ __launch_bounds__(SM_THREADS) void softmax_rows_kernel(SoftmaxArgs a)
             }
         } else {
             int32_t* yr = reinterpret_cast<int32_t*>(a.y) + row * a.ldy;
-            if (ALIGNED && col + 3 < a.cols) {
-                *reinterpret_cast<int4*>(yr + col) = make_int4((int)o[0], (int)o[1], (int)o[2], (int)o[3]);
+            if (VECTORS) {
+                if (own_of(c) < a.cols)
+                    *reinterpret_cast<i32x4_any*>(yr + col) = i32x4_any{(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -184,22 +205,14 @@ int check_softmax(const ibert_softmax_params& p, int32_t cols)
     return IBERT_OK;
 }
 
-template <int LPR, int NCH>
-static void launch_rows(const SoftmaxArgs& a, bool al, bool i8, bool fast, hipStream_t stream)
+template <int LPR, int NCH, bool VECTORS = true>
+static void launch_rows(const SoftmaxArgs& a, bool i8, bool fast, hipStream_t stream)
 {
     constexpr int rpb = SM_THREADS / LPR;
     const dim3 grid((unsigned)((a.rows + rpb - 1) / rpb)), block(SM_THREADS);
-    if (al && i8 && fast) {                 // the layer's case
-        hipLaunchKernelGGL((softmax_rows_kernel<LPR, NCH, true, true, true>), grid, block, 0, stream, a);
-    } else if (al && i8) {
-        hipLaunchKernelGGL((softmax_rows_kernel<LPR, NCH, true, true, false>), grid, block, 0, stream, a);
-    } else if (al) {
-        hipLaunchKernelGGL((softmax_rows_kernel<LPR, NCH, true, false, false>), grid, block, 0, stream, a);
-    } else if (i8) {
-        hipLaunchKernelGGL((softmax_rows_kernel<LPR, NCH, false, true, false>), grid, block, 0, stream, a);
-    } else {
-        hipLaunchKernelGGL((softmax_rows_kernel<LPR, NCH, false, false, false>), grid, block, 0, stream, a);
-    }
+    if (i8 && fast) hipLaunchKernelGGL((softmax_rows_kernel<LPR, NCH, VECTORS, true, true>), grid, block, 0, stream, a);
+    else if (i8) hipLaunchKernelGGL((softmax_rows_kernel<LPR, NCH, VECTORS, true, false>), grid, block, 0, stream, a);
+    else hipLaunchKernelGGL((softmax_rows_kernel<LPR, NCH, VECTORS, false, false>), grid, block, 0, stream, a);
 }
 
 int launch_softmax(const int32_t* x, void* y, int64_t rows, int32_t cols, int64_t ldx, int64_t ldy,
@@ -212,15 +225,15 @@ int launch_softmax(const int32_t* x, void* y, int64_t rows, int32_t cols, int64_
     a.c = softmax_const(p);
     const bool i8 = p.out_dtype == IBERT_I8;
     const bool fast = softmax_fast_ok(p);
-    const bool al = aligned(x, 16) && ldx % 4 == 0 && (i8 ? (aligned(y, 4) && ldy % 4 == 0) : (aligned(y, 16) && ldy % 4 == 0));
     if (rows > 0x7fffffffLL) return IBERT_ERR_SHAPE;
 
-    if (cols <= 16 * 4) launch_rows<16, 1>(a, al, i8, fast, stream);
-    else if (cols <= 16 * 8) launch_rows<16, 2>(a, al, i8, fast, stream);
-    else if (cols <= 32 * 8) launch_rows<32, 2>(a, al, i8, fast, stream);
-    else if (cols <= 64 * 8) launch_rows<64, 2>(a, al, i8, fast, stream);
-    else if (cols <= 64 * 16) launch_rows<64, 4>(a, al, i8, fast, stream);
-    else if (cols <= 64 * 32) launch_rows<64, 8>(a, al, i8, fast, stream);
+    if (cols < 4) launch_rows<16, 1, false>(a, i8, fast, stream);
+    else if (cols <= 16 * 4) launch_rows<16, 1>(a, i8, fast, stream);
+    else if (cols <= 16 * 8) launch_rows<16, 2>(a, i8, fast, stream);
+    else if (cols <= 32 * 8) launch_rows<32, 2>(a, i8, fast, stream);
+    else if (cols <= 64 * 8) launch_rows<64, 2>(a, i8, fast, stream);
+    else if (cols <= 64 * 16) launch_rows<64, 4>(a, i8, fast, stream);
+    else if (cols <= 64 * 32) launch_rows<64, 8>(a, i8, fast, stream);
     else {
         if (i8) hipLaunchKernelGGL(softmax_long_kernel<true>, dim3((unsigned)rows), dim3(SM_THREADS), 0, stream, a);
         else hipLaunchKernelGGL(softmax_long_kernel<false>, dim3((unsigned)rows), dim3(SM_THREADS), 0, stream, a);

@@ -129,3 +129,28 @@ def test_gemm_few_rows(G, cfg, bm, bn, kind):
     for M, N, K, shift in [(1, bn, 128, 40), (bm, 8 * bn, 640, 40), (bm + 1, 3 * bn, 1024, 40), (3 * bm + 7, 12 * bn, 1152, 40),
                            (2 * bm - 1, 2 * bn, 5248, 40), (bm + 3, 5 * bn, 256, 30), (17 * bm, 9 * bn, 384, 40)]:
         _stream_case(G, cfg, M, N, K, kind, shift, seed=M + N + K, form=False)
+
+
+# ------------------------------------------------------------------------------------------- Softmax, rows that start anywhere
+@pytest.mark.parametrize("cols", [1, 3, 4, 5, 7, 61, 62, 63, 65, 127, 129, 251, 257, 511, 513, 1023, 1025, 2045])
+@pytest.mark.parametrize("k,od", [(7, I8), (24, I32)])
+def test_softmax_rows_at_any_address(G, cols, k, od):
+    # the last chunk of a row is moved back over the one before it: its columns count once, nothing outside the row is written,
+    # and a mask that ends before, inside and after the columns that are read twice is kept
+    from paper_2101_01321_amd import binding as B
+    rows = 19
+    S = 2.0 ** -6
+    x, _ = synth.softmax_logits(rows, cols, scale=S)
+    x[0, :], x[1, :] = 5, -2 ** 31
+    x[2, -1], x[3, 0] = x.max() + 1, x.max() + 1
+    sp, op = B.ibert_softmax_params_from_scale(S, cols, k, od), P.softmax_params(S, k, od)
+    for ldx, ldy, xo, yo in [(cols, cols, 0, 0), (cols + 1, cols + 2, 1, 1), (cols + 4 - cols % 4, cols + 4 - cols % 4, 0, 0)]:
+        G.say("softmax cols=%d ldx=%d ldy=%d out=%d" % (cols, ldx, ldy, od))
+        got = G.softmax(x, sp, ldx=ldx, ldy=ldy, x_off=xo, y_off=yo)
+        _eq(got[:, :cols], oracle.softmax(x, op), "softmax cols=%d" % cols)
+        assert np.all(got[:, cols:] == 77)
+        lens = np.array([max(1, cols - 5), max(1, cols - 2), cols, 1] * 5, np.int32)[:rows]
+        masked = np.where(np.arange(cols)[None, :] < lens[:, None], x, np.int32(-2 ** 31)).astype(np.int32)
+        got = G.softmax(x, sp, ldx=ldx, ldy=ldy, x_off=xo, y_off=yo, key_lens=lens)
+        _eq(got[:, :cols], oracle.softmax(masked, op), "masked softmax cols=%d" % cols)
+        assert np.all(got[:, cols:] == 77)
