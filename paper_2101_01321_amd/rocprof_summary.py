@@ -43,6 +43,9 @@ def step_of(name):
         return "EMB" if len(a) > 3 and a[3] == "true" else "LN"
     if name.startswith("gelu_kernel"):
         return "hGELU" if name.endswith("true>") else "GELU"
+    m = re.match(r"gemm_(?:stream|few)_kernel<.*, (\w+), (\w+)>$", name)
+    if m:
+        return "S7+8" if m.group(2) == "true" else "S1" if m.group(1) == "true" else "S5/S9"
     m = re.match(r"gemm_nt_mfma_kernel<(\d+), (\d+), (\d+), (\d+), (\w+), (\d), (\w+), (\w+), (\w+), (\d+), (\d+)>", name)
     if not m:
         return "?"
