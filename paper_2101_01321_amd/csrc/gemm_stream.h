@@ -268,6 +268,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
             // this half) group 0 of the one after
             if (REQ == 1 && left >= 3) __builtin_amdgcn_s_waitcnt(vm(N1 + N0));
             else if (left >= 2) __builtin_amdgcn_s_waitcnt(vm(N1));
+        } else if (REQ == 2 && g.nk == 1) {
+            // the tile has no later step whose wait covers the constants requested at its head; behind them nothing has been
+            // requested yet (counting would not do: the last tile's stores stand in the queue before them)
+            __builtin_amdgcn_s_waitcnt(vm(0));
         }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         quadrant(w0, NI0{}, 0, ab, FMH, [&](int idx) {
@@ -300,7 +304,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         for (int q = 0; q < 2 * FMH; ++q) read_a(at, stage, 0, q);
 #pragma unroll
         for (int q = 0; q < 2 * FN0; ++q) read_w0(stage, q);
-        // (the first two steps of a tile that follows another were waited for before that one's stores, see below)
+        // (the first two steps of a tile that follows another were waited for before that one's stores, see below; its constants,
+        // requested just now, are covered by the first wait of its second step, which leaves only younger requests outstanding --
+        // a tile of one step waits for them by itself)
         step(R2{}, first);
         for (int kt = 1; kt < g.nk; ++kt) step(R1{}, true);
 

@@ -110,6 +110,54 @@ def test_gemm_persistent_tiles(G, cfg, bn, kind):
         _stream_case(G, cfg, M, N, K, kind, shift, seed=M + N + K)
 
 
+@pytest.mark.parametrize("cfg,bn", [(23, 256), (24, 192)])
+@pytest.mark.parametrize("kind", ["i8", "i16", "i16res", "gelu"])
+@pytest.mark.parametrize("cols,shift", [(3, 40), (9, 40), (3, 30)])
+def test_gemm_persistent_tiles_of_one_step(G, cfg, bn, kind, cols, shift):
+    # K 128: a tile is a single K step, so the constants of its columns, requested at its head, have that step alone to arrive
+    # in.  More than four tiles for every workgroup, in another tile column each time (3 and 9 do not divide the 32
+    # workgroups of an XCD), and constants that differ from column to column by far more than an output step.  The rows
+    # repeat after 509 (which no tile edge does), so that the oracle's work stays small.
+    import torch
+    from paper_2101_01321_amd import binding as B
+    P_, M, N, K = 509, 256 * (4 * 256 // cols + 8) + 3, cols * bn, 128
+    rng = np.random.default_rng(cfg + cols + shift)
+    A, W = (rng.integers(-127, 128, size=(n, K), dtype=np.int8) for n in (P_, N))
+    R = rng.integers(-127, 128, size=(P_, N), dtype=np.int8) if kind == "i16res" else None
+    col = np.arange(N) // bn                                       # (one sign and size of the constants per tile column)
+    bias = ((col % 2 * 2 - 1) * (40000 + 30000 * col) + np.arange(N) % 97).astype(np.int32)
+    mult = ((2 ** 28 + 2 ** 26 * col) * (1 - 2 * (col % 3 == 1))).astype(np.int32)
+    shifts = (34 if kind == "gelu" and shift == 40 else shift) + (col % 3 if shift == 40 else 0 * col).astype(np.int32)
+    res_dy = (1717986918, 23)
+    rows = torch.arange(M, device=G.DEV) % P_
+    tA, tW, tb, tm, ts = G.to_dev(A)[rows], G.to_dev(W), G.to_dev(bias), G.to_dev(mult), G.to_dev(shifts)
+    d = B.GemmDesc()
+    for k, v in dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K, ldw=K, ldc=N, ldr=N, per_channel=1,
+                     residual_dy=B.Dyadic(*res_dy), out_dtype=I16 if kind[:3] == "i16" else I8,
+                     out_clamp=127 if kind == "i8" else 32767).items():
+        setattr(d, k, v)
+    tC = torch.full((M, N), 77, dtype=torch.int16 if kind[:3] == "i16" else torch.int8, device=G.DEV)
+    gp, op = B.ibert_gelu_params_from_scale(2.0 ** -6, 0.7), P.gelu_params(2.0 ** -6, 0.7)
+    B.lib().ibert_gemm_config_override(cfg)
+    try:
+        G.say("persistent gemm of one step cfg %d M=%d N=%d %s shift=%d" % (cfg, M, N, kind, shift))
+        if kind == "gelu":
+            B.ibert_gemm_i8_gelu(d, tA, tW, tb, tm, ts, gp, tC, torch.empty(M * N, dtype=torch.int32, device=G.DEV))
+        else:
+            B.ibert_gemm_i8_requant(d, tA, tW, tb, tm, ts, None if R is None else G.to_dev(R)[rows], tC)
+        torch.cuda.synchronize()
+    finally:
+        B.lib().ibert_gemm_config_override(-1)
+    spec = GemmSpec(P_, N, K, per_channel=1, dy=(1, 0), out_dtype=I8 if kind == "i8" else I32,
+                    out_clamp={"i8": 127, "gelu": gp.q_max}.get(kind, 32767), res_dy=res_dy)
+    want = oracle.gemm_requant(spec, A, W, bias, mult, shifts, R).reshape(P_, N)
+    if kind == "gelu":
+        want = oracle.gelu(want.reshape(-1), op).reshape(P_, N)
+    assert len(np.unique(want)) > 20
+    bad = (tC != G.to_dev(want.astype(np.int16 if kind[:3] == "i16" else np.int8))[rows]).sum().item()
+    assert bad == 0, "%d of %d values differ" % (bad, M * N)
+
+
 @pytest.mark.parametrize("cfg,bm,bn", [(6, 256, 192), (7, 128, 128), (8, 256, 256), (9, 128, 96), (10, 256, 128), (11, 128, 96),
                                        (12, 128, 128), (13, 256, 192), (14, 256, 128), (16, 256, 256), (17, 64, 96), (18, 64, 96),
                                        (19, 64, 128), (20, 128, 96), (21, 128, 96), (22, 128, 128)])
