@@ -405,7 +405,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             const bool is_a = q < NLA;
             const int i = is_a ? q : q - NLA;
             const int first = row_in(i * RG + wv * 8);              // (A: the block's first row, and how far its rows may reach)
-            const uint32_t most = (uint32_t)(rlast - first) * (uint32_t)g.lda;
+            const uint32_t most = (uint32_t)(rlast - first < 7 ? rlast - first : 7) * (uint32_t)g.lda;   // (rlast * lda may pass 2^32)
             const int8_t* sb = (is_a ? ga + (int64_t)first * g.lda : gw + (int64_t)i * RG * g.ldw) + (int64_t)kt * BK;
             const uint32_t la = lds0 + (uint32_t)(buf * STAGE + (is_a ? 0 : BM * BK) + i * (RG * BK));
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"

@@ -129,7 +129,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         const uint32_t la = rstage + (uint32_t)((is_a ? 0 : BM * 128) + row * 128);
         const int first = is_a ? (row < rlast ? row : rlast) : row;
         const int8_t* sb = is_a ? ra + (int64_t)first * g.lda : rw + (int64_t)first * g.ldw;
-        const uint32_t most = (uint32_t)(rlast - first) * (uint32_t)g.lda;
+        const uint32_t most = (uint32_t)(rlast - first < 7 ? rlast - first : 7) * (uint32_t)g.lda;   // (rlast * lda may pass 2^32)
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                      :: "s"(la), "v"(is_a ? (va < most ? va : most) + chunk : vw), "s"(sb) : "memory", "m0");
     };

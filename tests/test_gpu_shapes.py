@@ -169,6 +169,36 @@ def test_gemm_direct_to_lds_ragged_rows(G, cfg, bm, bn):
             _stream_case(G, cfg, M, N, K, kind, 40, seed=M + N + K, form=False)
 
 
+@pytest.mark.parametrize("cfg,bn,lda,M", [(7, 128, 1 << 22, 1025), (9, 96, 1 << 22, 1030), (13, 192, 1 << 22, 1025), (14, 128, 1 << 22, 1033),
+                                          (17, 96, 1 << 22, 1025), (21, 96, 1 << 22, 1025), (22, 128, 1 << 22, 1025),
+                                          (23, 256, 1 << 19, 8193), (24, 192, 1 << 19, 8198)])
+def test_gemm_rows_four_gigabytes_apart(G, cfg, bn, lda, M):
+    # rows of A that lie more than 2^32 bytes behind a tile's first row: the distance to the last row, which a ragged tile's
+    # addresses are clamped by, does not wrap around (M - 1 rows are 2^32 bytes, or a few rows more)
+    import torch
+    from paper_2101_01321_amd import binding as B
+    N, K = 2 * bn, 256
+    rng = np.random.default_rng(cfg)
+    A, W = (rng.integers(-127, 128, size=(n, K), dtype=np.int8) for n in (M, N))
+    bias, mult, shift = np.arange(N, dtype=np.int32), np.full(N, 2 ** 30, np.int32), np.full(N, 41, np.int32)
+    tA = torch.empty(M * lda, dtype=torch.int8, device=G.DEV)
+    tA.view(M, lda)[:, :K] = G.to_dev(A)
+    tC = torch.full((M, N), 77, dtype=torch.int8, device=G.DEV)
+    d = B.GemmDesc()
+    d.M, d.N, d.K, d.batch_outer, d.batch_inner = M, N, K, 1, 1
+    d.lda, d.ldw, d.ldc, d.ldr = lda, K, N, N
+    d.per_channel, d.out_dtype, d.out_clamp = 1, I8, 127
+    B.lib().ibert_gemm_config_override(cfg)
+    try:
+        G.say("gemm rows far apart cfg %d M=%d lda=%d" % (cfg, M, lda))
+        B.ibert_gemm_i8_requant(d, tA, G.to_dev(W), G.to_dev(bias), G.to_dev(mult), G.to_dev(shift), None, tC)
+        torch.cuda.synchronize()
+    finally:
+        B.lib().ibert_gemm_config_override(-1)
+    spec = GemmSpec(M, N, K, per_channel=1, dy=(1, 0), out_dtype=I8, out_clamp=127)
+    _eq(tC.cpu().numpy(), oracle.gemm_requant(spec, A, W, bias, mult, shift, None).reshape(M, N), "gemm, rows far apart")
+
+
 @pytest.mark.parametrize("cfg,bm,bn", [(25, 16, 16), (26, 16, 32), (27, 32, 32), (28, 32, 64), (29, 32, 96), (30, 64, 64)])
 @pytest.mark.parametrize("kind", ["i8", "i16", "i16res", "gelu"])
 def test_gemm_few_rows(G, cfg, bm, bn, kind):
