@@ -334,6 +334,7 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
             }
             return IBERT_ERR_NOT_IMPLEMENTED;
         }
+        int rc = IBERT_ERR_NOT_IMPLEMENTED;                         // (a problem that the kernel does not serve)
         switch (cfg) {
             case 2: return launch_mfma<128, 128, 64, 2>(g, i8, stream);
             case 3: return launch_mfma<64, 64, 128, 3>(g, i8, stream);
@@ -348,17 +349,17 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
             case 19: if (dma_ok(d, 128)) return launch_mfma<64, 128, 128, 2, false, true>(g, i8, stream); break;
             case 11: case 20: case 21: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
             case 12: case 22: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 3, false, true, false, 8, 4>(g, i8, stream); break;
-            case 8: case 16: case 23: if (launch_stream<256, 256, 8, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
-            case 24: if (launch_stream<256, 192, 8, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
-            case 25: if (launch_few<1, 1, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
-            case 26: if (launch_few<1, 2, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
-            case 27: if (launch_few<2, 2, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
-            case 28: if (launch_few<2, 4, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
-            case 29: if (launch_few<2, 6, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
-            case 30: if (launch_few<4, 4, false>(g, i8, stream) == IBERT_OK) return IBERT_OK; break;
+            case 8: case 16: case 23: rc = launch_stream<256, 256, 8, false>(g, i8, stream); break;
+            case 24: rc = launch_stream<256, 192, 8, false>(g, i8, stream); break;
+            case 25: rc = launch_few<1, 1, false>(g, i8, stream); break;
+            case 26: rc = launch_few<1, 2, false>(g, i8, stream); break;
+            case 27: rc = launch_few<2, 2, false>(g, i8, stream); break;
+            case 28: rc = launch_few<2, 4, false>(g, i8, stream); break;
+            case 29: rc = launch_few<2, 6, false>(g, i8, stream); break;
+            case 30: rc = launch_few<4, 4, false>(g, i8, stream); break;
             default: break;
         }
-        return launch_mfma<128, 128, 64, 2>(g, i8, stream);
+        return rc != IBERT_ERR_NOT_IMPLEMENTED ? rc : launch_mfma<128, 128, 64, 2>(g, i8, stream);
     }
     const bool fast_tw = d.trans_w == 1 && d.K > 0 && d.K % 16 == 0 && d.N >= 4 && d.N % 4 == 0 && aligned(A, 16) &&
                          aligned(W, 4) && d.lda % 16 == 0 && d.ldw % 4 == 0 && d.strideA_outer % 16 == 0 &&

@@ -267,7 +267,7 @@ int launch_few(const GemmArgs& g, bool i8, hipStream_t stream)
     f.c16 = g.c16;
     f.gelu_fast = g.gelu_fast; f.gelu = g.gelu;
     const int64_t blocks = 8 * fg.per_xcd;
-    if (blocks > 0x7fffffffLL) return IBERT_ERR_SHAPE;
+    if (blocks > 0x7fffffffLL) return IBERT_ERR_NOT_IMPLEMENTED;         // (larger tiles make fewer of them)
     const FewShape fs = few_shape(16 * HM, 16 * HN, f.nk);
     f.nwl = fs.nwl; f.stages = fs.stages;
 #define IBERT_FEW_LAUNCH(I8_)                                                                                       \

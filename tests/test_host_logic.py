@@ -229,6 +229,37 @@ def test_fused_entry_points_reject_bad_arguments_before_touching_the_gpu():
     assert B.ibert_layer_quant_from_scales(synth.static_scales(synth.CONFIGS["tiny"], 0.03), 128, 64).route == 0
 
 
+def _matmul_desc(M, N, K, **kw):
+    d = B.GemmDesc()
+    d.M, d.N, d.K, d.batch_outer, d.batch_inner = M, N, K, 1, 1
+    d.lda, d.ldw, d.ldc, d.ldr = K, K, N, N
+    d.per_channel, d.out_dtype, d.out_clamp = 1, B.I8, 127
+    for k, v in kw.items():
+        setattr(d, k, v)
+    return d
+
+
+def _needs_no_gpu():
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("made-up pointers: only where nothing can be launched")
+
+
+@pytest.mark.parametrize("cfg", [23, 24, 25, 26, 27, 28, 29, 30])
+def test_a_hip_error_of_the_chosen_matmul_kernel_reaches_the_caller(cfg):
+    # (without a device every HIP call fails: the error to come back is that of the kernel the configuration names, not the
+    # one of another kernel tried in its place)
+    _needs_no_gpu()
+    L = B.lib()
+    d = _matmul_desc(256, 768, 256)
+    L.ibert_gemm_config_override(cfg)
+    try:
+        assert L.ibert_gemm_i8_requant(C.byref(d), 4096, 4096, 4096, 4096, 4096, None, 4096, None) == -6
+    finally:
+        L.ibert_gemm_config_override(-1)
+    assert b"MaxDynamicSharedMemorySize, 163840)" in L.ibert_last_hip_error(), L.ibert_last_hip_error()
+
+
 def test_embedding_and_masked_entry_points_reject_bad_arguments_before_touching_the_gpu():
     L = B.lib()
     dy = B.Dyadic(1518500250, 36)
