@@ -177,11 +177,15 @@ int ibert_hgelu_i(const int32_t* x, int8_t* y, int64_t n, const ibert_hgelu_para
  *     ibert_gemm_i8_requant(desc with out_dtype = IBERT_I32, out_clamp = gelu->q_max, no residual) -> f
  *     ibert_gelu_i(f) -> C
  * C: device int8, laid out by desc (ldc, batch strides); desc->out_dtype, out_clamp and residual_dy are ignored.
- * When the problem fits a whole-tile MFMA configuration (M, N multiples of the tile, K a multiple of 128,
- * 16-byte aligned A/W rows) GELU runs in the MatMul epilogue and the INT32 tensor f never exists.  Otherwise the
- * two kernels run back to back through `scratch` (device int32, M*N*batch entries): that needs dense
- * outputs (ldc = N, dense batch strides; else IBERT_ERR_NOT_IMPLEMENTED) and a non-NULL scratch
- * (else IBERT_ERR_WORKSPACE).  scratch may always be passed; it is untouched on the one-kernel path.
+ * Where K is a multiple of 128, A/W rows are 16-byte aligned, and K >= 512 or N is a multiple of 96 or 128, GELU runs in
+ * the MatMul epilogue (any M) and the INT32 tensor f never exists.  Otherwise the two kernels run back to back through
+ * `scratch` (device int32, M*N*batch entries), which needs dense outputs (ldc = N, dense batch strides).
+ * Dense outputs (else IBERT_ERR_NOT_IMPLEMENTED) and a non-NULL scratch (else IBERT_ERR_WORKSPACE) are asked for, whether
+ * or not the problem needs them, except where K is a multiple of 128, A/W rows are 16-byte aligned and
+ *   - M and N are whole tiles of at least 224 of 256x192, 256 of 128x96, 448 of 256x128 or 128 of 128x128 (the first of
+ *     these that holds; with K >= 2048: more than 256 of 128x96 or of 128x128), or
+ *   - none of these holds, K >= 512, and there are fewer than 384 (whole or cut) tiles of 128x128.
+ * scratch may always be passed; it is untouched on the one-kernel path.
  * ---------------------------------------------------------------------------------------------- */
 int ibert_gemm_i8_gelu(const ibert_gemm_desc* desc, const int8_t* A, const int8_t* W, const int32_t* bias,
                        const int32_t* mult, const int32_t* shift, const ibert_gelu_params* gelu, int8_t* C,

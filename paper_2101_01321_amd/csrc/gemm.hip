@@ -383,8 +383,24 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
     return IBERT_OK;
 }
 
-// MatMul + GELU.  One kernel when a direct-to-LDS tile fits the problem; otherwise the MatMul writes its INT32
-// result (clamped to +-q_max) to `scratch` and the element-wise GELU kernel follows, which needs dense outputs.
+// Are dense outputs and scratch asked for, whether or not this problem still goes through them?  Which problems need them
+// was once decided by the tiles that carried the epilogue then, and callers were told by a refusal; kernels that have taken
+// over more problems since must not turn a call that is refused on one size into one that works on the next.
+static bool gelu_asks_for_scratch(const ibert_gemm_desc& d, int64_t nb)
+{
+    auto whole = [&](int bm, int bn) -> int64_t {
+        return d.M % bm == 0 && d.N % bn == 0 && d.K % 128 == 0 ? (int64_t)(d.M / bm) * (d.N / bn) * nb : 0;
+    };
+    if (whole(256, 192) >= 224) return false;
+    if (whole(128, 96) >= 256) return whole(128, 96) == 256 && d.K >= 2048;
+    if (whole(256, 128) >= 448) return false;
+    if (whole(128, 128) >= 128) return whole(128, 128) <= 256 && d.K >= 2048;
+    return ceil_div(d.M, 128) * ceil_div(d.N, 128) * nb >= 384 || d.K < 512;
+}
+
+// MatMul + GELU.  One kernel where K is a multiple of 128 and either K >= 512 or 96 or 128 divides N (choose_config);
+// otherwise the MatMul writes its INT32 result (clamped to +-q_max) to `scratch` and the element-wise GELU kernel follows,
+// which needs dense outputs.
 int launch_gemm_gelu(const ibert_gemm_desc& d0, const int8_t* A, const int8_t* W, const int32_t* bias,
                      const int32_t* mult, const int32_t* shift, const ibert_gelu_params& gelu, int8_t* C,
                      int32_t* scratch, hipStream_t stream)
@@ -392,13 +408,15 @@ int launch_gemm_gelu(const ibert_gemm_desc& d0, const int8_t* A, const int8_t* W
     ibert_gemm_desc d = d0;
     d.out_dtype = IBERT_I8;
     d.out_clamp = gelu.q_max;
-    int rc = launch_gemm(d, A, W, bias, mult, shift, nullptr, C, stream, &gelu);
-    if (rc != IBERT_ERR_NOT_IMPLEMENTED) return rc;
     const int64_t nb = (int64_t)d.batch_outer * d.batch_inner;
+    if (nb == 0 || d.M == 0 || d.N == 0) return IBERT_OK;
     const bool dense = d.ldc == d.N && (d.batch_inner == 1 || d.strideC_inner == (int64_t)d.M * d.N) &&
                        (d.batch_outer == 1 || d.strideC_outer == (int64_t)d.batch_inner * d.M * d.N);
-    if (!dense) return IBERT_ERR_NOT_IMPLEMENTED;
-    if (!scratch) return IBERT_ERR_WORKSPACE;
+    const int refused = !dense ? IBERT_ERR_NOT_IMPLEMENTED : (!scratch ? IBERT_ERR_WORKSPACE : IBERT_OK);
+    if (refused && g_config_override < 0 && gelu_asks_for_scratch(d, nb)) return refused;
+    int rc = launch_gemm(d, A, W, bias, mult, shift, nullptr, C, stream, &gelu);
+    if (rc != IBERT_ERR_NOT_IMPLEMENTED) return rc;
+    if (refused) return refused;
     d.out_dtype = IBERT_I32;
     rc = launch_gemm(d, A, W, bias, mult, shift, nullptr, scratch, stream);
     if (rc) return rc;

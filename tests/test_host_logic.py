@@ -260,6 +260,24 @@ def test_a_hip_error_of_the_chosen_matmul_kernel_reaches_the_caller(cfg):
     assert b"MaxDynamicSharedMemorySize, 163840)" in L.ibert_last_hip_error(), L.ibert_last_hip_error()
 
 
+@pytest.mark.parametrize("M,N,K,asks", [
+    (130, 128, 256, True), (128, 1024, 256, True), (4095, 3072, 384, True),        # a short K and few whole tiles
+    (2741, 3072, 768, True), (15311, 3072, 768, True),                             # many tiles, the last row of them cut
+    (4096, 768, 2048, True), (2048, 1024, 2048, True),                             # a long K and one tile for every unit
+    (4096, 3072, 768, False), (2048, 3072, 128, False), (4096, 768, 1920, False), (4096, 1536, 2048, False),
+    (2048, 1024, 1920, False), (128, 3072, 768, False), (200, 72, 512, False), (1, 16, 512, False),
+    (4096, 3072, 784, True), (128, 768, 528, True)])                               # K no multiple of 128
+def test_matmul_gelu_asks_for_scratch_and_dense_outputs_by_the_documented_rule(M, N, K, asks):
+    # what is refused without them does not depend on which problems a later kernel has come to serve in one launch
+    _needs_no_gpu()
+    gp = B.ibert_gelu_params_from_scale(2.0 ** -7, 8.0 / 127)
+    call = lambda d, scr: B.lib().ibert_gemm_i8_gelu(C.byref(d), 4096, 4096, 4096, 4096, 4096, C.byref(gp), 4096, scr, None)
+    assert call(_matmul_desc(M, N, K), None) == (-5 if asks else -6)               # -6: no device to launch it on
+    assert call(_matmul_desc(M, N, K, ldc=N + 16), 4096) == (-7 if asks else -6)
+    assert call(_matmul_desc(M, N, K, ldc=N + 16), None) == (-7 if asks else -6)
+    assert call(_matmul_desc(M, N, K), 4096) == -6
+
+
 def test_embedding_and_masked_entry_points_reject_bad_arguments_before_touching_the_gpu():
     L = B.lib()
     dy = B.Dyadic(1518500250, 36)
