@@ -394,7 +394,13 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         // the wavefront's parity and the lane only
         const int lsw = ((wv & 1) << 2) | (lr8 >> 1);
         const uint32_t chunk = (uint32_t)((lp ^ lsw) << 4);
-        const uint32_t voff_a = (uint32_t)lr8 * (uint32_t)g.lda;
+        // The lane's byte of each A request, counted from the tile's first row (below 2^8 rows of less than 2^23 bytes): with the
+        // rows limited here, a request in the loop is a load from the step's base, whether or not the tile is cut.  Limited per
+        // request instead, the products and minima cost the loop a quarter more scalar instructions: 256x192 tiles, us,
+        // [4096,2304] x K 768 INT8 12.7 -> 12.5 (12.3 where no row is limited at all), [4096,3072] x K 768 with GELU 16.3 -> 15.6.
+        uint32_t voff_a[NLA];
+#pragma unroll
+        for (int i = 0; i < NLA; ++i) voff_a[i] = umul24((uint32_t)row_in(i * RG + wv * 8 + lr8), (uint32_t)g.lda) + chunk;
         const uint32_t voff_w = (uint32_t)lr8 * (uint32_t)g.ldw + chunk;
         const int8_t* ga = A + (int64_t)m0 * g.lda;
         const int8_t* gw = W + (int64_t)(n0 + wv * 8) * g.ldw;
@@ -404,12 +410,10 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         auto dma_one = [&](int q, int kt, int buf) {
             const bool is_a = q < NLA;
             const int i = is_a ? q : q - NLA;
-            const int first = row_in(i * RG + wv * 8);              // (A: the block's first row, and how far its rows may reach)
-            const uint32_t most = (uint32_t)(rlast - first < 7 ? rlast - first : 7) * (uint32_t)g.lda;   // (rlast * lda may pass 2^32)
-            const int8_t* sb = (is_a ? ga + (int64_t)first * g.lda : gw + (int64_t)i * RG * g.ldw) + (int64_t)kt * BK;
+            const int8_t* sb = (is_a ? ga : gw + (int64_t)i * RG * g.ldw) + (int64_t)kt * BK;
             const uint32_t la = lds0 + (uint32_t)(buf * STAGE + (is_a ? 0 : BM * BK) + i * (RG * BK));
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         :: "s"(la), "v"(is_a ? (voff_a < most ? voff_a : most) + chunk : voff_w), "s"(sb) : "memory", "m0");
+                         :: "s"(la), "v"(is_a ? voff_a[is_a ? i : 0] : voff_w), "s"(sb) : "memory", "m0");
         };
         auto read_one = [&](int q, int buf, int s, v4i (&xa)[FM], v4i (&wb)[FN]) {
             const int8_t* base = lds + buf * STAGE + (((s * 4 + fch) ^ rd_swz) << 4);
@@ -779,7 +783,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
                     res[2] = (int8_t)((pk[u] >> 16) & 0xff); res[3] = (int8_t)(pk[u] >> 24);
                     int32_t o[4];
                     requant4(a4[u], res, R != nullptr, fast_tag, o);
-                    char* cp = c_lane + (uint32_t)row_in(tr[u]) * c_pitch;
+                    char* cp = c_lane + umul24((uint32_t)row_in(tr[u]), c_pitch);
                     if (OUT_I8) *reinterpret_cast<uint32_t*>(cp) = pack4_i8(o[0], o[1], o[2], o[3]);
                     else if (g.c16) *reinterpret_cast<uint2*>(cp) = uint2{pack2_i16(o[0], o[1]), pack2_i16(o[2], o[3])};
                     else *reinterpret_cast<v4i*>(cp) = v4i{o[0], o[1], o[2], o[3]};
@@ -853,8 +857,15 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         static_assert(SM == 0 || ES != 1 || OST_PAD || OST_SWZ, "the INT8 staging tile fits in front of the constants");
         static_assert(SM == 0 || ES != 4, "INT32 outputs are stored by the lanes themselves");
         int8_t* const ostage = lds;
-        char* const c_base = reinterpret_cast<char*>(g.C) + (c_off + (int64_t)m0 * g.ldc + n0 + wn0 + 4 * fch) * (int64_t)ES;
-        const uint32_t pitch = (uint32_t)g.ldc * ES;
+        char* const ct = reinterpret_cast<char*>(g.C) + (c_off + (int64_t)m0 * g.ldc + n0) * (int64_t)ES;
+        const uint32_t pitch = (uint32_t)g.ldc * ES;               // (below 2^24)
+        // Lane-owned bytes of block row j: tile row wm0 + 16 j + frow, or the last one, `col` bytes into it.  The minimum is taken
+        // over byte offsets, so that a row costs an add and a minimum and no multiplication (all of it fits 32 bits).
+        const uint32_t off_row = umul24((uint32_t)(wm0 + frow), pitch), off_last = umul24((uint32_t)(rlast < BM ? rlast : BM - 1), pitch);
+        auto c_at = [&](int j, uint32_t col) {
+            const uint32_t off = off_row + col + (uint32_t)(16 * j) * pitch, last = off_last + col;
+            return ct + (!DMA || off < last ? off : last);
+        };
         const uint32_t* const r_base = resl + (wm0 + frow) * G4 + (wn0 >> 2) + fch;
         static_assert(SM != 2 || (ES == 1 && FN <= 4), "lane-transposed stores: INT8, at most four block columns a wavefront");
         uint32_t pq[SM == 2 ? 4 : 1][FM];                          // SM 2: the packed dwords, by block column
@@ -896,7 +907,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
 #pragma unroll
                 for (int j = 0; j < FM; ++j) {
                     const uint32_t pk4 = (by[j][0] | (by[j][1] << 8)) | ((by[j][2] | (by[j][3] << 8)) << 16);
-                    char* cp = c_base + ((uint32_t)row_in(wm0 + 16 * j + frow) * pitch + (uint32_t)(i * 16) * ES);
+                    char* cp = c_at(j, (uint32_t)(wn0 + 4 * fch) * ES) + i * 16 * ES;
                     const int row = wm0 + 16 * j + frow, colb = wn0 + 16 * i + 4 * fch;
                     if (SM == 2) pq[i < 4 ? i : 0][j] = pk4;
                     else if (SM == 1) *reinterpret_cast<uint32_t*>(ostage + ost_at(row, colb)) = pk4;
@@ -936,7 +947,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             }
 #pragma unroll
             for (int j = 0; j < FM; ++j) {
-                char* cp = c_base + ((uint32_t)row_in(wm0 + 16 * j + frow) * pitch + (uint32_t)(i * 16) * ES);
+                char* cp = c_at(j, (uint32_t)(wn0 + 4 * fch) * ES) + i * 16 * ES;
                 const int row = wm0 + 16 * j + frow, colb = wn0 + 16 * i + 4 * fch;
                 if (ES == 1) {
                     const uint32_t pk4 = pack4_i8(o[j][0], o[j][1], o[j][2], o[j][3]);
@@ -959,7 +970,6 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             // block column b, which leave as one 16-byte store -- 16 tokens x 16 FN bytes per instruction, no trip
             // through LDS and no barrier.
             typedef unsigned v2u __attribute__((ext_vector_type(2)));
-            char* const c16 = reinterpret_cast<char*>(g.C) + c_off + (int64_t)m0 * g.ldc + n0 + wn0 + 16 * fch;
 #pragma unroll
             for (int j = 0; j < FM; ++j) {
                 uint32_t r0 = pq[0][j], r1 = pq[SM == 2 ? 1 : 0][j], r2 = pq[SM == 2 ? 2 : 0][j], r3 = pq[SM == 2 ? 3 : 0][j];
@@ -968,20 +978,19 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
                 t = __builtin_amdgcn_permlane16_swap(r0, r1, false, false); r0 = t.x; r1 = t.y;
                 t = __builtin_amdgcn_permlane16_swap(r2, r3, false, false); r2 = t.x; r3 = t.y;
                 if (fch < FN) {
-                    *reinterpret_cast<v4i*>(c16 + (uint32_t)row_in(wm0 + 16 * j + frow) * pitch) = v4i{(int)r0, (int)r1, (int)r2, (int)r3};
+                    *reinterpret_cast<v4i*>(c_at(j, (uint32_t)(wn0 + 16 * fch))) = v4i{(int)r0, (int)r1, (int)r2, (int)r3};
                 }
             }
         }
         if (SM == 1 && ES == 2) {
             __syncthreads();
             constexpr int P8 = BN / 4, CH = BM * P8;               // 8-byte pieces per row, per tile
-            char* const ct = reinterpret_cast<char*>(g.C) + (c_off + (int64_t)m0 * g.ldc + n0) * 2;
 #pragma unroll 4
             for (int q0 = 0; q0 < CH; q0 += NT) {
                 const int q = q0 + tid;
                 if (CH % NT == 0 || q < CH) {
                     const int row = q / P8, c8 = q - row * P8;
-                    *reinterpret_cast<uint2*>(ct + (uint32_t)row_in(row) * pitch + c8 * 8) =
+                    *reinterpret_cast<uint2*>(ct + umul24((uint32_t)row_in(row), pitch) + c8 * 8) =
                         *reinterpret_cast<const uint2*>(ostage + row * SPH + c8 * 8);
                 }
             }
@@ -989,13 +998,12 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         if (SM == 1 && ES == 1) {
             __syncthreads();
             constexpr int C16 = BN / 16, CH = BM * C16;            // 16-byte chunks per row, per tile
-            char* const ct = reinterpret_cast<char*>(g.C) + c_off + (int64_t)m0 * g.ldc + n0;
 #pragma unroll
             for (int q0 = 0; q0 < CH; q0 += NT) {
                 const int q = q0 + tid;
                 if (CH % NT == 0 || q < CH) {
                     const int row = q / C16, c16 = q - row * C16;
-                    *reinterpret_cast<v4i*>(ct + (uint32_t)row_in(row) * pitch + c16 * 16) =
+                    *reinterpret_cast<v4i*>(ct + umul24((uint32_t)row_in(row), pitch) + c16 * 16) =
                         *reinterpret_cast<const v4i*>(ostage + ost_at(row, c16 * 16));
                 }
             }
