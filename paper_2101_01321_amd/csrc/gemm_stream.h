@@ -110,7 +110,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
     auto block_row = [&](int k, int nb, int rows, int first) { const int q = wave + NW * k; return q / nb * rows + first + q % nb * 8; };
     const int8_t *ra, *rw;                                         // request stream: operand rows of its tile, at its step
     const uint32_t va = (uint32_t)r8 * (uint32_t)g.lda, vw = (uint32_t)r8 * (uint32_t)g.ldw + chunk;
-    int rlast = 0;                                                 // last row of A, counted from the tile's first
+    int rlast = 0;                                                 // last row of A, counted from the tile's first, or any beyond BM + 6
     int rlt = lt, rk = 0;
     uint32_t rstage = lds0;
     bool rlive = true;
@@ -119,7 +119,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         tile_at(l, m0, n0);
         ra = g.A + (int64_t)m0 * g.lda;
         rw = g.W + (int64_t)n0 * g.ldw;
-        rlast = g.M - 1 - m0;
+        // (a request reaches seven rows beyond its first; more rows than that could take the distance in bytes past 2^32)
+        rlast = g.M - 1 - m0 < BM + 7 ? g.M - 1 - m0 : BM + 7;
     };
     // request q of group h (0 or 1): the A rows first
     auto request_one = [&](int h, int q) {
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         const uint32_t la = rstage + (uint32_t)((is_a ? 0 : BM * 128) + row * 128);
         const int first = is_a ? (row < rlast ? row : rlast) : row;
         const int8_t* sb = is_a ? ra + (int64_t)first * g.lda : rw + (int64_t)first * g.ldw;
-        const uint32_t most = (uint32_t)(rlast - first < 7 ? rlast - first : 7) * (uint32_t)g.lda;   // (rlast * lda may pass 2^32)
+        const uint32_t most = (uint32_t)(rlast - first) * (uint32_t)g.lda;
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                      :: "s"(la), "v"(is_a ? (va < most ? va : most) + chunk : vw), "s"(sb) : "memory", "m0");
     };
