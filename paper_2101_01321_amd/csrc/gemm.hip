@@ -239,6 +239,12 @@ static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb
             if (w.first[0] == 0 || (f.direct && !dma_ok(d, f.bn))) continue;
             if (c.config == 23 && !stream_ok<256, 256, 8>(g, i8)) continue;
             if (c.config == 24 && !stream_ok<256, 192, 8>(g, i8)) continue;
+            // One 256x192 tile for every unit, dealt evenly to the XCDs: the persistent kernel has nothing to stream, and the estimates
+            // of the two kernels are closer than their fits.  us, persistent / not: with GELU, K 768, [4096,3072] 18.0 / 17.0,
+            // [16384,768] 17.5 / 16.9, [2048,3072] 15.2 / 14.4, and at K 128 11.0 / 10.7, K 4096 49.8 / 44.3; INT8 even up to
+            // K 256, 15.5 / 14.9 at 768.  (An uneven deal has no XCD blocks in the kernel that is not persistent, and the
+            // persistent one is ahead there: [16072,768] x K 768 with GELU 17.1 / 18.3; INT16: as estimated.)
+            if (c.config == 24 && i8 && tiles(256, 192) <= 256 && tiles(256, 192) % 8 == 0) continue;
             const int64_t k = d.K / 128;
             int64_t n, share = c.share;
             if (share == 0) {
