@@ -18,12 +18,19 @@ extern "C" {
 int ibert_gemm_config_override(int32_t config);
 
 /* Switch for A/B measurements: with `on` = 0 the MFMA MatMul gives each XCD a linear run of tiles instead of a near-square
- * block of the tile grid (the default, which fetches fewer operand bytes over the fabric).  Process-wide. */
+ * block of the tile grid (the default, which fetches fewer operand bytes over the fabric).  Process-wide.  The persistent and
+ * the few-token kernels deal their tiles to the XCDs in ways of their own, which it does not change. */
 void ibert_gemm_xcd_blocks(int32_t on);
 
-/* While `device_word` (device uint32, owned by the caller) is non-NULL, every MFMA MatMul launch of this process has its
- * first workgroup store there which form of the epilogue it ran -- the choice depends on the per-channel shifts and
- * biases, which only the device sees.  NULL switches the record off.  Process-wide, not thread-safe. */
+/* Name and tile parameters of the kernel that this process launched last, as a profiler shows them ("" before the first launch).
+ * Not thread-safe. */
+const char* ibert_last_kernel(void);
+
+/* While `device_word` (device uint32, owned by the caller) is non-NULL, every launch of the MFMA MatMul and of its persistent
+ * form has its first workgroup store there which form of the epilogue it ran -- the choice depends on the per-channel shifts
+ * and biases, which only the device sees.  The few-token kernel (ibert_last_kernel() tells) chooses the arithmetic for every
+ * wavefront and stores nothing: the test for it alone made the forward of one sequence 0.8 % slower.  NULL switches the record
+ * off.  Process-wide, not thread-safe. */
 enum {
     IBERT_EPILOGUE_STAGED = 1,            /* through LDS, general 64-bit requantization, arithmetic GELU          */
     IBERT_EPILOGUE_DIRECT = 2,            /* register-direct (all shifts in [33, 62], |bias| < 2^30)              */

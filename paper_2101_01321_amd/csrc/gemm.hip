@@ -439,6 +439,8 @@ extern "C" int ibert_gemm_config_override(int32_t config)
 }
 
 
+extern "C" const char* ibert_last_kernel(void) { return ibert::g_last_kernel; }
+
 extern "C" void ibert_gemm_xcd_blocks(int32_t on) { ibert::g_xcd_blocks = on != 0; }
 
 extern "C" void ibert_gemm_epilogue_record(uint32_t* device_word) { ibert::g_path_word = device_word; }

@@ -19,6 +19,19 @@ def to_dev(a, dtype=None):
     return torch.from_numpy(a).to(DEV)
 
 
+def kernel_of(cfg):
+    """The kernel and tile that a forced configuration stands for, as the start of the name it is launched by."""
+    mfma = "gemm_nt_mfma_kernel<%d, %d, 128, %d, "
+    direct = {0: (256, 192, 2), 1: (128, 128, 2), 5: (128, 96, 2), 6: (256, 192, 2), 7: (128, 128, 2), 9: (128, 96, 2),
+              10: (256, 128, 2), 11: (128, 96, 3), 12: (128, 128, 3), 13: (256, 192, 2), 14: (256, 128, 2), 17: (64, 96, 3),
+              18: (64, 96, 2), 19: (64, 128, 2), 20: (128, 96, 3), 21: (128, 96, 3), 22: (128, 128, 3)}
+    if cfg in direct:
+        return mfma % direct[cfg]
+    if cfg >= 25:
+        return "gemm_few_kernel<%d, %d, " % {25: (1, 1), 26: (1, 2), 27: (2, 2), 28: (2, 4), 29: (2, 6), 30: (4, 4)}[cfg]
+    return "gemm_stream_kernel<%d, %d, " % {8: (256, 256), 16: (256, 256), 23: (256, 256), 24: (256, 192)}[cfg]
+
+
 def gemm(desc_kwargs, A, W, bias=None, mult=None, shift=None, residual=None, out_elems=None, offsets=None):
     """Flat-buffer GEMM call.  desc_kwargs: fields of GemmDesc (requant / residual_dy as (m, s) tuples).
     offsets: optional dict of element offsets {'A':..,'W':..,'C':..,'R':..} applied to the device pointers."""

@@ -62,8 +62,9 @@ def test_layer_of_any_length_keeps_scores_and_probabilities(G):
 
 
 # ------------------------------------------------------------------------------------------- persistent MatMul
-def _stream_case(G, cfg, M, N, K, kind, shift, seed, form=True):
-    """One MatMul through tile configuration cfg; shift 40: every tile takes the fast epilogue, 30: the 64-bit one."""
+def _stream_case(G, cfg, M, N, K, kind, shift, seed, kernel=None):
+    """One MatMul through tile configuration cfg; shift 40: every tile takes the fast epilogue, 30: the 64-bit one.
+    kernel: start of the name of the kernel that is to have run (default: the one that cfg stands for)."""
     import torch
     from paper_2101_01321_amd import binding as B
     rng = np.random.default_rng(seed)
@@ -90,8 +91,15 @@ def _stream_case(G, cfg, M, N, K, kind, shift, seed, form=True):
     finally:
         B.ibert_gemm_epilogue_record(None)
         B.lib().ibert_gemm_config_override(-1)
-    want_form = B.EPILOGUE_STAGED if shift < 33 else (B.EPILOGUE_DIRECT_GELU_TABLE if kind == "gelu" else B.EPILOGUE_DIRECT)
-    assert not form or int(word.item()) == want_form, (int(word.item()), want_form)
+    name = B.lib().ibert_last_kernel().decode()
+    assert name.startswith(kernel or G.kernel_of(cfg)), name
+    # (the few-row kernel stores no record; of the tiles that are not persistent only some have room for a GELU table)
+    want_form = [B.EPILOGUE_STAGED] if shift < 33 else ([B.EPILOGUE_DIRECT_GELU_TABLE] if kind == "gelu" else [B.EPILOGUE_DIRECT])
+    if cfg >= 25:
+        want_form = [0]
+    elif kind == "gelu" and shift >= 33 and "stream" not in name:
+        want_form = [B.EPILOGUE_DIRECT, B.EPILOGUE_DIRECT_GELU_TABLE]
+    assert int(word.item()) in want_form, (int(word.item()), want_form)
     spec = GemmSpec(M, N, K, per_channel=1, dy=(1, 0), out_dtype=I8 if kind == "i8" else I32,
                     out_clamp={"i8": 127, "gelu": gp.q_max if kind == "gelu" else 0}.get(kind, 32767), res_dy=res_dy)
     want = oracle.gemm_requant(spec, A, W, bias, mult, shifts, R).reshape(-1)
@@ -108,6 +116,57 @@ def test_gemm_persistent_tiles(G, cfg, bn, kind):
     for M, N, K, shift in [(1, bn, 128, 40), (255, bn, 128, 40), (256, 2 * bn, 256, 40), (257, bn, 384, 40), (300, bn, 256, 30),
                            (1000, 3 * bn, 640, 40), (256 * 90 + 17, 3 * bn, 128, 40), (256 * 130 + 1, 2 * bn, 256, 40)]:
         _stream_case(G, cfg, M, N, K, kind, shift, seed=M + N + K)
+
+
+@pytest.mark.parametrize("M,N,K,kind,kernel", [(4096, 3072, 256, "gelu", "gemm_nt_mfma_kernel<256, 192, "),     # 16 x 16 tiles
+                                               (4096, 3072, 768, "i8", "gemm_nt_mfma_kernel<256, 192, "),
+                                               (16072, 768, 256, "gelu", "gemm_stream_kernel<256, 192, "),      # 63 x 4: uneven
+                                               (16385, 768, 256, "gelu", "gemm_stream_kernel<256, ")])          # a second round
+def test_gemm_tile_chosen_for_one_round(G, M, N, K, kind, kernel):
+    # 256x192 tiles with one for every compute unit: persistent only where the XCDs get unequal shares, or there are more
+    _stream_case(G, -1, M, N, K, kind, 40, seed=M, kernel=kernel)
+
+
+@pytest.mark.parametrize("cfg,bn", [(23, 256), (24, 192)])
+@pytest.mark.parametrize("kind", ["i8", "i16", "i16res", "gelu"])
+@pytest.mark.parametrize("constants", ["one multiplier", "no bias", "neither", "large shifts", "one slow column"])
+def test_gemm_persistent_tiles_constants(G, cfg, bn, kind, constants):
+    # constants that are filled in by hand where the caller has no array of them, in the first tile and after a change of tile
+    # column; shifts of 44 to 62 (with GELU: the table address is no longer folded into the constants); a column of the second
+    # tile column that sends all of it, and no other, through the 64-bit epilogue
+    from paper_2101_01321_amd import binding as B
+    M, N, K = 256 * 90 + 17, 3 * bn, 256
+    rng = np.random.default_rng(cfg)
+    A, W = (rng.integers(-127, 128, size=(n, K), dtype=np.int8) for n in (M, N))
+    large = constants == "large shifts"
+    bias = rng.integers(-2 ** 29, 2 ** 29, size=N, dtype=np.int32) if large else rng.integers(-50000, 50000, size=N, dtype=np.int32)
+    mult = rng.integers(2 ** 29, 2 ** 30, size=N, dtype=np.int64).astype(np.int32)
+    shifts = np.resize(np.array([44, 45, 46, 47, 50, 62], np.int32), N) if large else np.full(N, 37, np.int32)
+    if constants == "one slow column":
+        shifts[bn + 5] = 32
+    bias = None if constants in ("no bias", "neither") else bias
+    pc = 0 if constants in ("one multiplier", "neither") else 1
+    dy = (1518500250, 37) if pc == 0 else (1, 0)
+    R = rng.integers(-127, 128, size=(M, N), dtype=np.int8) if kind == "i16res" else None
+    res_dy = (1717986918, 23)
+    kw = dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K, ldw=K, ldc=N, ldr=N, per_channel=pc, requant=dy, residual_dy=res_dy,
+              out_dtype=I16 if kind[:3] == "i16" else I8, out_clamp=127 if kind == "i8" else 32767)
+    arrays = (bias, mult if pc else None, shifts if pc else None)
+    gp, op = B.ibert_gelu_params_from_scale(2.0 ** -6, 0.7), P.gelu_params(2.0 ** -6, 0.7)
+    B.lib().ibert_gemm_config_override(cfg)
+    try:
+        G.say("persistent gemm cfg %d %s %s" % (cfg, kind, constants))
+        got = G.gemm_gelu(kw, A, W, *arrays, gp, M * N)[0] if kind == "gelu" else G.gemm(kw, A, W, *arrays, R, out_elems=M * N)
+    finally:
+        B.lib().ibert_gemm_config_override(-1)
+    assert B.lib().ibert_last_kernel().decode().startswith(G.kernel_of(cfg))
+    spec = GemmSpec(M, N, K, per_channel=pc, dy=dy, out_dtype=I8 if kind == "i8" else I32,
+                    out_clamp={"i8": 127, "gelu": gp.q_max}.get(kind, 32767), res_dy=res_dy)
+    want = oracle.gemm_requant(spec, A, W, *arrays, R).reshape(-1)
+    if kind == "gelu":
+        want = oracle.gelu(want, op)
+    assert len(np.unique(want)) > 20
+    _eq(got.astype(np.int64), want.astype(np.int64), "persistent gemm, constants")
 
 
 @pytest.mark.parametrize("cfg,bn", [(23, 256), (24, 192)])
@@ -148,6 +207,7 @@ def test_gemm_persistent_tiles_of_one_step(G, cfg, bn, kind, cols, shift):
         torch.cuda.synchronize()
     finally:
         B.lib().ibert_gemm_config_override(-1)
+    assert B.lib().ibert_last_kernel().decode().startswith(G.kernel_of(cfg))
     spec = GemmSpec(P_, N, K, per_channel=1, dy=(1, 0), out_dtype=I8 if kind == "i8" else I32,
                     out_clamp={"i8": 127, "gelu": gp.q_max}.get(kind, 32767), res_dy=res_dy)
     want = oracle.gemm_requant(spec, A, W, bias, mult, shifts, R).reshape(P_, N)
@@ -166,7 +226,7 @@ def test_gemm_direct_to_lds_ragged_rows(G, cfg, bm, bn):
     kinds = ["i8", "i16res"] + (["gelu"] if cfg in (6, 7, 9, 10, 13, 14) else [])
     for M, N, K in [(1, bn, 128), (bm - 1, 2 * bn, 256), (bm + 1, bn, 512), (3 * bm + 37, 2 * bn, 384)]:
         for kind in kinds:
-            _stream_case(G, cfg, M, N, K, kind, 40, seed=M + N + K, form=False)
+            _stream_case(G, cfg, M, N, K, kind, 40, seed=M + N + K)
 
 
 @pytest.mark.parametrize("cfg,bn,lda,M", [(7, 128, 1 << 22, 1025), (9, 96, 1 << 22, 1030), (13, 192, 1 << 22, 1025), (14, 128, 1 << 22, 1033),
@@ -195,6 +255,7 @@ def test_gemm_rows_four_gigabytes_apart(G, cfg, bn, lda, M):
         torch.cuda.synchronize()
     finally:
         B.lib().ibert_gemm_config_override(-1)
+    assert B.lib().ibert_last_kernel().decode().startswith(G.kernel_of(cfg))
     spec = GemmSpec(M, N, K, per_channel=1, dy=(1, 0), out_dtype=I8, out_clamp=127)
     _eq(tC.cpu().numpy(), oracle.gemm_requant(spec, A, W, bias, mult, shift, None).reshape(M, N), "gemm, rows far apart")
 
@@ -206,7 +267,7 @@ def test_gemm_few_rows(G, cfg, bm, bn, kind):
     # past and off a tile edge; tile columns that do and do not divide by the XCDs; both epilogue forms
     for M, N, K, shift in [(1, bn, 128, 40), (bm, 8 * bn, 640, 40), (bm + 1, 3 * bn, 1024, 40), (3 * bm + 7, 12 * bn, 1152, 40),
                            (2 * bm - 1, 2 * bn, 5248, 40), (bm + 3, 5 * bn, 256, 30), (17 * bm, 9 * bn, 384, 40)]:
-        _stream_case(G, cfg, M, N, K, kind, shift, seed=M + N + K, form=False)
+        _stream_case(G, cfg, M, N, K, kind, shift, seed=M + N + K)
 
 
 # ------------------------------------------------------------------------------------------- Softmax, rows that start anywhere
