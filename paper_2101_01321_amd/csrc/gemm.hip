@@ -93,43 +93,43 @@ int check_gemm(const ibert_gemm_desc& d, const void* A, const void* W, const voi
 
 // Tile configurations of the MFMA kernel.
 struct GemmConfig {
-    int bm, bn, bk, ring;
-    bool direct;          // direct-to-LDS loader (N and K in whole tiles; ring = LDS stages) or register ring
+    int bm, bn;
+    bool direct;          // direct-to-LDS loader (N in whole tiles, K in whole steps) or register ring
 };
-// (0, 1, 5, 6, 8, 10, 11, 12, 16 and 20 were tiles that the rule below never takes any more, as another kernel with the same
-//  tile is faster for every problem; their numbers stand for that one.)
+// (0, 1, 5, 6, 8, 10, 11, 12, 16 and 20 were kernels that the rule below never takes any more, as another one with the same
+//  tile is faster for every problem; their numbers stand for that one, and so they do with GELU where it carries GELU.)
 static const GemmConfig kConfigs[] = {      // index = configuration number of ibert_gemm_config_override
-    {256, 192, 128, 2, true},       // = 13
-    {128, 128, 128, 2, true},       // = 7
-    {128, 128, 64, 2, false},
-    {64, 64, 128, 3, false},
-    {64, 128, 64, 3, false},
-    {128, 96, 128, 2, true},        // = 9
-    {256, 192, 128, 2, true},       // = 13
-    {128, 128, 128, 2, true},
-    {256, 256, 128, 2, true},       // = 23
-    {128, 96, 128, 2, true},
-    {256, 128, 128, 2, true},       // = 14
-    {128, 96, 128, 3, true},        // = 21
-    {128, 128, 128, 3, true},       // = 22
-    {256, 192, 128, 2, true},       // eight wavefronts
-    {256, 128, 128, 2, true},       // eight wavefronts
-    {32, 32, 128, 4, false},
-    {256, 256, 128, 2, true},       // = 23
-    {64, 96, 128, 3, true},
-    {64, 96, 128, 2, true},
-    {64, 128, 128, 2, true},
-    {128, 96, 128, 3, true},        // = 21
-    {128, 96, 128, 3, true},        // eight wavefronts in four rows of two and four that only request tiles
-    {128, 128, 128, 3, true},       // the same
-    {256, 256, 128, 2, true},       // persistent (gemm_stream.h)
-    {256, 192, 128, 2, true},       // persistent
-    {16, 16, 128, 4, true},         // K split over the wavefronts (gemm_few.h)
-    {16, 32, 128, 4, true},
-    {32, 32, 128, 4, true},
-    {32, 64, 128, 4, true},
-    {32, 96, 128, 4, true},
-    {64, 64, 128, 4, true},
+    {256, 192, true},       // = 13
+    {128, 128, true},       // = 7
+    {128, 128, false},
+    {64, 64, false},
+    {64, 128, false},
+    {128, 96, true},        // = 9
+    {256, 192, true},       // = 13
+    {128, 128, true},
+    {256, 256, true},       // = 23
+    {128, 96, true},
+    {256, 128, true},       // = 14
+    {128, 96, true},        // = 21
+    {128, 128, true},       // = 22
+    {256, 192, true},       // eight wavefronts
+    {256, 128, true},       // eight wavefronts
+    {32, 32, false},
+    {256, 256, true},       // = 23
+    {64, 96, true},
+    {64, 96, true},
+    {64, 128, true},
+    {128, 96, true},        // = 21
+    {128, 96, true},        // eight wavefronts in four rows of two and four that only request tiles
+    {128, 128, true},       // the same
+    {256, 256, true},       // persistent (gemm_stream.h)
+    {256, 192, true},       // persistent
+    {16, 16, true},         // K split over the wavefronts (gemm_few.h)
+    {16, 32, true},
+    {32, 32, true},
+    {32, 64, true},
+    {32, 96, true},
+    {64, 64, true},
 };
 constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
 static int g_config_override = -1;
@@ -271,8 +271,8 @@ static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb
     return 4;
 }
 
-// gelu != nullptr asks for the GELU epilogue (INT8 output, no residual; out_clamp must be gelu->q_max): only the
-// direct-to-LDS tiles carry it, any other problem returns IBERT_ERR_NOT_IMPLEMENTED without launching.
+// gelu != nullptr asks for the GELU epilogue (INT8 output, no residual; out_clamp must be gelu->q_max): a tile
+// that does not carry it, and a problem that the tile does not serve, return IBERT_ERR_NOT_IMPLEMENTED without launching.
 int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias,
                 const int32_t* mult, const int32_t* shift, const int8_t* residual, void* C, hipStream_t stream,
                 const ibert_gelu_params* gelu)
@@ -324,11 +324,11 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
             switch (cfg) {
                 case 3: return launch_mfma<64, 64, 128, 3, false, false, true>(g, i8, stream);
                 case 15: return launch_mfma<32, 32, 128, 4, false, false, true>(g, i8, stream);
-                case 7: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 2, false, true, true>(g, i8, stream); break;
-                case 9: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 2, false, true, true>(g, i8, stream); break;
-                case 6: case 13: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true, true, 8>(g, i8, stream); break;
+                case 1: case 7: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 2, false, true, true>(g, i8, stream); break;
+                case 5: case 9: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 2, false, true, true>(g, i8, stream); break;
+                case 0: case 6: case 13: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true, true, 8>(g, i8, stream); break;
                 case 10: case 14: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true, true, 8>(g, i8, stream); break;
-                case 23: return launch_stream<256, 256, 8, true>(g, i8, stream);
+                case 8: case 16: case 23: return launch_stream<256, 256, 8, true>(g, i8, stream);
                 case 24: return launch_stream<256, 192, 8, true>(g, i8, stream);
                 case 25: return launch_few<1, 1, true>(g, i8, stream);
                 case 26: return launch_few<1, 2, true>(g, i8, stream);

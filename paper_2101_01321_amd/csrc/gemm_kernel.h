@@ -8,8 +8,8 @@
 //   * Both operands are K-contiguous in memory; a lane's MFMA operand is 16 consecutive K bytes, one
 //     ds_read_b128.  LDS rows are BK bytes (64 or 128) with the 16-byte chunk index XOR-swizzled by the row
 //     so that the rows a group of lanes reads in one cycle fall into distinct banks.
-//   * Two tile loaders: global memory straight into LDS (whole tiles, K a multiple of 128), or through a ring
-//     of registers (everything else that is 16-byte aligned, and W given as [K,N] with aligned rows).
+//   * Two tile loaders: global memory straight into LDS (any M, N in whole tiles, K a multiple of 128), or through a
+//     ring of registers (everything else that is 16-byte aligned, and W given as [K,N] with aligned rows).
 //   * Integer accumulation is exact, so any consistent K order gives the oracle's bits.
 //   * The epilogue can also apply integer GELU (Alg. 2) to its own INT8 output.
 //   * Four wavefronts per workgroup, or eight (two per SIMD) for the big INT8 tiles.
@@ -141,7 +141,7 @@ struct EpiLayout {
 // block as four dwords, transposes it in registers with byte permutes and writes four dwords (4 consecutive
 // k of one n) into the same K-contiguous LDS layout the MFMA loop reads.
 //
-// DMA = true (whole tiles only, BK = 128): the tiles go from global memory straight into LDS
+// DMA = true (N in whole tiles, K in whole steps, BK = 128): the tiles go from global memory straight into LDS
 // (global_load_lds_dwordx4: lane l of a wavefront writes bytes [16 l, 16 l + 16) of a 1 KB LDS block, so a
 // block is 8 tile rows and the lane fetches the chunk that the swizzle puts at its position).  No register
 // ring and no LDS write instructions; a K step is two phases of MFMAs, each of which also issues the
@@ -842,19 +842,11 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         const int8_t* const lut = lds + EL::LDS_BYTES + PAR_BYTES;
         const uint32_t lut_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)lds + (uint32_t)(EL::LDS_BYTES + PAR_BYTES);
         const int32_t lut_hi = g.gelu_lut_n - 1;
-        // staged row pitch in bytes (16-byte aligned rows): padded by one piece, or -- where only the bare tile fits and
-        // a row is a whole number of 256-byte bank cycles -- unpadded with the pieces of a row permuted by the row
-        // number, so that the 16 rows a wavefront writes at once still land on 16 different bank groups
-        constexpr bool OST_PAD = BM * (BN + 16) <= 32 * JC * SP * 4;
-        constexpr bool OST_SWZ = !OST_PAD && BN == 256 && BM * BN <= 32 * JC * SP * 4;
-        constexpr int SPB = OST_PAD ? BN + 16 : BN;
-        auto ost_at = [&](int row, int col) {                      // byte offset of column col (a multiple of 4) of a staged row
-            const int piece = OST_SWZ ? ((col >> 4) ^ (row & 15)) : (col >> 4);
-            return row * SPB + (piece << 4) + (col & 15);
-        };
+        constexpr int SPB = BN + 16;                               // staged INT8 rows: 16-byte pieces, padded by one
+        auto ost_at = [&](int row, int col) { return row * SPB + col; };
         constexpr int SPH = 2 * BN + 8;                            // int16 rows: 8-byte pieces, padded by one
         static_assert(SM == 0 || ES != 2 || BM * SPH <= 32 * JC * SP * 4, "the 16-bit staging tile ends where the constants begin");
-        static_assert(SM == 0 || ES != 1 || OST_PAD || OST_SWZ, "the INT8 staging tile fits in front of the constants");
+        static_assert(SM != 1 || ES != 1 || BM * SPB <= 32 * JC * SP * 4, "the INT8 staging tile fits in front of the constants");
         static_assert(SM == 0 || ES != 4, "INT32 outputs are stored by the lanes themselves");
         int8_t* const ostage = lds;
         char* const ct = reinterpret_cast<char*>(g.C) + (c_off + (int64_t)m0 * g.ldc + n0) * (int64_t)ES;
@@ -1015,7 +1007,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
     // 512 tokens x 64: 133.8 -> 125.5 us; the four-wavefront GELU tiles gain nothing from it and 256x128 loses); int16
     // tiles of eight wavefronts (256x192, [32768,768] outputs: K 768 48.3 -> 43.5 us, K 3072 91.7 -> 89.5 us; the
     // four-wavefront tiles lose by it -- 128x96: 9.6 -> 11.0 us; 256x128: 66.5 -> 76.4 us).
-    constexpr bool OST_FITS = BM * (BN + 16) <= 32 * JC * SP * 4 || (BN == 256 && BM * BN <= 32 * JC * SP * 4);
+    constexpr bool OST_FITS = BM * (BN + 16) <= 32 * JC * SP * 4;
     constexpr bool OST = OUT_I8 && (!GELU || NW == 8) && OST_FITS;
     constexpr bool LTS = OUT_I8 && NW == 8 && FN <= 4;             // lane-transposed 16-byte stores instead
     constexpr bool OST16 = !OUT_I8 && NW == 8 && BM <= 64 * JC;

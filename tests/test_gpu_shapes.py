@@ -223,7 +223,7 @@ def test_gemm_persistent_tiles_of_one_step(G, cfg, bn, kind, cols, shift):
                                        (19, 64, 128), (20, 128, 96), (21, 128, 96), (22, 128, 128)])
 def test_gemm_direct_to_lds_ragged_rows(G, cfg, bm, bn):
     # direct-to-LDS tiles whose last tile row is not whole: one row, one less and one more than a tile, several tiles and some
-    kinds = ["i8", "i16res"] + (["gelu"] if cfg in (6, 7, 9, 10, 13, 14) else [])
+    kinds = ["i8", "i16res"] + (["gelu"] if cfg in (6, 7, 8, 9, 10, 13, 14, 16) else [])
     for M, N, K in [(1, bn, 128), (bm - 1, 2 * bn, 256), (bm + 1, bn, 512), (3 * bm + 37, 2 * bn, 384)]:
         for kind in kinds:
             _stream_case(G, cfg, M, N, K, kind, 40, seed=M + N + K)
