@@ -286,11 +286,9 @@ int launch_few(const GemmArgs& g, bool i8, hipStream_t stream)
     else IBERT_FEW_LAUNCH(false);
 #undef IBERT_FEW_LAUNCH
     IBERT_LAUNCH_CHECK("gemm_few_kernel");
-    static char label[2][64];
-    char* l = label[i8 ? 1 : 0];
-    if (!l[0])
-        std::snprintf(l, sizeof label[0], "gemm_few_kernel<%d, %d, %s, %s>", HM, HN, i8 ? "true" : "false", GELU ? "true" : "false");
-    g_last_kernel = l;
+    static const KernelName names[2] = {{"gemm_few_kernel<%d, %d, %s, %s>", HM, HN, "false", GELU ? "true" : "false"},
+                                        {"gemm_few_kernel<%d, %d, %s, %s>", HM, HN, "true", GELU ? "true" : "false"}};
+    g_last_kernel = names[i8 ? 1 : 0].text;
     return IBERT_OK;
 }
 

@@ -1083,6 +1083,13 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
 // Launchers.  Each tile configuration is instantiated in exactly one translation unit (gemm_inst_*.hip, which list
 // their configurations in gemm_instances_*.inc); gemm.hip sees them as extern templates.
 // ---------------------------------------------------------------------------------------------
+// A kernel's name as a profiler shows it, for static objects: made once, also where several threads launch first together.
+struct KernelName {
+    char text[96];
+    template <typename... A>
+    KernelName(const char* format, A... a) { std::snprintf(text, sizeof text, format, a...); }
+};
+
 bool xcd_blocks_enabled();       // (gemm.hip: a switch for A/B measurements, on by default)
 
 template <int BM, int BN, int BK, int RING, bool TW = false, bool DMA = false, bool GELU = false, int NW = 4, int NLD = 0>
@@ -1151,13 +1158,12 @@ int launch_mfma(GemmArgs& g, bool i8, hipStream_t stream)
 #undef IBERT_GEMM_LAUNCH
     IBERT_LAUNCH_CHECK("gemm_nt_mfma_kernel");
     // the name a profiler shows for this instantiation
-    static char label[2][2][96];
-    char* l = label[i8 ? 1 : 0][g.K % BK == 0 ? 0 : 1];
-    if (!l[0])
-        std::snprintf(l, sizeof label[0][0], "gemm_nt_mfma_kernel<%d, %d, %d, %d, %s, %d, %s, %s, %s, %d, %d>", BM, BN, BK, RING,
-                      i8 ? "true" : "false", g.K % BK == 0 ? 0 : 1, TW ? "true" : "false", DMA ? "true" : "false",
-                      GELU ? "true" : "false", NW, NLD);
-    g_last_kernel = l;
+    auto name = [](const char* i8_text, int k_tail) {
+        return KernelName("gemm_nt_mfma_kernel<%d, %d, %d, %d, %s, %d, %s, %s, %s, %d, %d>", BM, BN, BK, RING, i8_text, k_tail,
+                          TW ? "true" : "false", DMA ? "true" : "false", GELU ? "true" : "false", NW, NLD);
+    };
+    static const KernelName names[2][2] = {{name("false", 0), name("false", 1)}, {name("true", 0), name("true", 1)}};
+    g_last_kernel = names[i8 ? 1 : 0][g.K % BK == 0 ? 0 : 1].text;
     return IBERT_OK;
 }
 

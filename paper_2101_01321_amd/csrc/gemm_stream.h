@@ -605,11 +605,9 @@ int launch_stream(GemmArgs& g, bool i8, hipStream_t stream)
     else IBERT_STREAM_LAUNCH(false);
 #undef IBERT_STREAM_LAUNCH
     IBERT_LAUNCH_CHECK("gemm_stream_kernel");
-    static char label[2][96];
-    char* l = label[i8 ? 1 : 0];
-    if (!l[0])
-        std::snprintf(l, sizeof label[0], "gemm_stream_kernel<%d, %d, %d, %s, %s>", BM, BN, NW, i8 ? "true" : "false", GELU ? "true" : "false");
-    g_last_kernel = l;
+    static const KernelName names[2] = {{"gemm_stream_kernel<%d, %d, %d, %s, %s>", BM, BN, NW, "false", GELU ? "true" : "false"},
+                                        {"gemm_stream_kernel<%d, %d, %d, %s, %s>", BM, BN, NW, "true", GELU ? "true" : "false"}};
+    g_last_kernel = names[i8 ? 1 : 0].text;
     return IBERT_OK;
 }
 
