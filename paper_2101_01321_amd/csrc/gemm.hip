@@ -218,8 +218,8 @@ static const TileCost kTileCost[] = {
     {9, 2, {{4894, 572, 2930, 70, 1293, 436}, {3579, 626, 1375, 102, 650, 459}, {5662, 625, 2550, 55, 1694, 526}}}, // 128x96
     {14, 1, {{7647, 840, 9487, 865, 0, 0}, {5131, 882, 4119, 883, 0, 0}, {7561, 833, 6938, 815, 0, 0}}},            // 256x128
     {13, 1, {{10461, 862, 13760, 999, 0, 0}, {6109, 963, 5826, 1068, 0, 0}, {9129, 952, 8517, 1062, 0, 0}}},        // 256x192
-    {24, 1, {{10329, 1000, 8312, 1109, 0, 0}, {6078, 997, 3462, 1137, 0, 0}, {8740, 1000, 4486, 1135, 0, 0}}},      // 256x192, persistent
-    {23, 1, {{11503, 1183, 9054, 1420, 0, 0}, {7019, 1225, 3640, 1465, 0, 0}, {9724, 1177, 5830, 1324, 0, 0}}},     // 256x256, persistent
+    {24, 1, {{9960, 1023, 8159, 1144, 0, 0}, {5910, 966, 3317, 1064, 0, 0}, {8250, 967, 4273, 1092, 0, 0}}},        // 256x192, persistent
+    {23, 1, {{11880, 1206, 7950, 1383, 0, 0}, {7107, 1233, 4365, 1317, 0, 0}, {9420, 1269, 5330, 1342, 0, 0}}},     // 256x256, persistent
 };
 
 static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb, bool gelu)
@@ -239,13 +239,13 @@ static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb
             if (w.first[0] == 0 || (f.direct && !dma_ok(d, f.bn))) continue;
             if (c.config == 23 && !stream_ok<256, 256, 8>(g, i8)) continue;
             if (c.config == 24 && !stream_ok<256, 192, 8>(g, i8)) continue;
-            // One 256x192 tile for every unit, dealt evenly to the XCDs: the persistent kernel has nothing to stream, and the estimates
-            // of the two kernels are closer than their fits.  us, persistent / not: with GELU, K 768, [4096,3072] 18.0 / 17.0,
-            // [16384,768] 17.5 / 16.9, [2048,3072] 15.2 / 14.4, and at K 128 11.0 / 10.7, K 4096 49.8 / 44.3; INT8 even up to
-            // K 256, 15.5 / 14.9 at 768.  (An uneven deal has no XCD blocks in the kernel that is not persistent, and the
-            // persistent one is ahead there: [16072,768] x K 768 with GELU 17.1 / 18.3; INT16: as estimated.)
-            if (c.config == 24 && i8 && tiles(256, 192) <= 256 && tiles(256, 192) % 8 == 0) continue;
             const int64_t k = d.K / 128;
+            // One 256x192 tile for every unit, dealt evenly to the XCDs, and few steps: the persistent kernel has nothing to stream.
+            // Back to back on one problem the two are within 2 % of each other (us, persistent / not, [4096,3072]: GELU at K 128 10.8 / 10.4,
+            // 256 11.8 / 12.0, 768 15.3 / 15.5; INT8 at K 128 9.1 / 9.1, 768 13.2 / 13.4, 1024 15.1 / 15.1); between other kernels, where
+            // each starts with cold instruction and constant caches, the smaller code of the persistent one is ahead (S7+S8 of Base
+            // b32 inside the forward 16.4 / 17.4), which is where the longer loops are met.
+            if (c.config == 24 && i8 && tiles(256, 192) == 256 && k <= (gelu ? 2 : 6)) continue;
             int64_t n, share = c.share;
             if (share == 0) {
                 if (!few_ok(g, f.bn, i8)) continue;

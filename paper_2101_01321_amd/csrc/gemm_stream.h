@@ -15,13 +15,19 @@
 //     (With a step as one unit all its requests fall into the half after the barrier and take longer than the MFMAs.)
 //   * The stream of steps runs on into the next tile: while the epilogue of a tile runs, the first two steps of the next
 //     one arrive.  The GELU table is built once per workgroup.
-//   * What bounds it: a 256x256 step takes about 2900 cycles for 2048 of MFMA (the rest is address work, barriers and the clock
-//     that the matrix cores' power draw brings down: 2.7-2.85 POP/s in the loop, 3.7-3.85 for MFMA alone on random data), an
-//     epilogue 6000 (INT8), 9000 (GELU) or 13000 (INT16 + residual).  Measured against one workgroup per tile, us, W cold:
-//     [32768,4096] x K 1024 with GELU 212 -> 142, [15311,3072] x K 768 with GELU 115 -> 45 (any M: tiles may be ragged),
-//     [32768,1024] x K 1024 + residual 62 -> 44, [32768,768] x K 768 at 512 tokens 38.5 -> 34; K 3072, N 768 loses 3 %.
+//   * What bounds it: a 256x256 step takes about 2500 cycles for 2048 of MFMA (the rest is barriers and waiting for the address
+//     unit), at a clock that the denser loop itself brings down (sclk read during [32768,1024] x K 4096: 1.91 GHz; 1.98 when a step took
+//     2900 cycles; 3.7-4.0 POP/s is MFMA alone on random data).  What the loop issues beside the MFMAs counts: operands addressed as
+//     buffers, with the step as the scalar offset, in place of 64-bit addresses with a row minimum and a test for every request: a third
+//     of the scalar instructions (1.24e7 -> 4.1e6 for 8.4e6 MFMAs), us: [32768,1024] x K 4096 INT8 117.6 -> 108.9, [32768,4096] x
+//     K 1024 + GELU 150.6 -> 141.5, 256x192: [32768,768] x K 3072 INT8 77.3 -> 67.7, INT16 83.5 -> 79.0, [4096,3072] x K 768 + GELU 17.9 -> 17.1.
+//     (Requests of the two wavefronts of a SIMD half a slot apart, behind a branch each, gave all of it back.)  An epilogue is
+//     6000 cycles (INT8), 9000 (GELU) or 13000 (INT16 + residual).
+//   * Measured against one workgroup per tile, us, W cold, when it came: [32768,4096] x K 1024 with GELU 212 -> 142, [15311,3072] x K 768
+//     with GELU 115 -> 45 (any M: tiles may be ragged), [32768,1024] x K 1024 + residual 62 -> 44.
 //   * Everything must fit the registers: with one spill the loop takes 1.6 times as long, even where no scratch is touched.
-//   * Rows past M (any M is allowed) are read from the last row, computed like it and stored onto it: the same bytes again.
+//   * Rows past M (any M is allowed) are computed from zeros and not stored: operands, residual and output are addressed as buffers
+//     that end with the last row.
 #pragma once
 #include "gemm_kernel.h"
 
@@ -92,6 +98,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
     const int x = blockIdx.x & 7;
     const int nb = (x & ((1 << g.xs) - 1)) * g.bn, group = g.tiles_m * g.bn, xm = x >> g.xs;
     const int t0 = (int)(((int64_t)xm * group) >> g.gs), count = (int)(((int64_t)(xm + 1) * group) >> g.gs) - t0;
+    const uint32_t kbytes = (uint32_t)g.nk * 128u;                 // bytes of a row that the K steps cover
     int lt = blockIdx.x >> 3;                                      // index inside the run
     if (lt >= count) return;
     auto tile_at = [&](int l, int& m0, int& n0) {
@@ -103,47 +110,66 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
     // ---- requests -------------------------------------------------------------------------------
     // lane l of a request brings, for row l / 8 of its 8, the chunk that the swizzle (row / 2 mod 8) puts at byte 16 l.  Request k
     // of a wavefront in a region whose wavefront tiles have nb blocks of 8 rows there: block (wave + NW k) % nb of tile
-    // (wave + NW k) / nb -- its parity is the wavefront's, so the lane's chunk is the same in all of them.
+    // (wave + NW k) / nb -- its parity is the wavefront's, so the lane's chunk is the same in all of them, and the next request of
+    // the region is a fixed number of rows on.
+    // The operands of the tile are buffers: their descriptors hold the tile's first row and its bytes, the lanes' row offsets stay
+    // the same from tile to tile, and the K step is the scalar offset.  Rows past M, and whole steps past the last tile, lie outside
+    // the buffer and read as zeros, so a request is one addition for its place in LDS and the load, with no test and no minimum.
     const int r8 = lane >> 3;
     const uint32_t chunk = (uint32_t)(((lane & 7) ^ (((wave & 1) << 2) | (r8 >> 1))) << 4);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)lds;
-    auto block_row = [&](int k, int nb, int rows, int first) { const int q = wave + NW * k; return q / nb * rows + first + q % nb * 8; };
-    const int8_t *ra, *rw;                                         // request stream: operand rows of its tile, at its step
-    const uint32_t va = (uint32_t)r8 * (uint32_t)g.lda, vw = (uint32_t)r8 * (uint32_t)g.ldw + chunk;
-    int rlast = 0;                                                 // last row of A, counted from the tile's first, or any beyond BM + 6
-    int rlt = lt, rk = 0;
-    uint32_t rstage = lds0;
-    bool rlive = true;
+    static_assert(FMH * 2 % NW == 0 || NW % (FMH * 2) == 0, "rows of the requests of a region at a fixed distance");
+    auto first_row = [&](int nb, int rows) { return wave / nb * rows + wave % nb * 8; };
+    constexpr int SA = NW / (FMH * 2) * WM, SW0 = NW / (FN0 * 2) * WN, SW1 = NW / (FN1 * 2) * WN;     // rows from request to request
+    const int pa = first_row(FMH * 2, WM), pw0 = first_row(FN0 * 2, WN), pw1 = first_row(FN1 * 2, WN) + FN0 * 16;
+    uint32_t va[2][QA];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < QA; ++q) va[h][q] = (uint32_t)(pa + h * (WM / 2) + q * SA + r8) * (uint32_t)g.lda + chunk;
+    const uint32_t vw0 = (uint32_t)(pw0 + r8) * (uint32_t)g.ldw + chunk, vw1 = (uint32_t)(pw1 + r8) * (uint32_t)g.ldw + chunk;
+    const uint32_t sw0 = (uint32_t)(SW0 * g.ldw), sw1 = (uint32_t)(SW1 * g.ldw);
+    static_assert(QW0 <= 2 && QW1 <= 2, "scalar offsets of the W requests");
+    v4i da, dw;                                                    // request stream: descriptors of its tile's operands
+    da[3] = dw[3] = 0x00020000;                                    // (32-bit data, raw)
+    uint32_t koff = 0, kinc = 128, rstage = lds0;                  // byte of its K step, bytes to the next one; stage
+    int rlt = lt;
+    auto buffer = [](v4i& d, const void* p, uint32_t bytes) {
+        const uint64_t u = (uint64_t)(uintptr_t)p;
+        d[0] = (int32_t)(uint32_t)u;
+        d[1] = (int32_t)((uint32_t)(u >> 32) & 0xffffu);
+        d[2] = (int32_t)bytes;
+    };
     auto request_tile = [&](int l) {
-        int m0, n0;
-        tile_at(l, m0, n0);
-        ra = g.A + (int64_t)m0 * g.lda;
-        rw = g.W + (int64_t)n0 * g.ldw;
-        // (a request reaches seven rows beyond its first; more rows than that could take the distance in bytes past 2^32)
-        rlast = g.M - 1 - m0 < BM + 7 ? g.M - 1 - m0 : BM + 7;
+        if (l < count) {
+            int m0, n0;
+            tile_at(l, m0, n0);
+            const int rows = g.M - m0 < BM ? g.M - m0 : BM;
+            buffer(da, g.A + (int64_t)m0 * g.lda, (uint32_t)rows * (uint32_t)g.lda);
+            buffer(dw, g.W + (int64_t)n0 * g.ldw, (uint32_t)BN * (uint32_t)g.ldw);
+            kinc = 128;
+        } else {                                                   // empty buffers, for good
+            da[2] = dw[2] = 0;
+            kinc = 0;
+        }
     };
     // request q of group h (0 or 1): the A rows first
     auto request_one = [&](int h, int q) {
         const bool is_a = q < QA;
-        const int row = is_a ? block_row(q, FMH * 2, WM, h * (WM / 2))
-                             : (h == 0 ? block_row(q - QA, FN0 * 2, WN, 0) : block_row(q - QA, FN1 * 2, WN, FN0 * 16));
-        const uint32_t la = rstage + (uint32_t)((is_a ? 0 : BM * 128) + row * 128);
-        const int first = is_a ? (row < rlast ? row : rlast) : row;
-        const int8_t* sb = is_a ? ra + (int64_t)first * g.lda : rw + (int64_t)first * g.ldw;
-        const uint32_t most = (uint32_t)(rlast - first) * (uint32_t)g.lda;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                     :: "s"(la), "v"(is_a ? (va < most ? va : most) + chunk : vw), "s"(sb) : "memory", "m0");
+        const int k = is_a ? q : q - QA;
+        const int row = is_a ? h * (WM / 2) + k * SA : k * (h == 0 ? SW0 : SW1);
+        const uint32_t place = rstage + (uint32_t)((is_a ? pa : BM + (h == 0 ? pw0 : pw1)) * 128);
+        asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tbuffer_load_dwordx4 %2, %3, %4 offen lds"
+                     :: "s"(place), "i"(row * 128), "v"(is_a ? va[h][is_a ? k : 0] : (h == 0 ? vw0 : vw1)), "s"(is_a ? da : dw),
+                        "s"(is_a || k == 0 ? koff : koff + (h == 0 ? sw0 : sw1)) : "memory", "m0", "scc");
     };
     auto request_advance = [&]() {
-        if (!rlive) return;
-        ra += 128;
-        rw += 128;
+        koff += kinc;
         rstage = 2 * lds0 + (uint32_t)SL::STAGE - rstage;
-        if (++rk == g.nk) {
-            rk = 0;
+        if (koff == kbytes) {
+            koff = 0;
             rlt += g.per_xcd;
-            rlive = rlt < count;
-            if (rlive) request_tile(rlt);
+            request_tile(rlt);
         }
     };
     // Constants of a tile's columns (bias, mult, shift: 3 x BN dwords) by DMA, 64 dwords per request, dealt round the
@@ -200,10 +226,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
     tile_at(lt, m0, n0);
     request_constants(n0);
     request_tile(lt);
-    int left = ((count - lt + g.per_xcd - 1) / g.per_xcd) * g.nk;  // steps not yet computed
     auto request_two_steps = [&]() {
 #pragma unroll 1
-        for (int st = 0; st < 2 && rlive; ++st) {
+        for (int st = 0; st < 2; ++st) {
 #pragma unroll
             for (int q = 0; q < N0; ++q) request_one(0, q);
 #pragma unroll
@@ -220,8 +245,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
             lut[e] = (int8_t)(g.gelu_fast ? gelu_one_fast(q, g.gelu, rnd, sh) : gelu_one(q, g.gelu));
         }
     }
-    if (left >= 2) __builtin_amdgcn_s_waitcnt(vm(N0 + N1));
-    else __builtin_amdgcn_s_waitcnt(vm(0));
+    __builtin_amdgcn_s_waitcnt(vm(N0 + N1));
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
     // The MFMAs of one quadrant: W blocks i0 .. i0 + NI - 1 (operands xw) by A blocks j0 .. j0 + FMH - 1 (operands xa), slice by
@@ -254,7 +278,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         auto ask = [&](int h, int n, int idx) {
 #pragma unroll
             for (int r = 0; r < N0 + N1; ++r)
-                if (r < n && idx == (2 * r + 1) * (M0 + M1) / (2 * n) && rlive) request_one(REQ == 2 ? (r < N0 ? 0 : 1) : h, REQ == 2 && r >= N0 ? r - N0 : r);
+                if (r < n && idx == (2 * r + 1) * (M0 + M1) / (2 * n)) request_one(REQ == 2 ? (r < N0 ? 0 : 1) : h, REQ == 2 && r >= N0 ? r - N0 : r);
         };
         quadrant(w0, NI0{}, 0, at, 0, [&](int idx) {
             if (idx < 2 * FN1) read_w1(stage, idx);
@@ -267,14 +291,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         if (wait) {
             // group 0 of the next step has landed when only younger requests are outstanding: group 1 of that step and (made in
             // this half) group 0 of the one after
-            if (REQ == 1 && left >= 3) __builtin_amdgcn_s_waitcnt(vm(N1 + N0));
-            else if (left >= 2) __builtin_amdgcn_s_waitcnt(vm(N1));
-        } else if (REQ == 2 && rk == 0) {
+            __builtin_amdgcn_s_waitcnt(vm(REQ == 1 ? N1 + N0 : N1));
+        } else if (REQ == 2 && koff == 0) {
             // A tile of one step has no later step whose wait covers the constants requested at its head; behind them nothing has
             // been requested yet (counting would not do: the last tile's stores stand in the queue before them).  The requests
-            // are two steps ahead here, at step 2 of nk: rk is 0 for one step always, for two where the wait does no harm, and
-            // for none with more.  (g.nk itself, kept for this test, costs scalar registers that the loop then spills: with K
-            // 1024 and 4096 and 32768 rows 0.5 %.)
+            // are two steps ahead here, at step 2 of nk: koff is 0 for one step always, for two where the wait does no harm, and
+            // for none with more.
             __builtin_amdgcn_s_waitcnt(vm(0));
         }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -287,13 +309,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
             ask(1, REQ == 2 ? N0 + N1 : N1, M0 + idx);
         });
         request_advance();
-        if (wait) {
-            if (left >= 3) __builtin_amdgcn_s_waitcnt(vm(N0 + N1));    // the same for its group 1
-            else __builtin_amdgcn_s_waitcnt(vm(0));
-        }
+        if (wait) __builtin_amdgcn_s_waitcnt(vm(N0 + N1));             // the same for its group 1
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         stage = nst;
-        --left;
     };
 
     bool first = true;
@@ -312,7 +330,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         // requested just now, are covered by the first wait of its second step, which leaves only younger requests outstanding --
         // a tile of one step waits for them by itself)
         step(R2{}, first);
-        for (int kt = 1; kt < g.nk; ++kt) step(R1{}, true);
+        for (uint32_t kt = 128; kt < kbytes; kt += 128) step(R1{}, true);
 
         // ---- epilogue ---------------------------------------------------------------------------
         // acc[i][j][e] = C[m0 + wm0 + 16 j + frow][n0 + wn0 + 16 i + 4 fch + e]
@@ -327,13 +345,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         kernel_args ga = nullptr;
 #endif
         const int last = ga->M - 1 - m0;
-        auto row_of = [&](int j) {                                 // row of the tile, clamped to the last one
-            const int row = wm0 + 16 * j + frow;
-            return (uint32_t)(row < last ? row : last);
-        };
+        // Output and residual are buffers that end with the last row: lanes past it load zeros and store nothing.
+        const int rows = last < BM ? last : BM - 1;                // (whole rows of them before the last one's BN columns)
+        const uint32_t row0 = (uint32_t)(wm0 + frow);
         // Residual: 16 bytes of a row per lane, then the same transposition as for the stores (an involution) hands
         // every lane the four channels it holds accumulators of.
         typedef unsigned v2u __attribute__((ext_vector_type(2)));
+        typedef unsigned v4u __attribute__((ext_vector_type(4)));
         auto transpose4 = [](uint32_t& r0, uint32_t& r1, uint32_t& r2, uint32_t& r3) {
             v2u t = __builtin_amdgcn_permlane32_swap(r0, r2, false, false); r0 = t.x; r2 = t.y;
             t = __builtin_amdgcn_permlane32_swap(r1, r3, false, false); r1 = t.x; r3 = t.y;
@@ -348,10 +366,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
 #pragma unroll
             for (int j = 0; j < (OUT_I8 ? 1 : JH); ++j) rt[H][j] = v4i{0, 0, 0, 0};
             if (!OUT_I8 && has_res) {
-                const int8_t* rb = ga->R + (int64_t)m0 * ga->ldr + n0 + wn0;
+                const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(ga->R + (int64_t)m0 * ga->ldr + n0), 0,
+                                                                  (int)((uint32_t)rows * (uint32_t)ga->ldr + BN), 0x00020000);
 #pragma unroll
                 for (int j = 0; j < JH; ++j)
-                    rt[H][j] = *reinterpret_cast<const v4i*>(rb + row_of(H * JH + j) * (uint32_t)ga->ldr + (uint32_t)((fch < FN ? fch : 0) * 16));
+                    rt[H][j] = __builtin_amdgcn_raw_buffer_load_b128(rb, (int)((row0 + 16 * (H * JH + j)) * (uint32_t)ga->ldr +
+                                                                               (uint32_t)(wn0 + (fch < FN ? fch : 0) * 16)), 0, 0);
             }
         };
         // Fast form: every shift in [33, 62], every |bias| and K * 127^2 below 2^30, the residual shift in [8, 62] (see gemm_kernel.h),
@@ -372,7 +392,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         const int32_t lut_hi = ga->gelu_lut_n - 1;
         const int32_t clamp_lo = -ga->out_clamp, clamp_hi = ga->out_clamp;
         constexpr uint32_t ES = OUT_I8 ? 1 : 2;
-        char* const cb = reinterpret_cast<char*>(ga->C) + ((int64_t)m0 * ga->ldc + n0 + wn0) * ES;
+        const auto cb = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(ga->C) + ((int64_t)m0 * ga->ldc + n0) * ES, 0,
+                                                          (int)(((uint32_t)rows * (uint32_t)ga->ldc + BN) * ES), 0x00020000);
         if (ga->path_word && m0 == 0 && n0 == 0 && tid == 0)
             *ga->path_word = !fast ? IBERT_EPILOGUE_STAGED : (GELU ? IBERT_EPILOGUE_DIRECT_GELU_TABLE : IBERT_EPILOGUE_DIRECT);
         // INT16: the rows of the wavefront in two halves, which keeps the packed results (two dwords a group) and the residual
@@ -466,10 +487,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int j = 0; j < JH; ++j) {
-                const uint32_t off = (row_of(jh + j) * (uint32_t)ga->ldc + (uint32_t)(16 / ES * fch)) * ES;
+                const uint32_t off = ((row0 + 16 * (jh + j)) * (uint32_t)ga->ldc + (uint32_t)(wn0 + 16 / ES * fch)) * ES;
                 if constexpr (OUT_I8) {
                     transpose4(pq[0][j][0], pq[0][j][1], pq[0][j][2], pq[0][j][3]);
-                    if (fch < FN) *reinterpret_cast<v4i*>(cb + off) = v4i{(int)pq[0][j][0], (int)pq[0][j][1], (int)pq[0][j][2], (int)pq[0][j][3]};
+                    if (fch < FN) __builtin_amdgcn_raw_buffer_store_b128(v4u{pq[0][j][0], pq[0][j][1], pq[0][j][2], pq[0][j][3]}, cb, (int)off, 0, 0);
                 } else {
                     // two block columns are 64 bytes of a row: lane group u takes bytes 16 u .. +15, which are the dword pairs of
                     // column u / 2 from the groups 2 (u % 2) and the next -- the same two swaps
@@ -481,7 +502,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
                         v2u u = __builtin_amdgcn_permlane32_swap(pq[H][j][p], pq[H][j][p + 1], false, false);
                         u = __builtin_amdgcn_permlane16_swap(u.x, u.y, false, false);
                         if (p + 1 < FN || fch < 2)
-                            *reinterpret_cast<v4i*>(cb + off + 32 * p) = v4i{(int)t.x, (int)u.x, (int)t.y, (int)u.y};
+                            __builtin_amdgcn_raw_buffer_store_b128(v4u{t.x, u.x, t.y, u.y}, cb, (int)(off + 32 * p), 0, 0);
                     }
                 }
             }
@@ -532,15 +553,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
                 __syncthreads();
             }
             rlt = lt + g.per_xcd;
-            rlive = rlt < count;
-            if (rlive) {
-                rk = 0;
-                rstage = lds0 + (uint32_t)stage;
-                request_tile(rlt);
-                request_two_steps();
-                __builtin_amdgcn_s_waitcnt(vm(0));
-                asm volatile("s_barrier" ::: "memory");
-            }
+            koff = 0;
+            rstage = lds0 + (uint32_t)stage;
+            request_tile(rlt);
+            request_two_steps();
+            __builtin_amdgcn_s_waitcnt(vm(0));
+            asm volatile("s_barrier" ::: "memory");
         }
         lt += g.per_xcd;
         if (lt >= count) break;

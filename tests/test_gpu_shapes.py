@@ -118,6 +118,53 @@ def test_gemm_persistent_tiles(G, cfg, bn, kind):
         _stream_case(G, cfg, M, N, K, kind, shift, seed=M + N + K)
 
 
+@pytest.mark.parametrize("cfg,bn", [(23, 256), (24, 192)])
+@pytest.mark.parametrize("kind", ["i8", "i16", "i16res"])
+def test_gemm_persistent_tiles_inside_wider_rows(G, cfg, bn, kind):
+    # operands, residual and output as columns of wider rows, the last tile row ragged: rows past M are neither read into the result
+    # nor stored, and nothing beside the output's own columns changes (buffers end with the last row's last column)
+    import torch
+    from paper_2101_01321_amd import binding as B
+    rng = np.random.default_rng(bn)
+    for M, N, K in [(1, bn, 128), (249, 2 * bn, 256), (257, bn, 384), (256 * 34 + 5, 2 * bn, 128)]:
+        pa, pw, pc, pr = 48, 16, 32, 64                            # columns beside the problem's own
+        A, W = (rng.integers(-127, 128, size=(n, K + p), dtype=np.int8) for n, p in ((M + 9, pa), (N, pw)))
+        R = rng.integers(-127, 128, size=(M + 9, N + pr), dtype=np.int8) if kind == "i16res" else None
+        bias = rng.integers(-50000, 50000, size=N, dtype=np.int32)
+        mult = rng.integers(2 ** 29, 2 ** 30, size=N, dtype=np.int64).astype(np.int32)
+        shifts = np.full(N, 40, np.int32)
+        d = B.GemmDesc()
+        for k, v in dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K + pa, ldw=K + pw, ldc=N + pc, ldr=N + pr, per_channel=1,
+                         residual_dy=B.Dyadic(1717986918, 23), out_dtype=I8 if kind == "i8" else I16,
+                         out_clamp=127 if kind == "i8" else 32767).items():
+            setattr(d, k, v)
+        dt = np.int8 if kind == "i8" else np.int16
+        tC = G.to_dev(np.full((M + 9, N + pc), 77, dt))
+        B.lib().ibert_gemm_config_override(cfg)
+        try:
+            G.say("persistent gemm inside wider rows cfg %d M=%d N=%d K=%d %s" % (cfg, M, N, K, kind))
+            B.ibert_gemm_i8_requant(d, G.to_dev(A), G.to_dev(W), G.to_dev(bias), G.to_dev(mult), G.to_dev(shifts),
+                                    None if R is None else G.to_dev(R), tC)
+            torch.cuda.synchronize()
+        finally:
+            B.lib().ibert_gemm_config_override(-1)
+        assert B.lib().ibert_last_kernel().decode().startswith(G.kernel_of(cfg))
+        spec = GemmSpec(M, N, K, per_channel=1, dy=(1, 0), out_dtype=I8 if kind == "i8" else I32,
+                        out_clamp=127 if kind == "i8" else 32767, res_dy=(1717986918, 23))
+        dense = [np.ascontiguousarray(t) for t in (A[:M, :K], W[:, :K])]
+        want = oracle.gemm_requant(spec, *dense, bias, mult, shifts, None if R is None else np.ascontiguousarray(R[:M, :N])).reshape(M, N)
+        got = tC.cpu().numpy()
+        _eq(got[:M, :N].astype(np.int64), want.astype(np.int64), "persistent gemm inside wider rows")
+        assert np.all(got[M:] == 77) and np.all(got[:, N:] == 77), "wrote beside the output"
+
+
+@pytest.mark.parametrize("M,N,K,kind,kernel", [(4096, 3072, 768, "gelu", "gemm_stream_kernel<256, 192, "),      # one tile a unit, longer loops
+                                               (4096, 3072, 1024, "i8", "gemm_stream_kernel<256, 192, "),
+                                               (4096, 2304, 768, "i8", "gemm_stream_kernel<256, 192, ")])
+def test_gemm_persistent_tile_chosen(G, M, N, K, kind, kernel):
+    _stream_case(G, -1, M, N, K, kind, 40, seed=M, kernel=kernel)
+
+
 @pytest.mark.parametrize("M,N,K,kind,kernel", [(4096, 3072, 256, "gelu", "gemm_nt_mfma_kernel<256, 192, "),     # 16 x 16 tiles
                                                (4096, 3072, 768, "i8", "gemm_nt_mfma_kernel<256, 192, "),
                                                (16072, 768, 256, "gelu", "gemm_stream_kernel<256, 192, "),      # 63 x 4: uneven
