@@ -194,6 +194,10 @@ static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // counts, which this replaces, took 16 % longer with the same configurations.  Some lines they could not draw: [4096,1024] x
 // K 4096 to 4096 rows more, 52 -> 40 us at 8192 rows; 2741 rows of [768] x K 3072 25.1 -> 14.5 us (the last tile row is
 // ragged); a second round of large tiles that would be nearly empty, [5120,1024] x K 1024 19.7 -> 13.3 us.
+// (GELU on the tiles with loaders, from 13 problems with up to 2741 rows, and the persistent tiles, from 240 with the INT8
+// 256x192 tile as the yardstick, were fitted later.  The wavefronts that only multiply have nothing to do until the first tiles
+// arrive and build the GELU table then: [488,3072] x K 768 8.4 -> 7.5 us, [1024,4096] x K 1024 12.0 -> 9.4, which are
+// one tile for at most every unit; 64x96 and 64x128 tiles with GELU were slower than these wherever they were tried.)
 struct TileCost {
     int config, share;                      // share 0: gemm_few.h
     struct { int first[2], more[2], again[2]; } kind[3];
@@ -211,9 +215,9 @@ static const TileCost kTileCost[] = {
     {2, 2, {{7472, 628, 4126, 395, 0, 310}, {6288, 662, 2788, 409, 0, 256}, {0, 0, 0, 0, 0, 0}}},                   // 128x128, ring
     {17, 2, {{4020, 347, 1212, 163, 1459, 70}, {3501, 377, 823, 116, 1047, 203}, {0, 0, 0, 0, 0, 0}}},              // 64x96, three stages
     {18, 3, {{3525, 511, 1447, 72, 682, 329}, {3070, 557, 758, 56, 683, 435}, {0, 0, 0, 0, 0, 0}}},                 // 64x96
-    {21, 1, {{5825, 320, 4836, 333, 0, 0}, {4587, 353, 3465, 353, 0, 0}, {0, 0, 0, 0, 0, 0}}},                      // 128x96, with loaders
+    {21, 1, {{5825, 320, 4836, 333, 0, 0}, {4587, 353, 3465, 353, 0, 0}, {5450, 353, 4050, 353, 0, 0}}},            // 128x96, with loaders
     {19, 3, {{3722, 557, 1848, 109, 0, 409}, {3329, 618, 916, 82, 254, 483}, {0, 0, 0, 0, 0, 0}}},                  // 64x128
-    {22, 1, {{6537, 376, 5539, 420, 0, 0}, {4967, 408, 3662, 420, 0, 0}, {0, 0, 0, 0, 0, 0}}},                      // 128x128, with loaders
+    {22, 1, {{6537, 376, 5539, 420, 0, 0}, {4967, 408, 3662, 420, 0, 0}, {5700, 408, 4450, 420, 0, 0}}},            // 128x128, with loaders
     {7, 2, {{5451, 645, 5215, 637, 0, 0}, {3978, 690, 2886, 617, 0, 0}, {6445, 655, 5733, 630, 0, 0}}},             // 128x128
     {9, 2, {{4894, 572, 2930, 70, 1293, 436}, {3579, 626, 1375, 102, 650, 459}, {5662, 625, 2550, 55, 1694, 526}}}, // 128x96
     {14, 1, {{7647, 840, 9487, 865, 0, 0}, {5131, 882, 4119, 883, 0, 0}, {7561, 833, 6938, 815, 0, 0}}},            // 256x128
@@ -328,6 +332,8 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
                 case 5: case 9: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 2, false, true, true>(g, i8, stream); break;
                 case 0: case 6: case 13: if (dma_ok(d, 192)) return launch_mfma<256, 192, 128, 2, false, true, true, 8>(g, i8, stream); break;
                 case 10: case 14: if (dma_ok(d, 128)) return launch_mfma<256, 128, 128, 2, false, true, true, 8>(g, i8, stream); break;
+                case 11: case 20: case 21: if (dma_ok(d, 96)) return launch_mfma<128, 96, 128, 3, false, true, true, 8, 4>(g, i8, stream); break;
+                case 12: case 22: if (dma_ok(d, 128)) return launch_mfma<128, 128, 128, 3, false, true, true, 8, 4>(g, i8, stream); break;
                 case 8: case 16: case 23: return launch_stream<256, 256, 8, true>(g, i8, stream);
                 case 24: return launch_stream<256, 192, 8, true>(g, i8, stream);
                 case 25: return launch_few<1, 1, true>(g, i8, stream);

@@ -165,7 +165,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
     constexpr int NT = 64 * NW;
     static_assert(NW == 4 || (NW == 8 && DMA), "four wavefronts, or eight for the direct-to-LDS loader");
     static_assert(!GELU || OUT_I8, "the GELU epilogue writes INT8");
-    static_assert(NLD == 0 || (NLD == 4 && DMA && !GELU), "loader wavefronts: four, direct-to-LDS tiles");
+    static_assert(NLD == 0 || (NLD == 4 && DMA), "loader wavefronts: four, direct-to-LDS tiles");
     constexpr int CPR = BK / 16;                       // 16-byte chunks per tile row
     constexpr int RPP = NT / CPR;            // tile rows loaded per pass of the workgroup
     constexpr int LA = BM / RPP, LW = BN / RPP;        // chunks per lane per K step
@@ -512,12 +512,12 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             // outside of which it is constant -- below q_b the result is DY(0), from the first saturated value up
             // it stays saturated -- so that the epilogue replaces ~17 instructions per value by a clamp and a byte
             // read.  Every workgroup builds its own copy with the very function the table stands for.
-            // (by the wavefronts that request no tiles, where there are such: the others are busy asking)
+            // (by the wavefronts that request no tiles, where there are such, and not by those that request only)
             int8_t* lut = lds + EL::LDS_BYTES + PAR_BYTES;
             const int32_t rnd = 1 << ((g.gelu.s - 33) & 31), sh = (g.gelu.s - 32) & 31;
-            constexpr int NB = ND < NW ? NT - 64 * ND : NT;            // threads that build
-            if (ND == NW || !asker) {
-                for (int e = ND < NW ? tid - 64 * ND : tid; e < g.gelu_lut_n; e += NB) {
+            constexpr int B0 = NLD == 0 && ND < NW ? 64 * ND : 0;      // first of the threads that build
+            if (NLD > 0 ? !loader : (ND == NW || !asker)) {
+                for (int e = tid - B0; e < g.gelu_lut_n; e += NT - B0) {
                     const int32_t q = g.gelu_lut_lo + e;
                     lut[e] = (int8_t)(g.gelu_fast ? gelu_one_fast(q, g.gelu, rnd, sh) : gelu_one(q, g.gelu));
                 }
@@ -1001,7 +1001,10 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             }
         }
     };
-    // Which tiles leave through LDS (measured): INT8 tiles without GELU, and with GELU those of eight wavefronts -- a lane's
+    // How INT8 tiles leave: lane-transposed 16-byte stores where the wavefronts are narrow enough and there is no residual (all
+    // direct-to-LDS tiles; four wavefronts against whole rows through LDS or a lane's own stores, us: [488,2304] x K 768 5.86 -> 5.74,
+    // [2048,2304] x K 768 8.81 -> 8.66, with GELU [1024,4096] x K 1024 on 64x128 11.5 -> 11.2).
+    // Which others leave through LDS (measured): INT8 tiles without GELU, and with GELU those of eight wavefronts -- a lane's
     // own store would be 4 bytes in each of 16 rows per instruction, which the address unit takes an order of magnitude
     // longer over than whole rows (a gain of 1.5-2 us on the QKV projections; S7+S8 of Base 18.9 -> 17.9 us, of Base at
     // 512 tokens x 64: 133.8 -> 125.5 us; the four-wavefront GELU tiles gain nothing from it and 256x128 loses); int16
@@ -1009,7 +1012,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
     // four-wavefront tiles lose by it -- 128x96: 9.6 -> 11.0 us; 256x128: 66.5 -> 76.4 us).
     constexpr bool OST_FITS = BM * (BN + 16) <= 32 * JC * SP * 4;
     constexpr bool OST = OUT_I8 && (!GELU || NW == 8) && OST_FITS;
-    constexpr bool LTS = OUT_I8 && NW == 8 && FN <= 4;             // lane-transposed 16-byte stores instead
+    constexpr bool LTS = OUT_I8 && FN <= 4;                        // lane-transposed 16-byte stores instead
     constexpr bool OST16 = !OUT_I8 && NW == 8 && BM <= 64 * JC;
     using T = std::true_type;
     using F = std::false_type;

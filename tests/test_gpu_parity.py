@@ -573,6 +573,12 @@ def test_gemm_gelu_every_gelu_input_value(G, cfg, table, S_in, S_out):
     _eq(got, want, "gemm+gelu sweep")
 
 
+@pytest.mark.parametrize("cfg", [21, 22])
+@pytest.mark.parametrize("table", [True, False])
+def test_gemm_gelu_every_gelu_input_value_on_tiles_with_loaders(G, cfg, table):
+    test_gemm_gelu_every_gelu_input_value(G, cfg, table, 2.0 ** -6, 0.748)
+
+
 def test_gemm_base_shapes_full(G):
     # the four projection GEMMs of RoBERTa-Base at batch 32 (T = 4096), full outputs
     for M, N, K, od, res in [(4096, 2304, 768, I8, False), (4096, 768, 768, I32, True), (4096, 3072, 768, I32, False),

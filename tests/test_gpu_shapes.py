@@ -276,6 +276,15 @@ def test_gemm_direct_to_lds_ragged_rows(G, cfg, bm, bn):
             _stream_case(G, cfg, M, N, K, kind, 40, seed=M + N + K)
 
 
+@pytest.mark.parametrize("cfg,bm,bn", [(21, 128, 96), (22, 128, 128)])
+def test_gemm_gelu_on_tiles_with_loaders(G, cfg, bm, bn):
+    # GELU where four wavefronts only request tiles: one K step (fewer than stages) to more steps than stages, rows at and off a tile
+    # edge, one and several tiles a unit; the table and (shift 30) the 64-bit form
+    for M, N, K, shift in [(1, bn, 128, 40), (bm - 1, 2 * bn, 256, 40), (bm + 1, bn, 512, 40), (3 * bm + 37, 24 * bn, 384, 40),
+                           (33 * bm + 5, 9 * bn, 128, 40), (bm + 9, 3 * bn, 640, 30)]:
+        _stream_case(G, cfg, M, N, K, "gelu", shift, seed=M + N + K)
+
+
 @pytest.mark.parametrize("cfg,bn,lda,M", [(7, 128, 1 << 22, 1025), (9, 96, 1 << 22, 1030), (13, 192, 1 << 22, 1025), (14, 128, 1 << 22, 1033),
                                           (17, 96, 1 << 22, 1025), (21, 96, 1 << 22, 1025), (22, 128, 1 << 22, 1025),
                                           (23, 256, 1 << 19, 8193), (24, 192, 1 << 19, 8198)])
