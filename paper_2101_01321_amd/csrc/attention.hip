@@ -31,7 +31,8 @@ struct AttentionArgs {
     const int8_t* qkv;     // [batch*seq, 3*hidden]: Q | K | V, heads side by side
     int8_t* ctx;           // [batch*seq, hidden]
     int32_t heads, seq, qblks;
-    uint32_t qblks_magic, heads_magic;   // floor(2^32 / d) + 1: see udiv
+    int32_t blocks;        // workgroups of the attention itself; ahead_wgs further ones read ahead
+    uint32_t qblks_magic, heads_magic;   // floor(2^32 / d) + 1: see udiv_fix (a division by a run-time divisor is some thirty scalar instructions)
     int32_t xcd_q, xcd_r;  // workgroups per XCD and the remainder, see the kernel
     int32_t ld_qkv, ld_ctx;
     int32_t s_m, s_s;      // scores requantization
@@ -41,18 +42,11 @@ struct AttentionArgs {
     const int32_t* key_lens;   // optional [batch]: sequence b attends to its first key_lens[b] keys only
     int32_t* scores;       // FORM 0 only, optional: the INT32 scores [batch*heads, seq, seq] and
     int8_t* probs;         // the INT8 probabilities are also stored
+    int32_t ahead_wgs;
+    ReadAhead ahead;
 };
 
 constexpr int ATT_DH = 64, ATT_QB = 64, ATT_THREADS = 256;
-
-// floor(n / d) for 0 <= n < 2^31: the reciprocal multiply gives the quotient or one more.  (A division by a run-time
-// divisor is some thirty dependent scalar instructions at the head of every workgroup.)
-__device__ __forceinline__ int32_t udiv(int32_t n, int32_t d, uint32_t magic)
-{
-    if (magic == 0) return n;                              // d == 1
-    const int32_t q = (int32_t)__umulhi((uint32_t)n, magic);
-    return n - q * d < 0 ? q - 1 : q;
-}
 
 // LDS chunk swizzles of 64-byte rows: four rows share a 256-byte bank cycle.  K and Q: a lane group reads one chunk of 16
 // consecutive rows.  V: a transposing read takes one chunk of rows 16 apart and of 16 consecutive ones.
@@ -102,18 +96,46 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
     int8_t* const vs = ks + 64 * NKB * ATT_DH;                                // V_h [64 NKB][64]
 
     // every argument is in registers from here on: one trip to memory, not one at each first use
-    asm volatile("" :: "s"(a.qkv), "s"(a.ctx), "s"(a.heads), "s"(a.seq), "s"(a.qblks), "s"(a.qblks_magic), "s"(a.heads_magic),
+    asm volatile("" :: "s"(a.qkv), "s"(a.ctx), "s"(a.heads), "s"(a.seq), "s"(a.qblks), "s"(a.blocks), "s"(a.qblks_magic), "s"(a.heads_magic),
                  "s"(a.xcd_q), "s"(a.xcd_r), "s"(a.ld_qkv), "s"(a.ld_ctx), "s"(a.s_m), "s"(a.s_s), "s"(a.c_m), "s"(a.c_s),
                  "s"(a.sm.q_b), "s"(a.sm.q_c), "s"(a.sm.q_ln2), "s"(a.sm.k), "s"(a.z_m), "s"(a.z_c), "s"(a.z_s), "s"(a.key_lens));
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if ((int)blockIdx.x >= a.blocks) {
+        // Workgroups that read ahead (see ReadAhead), each for its own XCD: 1 KB a request into LDS that nobody reads.  They come last,
+        // one for every unit: the attention's own are on their way by then, and a unit that has some runs these beside them.
+        const int x = (int)blockIdx.x & 7, first = ((int)blockIdx.x - a.blocks) >> 3;
+        const uint32_t dst = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)att_lds + (uint32_t)wave * 1024u;
+        // (its arguments are fetched here: the attention's own workgroups have no use for them)
+        typedef const __attribute__((address_space(4))) AttentionArgs* kernel_args;
+#if defined(__HIP_DEVICE_COMPILE__)
+        kernel_args ga = (kernel_args)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(ga));
+#else
+        kernel_args ga = nullptr;
+#endif
+        const int wgs = ga->ahead_wgs >> 3;                // of an XCD
+#pragma unroll
+        for (int r = 0; r < ReadAhead::MOST; ++r) {
+            const auto& q = ga->ahead.part[r];
+            const int s = x & ((1 << q.xs) - 1), total = ((q.blocks - s + (1 << q.xs) - 1) >> q.xs) * q.kb;
+            for (int k = first * 4 + wave; k < total; k += 4 * wgs) {
+                const int j = udiv_fix(k, q.kb, q.kb_magic);
+                const int8_t* src = q.p + ((int64_t)((j << q.xs) + s) * q.kb + (k - j * q.kb)) * 1024;
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                             :: "s"(dst), "v"((uint32_t)lane * 16u), "s"(src) : "memory", "m0");
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0x0f70);                // (the LDS is given back only when nothing writes to it any more)
+        return;
+    }
     // Workgroups are dealt round-robin to the 8 XCDs.  The query blocks of a head read the same K and V,
     // and neighbouring heads share 128-byte lines of the packed QKV rows: give each XCD a contiguous run of
     // (batch, head, query block) -- xcd_q of them, one more for the first xcd_r XCDs -- so that those re-reads hit its own L2.
     const int xcd = blockIdx.x & 7;
     const int bid = xcd * a.xcd_q + (xcd < a.xcd_r ? xcd : a.xcd_r) + (int)(blockIdx.x >> 3);
-    const int bh = udiv(bid, a.qblks, a.qblks_magic);
+    const int bh = udiv_fix(bid, a.qblks, a.qblks_magic);
     const int qblk = bid - bh * a.qblks;                   // which 64 of the queries
-    const int b = udiv(bh, a.heads, a.heads_magic), h = bh - b * a.heads;
+    const int b = udiv_fix(bh, a.heads, a.heads_magic), h = bh - b * a.heads;
     const int L = a.seq, hidden = a.heads * ATT_DH;
     const int8_t* base = a.qkv + (int64_t)b * L * a.ld_qkv + h * ATT_DH;
     int nk = L;                                            // keys that are not masked
@@ -349,7 +371,7 @@ template <int NKB>
 static int launch_attention_l(const AttentionArgs& a, int64_t blocks, int form, hipStream_t stream)
 {
     constexpr size_t lds_bytes = (size_t)(ATT_QB + 2 * 64 * NKB) * ATT_DH;
-    const dim3 grid((unsigned)blocks), block(ATT_THREADS);
+    const dim3 grid((unsigned)(blocks + a.ahead_wgs)), block(ATT_THREADS);
 #define IBERT_ATT_LAUNCH(F_)                                                                                      \
     do {                                                                                                          \
         auto kern = attention_kernel<NKB, F_>;                                                                    \
@@ -372,14 +394,17 @@ static int launch_attention_l(const AttentionArgs& a, int64_t blocks, int form, 
 
 int launch_attention(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq, int32_t hidden, int32_t heads,
                      ibert_dyadic scores_dy, const ibert_softmax_params& sp, ibert_dyadic ctx_dy, hipStream_t stream,
-                     const int32_t* key_lens, int32_t* scores, int8_t* probs)
+                     const int32_t* key_lens, int32_t* scores, int8_t* probs, const ReadAhead* ahead)
 {
     if (!attention_fused_ok(qkv, ctx, seq, hidden, heads)) return IBERT_ERR_NOT_IMPLEMENTED;
     AttentionArgs a;
     a.qblks = (seq + ATT_QB - 1) / ATT_QB;
     const int64_t blocks = (int64_t)batch * heads * a.qblks;
     if (blocks == 0) return IBERT_OK;
-    if (blocks > 0x7fffffffLL) return IBERT_ERR_SHAPE;
+    if (blocks > 0x7fffffffLL - 256) return IBERT_ERR_SHAPE;
+    a.blocks = (int32_t)blocks;
+    a.ahead_wgs = ahead ? 256 : 0;
+    a.ahead = ahead ? *ahead : ReadAhead{};
     a.qkv = qkv; a.ctx = ctx; a.heads = heads; a.seq = seq;
     auto magic = [](int32_t d) { return d == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)d) + 1u; };
     a.qblks_magic = magic(a.qblks); a.heads_magic = magic(heads);

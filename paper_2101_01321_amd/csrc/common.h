@@ -129,13 +129,55 @@ __device__ __forceinline__ int32_t group_allreduce(int32_t v, Op op)
     return v;
 }
 
+// floor(n / d) for 0 <= n < 2^31 with magic = floor(2^32 / d) + 1 (0 for d == 1): the estimate is the quotient or one more.
+__device__ __forceinline__ int32_t udiv_fix(int32_t n, int32_t d, uint32_t magic)
+{
+    if (magic == 0) return n;
+    const int32_t q = (int32_t)__umulhi((uint32_t)n, magic);
+    return n - q * d < 0 ? q - 1 : q;
+}
+
 // Name of the kernel family chosen by the most recent launch_* call (for the optional profile).
 extern const char* g_last_kernel;
+
+// How the XCDs will share the weights of a MatMul (gemm.hip: plan_gemm): XCD x works on the row blocks (j << xs) + x % 2^xs,
+// j = 0, 1 ..., of `rows` rows each (rows 0: no such plan).
+struct GemmPlan {
+    int32_t rows = 0, xs = 0;
+};
+// Weights that the kernels after a launch will read and that it may bring into the L2 of the XCD that reads them: clean lines stay
+// in an XCD's L2 from one kernel to the next (2 MB an XCD read again by the next kernel: 2.5 us, from HBM 5.0).
+struct ReadAhead {
+    static constexpr int MOST = 4;
+    struct Part {
+        const int8_t* p;
+        int32_t kb, blocks, xs;        // KB of a row block; row blocks; see GemmPlan
+        uint32_t kb_magic;             // see udiv_fix
+    } part[MOST];
+    int n = 0;
+    void add(const int8_t* w, int64_t N, int64_t K, const GemmPlan& plan)
+    {
+        if (n == MOST || plan.rows < 1) return;
+        // Where half of the XCDs or more read the same rows, so many copies would cost more than they bring: each KB once then, by any
+        // XCD, which brings it as near as the memory-side cache and one L2.  us, Base b32 (W_o and W_2 go to all XCDs): 909 without,
+        // 903 with eight copies, 852 with one; Base b1 (an eighth for each): 327 without, 336 by any XCD, 316 by the one that reads.
+        const bool own = plan.xs >= 2;
+        const int32_t kb = own ? (int32_t)(plan.rows * K / 1024) : 1;
+        part[n++] = Part{w, kb, (int32_t)(N * K / 1024 / kb), own ? plan.xs : 3, kb == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)kb) + 1u};
+    }
+    ReadAhead()
+    {
+        for (Part& q : part) q = Part{nullptr, 1, 0, 0, 0};
+    }
+};
 
 // ---- internal launchers (validated arguments) -----------------------------------------------
 int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias,
                 const int32_t* mult, const int32_t* shift, const int8_t* residual, void* C,
                 hipStream_t stream, const ibert_gelu_params* gelu = nullptr);
+// How launch_gemm will share W (gelu: with the GELU epilogue).
+GemmPlan plan_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias, const int32_t* mult,
+                   const int32_t* shift, const int8_t* residual, const void* C, bool gelu);
 int launch_gemm_gelu(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias,
                      const int32_t* mult, const int32_t* shift, const ibert_gelu_params& gelu, int8_t* C,
                      int32_t* scratch, hipStream_t stream);
@@ -144,7 +186,8 @@ bool attention_whole_blocks(int32_t seq);
 // scores, probs (optional): where the one-kernel form also stores those two tensors
 int launch_attention(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq, int32_t hidden, int32_t heads,
                      ibert_dyadic scores_dy, const ibert_softmax_params& sp, ibert_dyadic ctx_dy, hipStream_t stream,
-                     const int32_t* key_lens = nullptr, int32_t* scores = nullptr, int8_t* probs = nullptr);
+                     const int32_t* key_lens = nullptr, int32_t* scores = nullptr, int8_t* probs = nullptr,
+                     const ReadAhead* ahead = nullptr);
 // key_lens (device, optional): row r keeps its first key_lens[r / rows_per_len] columns
 int launch_softmax(const int32_t* x, void* y, int64_t rows, int32_t cols, int64_t ldx, int64_t ldy,
                    const ibert_softmax_params& p, hipStream_t stream, const int32_t* key_lens = nullptr,

@@ -275,18 +275,15 @@ static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb
     return 4;
 }
 
-// gelu != nullptr asks for the GELU epilogue (INT8 output, no residual; out_clamp must be gelu->q_max): a tile
-// that does not carry it, and a problem that the tile does not serve, return IBERT_ERR_NOT_IMPLEMENTED without launching.
-int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias,
-                const int32_t* mult, const int32_t* shift, const int8_t* residual, void* C, hipStream_t stream,
-                const ibert_gelu_params* gelu)
+// The arguments of a problem, all but what the kernel's launcher and the GELU epilogue fill in.
+static GemmArgs gemm_args(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias,
+                          const int32_t* mult, const int32_t* shift, const int8_t* residual, void* C)
 {
-    const int64_t nb = (int64_t)d.batch_outer * d.batch_inner;
-    if (nb == 0 || d.M == 0 || d.N == 0) return IBERT_OK;
+    const bool i8 = d.out_dtype == IBERT_I8;
     GemmArgs g;
     g.A = A; g.W = W; g.bias = bias; g.mult = mult; g.shift = shift; g.R = residual; g.C = C;
     g.M = d.M; g.N = d.N; g.K = d.K;
-    g.batch_inner = d.batch_inner; g.nbatch = (int32_t)nb;
+    g.batch_inner = d.batch_inner; g.nbatch = (int32_t)((int64_t)d.batch_outer * d.batch_inner);
     g.tiles_m = g.tiles_n = 0;
     g.xcd_chunk = 0;
     g.xcd_xn = g.xcd_xs = g.xcd_bm = g.xcd_bn = 0;
@@ -301,25 +298,66 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
     g.res_m = d.residual_dy.m; g.res_s = d.residual_dy.s;
     g.res_fast = (!residual || (d.residual_dy.s >= 8 && d.residual_dy.s <= 62)) ? 1 : 0;
     g.res_rnd = (residual && d.residual_dy.s >= 1 && d.residual_dy.s <= 62) ? ((int64_t)1 << (d.residual_dy.s - 1)) : 0;
-    const bool i8 = d.out_dtype == IBERT_I8;
     g.c16 = d.out_dtype == IBERT_I16 ? 1 : 0;
     g.path_word = g_path_word;
     g.gelu_fast = 0;
     g.gelu = GeluConst{0, 0, 0, 0, 0, 0};
     g.gelu_lut_lo = g.gelu_lut_n = 0;
+    g.c_vec = aligned(C, i8 ? 4 : (g.c16 ? 8 : 16)) && d.ldc % 4 == 0 && d.strideC_outer % 4 == 0 && d.strideC_inner % 4 == 0;
+    g.c_vec16 = i8 && aligned(C, 16) && d.ldc % 16 == 0 && d.strideC_outer % 16 == 0 && d.strideC_inner % 16 == 0;
+    g.r_vec = residual && aligned(residual, 16) && d.ldr % 16 == 0 && d.strideR_outer % 16 == 0 && d.strideR_inner % 16 == 0;
+    return g;
+}
+
+// Rows whose 16-byte chunks are aligned, W as [N,K].
+static bool rows_aligned(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W)
+{
+    return d.trans_w == 0 && d.K > 0 && aligned(A, 16) && aligned(W, 16) && d.lda % 16 == 0 && d.ldw % 16 == 0 &&
+           d.strideA_outer % 16 == 0 && d.strideA_inner % 16 == 0 && d.strideW_outer % 16 == 0 && d.strideW_inner % 16 == 0;
+}
+
+GemmPlan plan_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias, const int32_t* mult,
+                   const int32_t* shift, const int8_t* residual, const void* C, bool gelu)
+{
+    GemmPlan p;
+    if (d.batch_outer != 1 || d.batch_inner != 1 || d.M < 1 || d.N < 1 || d.ldw != d.K || d.K % 128 != 0 || !rows_aligned(d, A, W)) return p;
+    const GemmArgs g = gemm_args(d, A, W, bias, mult, shift, residual, const_cast<void*>(C));
+    const int cfg = choose_config(d, g, 1, gelu);
+    const GemmConfig& f = kConfigs[cfg];
+    if (d.N % f.bn != 0) return p;
+    const int32_t tiles_m = (int32_t)ceil_div(d.M, f.bm), tiles_n = d.N / f.bn;
+    if (cfg >= 25) {
+        p.xs = few_grid(tiles_m, tiles_n).xs;
+        p.rows = f.bn;
+    } else if (cfg == 23 || cfg == 24) {
+        p.xs = stream_shares(g, tiles_m, tiles_n);
+        p.rows = d.N >> p.xs;
+    } else {
+        const bool even = (int64_t)tiles_m * tiles_n % 8 == 0 && (int64_t)tiles_m * tiles_n >= 16;
+        p.xs = even ? xcd_shares(g, tiles_m, tiles_n) : -1;
+        if (p.xs < 0) p.xs = tiles_n % 8 == 0 ? 3 : 0;             // (dealt in other ways: near is better than far)
+        p.rows = d.N >> p.xs;
+    }
+    return p;
+}
+
+// gelu != nullptr asks for the GELU epilogue (INT8 output, no residual; out_clamp must be gelu->q_max): a tile
+// that does not carry it, and a problem that the tile does not serve, return IBERT_ERR_NOT_IMPLEMENTED without launching.
+int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias,
+                const int32_t* mult, const int32_t* shift, const int8_t* residual, void* C, hipStream_t stream,
+                const ibert_gelu_params* gelu)
+{
+    const int64_t nb = (int64_t)d.batch_outer * d.batch_inner;
+    if (nb == 0 || d.M == 0 || d.N == 0) return IBERT_OK;
+    GemmArgs g = gemm_args(d, A, W, bias, mult, shift, residual, C);
+    const bool i8 = d.out_dtype == IBERT_I8;
     if (gelu) {
         if (!i8 || residual || d.out_clamp != gelu->q_max) return IBERT_ERR_NOT_IMPLEMENTED;
         g.gelu = GeluConst{gelu->q_b, gelu->q_c, gelu->q_1, gelu->q_max, gelu->out.m, gelu->out.s};
         g.gelu_fast = gelu_fast_ok(*gelu) ? 1 : 0;
         gelu_table_range(*gelu, &g.gelu_lut_lo, &g.gelu_lut_n);
     }
-    g.c_vec = aligned(C, i8 ? 4 : (g.c16 ? 8 : 16)) && d.ldc % 4 == 0 && d.strideC_outer % 4 == 0 && d.strideC_inner % 4 == 0;
-    g.c_vec16 = i8 && aligned(C, 16) && d.ldc % 16 == 0 && d.strideC_outer % 16 == 0 && d.strideC_inner % 16 == 0;
-    g.r_vec = residual && aligned(residual, 16) && d.ldr % 16 == 0 && d.strideR_outer % 16 == 0 && d.strideR_inner % 16 == 0;
-
-    const bool fast = d.trans_w == 0 && d.K > 0 && aligned(A, 16) && aligned(W, 16) && d.lda % 16 == 0 && d.ldw % 16 == 0 &&
-                      d.strideA_outer % 16 == 0 && d.strideA_inner % 16 == 0 && d.strideW_outer % 16 == 0 &&
-                      d.strideW_inner % 16 == 0;
+    const bool fast = rows_aligned(d, A, W);
     if (gelu && !(fast && d.K % 16 == 0)) return IBERT_ERR_NOT_IMPLEMENTED;
     if (fast) {
         if (d.K % 16 != 0) return launch_tail(g, i8, stream);       // bytewise K tail

@@ -1095,6 +1095,21 @@ struct KernelName {
 
 bool xcd_blocks_enabled();       // (gemm.hip: a switch for A/B measurements, on by default)
 
+// How one problem's tile grid is dealt to the XCDs in blocks: log2 of the blocks side by side, -1 where it does not divide.
+// Fabric bytes of the operands ~ XN * M + XM * N (times K) for XM x XN blocks, XM * XN = 8.
+inline int xcd_shares(const GemmArgs& g, int tiles_m, int tiles_n)
+{
+    int best_xs = -1;
+    int64_t best = 0;
+    for (int xs = 0; xs <= (xcd_blocks_enabled() ? 3 : 0); ++xs) {
+        const int xn = 1 << xs, xm = 8 >> xs;
+        if (tiles_m % xm != 0 || tiles_n % xn != 0) continue;
+        const int64_t cost = (int64_t)xn * g.M + (int64_t)xm * g.N;
+        if (best_xs < 0 || cost < best) { best = cost; best_xs = xs; }
+    }
+    return best_xs;
+}
+
 template <int BM, int BN, int BK, int RING, bool TW = false, bool DMA = false, bool GELU = false, int NW = 4, int NLD = 0>
 int launch_mfma(GemmArgs& g, bool i8, hipStream_t stream)
 {
@@ -1106,20 +1121,12 @@ int launch_mfma(GemmArgs& g, bool i8, hipStream_t stream)
     g.xcd_xn = g.xcd_xs = 0;
     g.xcd_bm = g.xcd_bn = 0;
     if (g.xcd_chunk > 0 && g.nbatch == 1) {
-        // fabric bytes of the operands ~ XN * M + XM * N (times K) for XM x XN blocks, XM * XN = 8
-        int best_xn = 0, best_xs = 0;
-        int64_t best = 0;
-        for (int xs = 0; xs <= (xcd_blocks_enabled() ? 3 : 0); ++xs) {
-            const int xn = 1 << xs, xm = 8 >> xs;
-            if (g.tiles_m % xm != 0 || g.tiles_n % xn != 0) continue;
-            const int64_t cost = (int64_t)xn * g.M + (int64_t)xm * g.N;
-            if (best_xn == 0 || cost < best) { best = cost; best_xn = xn; best_xs = xs; }
-        }
-        if (best_xn > 0) {
-            g.xcd_xn = best_xn;
-            g.xcd_xs = best_xs;
-            g.xcd_bm = g.tiles_m / (8 / best_xn);
-            g.xcd_bn = g.tiles_n / best_xn;
+        const int xs = xcd_shares(g, g.tiles_m, g.tiles_n);
+        if (xs >= 0) {
+            g.xcd_xn = 1 << xs;
+            g.xcd_xs = xs;
+            g.xcd_bm = g.tiles_m / (8 >> xs);
+            g.xcd_bn = g.tiles_n >> xs;
         }
     }
     const dim3 grid = g.xcd_xn >= 1 ? dim3(8u * (unsigned)g.xcd_bn, (unsigned)g.xcd_bm) : dim3((unsigned)blocks);

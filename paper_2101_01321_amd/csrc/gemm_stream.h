@@ -57,14 +57,6 @@ struct StreamArgs {
     uint32_t* path_word;
 };
 
-// floor(n / d) for 0 <= n < 2^31 with magic = floor(2^32 / d) + 1 (0 for d == 1): the estimate is the quotient or one more.
-__device__ __forceinline__ int32_t udiv_fix(int32_t n, int32_t d, uint32_t magic)
-{
-    if (magic == 0) return n;
-    const int32_t q = (int32_t)__umulhi((uint32_t)n, magic);
-    return n - q * d < 0 ? q - 1 : q;
-}
-
 template <int BM, int BN, int NW, bool OUT_I8, bool GELU>
 struct StreamLayout {
     static constexpr int STAGE = (BM + BN) * 128;
@@ -576,6 +568,15 @@ bool stream_ok(const GemmArgs& g, bool i8)
            c_ok && (i8 ? !g.R : (!g.R || (g.r_vec && g.ldr < (1 << 20)))) && (int64_t)((g.M + BM - 1) / BM) * (g.N / BN) < (1 << 26);
 }
 
+// An XCD reads its share of W again for every round of tiles: shares side by side until one is at most half of its 4 MB
+// L2 (each further one doubles the reads of A).  log2 of their number.
+inline int stream_shares(const GemmArgs& g, int tiles_m, int tiles_n)
+{
+    int xs = 0;
+    while (xs < 2 && tiles_n % (2 << xs) == 0 && (((int64_t)g.N * g.K) >> xs) > (2 << 20) && tiles_m >= (8 >> xs)) ++xs;
+    return xs;
+}
+
 template <int BM, int BN, int NW, bool GELU>
 int launch_stream(GemmArgs& g, bool i8, hipStream_t stream)
 {
@@ -586,10 +587,7 @@ int launch_stream(GemmArgs& g, bool i8, hipStream_t stream)
     s.lda = (int32_t)g.lda; s.ldw = (int32_t)g.ldw; s.ldc = (int32_t)g.ldc; s.ldr = (int32_t)g.ldr;
     s.tiles_m = (g.M + BM - 1) / BM;
     const int tiles_n = g.N / BN;
-    // An XCD reads its share of W again for every round of tiles: shares side by side until one is at most half of its 4 MB
-    // L2 (each further one doubles the reads of A).
-    s.xs = 0;
-    while (s.xs < 2 && tiles_n % (2 << s.xs) == 0 && (((int64_t)g.N * g.K) >> s.xs) > (2 << 20) && s.tiles_m >= (8 >> s.xs)) ++s.xs;
+    s.xs = stream_shares(g, s.tiles_m, tiles_n);
     s.gs = 3 - s.xs;
     s.bn = tiles_n >> s.xs;
     s.bn_magic = s.bn == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)s.bn) + 1u;

@@ -349,3 +349,40 @@ def test_softmax_rows_at_any_address(G, cols, k, od):
         got = G.softmax(x, sp, ldx=ldx, ldy=ldy, x_off=xo, y_off=yo, key_lens=lens)
         _eq(got[:, :cols], oracle.softmax(masked, op), "masked softmax cols=%d" % cols)
         assert np.all(got[:, cols:] == 77)
+
+
+# ------------------------------------------------------------------------------------------- weights read ahead
+@pytest.mark.parametrize("hidden,heads,ffn,seq,batch", [(256, 4, 1152, 61, 2), (256, 4, 128, 17, 1), (384, 6, 640, 200, 9),
+                                                        (768, 12, 3072, 77, 3), (256, 4, 1024, 300, 40)])
+def test_encoder_that_reads_weights_ahead(G, hidden, heads, ffn, seq, batch):
+    # the attention of each layer also reads the weights of the MatMuls that follow, up to the next layer's first (the last layer has
+    # none to follow): three layers of sizes that every kind of tile serves, with and without the separate GELU that leaves it out,
+    # a graph of it replayed, and the oracle's layers on the last sequence
+    import torch
+    from paper_2101_01321_amd import binding as B
+    cfg = synth.EncoderConfig("ahead", hidden, heads, ffn, seq, batch, 3)
+    x_q, S_x, _ = synth.input_activations(cfg)
+    model = G.DeviceModel(cfg, S_x)
+    x = G.to_dev(x_q)
+    G.say("encoder that reads ahead H=%d F=%d L=%d B=%d" % (hidden, ffn, seq, batch))
+    y = model.forward(x)
+    torch.cuda.synchronize()
+    got = y.cpu().numpy()
+    model.set_route(B.ROUTE_SEPARATE_GELU)
+    other = model.forward(x)
+    torch.cuda.synchronize()
+    _eq(got, other.cpu().numpy(), "route that does not read ahead")
+    model.set_route(0)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        yg = model.forward(x)
+    for _ in range(3):
+        yg.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        _eq(yg.cpu().numpy(), got, "replay")
+    cur = x_q[(batch - 1) * seq:]
+    for l in range(3):
+        w, q = P.layer_params(synth.layer_raw(cfg, l), model.scales[l], hidden, heads)
+        cur = oracle.encoder_layer(w, q, cur, 1, seq, hidden, heads, ffn)
+    _eq(got[(batch - 1) * seq:], cur, "the oracle's layers")
