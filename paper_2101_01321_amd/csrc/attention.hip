@@ -8,6 +8,7 @@
 // One workgroup of four wavefronts owns 64 queries of one (batch, head); a wavefront owns 16.  The kernel is instantiated
 // per number of 64-key blocks; rows past the end of the sequence are read from its last row, their keys are masked and
 // their queries not stored.
+//   * From 7 key blocks on K_h and V_h take turns in one LDS buffer (see att_may_share).
 //   * Everything goes from global memory straight into LDS (global_load_lds, 1 KB = 16 rows of 64 bytes per request), in
 //     row-major order with the 16-byte chunks of a row swizzled by the row: the wavefront's queries, K_h and V_h.
 //   * K_h rows are MFMA operands as they stand (one 16-byte read per lane).  V_h is needed transposed: ds_read_b64_tr_b8 hands
@@ -32,6 +33,7 @@ struct AttentionArgs {
     int8_t* ctx;           // [batch*seq, hidden]
     int32_t heads, seq, qblks;
     int32_t blocks;        // workgroups of the attention itself; ahead_wgs further ones read ahead
+    int32_t one_buffer;    // K_h and V_h share their place in LDS, see att_may_share
     uint32_t qblks_magic, heads_magic;   // floor(2^32 / d) + 1: see udiv_fix (a division by a run-time divisor is some thirty scalar instructions)
     int32_t xcd_q, xcd_r;  // workgroups per XCD and the remainder, see the kernel
     int32_t ld_qkv, ld_ctx;
@@ -47,6 +49,14 @@ struct AttentionArgs {
 };
 
 constexpr int ATT_DH = 64, ATT_QB = 64, ATT_THREADS = 256;
+
+// May K_h and V_h take turns in one LDS buffer?  From 7 key blocks on (61 and 69 KB with two buffers) only two workgroups fit a
+// compute unit, two wavefronts a SIMD, which do not hide the chains of the exponent from each other; with one buffer three do.
+// V_h is then requested when all scores have been made and arrives during the Softmax.  us, L = 512: 64 x 12 heads 108.3 -> 92.3,
+// 8 x 12 16.3 -> 15.3; L = 448, 72 x 12 97.8 -> 81.9.  (Six blocks and fewer: three workgroups fit, no change.)  Not where every
+// workgroup has its place with two buffers: V_h had better come early then (1 x 12 heads at L = 512: 7.8, with one buffer 8.1).
+constexpr bool att_may_share(int nkb) { return nkb >= 7; }
+constexpr int ATT_SHARE_WGS = 512;
 
 // LDS chunk swizzles of 64-byte rows: four rows share a 256-byte bank cycle.  K and Q: a lane group reads one chunk of 16
 // consecutive rows.  V: a transposing read takes one chunk of rows 16 apart and of 16 consecutive ones.
@@ -90,13 +100,14 @@ template <int NKB, int FORM>
 __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
 {
     constexpr int NI = 4 * NKB;
+    const bool one = att_may_share(NKB) && a.one_buffer;
     extern __shared__ __attribute__((aligned(16))) int8_t att_lds[];
     int8_t* const qs = att_lds;                                               // queries [64][64]
     int8_t* const ks = qs + ATT_QB * ATT_DH;                                  // K_h [64 NKB][64]
-    int8_t* const vs = ks + 64 * NKB * ATT_DH;                                // V_h [64 NKB][64]
+    int8_t* const vs = one ? ks : ks + 64 * NKB * ATT_DH;                     // V_h [64 NKB][64]
 
     // every argument is in registers from here on: one trip to memory, not one at each first use
-    asm volatile("" :: "s"(a.qkv), "s"(a.ctx), "s"(a.heads), "s"(a.seq), "s"(a.qblks), "s"(a.blocks), "s"(a.qblks_magic), "s"(a.heads_magic),
+    asm volatile("" :: "s"(a.qkv), "s"(a.ctx), "s"(a.heads), "s"(a.seq), "s"(a.qblks), "s"(a.blocks), "s"(a.one_buffer), "s"(a.qblks_magic), "s"(a.heads_magic),
                  "s"(a.xcd_q), "s"(a.xcd_r), "s"(a.ld_qkv), "s"(a.ld_ctx), "s"(a.s_m), "s"(a.s_s), "s"(a.c_m), "s"(a.c_s),
                  "s"(a.sm.q_b), "s"(a.sm.q_c), "s"(a.sm.q_ln2), "s"(a.sm.k), "s"(a.z_m), "s"(a.z_c), "s"(a.z_s), "s"(a.key_lens));
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -148,28 +159,32 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
     // ---- global -> LDS -------------------------------------------------------------------------
     const int frow = lane & 15, fch = lane >> 4;
     const int qrow0 = qblk * ATT_QB + wave * 16;           // the wavefront's first query
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)att_lds + (uint32_t)wave * 1024u;
+    const int r16 = lane >> 2;
+    auto request = [&](const int8_t* src, int row0, uint32_t chunk, uint32_t dst) {
+        int row = row0 + r16;
+        row = row < L ? row : L - 1;
+        const uint32_t voff = (uint32_t)row * (uint32_t)a.ld_qkv + chunk;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :: "s"(dst), "v"(voff), "s"(src) : "memory", "m0");
+    };
+    auto request_v = [&](int n) {
+        const uint32_t cv = (uint32_t)(((lane & 3) ^ swz_v(r16)) << 4);
+#pragma unroll
+        for (int p = 0; p < NKB; ++p)
+            if (p < n) request(base + 2 * hidden, 64 * p + 16 * wave, cv, lds0 + (uint32_t)(ATT_QB * ATT_DH + ((one ? 0 : NKB) + p) * 4096));
+    };
     {
         // lane l of a request brings, for row l / 4 of its 16, the chunk that the swizzle puts at byte 16 l
-        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)att_lds + (uint32_t)wave * 1024u;
-        const int r16 = lane >> 2;
-        const uint32_t ck = (uint32_t)(((lane & 3) ^ swz_k(r16)) << 4), cv = (uint32_t)(((lane & 3) ^ swz_v(r16)) << 4);
-        auto request = [&](const int8_t* src, int row0, uint32_t chunk, uint32_t dst) {
-            int row = row0 + r16;
-            row = row < L ? row : L - 1;
-            const uint32_t voff = (uint32_t)row * (uint32_t)a.ld_qkv + chunk;
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         :: "s"(dst), "v"(voff), "s"(src) : "memory", "m0");
-        };
+        const uint32_t ck = (uint32_t)(((lane & 3) ^ swz_k(r16)) << 4);
         request(base, qrow0, ck, lds0);
         const int n = opaque(nkb);
 #pragma unroll
         for (int p = 0; p < NKB; ++p)
             if (p < n) request(base + hidden, 64 * p + 16 * wave, ck, lds0 + (uint32_t)(ATT_QB * ATT_DH + p * 4096));
-#pragma unroll
-        for (int p = 0; p < NKB; ++p)
-            if (p < n) request(base + 2 * hidden, 64 * p + 16 * wave, cv, lds0 + (uint32_t)(ATT_QB * ATT_DH + NKB * 4096 + p * 4096));
+        if (!one) request_v(n);
         // the queries and K have landed (V may still be on its way: it is not needed before the context)
-        if (n == NKB) __builtin_amdgcn_s_waitcnt(0x0f70 | NKB);
+        if (!one && n == NKB) __builtin_amdgcn_s_waitcnt(0x0f70 | NKB);
         else __builtin_amdgcn_s_waitcnt(0x0f70);
         asm volatile("s_barrier" ::: "memory");
     }
@@ -189,6 +204,10 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
             const v4i kf = *reinterpret_cast<const v4i*>(ks + krow * 64 + ((fch ^ swz_k(krow)) << 4));
             sc[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(kf, qf, v4i{0, 0, 0, 0}, 0, 0, 0);
         }
+    }
+    if (one) {                                             // K has been read by every wavefront: V may take its place
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        request_v(opaque(nkb));
     }
     if constexpr (FORM == 0) {
 #pragma unroll
@@ -370,7 +389,7 @@ bool attention_whole_blocks(int32_t seq) { return seq % 128 == 0 && seq <= 512; 
 template <int NKB>
 static int launch_attention_l(const AttentionArgs& a, int64_t blocks, int form, hipStream_t stream)
 {
-    constexpr size_t lds_bytes = (size_t)(ATT_QB + 2 * 64 * NKB) * ATT_DH;
+    const size_t lds_bytes = (size_t)(ATT_QB + (att_may_share(NKB) && a.one_buffer ? 1 : 2) * 64 * NKB) * ATT_DH;
     const dim3 grid((unsigned)(blocks + a.ahead_wgs)), block(ATT_THREADS);
 #define IBERT_ATT_LAUNCH(F_)                                                                                      \
     do {                                                                                                          \
@@ -378,7 +397,7 @@ static int launch_attention_l(const AttentionArgs& a, int64_t blocks, int form, 
         static bool attr_done = false;                                                                            \
         if (!attr_done && lds_bytes > 65536) {                                                                    \
             IBERT_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                              \
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes));     \
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, (ATT_QB + 2 * 64 * NKB) * ATT_DH)); \
             attr_done = true;                                                                                     \
         }                                                                                                         \
         hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, a);                                              \
@@ -403,6 +422,7 @@ int launch_attention(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq,
     if (blocks == 0) return IBERT_OK;
     if (blocks > 0x7fffffffLL - 256) return IBERT_ERR_SHAPE;
     a.blocks = (int32_t)blocks;
+    a.one_buffer = blocks > ATT_SHARE_WGS;
     a.ahead_wgs = ahead ? 256 : 0;
     a.ahead = ahead ? *ahead : ReadAhead{};
     a.qkv = qkv; a.ctx = ctx; a.heads = heads; a.seq = seq;

@@ -55,6 +55,27 @@ def test_attention_any_length(G, L, S, k, sdy):
                     break                                    # (one key: every query gives the same; a few groups are enough)
 
 
+@pytest.mark.parametrize("B_,nh,L", [(8, 9, 447), (13, 5, 512), (8, 8, 449)])      # 504 / 520 / 512 workgroups: on both sides of the switch
+@pytest.mark.parametrize("sdy", [(1518500250, 36), (1187698534, 28), (-1518500250, 36)])
+def test_attention_keys_and_values_in_one_buffer(G, B_, nh, L, sdy):
+    # long sequences of more workgroups than find a place at once: V_h takes the place of K_h in LDS; also with masked blocks of
+    # keys, down to a single key, against the oracle on the last sequence
+    from paper_2101_01321_amd import binding as B
+    H, cdy = 64 * nh, (1073741824, 37)
+    qkv = _qkv(B_, L, H, L + nh)
+    sp, op = B.ibert_softmax_params_from_scale(2.0 ** -6, L, 7), P.softmax_params(2.0 ** -6, 7)
+    G.say("attention, one buffer, B=%d heads=%d L=%d s=%s" % (B_, nh, L, sdy))
+    got = G.attention(qkv, B_, L, H, nh, sdy, sp, cdy)
+    last = qkv[(B_ - 1) * L:]
+    _eq(got[(B_ - 1) * L:], _attention_oracle(last, 1, L, H, nh, sdy, op, cdy), "attention, last sequence")
+    lens = np.array([1 + (L - 1) * b // (B_ - 1) for b in range(B_)], np.int32)
+    masked = G.attention(qkv, B_, L, H, nh, sdy, sp, cdy, key_lens=lens)
+    _eq(masked[(B_ - 1) * L:], got[(B_ - 1) * L:], "all keys")
+    n = int(lens[2])                                         # a sequence that keeps the first n keys: its first n rows, alone
+    part = qkv[2 * L:2 * L + n]
+    _eq(masked[2 * L:2 * L + n], _attention_oracle(part, 1, n, H, nh, sdy, op, cdy), "masked attention")
+
+
 def test_layer_of_any_length_keeps_scores_and_probabilities(G):
     # a single layer call leaves every intermediate in the workspace for lengths that are no multiple of 128
     for seq in (33, 100, 131):
