@@ -157,7 +157,7 @@ struct ReadAhead {
     int n = 0;
     void add(const int8_t* w, int64_t N, int64_t K, const GemmPlan& plan)
     {
-        if (n == MOST || plan.rows < 1) return;
+        if (n == MOST || plan.rows < 1 || !aligned(w, 16)) return;      // (the plan may be of another layer's weights)
         // Where half of the XCDs or more read the same rows, so many copies would cost more than they bring: each KB once then, by any
         // XCD, which brings it as near as the memory-side cache and one L2.  us, Base b32 (W_o and W_2 go to all XCDs): 909 without,
         // 903 with eight copies, 852 with one; Base b1 (an eighth for each): 327 without, 336 by any XCD, 316 by the one that reads.

@@ -180,6 +180,8 @@ static bool dma_ok(const ibert_gemm_desc& d, int bn)
     return d.N % bn == 0 && d.K % 128 == 0 && d.lda < (1 << 23) && d.ldw < (1 << 23);
 }
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+// (0 <= n < 2^31: a 32-bit division)
+static uint32_t blocks_of(int32_t n, int b) { return ((uint32_t)n + (uint32_t)b - 1u) / (uint32_t)b; }
 
 // Tile choice for K % 128 == 0.  What a configuration takes is linear in the K steps and in the tiles that the fullest
 // compute unit gets: with k = K / 128, n = ceil(tiles / 256) and, for tiles of which `share` fit a compute unit side by
@@ -230,7 +232,7 @@ static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb
 {
     if (g_config_override >= 0 && g_config_override < kNumConfigs) return g_config_override;
     const bool i8 = d.out_dtype == IBERT_I8;
-    auto tiles = [&](int bm, int bn) -> int64_t { return ceil_div(d.M, bm) * ceil_div(d.N, bn) * nb; };
+    auto tiles = [&](int bm, int bn) -> int64_t { return (int64_t)blocks_of(d.M, bm) * blocks_of(d.N, bn) * nb; };
     const bool wide = d.N % 96 == 0 || d.N % 128 == 0;                  // some direct-to-LDS tile divides N
     // (GELU stays in a kernel of its own, behind a MatMul whose result the caller finds in its scratch, where K is short
     //  and no direct-to-LDS tile fits)
@@ -244,6 +246,8 @@ static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb
             if (c.config == 23 && !stream_ok<256, 256, 8>(g, i8)) continue;
             if (c.config == 24 && !stream_ok<256, 192, 8>(g, i8)) continue;
             const int64_t k = d.K / 128;
+            const int64_t one = w.first[0] + w.first[1] * k;            // (the other terms only add to it)
+            if (best >= 0 && one >= best_t) continue;
             // One 256x192 tile for every unit, dealt evenly to the XCDs, and few steps: the persistent kernel has nothing to stream.
             // Back to back on one problem the two are within 2 % of each other (us, persistent / not, [4096,3072]: GELU at K 128 10.8 / 10.4,
             // 256 11.8 / 12.0, 768 15.3 / 15.5; INT8 at K 128 9.1 / 9.1, 768 13.2 / 13.4, 1024 15.1 / 15.1); between other kernels, where
@@ -260,7 +264,7 @@ static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb
                 n = ceil_div(tiles(f.bm, f.bn), 256);
             }
             const int64_t r = ceil_div(n, share);
-            const int64_t t = w.first[0] + w.first[1] * k + (n - 1) * (w.more[0] + w.more[1] * k) +
+            const int64_t t = one + (n - 1) * (w.more[0] + w.more[1] * k) +
                               (r - 1) * (w.again[0] + w.again[1] * k);
             if (best < 0 || t < best_t) { best = c.config; best_t = t; }
         }

@@ -3,6 +3,7 @@
 // workspace carving, enqueueing.  No allocation, no synchronisation.
 #include <cstring>
 #include <mutex>
+#include <optional>
 
 #include "common.h"
 
@@ -161,8 +162,32 @@ static int run_attention(const int8_t* qkv, int32_t* scores, int8_t* probs, int8
     return run_attention_unfused(qkv, scores, probs, ctx, B, L, H, nh, scores_dy, softmax, ctx_dy, key_lens, stream);
 }
 
-// series: one of several layers in a call; next: the weights of the one that follows, if one does.
-static int run_layer(const ibert_layer_weights& w, bool series, const ibert_layer_weights* next, const ibert_layer_quant& q, const int8_t* x, int8_t* y,
+// How the MatMuls of a layer share their weights among the XCDs.  The layers of a call have one shape: made once a call, as a
+// forward of few tokens is bound by what the host does (a forward of Base, host, us: 220 without plans, 232 with twelve, 219 with one
+// and the choice of a tile in half its time).
+struct LayerPlan {
+    GemmPlan o, up, down, qkv;
+    LayerPlan(const ibert_layer_weights& w, const int8_t* x, int8_t* y, int64_t T, int64_t H, int64_t F, char* ws, const ibert_layer_workspace_layout& lo)
+    {
+        ibert_gemm_desc d;
+        std::memset(&d, 0, sizeof d);
+        d.M = (int32_t)T; d.batch_outer = d.batch_inner = 1; d.per_channel = 1;
+        auto plan = [&](int64_t N, int64_t K, int32_t dtype, const void* in, const int8_t* wt, const int32_t* bias, const int32_t* m,
+                        const int32_t* s, const void* res, const void* out, bool gelu) {
+            d.N = (int32_t)N; d.K = (int32_t)K;
+            d.lda = d.ldw = K; d.ldc = d.ldr = N;
+            d.out_dtype = dtype;
+            return plan_gemm(d, (const int8_t*)in, wt, bias, m, s, (const int8_t*)res, out, gelu);
+        };
+        o = plan(H, H, IBERT_I16, ws + lo.ctx, w.w_o, w.b_o, w.m_o, w.s_o, x, ws + lo.r1, false);
+        up = plan(F, H, IBERT_I8, ws + lo.h1, w.w_1, w.b_1, w.m_1, w.s_1, nullptr, ws + lo.g, true);
+        down = plan(H, F, IBERT_I16, ws + lo.g, w.w_2, w.b_2, w.m_2, w.s_2, ws + lo.h1, ws + lo.r2, false);
+        qkv = plan(3 * H, H, IBERT_I8, y, w.w_qkv, w.b_qkv, w.m_qkv, w.s_qkv, nullptr, ws + lo.qkv, false);
+    }
+};
+
+// plan: of a call with several layers (a layer by itself: nullptr); next: the weights of the layer that follows, if one does.
+static int run_layer(const ibert_layer_weights& w, const LayerPlan* plan, const ibert_layer_weights* next, const ibert_layer_quant& q, const int8_t* x, int8_t* y,
                      int32_t batch, int32_t seq, int32_t hidden, int32_t heads, int32_t ffn, const int32_t* key_lens,
                      char* ws, const ibert_layer_workspace_layout& lo, bool keep, hipStream_t stream)
 {
@@ -223,21 +248,11 @@ static int run_layer(const ibert_layer_weights& w, bool series, const ibert_laye
     // 1236 / 1182, Base b32 900 / 849, b61 s251 2243 / 2132, 32768 tokens the same.  (A layer called by itself, in a program that cycles
     // through few of them, finds its weights in the caches: 177 tokens 27.7 without, 27.9 with.)
     ReadAhead ahead;
-    if (series && fuse_attention && fuse_gelu && half) {
-        ibert_gemm_desc a;
-        std::memset(&a, 0, sizeof a);
-        a.M = (int32_t)T; a.batch_outer = a.batch_inner = 1; a.per_channel = 1;
-        auto add = [&](int64_t N, int64_t K, int32_t dtype, const int8_t* in, const int8_t* wt, const int32_t* bias, const int32_t* m,
-                       const int32_t* s, const int8_t* res, const void* out) {
-            a.N = (int32_t)N; a.K = (int32_t)K;
-            a.lda = a.ldw = K; a.ldc = a.ldr = N;
-            a.out_dtype = dtype;
-            ahead.add(wt, N, K, plan_gemm(a, in, wt, bias, m, s, res, out, wt == w.w_1));
-        };
-        add(H, H, IBERT_I16, ctx, w.w_o, w.b_o, w.m_o, w.s_o, x, r1);
-        add(F, H, IBERT_I8, h1, w.w_1, w.b_1, w.m_1, w.s_1, nullptr, g);
-        add(H, F, IBERT_I16, g, w.w_2, w.b_2, w.m_2, w.s_2, h1, r2);
-        if (next) add(3 * H, H, IBERT_I8, y, next->w_qkv, next->b_qkv, next->m_qkv, next->s_qkv, nullptr, qkv);
+    if (plan && fuse_attention && fuse_gelu && half) {
+        ahead.add(w.w_o, H, H, plan->o);
+        ahead.add(w.w_1, F, H, plan->up);
+        ahead.add(w.w_2, H, F, plan->down);
+        if (next) ahead.add(next->w_qkv, 3 * H, H, plan->qkv);
     }
     rc = run_attention(qkv, scores, probs, ctx, B, L, H, nh, q.scores_dy, q.softmax, q.ctx_dy, key_lens,
                        fuse_attention, keep, stream, ahead.n ? &ahead : nullptr);
@@ -458,7 +473,7 @@ int ibert_encoder_layer_masked_i(const ibert_layer_weights* weights, const ibert
     if (workspace_bytes < lo.total || !ibert::aligned(workspace, 256)) return IBERT_ERR_WORKSPACE;
     rc = ibert::check_layer(*weights, *quant, seq, hidden);
     if (rc) return rc;
-    return ibert::run_layer(*weights, false, nullptr, *quant, x, y, batch, seq, hidden, heads, ffn, key_lens, (char*)workspace, lo, true,
+    return ibert::run_layer(*weights, nullptr, nullptr, *quant, x, y, batch, seq, hidden, heads, ffn, key_lens, (char*)workspace, lo, true,
                             (hipStream_t)stream);
 }
 
@@ -487,7 +502,7 @@ int ibert_encoder_layer_static_i(const ibert_layer_weights* weights, const ibert
     if (rc) return rc;
     // every region of the workspace is written by the step that produces it before any step reads it, so nothing of
     // the previous call's contents has to be cleared
-    return ibert::run_layer(*weights, false, nullptr, *quant, x, y, batch, seq, hidden, heads, ffn, key_lens, (char*)ws, lo, false,
+    return ibert::run_layer(*weights, nullptr, nullptr, *quant, x, y, batch, seq, hidden, heads, ffn, key_lens, (char*)ws, lo, false,
                             (hipStream_t)stream);
 }
 
@@ -518,9 +533,11 @@ int ibert_encoder_masked_i(const ibert_layer_weights* weights, const ibert_layer
     char* ws = (char*)workspace;
     int8_t* pp[2] = {reinterpret_cast<int8_t*>(ws + lo.total), reinterpret_cast<int8_t*>(ws + lo.total + act)};
     const int8_t* in = x;
+    std::optional<ibert::LayerPlan> plan;
+    if (n_layers > 1) plan.emplace(weights[0], x, pp[0], (int64_t)batch * seq, hidden, ffn, ws, lo);
     for (int32_t l = 0; l < n_layers; ++l) {
         int8_t* out = (l == n_layers - 1) ? y : pp[l & 1];
-        rc = ibert::run_layer(weights[l], n_layers > 1, l + 1 < n_layers ? weights + l + 1 : nullptr, quant[l], in, out, batch, seq, hidden, heads, ffn, key_lens, ws, lo, false,
+        rc = ibert::run_layer(weights[l], plan ? &*plan : nullptr, l + 1 < n_layers ? weights + l + 1 : nullptr, quant[l], in, out, batch, seq, hidden, heads, ffn, key_lens, ws, lo, false,
                               (hipStream_t)stream);
         if (rc) return rc;
         in = out;
