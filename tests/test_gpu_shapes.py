@@ -407,3 +407,24 @@ def test_encoder_that_reads_weights_ahead(G, hidden, heads, ffn, seq, batch):
         w, q = P.layer_params(synth.layer_raw(cfg, l), model.scales[l], hidden, heads)
         cur = oracle.encoder_layer(w, q, cur, 1, seq, hidden, heads, ffn)
     _eq(got[(batch - 1) * seq:], cur, "the oracle's layers")
+
+
+def test_encoder_reads_ahead_weights_at_odd_addresses(G):
+    # the plan of what to read ahead is the first layer's; weights of a later layer may lie at any byte
+    import torch
+    cfg = synth.EncoderConfig("odd", 256, 4, 640, 61, 3, 3)
+    x_q, S_x, _ = synth.input_activations(cfg)
+    model = G.DeviceModel(cfg, S_x)
+    x = G.to_dev(x_q)
+    G.say("encoder that reads ahead, odd weights")
+    want = model.forward(x)
+    moved = []
+    for l, name, off in ((1, "w_o", 3), (1, "w_2", 1), (2, "w_qkv", 7), (2, "w_1", 16)):
+        w = model.layers[l].tensors[name].reshape(-1)
+        t = torch.zeros(w.numel() + 64, dtype=torch.int8, device=w.device)
+        t[off:off + w.numel()] = w
+        setattr(model.weights[l], name, t.data_ptr() + off)
+        moved.append(t)
+    got = model.forward(x)
+    torch.cuda.synchronize()
+    _eq(got.cpu().numpy(), want.cpu().numpy(), "weights at odd addresses")
