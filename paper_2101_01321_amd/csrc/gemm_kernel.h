@@ -524,7 +524,9 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             }
         }
         if (NLD == 0 || asker) wait_landed(npro - 1);
-        asm volatile("s_barrier" ::: "memory");
+        // (also what was written by hand: the constants that every wavefront reads behind this barrier -- all must decide alike for the
+        // epilogue, which branches around barriers -- and the GELU table.  A barrier by itself does not wait for LDS writes.)
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
         if (NLD > 0 && loader) {
             // the loop of a loader wavefront: the requests of the MFMA wavefronts' two phases, the same waits and barriers
             constexpr int QHL = NSTG >= 3 ? (NL + 1) / 2 : NL;

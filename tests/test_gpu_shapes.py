@@ -306,6 +306,49 @@ def test_gemm_gelu_on_tiles_with_loaders(G, cfg, bm, bn):
         _stream_case(G, cfg, M, N, K, "gelu", shift, seed=M + N + K)
 
 
+@pytest.mark.parametrize("cfg,bm,bn", [(7, 128, 128), (9, 128, 96), (13, 256, 192), (14, 256, 128), (17, 64, 96), (18, 64, 96), (19, 64, 128),
+                                       (21, 128, 96), (22, 128, 128)])
+@pytest.mark.parametrize("kind", ["i8", "i16res", "gelu"])
+@pytest.mark.parametrize("constants", ["one multiplier", "no bias", "neither"])
+@pytest.mark.parametrize("shift", [37, 30])
+def test_gemm_direct_to_lds_constants_filled_in_by_hand(G, cfg, bm, bn, kind, constants, shift):
+    # without an array of them the constants of a tile's columns are written to LDS by the wavefronts themselves; each then reads all of
+    # them to choose the form of the epilogue (shift 37 register-direct, 30 through LDS with barriers): one K step and several, the
+    # last tile row cut
+    import torch
+    from paper_2101_01321_amd import binding as B
+    if kind == "gelu" and cfg in (17, 18, 19):
+        pytest.skip("these tiles do not carry GELU")
+    gp, op = B.ibert_gelu_params_from_scale(2.0 ** -6, 0.7), P.gelu_params(2.0 ** -6, 0.7)
+    pc, res_dy, dy = int(constants == "no bias"), (1717986918, 23), (1518500250 >> (37 - shift), shift)
+    word = torch.zeros(1, dtype=torch.int32, device=G.DEV)
+    for M, N, K in [(bm + 3, bn, 128), (9 * bm + 37, 3 * bn, 640)]:
+        rng = np.random.default_rng(cfg + M + shift)
+        A, W = (rng.integers(-127, 128, size=(n, K), dtype=np.int8) for n in (M, N))
+        bias = rng.integers(-50000, 50000, size=N, dtype=np.int32) if constants == "one multiplier" else None
+        mult, shifts = (rng.integers(2 ** 29, 2 ** 30, size=N, dtype=np.int32) >> (37 - shift), np.full(N, shift, np.int32)) if pc else (None, None)
+        R = rng.integers(-127, 128, size=(M, N), dtype=np.int8) if kind == "i16res" else None
+        kw = dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K, ldw=K, ldc=N, ldr=N, per_channel=pc, requant=dy, residual_dy=res_dy,
+                  out_dtype=I16 if kind == "i16res" else I8, out_clamp=127 if kind == "i8" else 32767)
+        B.lib().ibert_gemm_config_override(cfg)
+        B.ibert_gemm_epilogue_record(word)
+        try:
+            G.say("constants by hand cfg %d %s %s shift=%d M=%d N=%d K=%d" % (cfg, kind, constants, shift, M, N, K))
+            got = G.gemm_gelu(kw, A, W, bias, mult, shifts, gp, M * N)[0] if kind == "gelu" else G.gemm(kw, A, W, bias, mult, shifts, R, out_elems=M * N)
+        finally:
+            B.ibert_gemm_epilogue_record(None)
+            B.lib().ibert_gemm_config_override(-1)
+        assert B.lib().ibert_last_kernel().decode().startswith(G.kernel_of(cfg))
+        assert (int(word.item()) == B.EPILOGUE_STAGED) == (shift < 33)
+        spec = GemmSpec(M, N, K, per_channel=pc, dy=dy, out_dtype=I8 if kind == "i8" else I32,
+                        out_clamp={"i8": 127, "gelu": gp.q_max}.get(kind, 32767), res_dy=res_dy)
+        want = oracle.gemm_requant(spec, A, W, bias, mult, shifts, R).reshape(-1)
+        if kind == "gelu":
+            want = oracle.gelu(want, op)
+        assert len(np.unique(want)) > 20
+        _eq(got.astype(np.int64), want.astype(np.int64), "constants by hand")
+
+
 @pytest.mark.parametrize("cfg,bn,lda,M", [(7, 128, 1 << 22, 1025), (9, 96, 1 << 22, 1030), (13, 192, 1 << 22, 1025), (14, 128, 1 << 22, 1033),
                                           (17, 96, 1 << 22, 1025), (21, 96, 1 << 22, 1025), (22, 128, 1 << 22, 1025),
                                           (23, 256, 1 << 19, 8193), (24, 192, 1 << 19, 8198)])
