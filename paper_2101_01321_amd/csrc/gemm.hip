@@ -248,12 +248,12 @@ static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb
             const int64_t k = d.K / 128;
             const int64_t one = w.first[0] + w.first[1] * k;            // (the other terms only add to it)
             if (best >= 0 && one >= best_t) continue;
-            // One 256x192 tile for every unit, dealt evenly to the XCDs, and few steps: the persistent kernel has nothing to stream.
-            // Back to back on one problem the two are within 2 % of each other (us, persistent / not, [4096,3072]: GELU at K 128 10.8 / 10.4,
-            // 256 11.8 / 12.0, 768 15.3 / 15.5; INT8 at K 128 9.1 / 9.1, 768 13.2 / 13.4, 1024 15.1 / 15.1); between other kernels, where
-            // each starts with cold instruction and constant caches, the smaller code of the persistent one is ahead (S7+S8 of Base
-            // b32 inside the forward 16.4 / 17.4), which is where the longer loops are met.
-            if (c.config == 24 && i8 && tiles(256, 192) == 256 && k <= (gelu ? 2 : 6)) continue;
+            // GELU on a single K step and at most one 256x192 tile for every unit: the persistent kernel has nothing to stream.
+            // It took 0.5 to 4.3 % longer at each of 24 such problems of 192 to 256 tiles (us, W changing from call to call, persistent / not:
+            // [4096,3072] 11.3 / 10.8, [8192,1536] 11.3 / 10.9, [16072,768] 11.05 / 10.9).  With two steps it is ahead more often than not,
+            // with more nearly always (K 768 17.0 / 17.2).  INT8 without GELU has no such line: [4096,3072] at K 128 to 512 2 to 5 %
+            // longer on one card, equal within 2 % on another, the other problems 15 % shorter to 6 % longer.
+            if (c.config == 24 && gelu && k == 1 && tiles(256, 192) <= 256) continue;
             int64_t n, share = c.share;
             if (share == 0) {
                 if (!few_ok(g, f.bn, i8)) continue;
