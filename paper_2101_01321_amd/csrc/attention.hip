@@ -8,7 +8,7 @@
 // One workgroup of four wavefronts owns 64 queries of one (batch, head); a wavefront owns 16.  The kernel is instantiated
 // per number of 64-key blocks; rows past the end of the sequence are read from its last row, their keys are masked and
 // their queries not stored.
-//   * From 7 key blocks on K_h and V_h take turns in one LDS buffer (see att_may_share).
+//   * From 7 key blocks on K_h and V_h may take turns in one LDS buffer (see att_may_share).
 //   * Everything goes from global memory straight into LDS (global_load_lds, 1 KB = 16 rows of 64 bytes per request), in
 //     row-major order with the 16-byte chunks of a row swizzled by the row: the wavefront's queries, K_h and V_h.
 //   * K_h rows are MFMA operands as they stand (one 16-byte read per lane).  V_h is needed transposed: ds_read_b64_tr_b8 hands
@@ -53,9 +53,12 @@ constexpr int ATT_DH = 64, ATT_QB = 64, ATT_THREADS = 256;
 // May K_h and V_h take turns in one LDS buffer?  From 7 key blocks on (61 and 69 KB with two buffers) only two workgroups fit a
 // compute unit, two wavefronts a SIMD, which do not hide the chains of the exponent from each other; with one buffer three do.
 // V_h is then requested when all scores have been made and arrives during the Softmax.  us, L = 512: 64 x 12 heads 108.3 -> 92.3,
-// 8 x 12 16.3 -> 15.3; L = 448, 72 x 12 97.8 -> 81.9.  (Six blocks and fewer: three workgroups fit, no change.)  Not where every
-// workgroup has its place with two buffers: V_h had better come early then (1 x 12 heads at L = 512: 7.8, with one buffer 8.1).
-constexpr bool att_may_share(int nkb) { return nkb >= 7; }
+// 8 x 12 16.3 -> 15.3; L = 448, 72 x 12 97.8 -> 81.9; FORM 0, L = 448: 64 x 12 229.4 -> 184.4, 11 x 7 39.6 -> 33.1.  (Six blocks and
+// fewer: three workgroups fit, no change.)  Not FORM 0 with 8 blocks: it needs 171 vector registers, more than three wavefronts of a
+// SIMD have, so V_h would only come later (L = 512: 64 x 12 heads 296.6, with one buffer 298.5; 60 x 16 at L = 500 372.0, 374.2).
+// Not where every workgroup has its place with two buffers: V_h had better come early then (1 x 12 heads at L = 512: 7.8, with
+// one buffer 8.1).
+constexpr bool att_may_share(int nkb, int form) { return nkb == 7 || (nkb == 8 && form != 0); }
 constexpr int ATT_SHARE_WGS = 512;
 
 // LDS chunk swizzles of 64-byte rows: four rows share a 256-byte bank cycle.  K and Q: a lane group reads one chunk of 16
@@ -100,7 +103,7 @@ template <int NKB, int FORM>
 __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
 {
     constexpr int NI = 4 * NKB;
-    const bool one = att_may_share(NKB) && a.one_buffer;
+    const bool one = att_may_share(NKB, FORM) && a.one_buffer;
     extern __shared__ __attribute__((aligned(16))) int8_t att_lds[];
     int8_t* const qs = att_lds;                                               // queries [64][64]
     int8_t* const ks = qs + ATT_QB * ATT_DH;                                  // K_h [64 NKB][64]
@@ -364,10 +367,10 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
             acc[cb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(v4i{lo.x, lo.y, hi.x, hi.y}, pf[kb], acc[cb], 0, 0, 0);
         }
     }
-    auto store = [&](auto one) {
+    auto store = [&](auto requantized) {
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
-            const uint32_t pk = pack4_perm(one(acc[cb][0]), one(acc[cb][1]), one(acc[cb][2]), one(acc[cb][3]));
+            const uint32_t pk = pack4_perm(requantized(acc[cb][0]), requantized(acc[cb][1]), requantized(acc[cb][2]), requantized(acc[cb][3]));
             if (qrow < L) *reinterpret_cast<uint32_t*>(out + 16 * cb) = pk;
         }
     };
@@ -386,10 +389,12 @@ bool attention_fused_ok(const int8_t* qkv, const int8_t* ctx, int32_t seq, int32
 // regions scores and probs are documented as untouched.
 bool attention_whole_blocks(int32_t seq) { return seq % 128 == 0 && seq <= 512; }
 
+static constexpr size_t att_lds_bytes(int nkb, bool one_buffer) { return (size_t)(ATT_QB + (one_buffer ? 1 : 2) * 64 * nkb) * ATT_DH; }
+
 template <int NKB>
 static int launch_attention_l(const AttentionArgs& a, int64_t blocks, int form, hipStream_t stream)
 {
-    const size_t lds_bytes = (size_t)(ATT_QB + (att_may_share(NKB) && a.one_buffer ? 1 : 2) * 64 * NKB) * ATT_DH;
+    const size_t lds_bytes = att_lds_bytes(NKB, att_may_share(NKB, form) && a.one_buffer);
     const dim3 grid((unsigned)(blocks + a.ahead_wgs)), block(ATT_THREADS);
 #define IBERT_ATT_LAUNCH(F_)                                                                                      \
     do {                                                                                                          \
@@ -397,7 +402,7 @@ static int launch_attention_l(const AttentionArgs& a, int64_t blocks, int form, 
         static bool attr_done = false;                                                                            \
         if (!attr_done && lds_bytes > 65536) {                                                                    \
             IBERT_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(kern),                              \
-                                                hipFuncAttributeMaxDynamicSharedMemorySize, (ATT_QB + 2 * 64 * NKB) * ATT_DH)); \
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)att_lds_bytes(NKB, false))); \
             attr_done = true;                                                                                     \
         }                                                                                                         \
         hipLaunchKernelGGL(kern, grid, block, lds_bytes, stream, a);                                              \
@@ -422,7 +427,7 @@ int launch_attention(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq,
     if (blocks == 0) return IBERT_OK;
     if (blocks > 0x7fffffffLL - 256) return IBERT_ERR_SHAPE;
     a.blocks = (int32_t)blocks;
-    a.one_buffer = blocks > ATT_SHARE_WGS;
+    a.one_buffer = blocks > ATT_SHARE_WGS;                         // (where the kernel may at all)
     a.ahead_wgs = ahead ? 256 : 0;
     a.ahead = ahead ? *ahead : ReadAhead{};
     a.qkv = qkv; a.ctx = ctx; a.heads = heads; a.seq = seq;
@@ -460,4 +465,25 @@ int launch_attention(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq,
     return IBERT_OK;
 }
 
+template <int NKB, int FORM>
+static int attention_occupancy(int32_t* two, int32_t* one)
+{
+    const void* kern = reinterpret_cast<const void*>(attention_kernel<NKB, FORM>);
+    IBERT_HIP_CHECK(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)att_lds_bytes(NKB, false)));
+    IBERT_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(two, kern, ATT_THREADS, att_lds_bytes(NKB, false)));
+    IBERT_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(one, kern, ATT_THREADS, att_lds_bytes(NKB, true)));
+    return IBERT_OK;
+}
+
 }  // namespace ibert
+
+extern "C" int ibert_attention_buffers(int32_t seq, int32_t form, int64_t workgroups, int32_t* shared, int32_t* fit_two, int32_t* fit_one)
+{
+    using namespace ibert;
+    if (!shared || !fit_two || !fit_one) return IBERT_ERR_NULL;
+    if (seq < 385 || seq > 512 || form < 0 || form > 2) return IBERT_ERR_SHAPE;
+    const int nkb = (seq + 63) / 64;
+    *shared = att_may_share(nkb, form) && workgroups > ATT_SHARE_WGS;
+    if (nkb == 7) return form == 0 ? attention_occupancy<7, 0>(fit_two, fit_one) : form == 1 ? attention_occupancy<7, 1>(fit_two, fit_one) : attention_occupancy<7, 2>(fit_two, fit_one);
+    return form == 0 ? attention_occupancy<8, 0>(fit_two, fit_one) : form == 1 ? attention_occupancy<8, 1>(fit_two, fit_one) : attention_occupancy<8, 2>(fit_two, fit_one);
+}

@@ -55,13 +55,35 @@ def test_attention_any_length(G, L, S, k, sdy):
                     break                                    # (one key: every query gives the same; a few groups are enough)
 
 
-@pytest.mark.parametrize("B_,nh,L", [(8, 9, 447), (13, 5, 512), (8, 8, 449)])      # 504 / 520 / 512 workgroups: on both sides of the switch
+def _buffers(L, form, workgroups):
+    import ctypes as C
+    from paper_2101_01321_amd import binding as B
+    out = [C.c_int32() for _ in range(3)]
+    assert B.lib().ibert_attention_buffers(L, form, workgroups, *[C.byref(o) for o in out]) == 0
+    return [o.value for o in out]
+
+
+@pytest.mark.parametrize("L", [385, 448, 449, 512])
+@pytest.mark.parametrize("form", [0, 1, 2])
+def test_attention_shares_a_buffer_only_where_more_workgroups_fit(G, L, form):
+    # one buffer is there to let a compute unit hold more workgroups: it is used where that is so and there are more than 512
+    shared, two, one = _buffers(L, form, 513)
+    assert two == 2 and shared == (one > two), (shared, two, one)
+    assert _buffers(L, form, 512)[0] == 0
+
+
+# 504 to 539 workgroups, on both sides of the switch at 512; lengths at, before and behind the ends of key blocks
+@pytest.mark.parametrize("B_,nh,L,many", [(8, 9, 447, 0), (8, 8, 449, 0), (11, 7, 385, 1), (11, 7, 447, 1), (11, 7, 448, 1), (13, 5, 449, 1),
+                                          (13, 5, 511, 1), (13, 5, 512, 1)])
 @pytest.mark.parametrize("sdy", [(1518500250, 36), (1187698534, 28), (-1518500250, 36)])
-def test_attention_keys_and_values_in_one_buffer(G, B_, nh, L, sdy):
-    # long sequences of more workgroups than find a place at once: V_h takes the place of K_h in LDS; also with masked blocks of
-    # keys, down to a single key, against the oracle on the last sequence
+def test_attention_keys_and_values_in_one_buffer(G, B_, nh, L, many, sdy):
+    # long sequences of more workgroups than find a place at once: V_h takes the place of K_h in LDS where that makes room for more; also
+    # with masked blocks of keys, down to a single key, against the oracle on the last sequence
     from paper_2101_01321_amd import binding as B
     H, cdy = 64 * nh, (1073741824, 37)
+    workgroups, form = B_ * nh * -(-L // 64), 0 if sdy[0] < 0 else (1 if sdy[1] >= 32 else 2)
+    assert (workgroups > 512) == bool(many)
+    assert _buffers(L, form, workgroups)[0] == (many and not (form == 0 and L > 448))
     qkv = _qkv(B_, L, H, L + nh)
     sp, op = B.ibert_softmax_params_from_scale(2.0 ** -6, L, 7), P.softmax_params(2.0 ** -6, 7)
     G.say("attention, one buffer, B=%d heads=%d L=%d s=%s" % (B_, nh, L, sdy))
