@@ -828,8 +828,8 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
     // stored, which form of GELU) is a template tag, so that the compiler can keep many values of many blocks in flight
     // -- one block column's 4 FM values go through requantization together, then (table form of GELU) their table reads
     // are issued back to back, then they are packed and stored.
-    // SM = how a lane's four values leave: 0 the lane's own store, 1 through LDS as whole row pieces (INT8: 16 bytes;
-    // int16: 8 bytes).  ES = bytes per stored element (1, 2, 4).
+    // SM = how a lane's four values leave: 0 the lane's own store, 1 through LDS as whole row pieces (INT8 with a residual: 16 bytes;
+    // int16: 8 bytes), 2 lane-transposed (INT8).  ES = bytes per stored element (1, 2, 4).
     // FOLD (table form of GELU with every shift at most 43): the table's LDS address is folded into the requantization
     // constant -- (acc m + c - (lo - base) 2^s) >> s = v - lo + base exactly, the subtrahend being a multiple of 2^s, and
     // below 2^62 in magnitude, so the sum stays inside 64 bits -- which leaves a multiply-add, a shift, a clamp and a
@@ -849,6 +849,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         constexpr int SPH = 2 * BN + 8;                            // int16 rows: 8-byte pieces, padded by one
         static_assert(SM == 0 || ES != 2 || BM * SPH <= 32 * JC * SP * 4, "the 16-bit staging tile ends where the constants begin");
         static_assert(SM != 1 || ES != 1 || BM * SPB <= 32 * JC * SP * 4, "the INT8 staging tile fits in front of the constants");
+        static_assert(SM != 1 || !LUT, "GELU tiles do not leave through LDS");
         static_assert(SM == 0 || ES != 4, "INT32 outputs are stored by the lanes themselves");
         int8_t* const ostage = lds;
         char* const ct = reinterpret_cast<char*>(g.C) + (c_off + (int64_t)m0 * g.ldc + n0) * (int64_t)ES;
@@ -901,11 +902,8 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
 #pragma unroll
                 for (int j = 0; j < FM; ++j) {
                     const uint32_t pk4 = (by[j][0] | (by[j][1] << 8)) | ((by[j][2] | (by[j][3] << 8)) << 16);
-                    char* cp = c_at(j, (uint32_t)(wn0 + 4 * fch) * ES) + i * 16 * ES;
-                    const int row = wm0 + 16 * j + frow, colb = wn0 + 16 * i + 4 * fch;
                     if (SM == 2) pq[i < 4 ? i : 0][j] = pk4;
-                    else if (SM == 1) *reinterpret_cast<uint32_t*>(ostage + ost_at(row, colb)) = pk4;
-                    else *reinterpret_cast<uint32_t*>(cp) = pk4;
+                    else *reinterpret_cast<uint32_t*>(c_at(j, (uint32_t)(wn0 + 4 * fch)) + i * 16) = pk4;
                 }
                 continue;
             }
@@ -1003,18 +1001,16 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             }
         }
     };
-    // How INT8 tiles leave: lane-transposed 16-byte stores where the wavefronts are narrow enough and there is no residual (all
-    // direct-to-LDS tiles; four wavefronts against whole rows through LDS or a lane's own stores, us: [488,2304] x K 768 5.86 -> 5.74,
-    // [2048,2304] x K 768 8.81 -> 8.66, with GELU [1024,4096] x K 1024 on 64x128 11.5 -> 11.2).
-    // Which others leave through LDS (measured): INT8 tiles without GELU, and with GELU those of eight wavefronts -- a lane's
-    // own store would be 4 bytes in each of 16 rows per instruction, which the address unit takes an order of magnitude
-    // longer over than whole rows (a gain of 1.5-2 us on the QKV projections; S7+S8 of Base 18.9 -> 17.9 us, of Base at
-    // 512 tokens x 64: 133.8 -> 125.5 us; the four-wavefront GELU tiles gain nothing from it and 256x128 loses); int16
-    // tiles of eight wavefronts (256x192, [32768,768] outputs: K 768 48.3 -> 43.5 us, K 3072 91.7 -> 89.5 us; the
-    // four-wavefront tiles lose by it -- 128x96: 9.6 -> 11.0 us; 256x128: 66.5 -> 76.4 us).
-    constexpr bool OST_FITS = BM * (BN + 16) <= 32 * JC * SP * 4;
-    constexpr bool OST = OUT_I8 && (!GELU || NW == 8) && OST_FITS;
-    constexpr bool LTS = OUT_I8 && FN <= 4;                        // lane-transposed 16-byte stores instead
+    // How INT8 tiles leave: without a residual as lane-transposed 16-byte stores, with GELU too, where the output is aligned for them.  (A
+    // lane's own store is 4 bytes in each of 16 rows per instruction, which the address unit takes an order of magnitude longer over.
+    // Four wavefronts, against whole rows through LDS or, with GELU, the lanes' own stores, us: 128x128 ring tiles [4096,2304] x K 272
+    // 17.7 -> 14.7, [32768,3072] x K 784 171.7 -> 156.4; [K,N] weights, 24 x [1024,64] x K 1024 11.5 -> 11.1; 64x96 [2048,2304] x K 768
+    // 9.38 -> 9.29; GELU on 128x96 [4096,3072] x K 768 21.2 -> 18.6, on 128x128 [1024,4096] x K 1024 11.4 -> 10.8; 64x64 ring tiles
+    // within 1 % without and 0 to 7 % faster with GELU.)  With a residual through LDS as whole rows, where the staging tile fits.
+    // int16 tiles go through LDS when eight wavefronts share one (256x192, [32768,768] outputs: K 768 48.3 -> 43.5 us, K 3072
+    // 91.7 -> 89.5 us; the four-wavefront tiles lose by it -- 128x96: 9.6 -> 11.0 us; 256x128: 66.5 -> 76.4 us).
+    constexpr bool OST = OUT_I8 && !GELU && BM * (BN + 16) <= 32 * JC * SP * 4;
+    static_assert(!OUT_I8 || FN <= 4, "INT8 tiles: at most four block columns a wavefront");
     constexpr bool OST16 = !OUT_I8 && NW == 8 && BM <= 64 * JC;
     using T = std::true_type;
     using F = std::false_type;
@@ -1029,36 +1025,20 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
     if (interior && fast) {
         // (GELU excludes a residual; without a table -- it did not fit, or the parameters are unusual -- the
         // arithmetic form runs, with the choice between its two variants made per value)
-        using I2s = std::integral_constant<int, 2>;
-        bool stored = false;
-        if constexpr (LTS) {
-            if (g.c_vec16 && !R) {
-                if constexpr (GELU) {
-                    if (g.gelu_lut_n > 0) if (fold_early) finish_direct(F{}, F{}, T{}, I2s{}, I1{}, T{}); else finish_direct(F{}, F{}, T{}, I2s{}, I1{}, F{});
-                    else finish_direct(F{}, F{}, F{}, I2s{}, I1{}, F{});
-                } else {
-                    finish_direct(F{}, F{}, F{}, I2s{}, I1{}, F{});
-                }
-                stored = true;
-            }
-        }
-        if (stored) {
-        } else if constexpr (OUT_I8) {
-            const bool via_lds = OST && g.c_vec16;
-            if constexpr (GELU) {
-                if (g.gelu_lut_n > 0) {
-                    if constexpr (OST) { if (via_lds) if (fold_early) finish_direct(F{}, F{}, T{}, I1{}, I1{}, T{}); else finish_direct(F{}, F{}, T{}, I1{}, I1{}, F{}); else if (fold_early) finish_direct(F{}, F{}, T{}, I0{}, I1{}, T{}); else finish_direct(F{}, F{}, T{}, I0{}, I1{}, F{}); }
-                    else if (fold_early) finish_direct(F{}, F{}, T{}, I0{}, I1{}, T{}); else finish_direct(F{}, F{}, T{}, I0{}, I1{}, F{});
-                } else {
-                    finish_direct(F{}, F{}, F{}, I0{}, I1{}, F{});
-                }
+        if constexpr (GELU) {
+            if (g.gelu_lut_n > 0) {
+                if (fold_early) { if (g.c_vec16) finish_direct(F{}, F{}, T{}, I2{}, I1{}, T{}); else finish_direct(F{}, F{}, T{}, I0{}, I1{}, T{}); }
+                else { if (g.c_vec16) finish_direct(F{}, F{}, T{}, I2{}, I1{}, F{}); else finish_direct(F{}, F{}, T{}, I0{}, I1{}, F{}); }
             } else {
-                if constexpr (OST) {
-                    if (via_lds) { if (R) finish_direct(T{}, F{}, F{}, I1{}, I1{}, F{}); else finish_direct(F{}, F{}, F{}, I1{}, I1{}, F{}); }
-                    else { if (R) finish_direct(T{}, F{}, F{}, I0{}, I1{}, F{}); else finish_direct(F{}, F{}, F{}, I0{}, I1{}, F{}); }
-                } else {
-                    if (R) finish_direct(T{}, F{}, F{}, I0{}, I1{}, F{}); else finish_direct(F{}, F{}, F{}, I0{}, I1{}, F{});
-                }
+                if (g.c_vec16) finish_direct(F{}, F{}, F{}, I2{}, I1{}, F{}); else finish_direct(F{}, F{}, F{}, I0{}, I1{}, F{});
+            }
+        } else if constexpr (OUT_I8) {
+            if (!R) {
+                if (g.c_vec16) finish_direct(F{}, F{}, F{}, I2{}, I1{}, F{}); else finish_direct(F{}, F{}, F{}, I0{}, I1{}, F{});
+            } else if (OST && g.c_vec16) {
+                if constexpr (OST) finish_direct(T{}, F{}, F{}, I1{}, I1{}, F{});
+            } else {
+                finish_direct(T{}, F{}, F{}, I0{}, I1{}, F{});
             }
         } else {
             if (g.c16) {

@@ -334,19 +334,17 @@ def test_gemm_gelu_on_tiles_with_loaders(G, cfg, bm, bn):
         _stream_case(G, cfg, M, N, K, "gelu", shift, seed=M + N + K)
 
 
-@pytest.mark.parametrize("cfg,bm,bn", [(7, 128, 128), (9, 128, 96), (13, 256, 192), (14, 256, 128), (17, 64, 96), (18, 64, 96), (19, 64, 128),
-                                       (21, 128, 96), (22, 128, 128)])
-@pytest.mark.parametrize("kind", ["i8", "i16res", "gelu"])
+@pytest.mark.parametrize("kind,cfg,bm,bn", [(kind, *t) for kind in ("i8", "i16res", "gelu") for t in
+                                            [(7, 128, 128), (9, 128, 96), (13, 256, 192), (14, 256, 128), (17, 64, 96), (18, 64, 96),
+                                             (19, 64, 128), (21, 128, 96), (22, 128, 128)] if kind != "gelu" or t[0] not in (17, 18, 19)])
 @pytest.mark.parametrize("constants", ["one multiplier", "no bias", "neither"])
 @pytest.mark.parametrize("shift", [37, 30])
-def test_gemm_direct_to_lds_constants_filled_in_by_hand(G, cfg, bm, bn, kind, constants, shift):
+def test_gemm_direct_to_lds_constants_filled_in_by_hand(G, kind, cfg, bm, bn, constants, shift):
     # without an array of them the constants of a tile's columns are written to LDS by the wavefronts themselves; each then reads all of
     # them to choose the form of the epilogue (shift 37 register-direct, 30 through LDS with barriers): one K step and several, the
     # last tile row cut
     import torch
     from paper_2101_01321_amd import binding as B
-    if kind == "gelu" and cfg in (17, 18, 19):
-        pytest.skip("these tiles do not carry GELU")
     gp, op = B.ibert_gelu_params_from_scale(2.0 ** -6, 0.7), P.gelu_params(2.0 ** -6, 0.7)
     pc, res_dy, dy = int(constants == "no bias"), (1717986918, 23), (1518500250 >> (37 - shift), shift)
     word = torch.zeros(1, dtype=torch.int32, device=G.DEV)
@@ -375,6 +373,57 @@ def test_gemm_direct_to_lds_constants_filled_in_by_hand(G, cfg, bm, bn, kind, co
             want = oracle.gelu(want, op)
         assert len(np.unique(want)) > 20
         _eq(got.astype(np.int64), want.astype(np.int64), "constants by hand")
+
+
+INT8_TILES = [(15, 32, 32), (3, 64, 64), (2, 128, 128), (4, 64, 128), (7, 128, 128), (9, 128, 96), (13, 256, 192), (14, 256, 128), (17, 64, 96),
+              (18, 64, 96), (19, 64, 128), (21, 128, 96), (22, 128, 128), (-1, 128, 64), (-1, 128, 128)]        # the last two: W as [K, N]
+
+
+@pytest.mark.parametrize("kind,cfg,bm,bn", [(kind, *t) for kind in ("plain", "residual", "gelu") for t in INT8_TILES
+                                            if kind != "gelu" or t[0] in (15, 3, 7, 9, 13, 14, 21, 22)])
+def test_gemm_int8_tiles_leave_in_every_way(G, kind, cfg, bm, bn):
+    # INT8 outputs leave lane-transposed, through LDS (with a residual) or by the lanes' own 4-byte stores, by the alignment of the
+    # output's rows; as columns of wider rows, so that whatever is written beside them shows.  Shift 45: GELU's table is not folded
+    import torch
+    from paper_2101_01321_amd import binding as B
+    tw, K = int(cfg < 0), 256
+    gp, op = B.ibert_gelu_params_from_scale(2.0 ** -6, 0.7), P.gelu_params(2.0 ** -6, 0.7)
+    for M, beside, at, shift in [(2 * bm, 16, 0, 40), (2 * bm, 4, 0, 40), (2 * bm, 16, 4, 40), (2 * bm, 1, 0, 40), (2 * bm, 16, 0, 30), (2 * bm + 5, 16, 0, 40)] + \
+                                ([(2 * bm, 16, 0, 45), (2 * bm, 4, 0, 45)] if kind == "gelu" else []):
+        N = 2 * bn if not tw else bn
+        rng = np.random.default_rng(M + beside + at + shift)
+        A = rng.integers(-127, 128, size=(M, K), dtype=np.int8)
+        W = rng.integers(-127, 128, size=(K, N) if tw else (N, K), dtype=np.int8)
+        bias = rng.integers(-50000, 50000, size=N, dtype=np.int32)
+        mult = rng.integers(2 ** 29, 2 ** 30, size=N, dtype=np.int32)
+        mult, shifts = {30: mult >> 10, 40: mult, 45: mult + 2 ** 30 - 1}[shift], np.full(N, shift, np.int32)
+        R = rng.integers(-127, 128, size=(M, N), dtype=np.int8) if kind == "residual" else None
+        d = B.GemmDesc()
+        for k, v in dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K, ldw=N if tw else K, ldc=N + beside, ldr=N, trans_w=tw, per_channel=1,
+                         residual_dy=B.Dyadic(1717986918, 31), out_dtype=I8, out_clamp=127).items():
+            setattr(d, k, v)
+        tC = torch.full((at + (M + 1) * (N + beside),), 77, dtype=torch.int8, device=G.DEV)
+        dev = [G.to_dev(t) for t in (A, W, bias, mult, shifts)]
+        B.lib().ibert_gemm_config_override(cfg)
+        try:
+            G.say("INT8 tiles leave cfg %d %s M=%d N=%d +%d @%d shift=%d" % (cfg, kind, M, N, beside, at, shift))
+            if kind == "gelu":
+                B.ibert_gemm_i8_gelu(d, *dev, gp, tC[at:], torch.empty((M, N), dtype=torch.int32, device=G.DEV))
+            else:
+                B.ibert_gemm_i8_requant(d, *dev, None if R is None else G.to_dev(R), tC[at:])
+            torch.cuda.synchronize()
+        finally:
+            B.lib().ibert_gemm_config_override(-1)
+        assert B.lib().ibert_last_kernel().decode().startswith("gemm_nt_mfma_kernel<%d, %d, " % (bm, bn))
+        spec = GemmSpec(M, N, K, per_channel=1, dy=(1, 0), out_dtype=I32 if kind == "gelu" else I8,
+                        out_clamp=gp.q_max if kind == "gelu" else 127, res_dy=(1717986918, 31))
+        want = oracle.gemm_requant(spec, A, np.ascontiguousarray(W.T) if tw else W, bias, mult, shifts, R).reshape(M, N)
+        if kind == "gelu":
+            want = oracle.gelu(want.reshape(-1), op).reshape(M, N)
+        got = tC.cpu().numpy()
+        rows = got[at:].reshape(M + 1, N + beside)
+        _eq(rows[:M, :N].astype(np.int64), want.astype(np.int64), "INT8 tiles leave")
+        assert np.all(got[:at] == 77) and np.all(rows[M:] == 77) and np.all(rows[:, N:] == 77), "wrote beside the output"
 
 
 @pytest.mark.parametrize("cfg,bn,lda,M", [(7, 128, 1 << 22, 1025), (9, 96, 1 << 22, 1030), (13, 192, 1 << 22, 1025), (14, 128, 1 << 22, 1033),
