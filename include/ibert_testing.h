@@ -7,6 +7,8 @@
 
 #include <stdint.h>
 
+#include "ibert.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -44,6 +46,14 @@ void ibert_gemm_epilogue_record(uint32_t* device_word);
  * workgroups that a compute unit holds at once with two buffers and with one.  form: 0 any constants, 1 and 2 the faster
  * forms (scores' shift at least 32, and below).  Asks the device. */
 int ibert_attention_buffers(int32_t seq, int32_t form, int64_t workgroups, int32_t* shared, int32_t* fit_two, int32_t* fit_one);
+
+/* What the XCDs read of W [N, K] (dense rows, K a multiple of 128, N * K of 1024) when this MatMul runs with all operands aligned, and
+ * what each reads ahead when an encoder plans for it.  plan: the tile configuration chosen, then rows and xs: XCD x is to have the row
+ * blocks (j << xs) + x % 2^xs of `rows` rows each.  readers[n] (N bytes, zeroed by the caller): bit x is set where a workgroup on XCD x
+ * multiplies row n, by the kernel's own dealing of tiles.  ahead[x * N K / 1024 + i] (8 N K / 1024 bytes, zeroed): how often XCD x reads
+ * the i-th KB ahead, by the attention kernel's own arithmetic.  gelu: with the GELU epilogue.  IBERT_ERR_NOT_IMPLEMENTED: nothing is
+ * planned for such operands; IBERT_ERR_SHAPE: a read past the end of W.  Host only. */
+int ibert_gemm_weight_plan(const ibert_gemm_desc* desc, int32_t gelu, int32_t plan[3], uint8_t* readers, uint8_t* ahead);
 
 #ifdef __cplusplus
 }

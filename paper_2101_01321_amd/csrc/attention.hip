@@ -131,10 +131,9 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
 #pragma unroll
         for (int r = 0; r < ReadAhead::MOST; ++r) {
             const auto& q = ga->ahead.part[r];
-            const int s = x & ((1 << q.xs) - 1), total = ((q.blocks - s + (1 << q.xs) - 1) >> q.xs) * q.kb;
+            const int total = ReadAhead::count(x, q.kb, q.blocks, q.xs);
             for (int k = first * 4 + wave; k < total; k += 4 * wgs) {
-                const int j = udiv_fix(k, q.kb, q.kb_magic);
-                const int8_t* src = q.p + ((int64_t)((j << q.xs) + s) * q.kb + (k - j * q.kb)) * 1024;
+                const int8_t* src = q.p + ReadAhead::at(x, k, q.kb, q.kb_magic, q.xs) * 1024;
                 asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                              :: "s"(dst), "v"((uint32_t)lane * 16u), "s"(src) : "memory", "m0");
             }
@@ -431,8 +430,7 @@ int launch_attention(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq,
     a.ahead_wgs = ahead ? 256 : 0;
     a.ahead = ahead ? *ahead : ReadAhead{};
     a.qkv = qkv; a.ctx = ctx; a.heads = heads; a.seq = seq;
-    auto magic = [](int32_t d) { return d == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)d) + 1u; };
-    a.qblks_magic = magic(a.qblks); a.heads_magic = magic(heads);
+    a.qblks_magic = udiv_magic(a.qblks); a.heads_magic = udiv_magic(heads);
     a.xcd_q = (int32_t)(blocks / 8); a.xcd_r = (int32_t)(blocks % 8);
     a.ld_qkv = 3 * hidden; a.ld_ctx = hidden;
     a.s_m = scores_dy.m; a.s_s = scores_dy.s; a.c_m = ctx_dy.m; a.c_s = ctx_dy.s;

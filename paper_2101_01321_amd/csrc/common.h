@@ -130,12 +130,17 @@ __device__ __forceinline__ int32_t group_allreduce(int32_t v, Op op)
 }
 
 // floor(n / d) for 0 <= n < 2^31 with magic = floor(2^32 / d) + 1 (0 for d == 1): the estimate is the quotient or one more.
-__device__ __forceinline__ int32_t udiv_fix(int32_t n, int32_t d, uint32_t magic)
+__host__ __device__ __forceinline__ int32_t udiv_fix(int32_t n, int32_t d, uint32_t magic)
 {
     if (magic == 0) return n;
+#if defined(__HIP_DEVICE_COMPILE__)
     const int32_t q = (int32_t)__umulhi((uint32_t)n, magic);
+#else
+    const int32_t q = (int32_t)(((uint64_t)(uint32_t)n * magic) >> 32);
+#endif
     return n - q * d < 0 ? q - 1 : q;
 }
+inline uint32_t udiv_magic(int32_t d) { return d == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)d) + 1u; }
 
 // Name of the kernel family chosen by the most recent launch_* call (for the optional profile).
 extern const char* g_last_kernel;
@@ -163,11 +168,21 @@ struct ReadAhead {
         // 903 with eight copies, 852 with one; Base b1 (an eighth for each): 327 without, 336 by any XCD, 316 by the one that reads.
         const bool own = plan.xs >= 2;
         const int32_t kb = own ? (int32_t)(plan.rows * K / 1024) : 1;
-        part[n++] = Part{w, kb, (int32_t)(N * K / 1024 / kb), own ? plan.xs : 3, kb == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)kb) + 1u};
+        part[n++] = Part{w, kb, (int32_t)(N * K / 1024 / kb), own ? plan.xs : 3, udiv_magic(kb)};
     }
     ReadAhead()
     {
         for (Part& q : part) q = Part{nullptr, 1, 0, 0, 0};
+    }
+    // KB of a part that XCD x reads, and the k-th of them, counted from the part's first.
+    static __host__ __device__ __forceinline__ int32_t count(int x, int32_t kb, int32_t blocks, int32_t xs)
+    {
+        return ((blocks - (x & ((1 << xs) - 1)) + (1 << xs) - 1) >> xs) * kb;
+    }
+    static __host__ __device__ __forceinline__ int64_t at(int x, int32_t k, int32_t kb, uint32_t kb_magic, int32_t xs)
+    {
+        const int j = udiv_fix(k, kb, kb_magic);
+        return (int64_t)((j << xs) + (x & ((1 << xs) - 1))) * kb + (k - j * kb);
     }
 };
 

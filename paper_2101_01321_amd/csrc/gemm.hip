@@ -325,24 +325,86 @@ GemmPlan plan_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, c
 {
     GemmPlan p;
     if (d.batch_outer != 1 || d.batch_inner != 1 || d.M < 1 || d.N < 1 || d.ldw != d.K || d.K % 128 != 0 || !rows_aligned(d, A, W)) return p;
-    const GemmArgs g = gemm_args(d, A, W, bias, mult, shift, residual, const_cast<void*>(C));
+    GemmArgs g = gemm_args(d, A, W, bias, mult, shift, residual, const_cast<void*>(C));
     const int cfg = choose_config(d, g, 1, gelu);
     const GemmConfig& f = kConfigs[cfg];
     if (d.N % f.bn != 0) return p;
-    const int32_t tiles_m = (int32_t)ceil_div(d.M, f.bm), tiles_n = d.N / f.bn;
     if (cfg >= 25) {
-        p.xs = few_grid(tiles_m, tiles_n).xs;
+        FewArgs a;
+        few_deal(a, g, f.bm, f.bn);
+        p.xs = a.xs;
         p.rows = f.bn;
     } else if (cfg == 23 || cfg == 24) {
-        p.xs = stream_shares(g, tiles_m, tiles_n);
+        StreamArgs a;
+        stream_deal(a, g, f.bm, f.bn);
+        p.xs = a.xs;
         p.rows = d.N >> p.xs;
     } else {
-        const bool even = (int64_t)tiles_m * tiles_n % 8 == 0 && (int64_t)tiles_m * tiles_n >= 16;
-        p.xs = even ? xcd_shares(g, tiles_m, tiles_n) : -1;
-        if (p.xs < 0) p.xs = tiles_n % 8 == 0 ? 3 : 0;             // (dealt in other ways: near is better than far)
+        dim3 grid;
+        if (!mfma_deal(g, f.bm, f.bn, grid)) return p;
+        // (not in blocks: one tile for every XCD, side by side, or any tile of W anywhere)
+        p.xs = g.xcd_xn >= 1 ? g.xcd_xs : (g.tiles_m == 1 && g.tiles_n == 8 ? 3 : 0);
         p.rows = d.N >> p.xs;
     }
     return p;
+}
+
+// For tests, see ibert_testing.h.
+static int weight_plan(const ibert_gemm_desc& d, bool gelu, int32_t out[3], uint8_t* readers, uint8_t* ahead)
+{
+    alignas(16) static const int32_t any[4] = {};                  // (an aligned address; nothing is read)
+    int8_t* const p = reinterpret_cast<int8_t*>(const_cast<int32_t*>(any));
+    const int8_t* const residual = d.out_dtype == IBERT_I8 ? nullptr : p;
+    const GemmPlan plan = plan_gemm(d, p, p, any, any, any, residual, p, gelu);
+    if (plan.rows < 1) return IBERT_ERR_NOT_IMPLEMENTED;
+    GemmArgs g = gemm_args(d, p, p, any, any, any, residual, p);
+    const int cfg = choose_config(d, g, 1, gelu);
+    const GemmConfig& f = kConfigs[cfg];
+    out[0] = cfg; out[1] = plan.rows; out[2] = plan.xs;
+    auto reads = [&](int xcd, int tm, int tn) {
+        if ((int64_t)tm * f.bm < d.M)
+            for (int n = tn * f.bn; n < (tn + 1) * f.bn && n < d.N; ++n) readers[n] |= (uint8_t)(1 << xcd);
+    };
+    int z, tm, tn;
+    if (cfg >= 25) {
+        FewArgs a;
+        const int64_t blocks = few_deal(a, g, f.bm, f.bn);
+        for (unsigned b = 0; b < blocks; ++b) {
+            few_tile(a, b, tm, tn);
+            reads(b & 7, tm, tn);
+        }
+    } else if (cfg == 23 || cfg == 24) {
+        StreamArgs a;
+        stream_deal(a, g, f.bm, f.bn);
+        for (int x = 0; x < 8; ++x) {
+            const StreamRun run = stream_run(a, x);
+            for (int l = 0; l < run.count; ++l) {
+                stream_tile(a, run, l, tm, tn);
+                reads(x, tm, tn);
+            }
+        }
+    } else {
+        dim3 grid;
+        if (!mfma_deal(g, f.bm, f.bn, grid)) return IBERT_ERR_SHAPE;
+        for (unsigned by = 0; by < grid.y; ++by)
+            for (unsigned bx = 0; bx < grid.x; ++bx) {
+                mfma_tile(g, bx, by, z, tm, tn);
+                reads((int)((by * grid.x + bx) & 7), tm, tn);
+            }
+    }
+    ReadAhead r;
+    r.add(p, d.N, d.K, plan);
+    const int64_t kbs = (int64_t)d.N * d.K / 1024;
+    for (int i = 0; i < r.n; ++i) {
+        const auto& q = r.part[i];
+        for (int x = 0; x < 8; ++x)
+            for (int32_t k = 0; k < ReadAhead::count(x, q.kb, q.blocks, q.xs); ++k) {
+                const int64_t at = ReadAhead::at(x, k, q.kb, q.kb_magic, q.xs);
+                if (at < 0 || at >= kbs) return IBERT_ERR_SHAPE;
+                ++ahead[x * kbs + at];
+            }
+    }
+    return IBERT_OK;
 }
 
 // gelu != nullptr asks for the GELU epilogue (INT8 output, no residual; out_clamp must be gelu->q_max): a tile
@@ -488,6 +550,12 @@ extern "C" int ibert_gemm_config_override(int32_t config)
 
 
 extern "C" const char* ibert_last_kernel(void) { return ibert::g_last_kernel; }
+
+extern "C" int ibert_gemm_weight_plan(const ibert_gemm_desc* desc, int32_t gelu, int32_t plan[3], uint8_t* readers, uint8_t* ahead)
+{
+    if (!desc || !plan || !readers || !ahead) return IBERT_ERR_NULL;
+    return ibert::weight_plan(*desc, gelu != 0, plan, readers, ahead);
+}
 
 extern "C" void ibert_gemm_xcd_blocks(int32_t on) { ibert::g_xcd_blocks = on != 0; }
 

@@ -42,6 +42,16 @@ struct FewArgs {
     GeluConst gelu;
 };
 
+// The tile of a workgroup, which need not exist (see few_grid).  Workgroups go round the XCDs.  2^xs of them share the tile columns,
+// 2^(3 - xs) the tile rows, so that each reads only its part of W (and of A).
+__host__ __device__ __forceinline__ void few_tile(const FewArgs& g, unsigned block, int& tm, int& tn)
+{
+    const int xcd = block & 7, j0 = block >> 3;
+    const int q = udiv_fix(j0, g.rm, g.rm_magic);
+    tm = (xcd >> g.xs) * g.rm + (j0 - q * g.rm);
+    tn = (q << g.xs) + (xcd & ((1 << g.xs) - 1));
+}
+
 // Tile of 16 HM rows x 16 HN columns.
 template <int HM, int HN, bool OUT_I8, bool GELU>
 __global__ __launch_bounds__(512) void gemm_few_kernel(FewArgs g)
@@ -53,11 +63,8 @@ __global__ __launch_bounds__(512) void gemm_few_kernel(FewArgs g)
     static_assert(TM * TN * 4 <= STAGE, "a wavefront's sums fit where its first stage was");
     extern __shared__ __align__(16) int8_t lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Workgroups go round the XCDs.  2^xs of them share the tile columns, 2^(3 - xs) the tile rows, so that each reads only its
-    // part of W (and of A).
-    const int xcd = blockIdx.x & 7, j0 = blockIdx.x >> 3;
-    const int q = udiv_fix(j0, g.rm, g.rm_magic);
-    const int tm = (xcd >> g.xs) * g.rm + (j0 - q * g.rm), tn = (q << g.xs) + (xcd & ((1 << g.xs) - 1));
+    int tm, tn;
+    few_tile(g, blockIdx.x, tm, tn);
     const int m0 = tm * TM, n0 = tn * TN;
     const int nw = 1 << g.nwl, nk = g.nk, stages = g.stages;
     // every argument is in registers from here on (one trip to memory, not one at each first use)
@@ -232,6 +239,17 @@ inline FewGrid few_grid(int32_t tiles_m, int32_t tiles_n)
     return best;
 }
 
+// Deals the tiles of a problem; returns the workgroups.
+inline int64_t few_deal(FewArgs& f, const GemmArgs& g, int bm, int bn)
+{
+    f.tiles_m = (g.M + bm - 1) / bm;
+    f.tiles_n = g.N / bn;
+    const FewGrid fg = few_grid(f.tiles_m, f.tiles_n);
+    f.xs = fg.xs; f.rm = fg.rm;
+    f.rm_magic = udiv_magic(f.rm);
+    return 8 * fg.per_xcd;
+}
+
 // Wavefronts, stages and LDS bytes of a workgroup.
 struct FewShape {
     int32_t nwl, stages;
@@ -256,17 +274,12 @@ int launch_few(const GemmArgs& g, bool i8, hipStream_t stream)
     f.A = g.A; f.W = g.W; f.bias = g.bias; f.mult = g.mult; f.shift = g.shift; f.R = g.R; f.C = g.C;
     f.M = g.M; f.nk = g.K / 128;
     f.lda = (int32_t)g.lda; f.ldw = (int32_t)g.ldw; f.ldc = (int32_t)g.ldc; f.ldr = (int32_t)g.ldr;
-    f.tiles_m = (g.M + 16 * HM - 1) / (16 * HM);
-    f.tiles_n = g.N / (16 * HN);
-    const FewGrid fg = few_grid(f.tiles_m, f.tiles_n);
-    f.xs = fg.xs; f.rm = fg.rm;
-    f.rm_magic = f.rm == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)f.rm) + 1u;
+    const int64_t blocks = few_deal(f, g, 16 * HM, 16 * HN);
     f.out_clamp = g.out_clamp;
     f.res_m = g.res_m; f.res_s = g.res_s; f.res_rnd = g.res_rnd;
     f.fast = g.res_fast && (int64_t)g.K * 16129 < (1 << 30);
     f.c16 = g.c16;
     f.gelu_fast = g.gelu_fast; f.gelu = g.gelu;
-    const int64_t blocks = 8 * fg.per_xcd;
     if (blocks > 0x7fffffffLL) return IBERT_ERR_NOT_IMPLEMENTED;         // (larger tiles make fewer of them)
     const FewShape fs = few_shape(16 * HM, 16 * HN, f.nk);
     f.nwl = fs.nwl; f.stages = fs.stages;

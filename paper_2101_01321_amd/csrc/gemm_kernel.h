@@ -137,6 +137,32 @@ struct EpiLayout {
     static constexpr int LDS_BYTES = 4 * (MAIN > EPI ? MAIN : EPI);
 };
 
+// The tile of a workgroup.  Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of tiles so that
+// the A panels and W panels it touches stay in its own L2.
+// One problem whose tile grid divides suitably (xcd_xn >= 1, the launcher's choice): the run is a rectangular block
+// of the tile grid -- xcd_bm tile rows by xcd_bn tile columns, xcd_xn such blocks side by side, 8 / xcd_xn above each
+// other -- so that an XCD fetches only its rows of A and its columns of W over the fabric: 8 (M K / XM + N K / XN)
+// bytes in all, least for near-square blocks.  The launch grid is then (8 xcd_bn, xcd_bm): the XCD is blockIdx.x % 8
+// and the tile's place inside the block comes from the block indices without a division.
+__host__ __device__ __forceinline__ void mfma_tile(const GemmArgs& g, unsigned bx, unsigned by, int& z, int& tm, int& tn)
+{
+    if (g.xcd_xn >= 1) {
+        const int x = bx & 7, ln = bx >> 3, lm = by;
+        const int xm = x >> g.xcd_xs, xn = x & (g.xcd_xn - 1);
+        z = 0;
+        tm = xm * g.xcd_bm + lm;
+        tn = xn * g.xcd_bn + ln;
+    } else {
+        int bid = bx;
+        if (g.xcd_chunk > 0) bid = (bid & 7) * g.xcd_chunk + (bid >> 3);
+        const int tiles = g.tiles_m * g.tiles_n;
+        z = bid / tiles;
+        bid -= z * tiles;
+        tm = bid / g.tiles_n;
+        tn = bid - tm * g.tiles_n;
+    }
+}
+
 // TW = true: W is [K,N] (N contiguous).  Only the W loader differs: each lane fetches a 4 (k) x 4 (n) byte
 // block as four dwords, transposes it in registers with byte permutes and writes four dwords (4 consecutive
 // k of one n) into the same K-contiguous LDS layout the MFMA loop reads.
@@ -200,29 +226,8 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
     const int lane = tid & 63, wave = tid >> 6;
     const int wm0 = (wave & (WR - 1)) * WM, wn0 = (wave / WR) * WN;
 
-    // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous run of tiles so that
-    // the A panels and W panels it touches stay in its own L2.
-    // One problem whose tile grid divides suitably (xcd_xn >= 1, the launcher's choice): the run is a rectangular block
-    // of the tile grid -- xcd_bm tile rows by xcd_bn tile columns, xcd_xn such blocks side by side, 8 / xcd_xn above each
-    // other -- so that an XCD fetches only its rows of A and its columns of W over the fabric: 8 (M K / XM + N K / XN)
-    // bytes in all, least for near-square blocks.  The launch grid is then (8 xcd_bn, xcd_bm): the XCD is blockIdx.x % 8
-    // and the tile's place inside the block comes from the block indices without a division.
     int z, tm, tn;
-    if (g.xcd_xn >= 1) {
-        const int x = blockIdx.x & 7, ln = blockIdx.x >> 3, lm = blockIdx.y;
-        const int xm = x >> g.xcd_xs, xn = x & (g.xcd_xn - 1);
-        z = 0;
-        tm = xm * g.xcd_bm + lm;
-        tn = xn * g.xcd_bn + ln;
-    } else {
-        int bid = blockIdx.x;
-        if (g.xcd_chunk > 0) bid = (bid & 7) * g.xcd_chunk + (bid >> 3);
-        const int tiles = g.tiles_m * g.tiles_n;
-        z = bid / tiles;
-        bid -= z * tiles;
-        tm = bid / g.tiles_n;
-        tn = bid - tm * g.tiles_n;
-    }
+    mfma_tile(g, blockIdx.x, blockIdx.y, z, tm, tn);
     const int m0 = tm * BM, n0 = tn * BN;
     const int zo = g.nbatch == 1 ? 0 : z / g.batch_inner, zi = z - zo * g.batch_inner;
 
@@ -1092,13 +1097,13 @@ inline int xcd_shares(const GemmArgs& g, int tiles_m, int tiles_n)
     return best_xs;
 }
 
-template <int BM, int BN, int BK, int RING, bool TW = false, bool DMA = false, bool GELU = false, int NW = 4, int NLD = 0>
-int launch_mfma(GemmArgs& g, bool i8, hipStream_t stream)
+// Deals the tiles of a problem; false where they are too many for a launch.
+inline bool mfma_deal(GemmArgs& g, int bm, int bn, dim3& grid)
 {
-    g.tiles_m = (g.M + BM - 1) / BM;
-    g.tiles_n = (g.N + BN - 1) / BN;
+    g.tiles_m = (g.M + bm - 1) / bm;
+    g.tiles_n = (g.N + bn - 1) / bn;
     const int64_t blocks = (int64_t)g.tiles_m * g.tiles_n * g.nbatch;
-    if (blocks > 0x7fffffffLL) return IBERT_ERR_SHAPE;
+    if (blocks > 0x7fffffffLL) return false;
     g.xcd_chunk = (blocks % 8 == 0 && blocks >= 16) ? (int32_t)(blocks / 8) : 0;
     g.xcd_xn = g.xcd_xs = 0;
     g.xcd_bm = g.xcd_bn = 0;
@@ -1111,7 +1116,15 @@ int launch_mfma(GemmArgs& g, bool i8, hipStream_t stream)
             g.xcd_bn = g.tiles_n >> xs;
         }
     }
-    const dim3 grid = g.xcd_xn >= 1 ? dim3(8u * (unsigned)g.xcd_bn, (unsigned)g.xcd_bm) : dim3((unsigned)blocks);
+    grid = g.xcd_xn >= 1 ? dim3(8u * (unsigned)g.xcd_bn, (unsigned)g.xcd_bm) : dim3((unsigned)blocks);
+    return true;
+}
+
+template <int BM, int BN, int BK, int RING, bool TW = false, bool DMA = false, bool GELU = false, int NW = 4, int NLD = 0>
+int launch_mfma(GemmArgs& g, bool i8, hipStream_t stream)
+{
+    dim3 grid;
+    if (!mfma_deal(g, BM, BN, grid)) return IBERT_ERR_SHAPE;
     constexpr size_t lds_tile = EpiLayout<BM, BN, BK, (DMA ? RING : 2)>::LDS_BYTES;
     static_assert(lds_tile <= 163840, "LDS budget");
     // (direct-to-LDS kernels keep the per-channel constants behind the stages)

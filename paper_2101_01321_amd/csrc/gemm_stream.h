@@ -57,6 +57,23 @@ struct StreamArgs {
     uint32_t* path_word;
 };
 
+// Workgroups are dealt round-robin to the 8 XCDs.  XCD x works on the tile columns of share x % 2^xs and, of those tiles in
+// row-major order, on the (x >> xs)-th of 2^gs runs; its workgroups take the tiles of the run in turn.
+struct StreamRun {
+    int first_col, first, count;   // the share's first tile column; the run's first tile, its tiles
+};
+__host__ __device__ __forceinline__ StreamRun stream_run(const StreamArgs& g, int x)
+{
+    const int group = g.tiles_m * g.bn, xm = x >> g.xs, t0 = (int)(((int64_t)xm * group) >> g.gs);
+    return StreamRun{(x & ((1 << g.xs) - 1)) * g.bn, t0, (int)(((int64_t)(xm + 1) * group) >> g.gs) - t0};
+}
+__host__ __device__ __forceinline__ void stream_tile(const StreamArgs& g, const StreamRun& run, int l, int& tm, int& tn)
+{
+    const int t = run.first + l;
+    tm = udiv_fix(t, g.bn, g.bn_magic);
+    tn = run.first_col + t - tm * g.bn;
+}
+
 template <int BM, int BN, int NW, bool OUT_I8, bool GELU>
 struct StreamLayout {
     static constexpr int STAGE = (BM + BN) * 128;
@@ -85,18 +102,16 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
     const int frow = lane & 15, fch = lane >> 4;
 
     // ---- the workgroup's tiles ------------------------------------------------------------------
-    // Workgroups are dealt round-robin to the 8 XCDs.  XCD x works on the tile columns of share x % 2^xs and, of those tiles in
-    // row-major order, on the (x >> xs)-th of 2^gs runs; its workgroups take the tiles of the run in turn.
-    const int x = blockIdx.x & 7;
-    const int nb = (x & ((1 << g.xs) - 1)) * g.bn, group = g.tiles_m * g.bn, xm = x >> g.xs;
-    const int t0 = (int)(((int64_t)xm * group) >> g.gs), count = (int)(((int64_t)(xm + 1) * group) >> g.gs) - t0;
+    const StreamRun run = stream_run(g, blockIdx.x & 7);
+    const int count = run.count;
     const uint32_t kbytes = (uint32_t)g.nk * 128u;                 // bytes of a row that the K steps cover
     int lt = blockIdx.x >> 3;                                      // index inside the run
     if (lt >= count) return;
     auto tile_at = [&](int l, int& m0, int& n0) {
-        const int t = t0 + l, tm = udiv_fix(t, g.bn, g.bn_magic);
+        int tm, tn;
+        stream_tile(g, run, l, tm, tn);
         m0 = tm * BM;
-        n0 = (nb + t - tm * g.bn) * BN;
+        n0 = tn * BN;
     };
 
     // ---- requests -------------------------------------------------------------------------------
@@ -577,6 +592,19 @@ inline int stream_shares(const GemmArgs& g, int tiles_m, int tiles_n)
     return xs;
 }
 
+// Deals the tiles of a problem.
+inline void stream_deal(StreamArgs& s, const GemmArgs& g, int bm, int bn)
+{
+    s.tiles_m = (g.M + bm - 1) / bm;
+    const int tiles_n = g.N / bn;
+    s.xs = stream_shares(g, s.tiles_m, tiles_n);
+    s.gs = 3 - s.xs;
+    s.bn = tiles_n >> s.xs;
+    s.bn_magic = udiv_magic(s.bn);
+    const int64_t run = ((int64_t)s.tiles_m * s.bn + (1 << s.gs) - 1) >> s.gs;      // the longest run of an XCD
+    s.per_xcd = (int32_t)(run < 32 ? run : 32);                    // one workgroup per CU
+}
+
 template <int BM, int BN, int NW, bool GELU>
 int launch_stream(GemmArgs& g, bool i8, hipStream_t stream)
 {
@@ -585,14 +613,7 @@ int launch_stream(GemmArgs& g, bool i8, hipStream_t stream)
     s.A = g.A; s.W = g.W; s.bias = g.bias; s.mult = g.mult; s.shift = g.shift; s.R = g.R; s.C = g.C;
     s.M = g.M; s.nk = g.K / 128;
     s.lda = (int32_t)g.lda; s.ldw = (int32_t)g.ldw; s.ldc = (int32_t)g.ldc; s.ldr = (int32_t)g.ldr;
-    s.tiles_m = (g.M + BM - 1) / BM;
-    const int tiles_n = g.N / BN;
-    s.xs = stream_shares(g, s.tiles_m, tiles_n);
-    s.gs = 3 - s.xs;
-    s.bn = tiles_n >> s.xs;
-    s.bn_magic = s.bn == 1 ? 0u : (uint32_t)(((uint64_t)1 << 32) / (uint32_t)s.bn) + 1u;
-    const int64_t run = ((int64_t)s.tiles_m * s.bn + (1 << s.gs) - 1) >> s.gs;      // the longest run of an XCD
-    s.per_xcd = (int32_t)(run < 32 ? run : 32);                    // one workgroup per CU
+    stream_deal(s, g, BM, BN);
     s.per_channel = g.per_channel; s.dy_m = g.dy_m; s.dy_s = g.dy_s; s.out_clamp = g.out_clamp;
     s.res_m = g.res_m; s.res_s = g.res_s; s.res_fast = g.res_fast; s.res_rnd = g.res_rnd;
     s.k_fast = (int64_t)g.K * 16129 < (1 << 30);

@@ -162,6 +162,17 @@ static int run_attention(const int8_t* qkv, int32_t* scores, int8_t* probs, int8
     return run_attention_unfused(qkv, scores, probs, ctx, B, L, H, nh, scores_dy, softmax, ctx_dy, key_lens, stream);
 }
 
+// [T,K] x W [N,K], all dense.  (A residual, where there is one, is as wide as the output.)
+static ibert_gemm_desc projection(int64_t T, int64_t N, int64_t K, int32_t out_dtype, int32_t out_clamp)
+{
+    ibert_gemm_desc d;
+    std::memset(&d, 0, sizeof d);
+    d.M = (int32_t)T; d.N = (int32_t)N; d.K = (int32_t)K; d.batch_outer = d.batch_inner = 1;
+    d.lda = d.ldw = K; d.ldc = d.ldr = N;
+    d.per_channel = 1; d.out_dtype = out_dtype; d.out_clamp = out_clamp;
+    return d;
+}
+
 // How the MatMuls of a layer share their weights among the XCDs.  The layers of a call have one shape: made once a call, as a
 // forward of few tokens is bound by what the host does (a forward of Base, host, us: 220 without plans, 232 with twelve, 219 with one
 // and the choice of a tile in half its time).
@@ -169,15 +180,9 @@ struct LayerPlan {
     GemmPlan o, up, down, qkv;
     LayerPlan(const ibert_layer_weights& w, const int8_t* x, int8_t* y, int64_t T, int64_t H, int64_t F, char* ws, const ibert_layer_workspace_layout& lo)
     {
-        ibert_gemm_desc d;
-        std::memset(&d, 0, sizeof d);
-        d.M = (int32_t)T; d.batch_outer = d.batch_inner = 1; d.per_channel = 1;
         auto plan = [&](int64_t N, int64_t K, int32_t dtype, const void* in, const int8_t* wt, const int32_t* bias, const int32_t* m,
                         const int32_t* s, const void* res, const void* out, bool gelu) {
-            d.N = (int32_t)N; d.K = (int32_t)K;
-            d.lda = d.ldw = K; d.ldc = d.ldr = N;
-            d.out_dtype = dtype;
-            return plan_gemm(d, (const int8_t*)in, wt, bias, m, s, (const int8_t*)res, out, gelu);
+            return plan_gemm(projection(T, N, K, dtype, 127), (const int8_t*)in, wt, bias, m, s, (const int8_t*)res, out, gelu);
         };
         o = plan(H, H, IBERT_I16, ws + lo.ctx, w.w_o, w.b_o, w.m_o, w.s_o, x, ws + lo.r1, false);
         up = plan(F, H, IBERT_I8, ws + lo.h1, w.w_1, w.b_1, w.m_1, w.s_1, nullptr, ws + lo.g, true);
@@ -233,9 +238,7 @@ static int run_layer(const ibert_layer_weights& w, const LayerPlan* plan, const 
     } while (0)
 
     // 1: QKV projection, one GEMM with N = 3H
-    std::memset(&d, 0, sizeof d);
-    d.M = (int32_t)T; d.N = (int32_t)(3 * H); d.K = (int32_t)H; d.batch_outer = d.batch_inner = 1;
-    d.lda = H; d.ldw = H; d.ldc = 3 * H; d.per_channel = 1; d.out_dtype = IBERT_I8; d.out_clamp = 127;
+    d = projection(T, 3 * H, H, IBERT_I8, 127);
     prof_before(stream);
     RUN_GEMM(x, w.w_qkv, w.b_qkv, w.m_qkv, w.s_qkv, nullptr, qkv);
     prof_after(stream, 1, 2.0 * T * 3 * H * H, gemm_bytes(T, 3 * H, H, 1, 1, false, true));
@@ -259,17 +262,13 @@ static int run_layer(const ibert_layer_weights& w, const LayerPlan* plan, const 
     if (rc) return rc;
 
     // 5: output projection + residual x, INT32 at the LayerNorm input scale
-    std::memset(&d, 0, sizeof d);
-    d.M = (int32_t)T; d.N = (int32_t)H; d.K = (int32_t)H; d.batch_outer = d.batch_inner = 1;
-    d.lda = H; d.ldw = H; d.ldc = H; d.ldr = H; d.per_channel = 1; d.out_dtype = IBERT_I32; d.out_clamp = 32767;
+    d = projection(T, H, H, IBERT_I32, 32767);
     d.residual_dy = q.res1_dy;
     // (+ 6: LayerNorm)
     RUN_GEMM_LN(5, ctx, w.w_o, w.b_o, w.m_o, w.s_o, x, r1, w.ln1_gamma_q, w.ln1_beta_q, q.ln1_shift, h1, 2.0 * T * H * H, H);
 
     // 7: FFN up-projection, INT32 at the GELU input scale
-    std::memset(&d, 0, sizeof d);
-    d.M = (int32_t)T; d.N = (int32_t)F; d.K = (int32_t)H; d.batch_outer = d.batch_inner = 1;
-    d.lda = H; d.ldw = H; d.ldc = F; d.per_channel = 1; d.out_dtype = IBERT_I32; d.out_clamp = q.gelu.q_max;
+    d = projection(T, F, H, IBERT_I32, q.gelu.q_max);
     bool fused78 = false;
     if (fuse_gelu) {
         // 7+8 in one kernel when a tile fits: f1 is then never written
@@ -299,9 +298,7 @@ static int run_layer(const ibert_layer_weights& w, const LayerPlan* plan, const 
     }
 
     // 9: FFN down-projection + residual h1
-    std::memset(&d, 0, sizeof d);
-    d.M = (int32_t)T; d.N = (int32_t)H; d.K = (int32_t)F; d.batch_outer = d.batch_inner = 1;
-    d.lda = F; d.ldw = F; d.ldc = H; d.ldr = H; d.per_channel = 1; d.out_dtype = IBERT_I32; d.out_clamp = 32767;
+    d = projection(T, H, F, IBERT_I32, 32767);
     d.residual_dy = q.res2_dy;
     // (+ 10: LayerNorm)
     RUN_GEMM_LN(9, g, w.w_2, w.b_2, w.m_2, w.s_2, h1, r2, w.ln2_gamma_q, w.ln2_beta_q, q.ln2_shift, y, 2.0 * T * H * F, F);

@@ -358,3 +358,57 @@ def test_shift_and_subtract_square_root_recipe_is_exact():
         res = np.where(ge, (res >> np.uint64(1)) + bit, res >> np.uint64(1))
         bit >>= np.uint64(2)
     _check_floor_sqrt(n0, res)
+
+
+# ------------------------------------------------------------------------------------------- weights read ahead
+def _weight_plan(M, N, K, kind):
+    d = B.GemmDesc()
+    for k, v in dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K, ldw=K, ldc=N, ldr=N, per_channel=1,
+                     out_dtype=B.I16 if kind == "i16res" else B.I8, out_clamp=127).items():
+        setattr(d, k, v)
+    plan, readers, ahead = (C.c_int32 * 3)(), np.zeros(N, np.uint8), np.zeros((8, N * K // 1024), np.uint8)
+    rc = B.lib().ibert_gemm_weight_plan(C.byref(d), kind == "gelu", plan, readers.ctypes.data, ahead.ctypes.data)
+    assert rc == 0, (M, N, K, kind, rc)                       # (a read past the end of W is an error)
+    return list(plan), readers, ahead
+
+
+def _check_weight_plan(M, N, K, kind):
+    (config, rows, xs), readers, ahead = _weight_plan(M, N, K, kind)
+    case = (M, N, K, kind, config, rows, xs)
+    assert readers.all() and N % rows == 0, case
+    assert ahead.max() == 1 and ahead.any(axis=0).all(), case            # all of W, nothing twice by one XCD
+    by_kb = np.bitwise_or.reduce(ahead << np.arange(8, dtype=np.uint8)[:, None], axis=0)
+    if xs < 2:
+        assert (ahead.sum(axis=0) == 1).all(), case                      # once, by any XCD
+        return config
+    # every XCD that multiplies a row has read each KB of it ahead, and no more XCDs than share it
+    assert (ahead.sum(axis=0) == 8 >> xs).all(), case
+    at = np.arange(N * K // 1024, dtype=np.int64) * 1024
+    for row in (at // K, (at + 1023) // K):
+        assert not (readers[row] & ~by_kb).any(), case
+    return config
+
+
+@pytest.mark.parametrize("H,F", [(128, 640), (256, 1024), (384, 640), (512, 2048), (768, 3072), (1024, 4096), (1024, 1152)])
+def test_weights_read_ahead_are_those_the_kernels_read(H, F):
+    # the plan an encoder makes before the attention against the dealing of tiles of the kernels themselves, and what the attention reads
+    # by it, over token counts from one to the largest
+    seen = set()
+    for M in [1, 2, 16, 17, 61, 128, 129, 300, 488, 777, 1000, 1024, 2048, 2741, 4096, 4100, 8192, 15311, 16384, 32768]:
+        for N, K, kind in ((3 * H, H, "i8"), (H, H, "i16res"), (F, H, "gelu"), (H, F, "i16res")):
+            seen.add(_check_weight_plan(M, N, K, kind))
+    assert len(seen) > 4, seen
+
+
+def test_weights_read_ahead_for_every_tile():
+    # the same for tiles that the choice takes rarely, forced
+    try:
+        for config, bn in [(25, 16), (26, 32), (27, 32), (28, 64), (29, 96), (30, 64), (15, 32), (3, 64), (17, 96), (18, 96), (19, 128), (21, 96),
+                           (22, 128), (7, 128), (9, 96), (13, 192), (14, 128), (23, 256), (24, 192)]:
+            B.lib().ibert_gemm_config_override(config)
+            for M in [1, 100, 256, 512, 1025, 4096, 9000]:
+                for tiles in (1, 2, 4, 7, 8, 12, 16):
+                    if tiles * bn * 256 % 1024 == 0:
+                        assert _check_weight_plan(M, tiles * bn, 256, "i8") == config
+    finally:
+        B.lib().ibert_gemm_config_override(-1)
