@@ -131,9 +131,9 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
 #pragma unroll
         for (int r = 0; r < ReadAhead::MOST; ++r) {
             const auto& q = ga->ahead.part[r];
-            const int total = ReadAhead::count(x, q.kb, q.blocks, q.xs);
+            const int s = ReadAhead::share(x, q.xs), total = ReadAhead::count(s, q.kb, q.blocks, q.xs);
             for (int k = first * 4 + wave; k < total; k += 4 * wgs) {
-                const int8_t* src = q.p + ReadAhead::at(x, k, q.kb, q.kb_magic, q.xs) * 1024;
+                const int8_t* src = q.p + ReadAhead::at(s, k, q.kb, q.kb_magic, q.xs) * 1024;
                 asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                              :: "s"(dst), "v"((uint32_t)lane * 16u), "s"(src) : "memory", "m0");
             }

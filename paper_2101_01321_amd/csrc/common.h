@@ -152,8 +152,12 @@ struct GemmPlan {
 };
 // Weights that the kernels after a launch will read and that it may bring into the L2 of the XCD that reads them: clean lines stay
 // in an XCD's L2 from one kernel to the next (2 MB an XCD read again by the next kernel: 2.5 us, from HBM 5.0).
+// Not a matrix larger than the L2s of the eight XCDs together: it has left them before it is used, and the launch waits for it.  Forward,
+// us, 24 (12 from FFN 32768 on) layers of hidden 1024, without W_1 and W_2 / with them, 128 tokens and 4096: FFN 16384 (16 MB each)
+// 1057 / 1023, 4677 / 4488; 32768 (32 MB) 676 / 698, 4000 / 3800; 65536 (64 MB) 1080 / 1232, 7540 / 7650.
 struct ReadAhead {
     static constexpr int MOST = 4;
+    static constexpr int64_t MOST_BYTES = 32 << 20;      // of a matrix
     struct Part {
         const int8_t* p;
         int32_t kb, blocks, xs;        // KB of a row block; row blocks; see GemmPlan
@@ -162,7 +166,7 @@ struct ReadAhead {
     int n = 0;
     void add(const int8_t* w, int64_t N, int64_t K, const GemmPlan& plan)
     {
-        if (n == MOST || plan.rows < 1 || !aligned(w, 16)) return;      // (the plan may be of another layer's weights)
+        if (n == MOST || plan.rows < 1 || !aligned(w, 16) || N * K > MOST_BYTES) return;      // (the plan may be of another layer's weights)
         // Where half of the XCDs or more read the same rows, so many copies would cost more than they bring: each KB once then, by any
         // XCD, which brings it as near as the memory-side cache and one L2.  us, Base b32 (W_o and W_2 go to all XCDs): 909 without,
         // 903 with eight copies, 852 with one; Base b1 (an eighth for each): 327 without, 336 by any XCD, 316 by the one that reads.
@@ -174,15 +178,16 @@ struct ReadAhead {
     {
         for (Part& q : part) q = Part{nullptr, 1, 0, 0, 0};
     }
-    // KB of a part that XCD x reads, and the k-th of them, counted from the part's first.
-    static __host__ __device__ __forceinline__ int32_t count(int x, int32_t kb, int32_t blocks, int32_t xs)
+    // The share of a part that XCD x reads, its KB, and the k-th of them, counted from the part's first.
+    static __host__ __device__ __forceinline__ int32_t share(int x, int32_t xs) { return x & ((1 << xs) - 1); }
+    static __host__ __device__ __forceinline__ int32_t count(int s, int32_t kb, int32_t blocks, int32_t xs)
     {
-        return ((blocks - (x & ((1 << xs) - 1)) + (1 << xs) - 1) >> xs) * kb;
+        return ((blocks - s + (1 << xs) - 1) >> xs) * kb;
     }
-    static __host__ __device__ __forceinline__ int64_t at(int x, int32_t k, int32_t kb, uint32_t kb_magic, int32_t xs)
+    static __host__ __device__ __forceinline__ int64_t at(int s, int32_t k, int32_t kb, uint32_t kb_magic, int32_t xs)
     {
         const int j = udiv_fix(k, kb, kb_magic);
-        return (int64_t)((j << xs) + (x & ((1 << xs) - 1))) * kb + (k - j * kb);
+        return (int64_t)((j << xs) + s) * kb + (k - j * kb);
     }
 };
 

@@ -397,12 +397,14 @@ static int weight_plan(const ibert_gemm_desc& d, bool gelu, int32_t out[3], uint
     const int64_t kbs = (int64_t)d.N * d.K / 1024;
     for (int i = 0; i < r.n; ++i) {
         const auto& q = r.part[i];
-        for (int x = 0; x < 8; ++x)
-            for (int32_t k = 0; k < ReadAhead::count(x, q.kb, q.blocks, q.xs); ++k) {
-                const int64_t at = ReadAhead::at(x, k, q.kb, q.kb_magic, q.xs);
+        for (int x = 0; x < 8; ++x) {
+            const int s = ReadAhead::share(x, q.xs);
+            for (int32_t k = 0; k < ReadAhead::count(s, q.kb, q.blocks, q.xs); ++k) {
+                const int64_t at = ReadAhead::at(s, k, q.kb, q.kb_magic, q.xs);
                 if (at < 0 || at >= kbs) return IBERT_ERR_SHAPE;
                 ++ahead[x * kbs + at];
             }
+        }
     }
     return IBERT_OK;
 }

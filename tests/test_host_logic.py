@@ -400,6 +400,15 @@ def test_weights_read_ahead_are_those_the_kernels_read(H, F):
     assert len(seen) > 4, seen
 
 
+@pytest.mark.parametrize("N,K,kind,read", [(32768, 1024, "gelu", 1), (32768 + 128, 1024, "gelu", 0), (1024, 32768, "i16res", 1),
+                                           (1024, 32768 + 128, "i16res", 0), (1024, 131072, "i16res", 0)])
+def test_weights_read_ahead_are_bounded(N, K, kind, read):
+    # matrices of up to 32 MB are read ahead, larger ones are not
+    for M in (1, 128, 4096):
+        _, _, ahead = _weight_plan(M, N, K, kind)
+        assert ahead.any(axis=0).all() if read else not ahead.any(), (M, N, K)
+
+
 def test_weights_read_ahead_for_every_tile():
     # the same for tiles that the choice takes rarely, forced
     try:
