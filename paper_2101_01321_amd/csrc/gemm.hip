@@ -191,15 +191,21 @@ static uint32_t blocks_of(int32_t n, int b) { return ((uint32_t)n + (uint32_t)b 
 // again[] the extra cost of a tile that has to wait for a place (0 where share is 1).  (Tiles of gemm_few.h: n from its own
 // dealing of tiles to XCDs, and a share that depends on K.)  The coefficients are least-squares fits to 640 problems timed
 // on MI355X (K 128 to 8192, N 128 to 4096, 1 to 32768 rows, W changing from call to call), for 16-bit outputs with a
-// residual (32-bit ones use them too), INT8 outputs and GELU outputs; the fits are within 4 to 13 % (r.m.s.), and the
-// configuration with the least t takes 0.5 % longer on average than the best of all would, at worst 22 %.  Thresholds on tile
-// counts, which this replaces, took 16 % longer with the same configurations.  Some lines they could not draw: [4096,1024] x
-// K 4096 to 4096 rows more, 52 -> 40 us at 8192 rows; 2741 rows of [768] x K 3072 25.1 -> 14.5 us (the last tile row is
-// ragged); a second round of large tiles that would be nearly empty, [5120,1024] x K 1024 19.7 -> 13.3 us.
-// (GELU on the tiles with loaders, from 13 problems with up to 2741 rows, and the persistent tiles, from 240 with the INT8
-// 256x192 tile as the yardstick, were fitted later.  The wavefronts that only multiply have nothing to do until the first tiles
-// arrive and build the GELU table then: [488,3072] x K 768 8.4 -> 7.5 us, [1024,4096] x K 1024 12.0 -> 9.4, which are
-// one tile for at most every unit; 64x96 and 64x128 tiles with GELU were slower than these wherever they were tried.)
+// residual (32-bit ones use them too), INT8 outputs and GELU outputs; the fits were within 4 to 13 % (r.m.s.).  On problems that
+// no fit has seen (N 96 to 4352, K 128 to 4096, 1 to 32768 rows) the choice by the present table takes 0.5 % longer on average
+// than the best of all configurations with 145 without GELU, at worst 16 % ([884,1664] x K 256 + residual 6.4 against 5.5 us), and
+// 0.3 % with 260 with GELU, at worst 12 %.  Thresholds on tile counts, which the table replaced, took 16 % longer on average.
+// Some lines they could not draw: [4096,1024] x K 4096 to 4096 rows more, 52 -> 40 us at 8192 rows; 2741 rows of [768] x K 3072
+// 25.1 -> 14.5 us (the last tile row is ragged); a second round of large tiles that would be nearly empty, [5120,1024] x K 1024
+// 19.7 -> 13.3 us.
+// (Later came the persistent tiles, fitted to 240 problems with the INT8 256x192 tile as the yardstick, and GELU on the tiles with
+// loaders, to 13 of up to 2741 rows.  Lane-transposed stores had made GELU on the other direct-to-LDS tiles up to 20 % faster than
+// their estimates, so that the tiles with loaders were taken where these are ahead, us: [5248,3968] x K 2304 83.0 / 69.5, [4009,768] x
+// K 128 5.9 / 5.4.  128x128, 128x96 and 256x128 with GELU are least-squares fits to 335 problems since; one more tile of 128x128 with
+// loaders costs what these show, and 256x192 starts as it does at K 128.
+// On the tiles with loaders the wavefronts that only multiply have nothing to do until the first tiles arrive and build the GELU table
+// then: [488,3072] x K 768 8.4 -> 7.5 us, [1024,4096] x K 1024 12.0 -> 9.4, which are one tile for at most every unit; 64x96 and 64x128
+// tiles with GELU were slower than these wherever they were tried.)
 struct TileCost {
     int config, share;                      // share 0: gemm_few.h
     struct { int first[2], more[2], again[2]; } kind[3];
@@ -219,11 +225,11 @@ static const TileCost kTileCost[] = {
     {18, 3, {{3525, 511, 1447, 72, 682, 329}, {3070, 557, 758, 56, 683, 435}, {0, 0, 0, 0, 0, 0}}},                 // 64x96
     {21, 1, {{5825, 320, 4836, 333, 0, 0}, {4587, 353, 3465, 353, 0, 0}, {5450, 353, 4050, 353, 0, 0}}},            // 128x96, with loaders
     {19, 3, {{3722, 557, 1848, 109, 0, 409}, {3329, 618, 916, 82, 254, 483}, {0, 0, 0, 0, 0, 0}}},                  // 64x128
-    {22, 1, {{6537, 376, 5539, 420, 0, 0}, {4967, 408, 3662, 420, 0, 0}, {5700, 408, 4450, 420, 0, 0}}},            // 128x128, with loaders
-    {7, 2, {{5451, 645, 5215, 637, 0, 0}, {3978, 690, 2886, 617, 0, 0}, {6445, 655, 5733, 630, 0, 0}}},             // 128x128
-    {9, 2, {{4894, 572, 2930, 70, 1293, 436}, {3579, 626, 1375, 102, 650, 459}, {5662, 625, 2550, 55, 1694, 526}}}, // 128x96
-    {14, 1, {{7647, 840, 9487, 865, 0, 0}, {5131, 882, 4119, 883, 0, 0}, {7561, 833, 6938, 815, 0, 0}}},            // 256x128
-    {13, 1, {{10461, 862, 13760, 999, 0, 0}, {6109, 963, 5826, 1068, 0, 0}, {9129, 952, 8517, 1062, 0, 0}}},        // 256x192
+    {22, 1, {{6537, 376, 5539, 420, 0, 0}, {4967, 408, 3662, 420, 0, 0}, {5700, 408, 4450, 560, 0, 0}}},            // 128x128, with loaders
+    {7, 2, {{5451, 645, 5215, 637, 0, 0}, {3978, 690, 2886, 617, 0, 0}, {5042, 844, 3592, 633, 0, 0}}},             // 128x128
+    {9, 2, {{4894, 572, 2930, 70, 1293, 436}, {3579, 626, 1375, 102, 650, 459}, {4535, 744, 1142, 158, 1331, 462}}}, // 128x96
+    {14, 1, {{7647, 840, 9487, 865, 0, 0}, {5131, 882, 4119, 883, 0, 0}, {6091, 1091, 5468, 922, 0, 0}}},            // 256x128
+    {13, 1, {{10461, 862, 13760, 999, 0, 0}, {6109, 963, 5826, 1068, 0, 0}, {8700, 952, 8517, 1062, 0, 0}}},        // 256x192
     {24, 1, {{9960, 1023, 8159, 1144, 0, 0}, {5910, 966, 3317, 1064, 0, 0}, {8250, 967, 4273, 1092, 0, 0}}},        // 256x192, persistent
     {23, 1, {{11880, 1206, 7950, 1383, 0, 0}, {7107, 1233, 4365, 1317, 0, 0}, {9420, 1269, 5330, 1342, 0, 0}}},     // 256x256, persistent
 };
