@@ -25,7 +25,9 @@
 //     6000 cycles (INT8), 9000 (GELU) or 13000 (INT16 + residual).
 //   * Measured against one workgroup per tile, us, W cold, when it came: [32768,4096] x K 1024 with GELU 212 -> 142, [15311,3072] x K 768
 //     with GELU 115 -> 45 (any M: tiles may be ragged), [32768,1024] x K 1024 + residual 62 -> 44.
-//   * Everything must fit the registers: with one spill the loop takes 1.6 times as long, even where no scratch is touched.
+//   * The vector registers must hold everything: with one of them spilled the loop takes 1.6 times as long, even where no scratch is
+//     touched.  None is (217 of 256x192, 253 of 256x256).  Scalars are kept in lanes of a vector register where they do not fit: 20 with
+//     GELU, 9 with INT16 and 2 with INT8 outputs on 256x192, 11, 2 and 0 on 256x256.
 //   * Rows past M (any M is allowed) are computed from zeros and not stored: operands, residual and output are addressed as buffers
 //     that end with the last row.
 #pragma once

@@ -248,8 +248,9 @@ static int run_layer(const ibert_layer_weights& w, const LayerPlan* plan, const 
     // MatMuls up to the next attention, which come from HBM otherwise -- a model's weights are more than the caches hold, or other
     // work has been there since (MatMul on weights from HBM against weights in L2, us: [128,768] x K 3072 5.2 / 4.1, [4096,768] x
     // K 3072 17.6 / 14.5, [1024,3072] x K 1024 8.4 / 7.4).  Forward, us, without and with: Base b1 330 / 315, b8 s61 449 / 433, Large b4 s256
-    // 1236 / 1182, Base b32 900 / 849, b61 s251 2243 / 2132, 32768 tokens the same.  (A layer called by itself, in a program that cycles
-    // through few of them, finds its weights in the caches: 177 tokens 27.7 without, 27.9 with.)
+    // 1236 / 1182, Base b32 900 / 849, b61 s251 2243 / 2132, 32768 tokens the same.  A program that runs one Base model and nothing else
+    // finds its 85 MB in the memory-side cache from forward to forward and gains little: b1 314 / 312, b8 s61 413 / 409, b32 837 / 834.  (So
+    // does a layer called by itself, in a program that cycles through few of them: 177 tokens 27.7 without, 27.9 with.)
     ReadAhead ahead;
     if (plan && fuse_attention && fuse_gelu && half) {
         ahead.add(w.w_o, H, H, plan->o);
