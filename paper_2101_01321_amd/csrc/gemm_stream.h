@@ -2,7 +2,7 @@
 // Arithmetic and epilogue are those of gemm_kernel.h (W as [N,K], bias, dyadic requantization, optional residual or
 // GELU, clamp); what differs is how the work is laid out in time.
 //
-//   * One workgroup of eight wavefronts (2 x 4) per CU owns a BM x BN tile at a time and walks over several tiles.
+//   * One workgroup of eight wavefronts (2 x 4; 4 x 2 on 192 columns) per CU owns a BM x BN tile at a time and walks over several tiles.
 //   * A K step is 128 bytes (whole cache lines: requests of 64-byte row pieces run at half the rate, 17 against 28-32 TB/s
 //     measured chip-wide).  LDS holds two steps.  A step is four phases, one per quadrant of the wavefront's tile, over its whole K:
 //         1: A top x W first   (reads W second)      3: A bottom x W first   (reads A top of the next step)
@@ -21,19 +21,46 @@
 //     buffers, with the step as the scalar offset, in place of 64-bit addresses with a row minimum and a test for every request: a third
 //     of the scalar instructions (1.24e7 -> 4.1e6 for 8.4e6 MFMAs), us: [32768,1024] x K 4096 INT8 117.6 -> 108.9, [32768,4096] x
 //     K 1024 + GELU 150.6 -> 141.5, 256x192: [32768,768] x K 3072 INT8 77.3 -> 67.7, INT16 83.5 -> 79.0, [4096,3072] x K 768 + GELU 17.9 -> 17.1.
-//     (Requests of the two wavefronts of a SIMD half a slot apart, behind a branch each, gave all of it back.)  An epilogue is
-//     6000 cycles (INT8), 9000 (GELU) or 13000 (INT16 + residual).
+//     (Requests of the two wavefronts of a SIMD half a slot apart, behind a branch each, gave all of it back.)
+//   * With many rows it is power that bounds it: the same launches on zeros take the same cycles and 14 to 24 % less time (2.2 GHz
+//     against 1.75 to 1.95; [32768,3072] x K 1024 105 -> 80 us).  A loop of nothing but the step's MFMAs sustains 4.05 POP/s on random
+//     operands, with its LDS reads 3.5, with its requests 3.0 -- 1425 ns a step, about what a step takes here.
+//   * An epilogue is what the address unit, then the ALU, make of it.  Rows leave and residuals come with neighbouring lanes on neighbouring
+//     bytes, through LDS (see `turn`), one unit of rows at a time while the next is being made; the MFMA's first operand are the rows of
+//     A, so that a lane has the same few channels for all its tokens and their constants are made once.  Cycles of a launch, thousands, with
+//     lane swaps in place of LDS and stores that left together at the end / as it is: [32768,1024] x K 1024 INT16 + residual 84.0 / 73.5,
+//     [32768,768] x K 768 63 / 56.5, x K 3072 133 / 125, [32768,3072] x K 1024 INT8 175 / 166, [32768,4096] x K 1024 + GELU 250 / 237; us: 45.3 /
+//     41.9, 35.6 / 32.0, 76.7 / 71.3, 104 / 101, 134 / 130.  Tried and not kept: the next tile's first operands held in registers over
+//     the epilogue, so that requests go on in its first half step (they queue behind the stores: 176 k -> 199 k cycles); a barrier at a tile's
+//     head in place of that (equal).
 //   * Measured against one workgroup per tile, us, W cold, when it came: [32768,4096] x K 1024 with GELU 212 -> 142, [15311,3072] x K 768
 //     with GELU 115 -> 45 (any M: tiles may be ragged), [32768,1024] x K 1024 + residual 62 -> 44.
 //   * The vector registers must hold everything: with one of them spilled the loop takes 1.6 times as long, even where no scratch is
-//     touched.  None is (217 of 256x192, 253 of 256x256).  Scalars are kept in lanes of a vector register where they do not fit: 20 with
-//     GELU, 9 with INT16 and 2 with INT8 outputs on 256x192, 11, 2 and 0 on 256x256.
+//     touched.  None is (225 at most of 256x192, 239 of 256x256): what an epilogue derives from the lane's index is made there.
 //   * Rows past M (any M is allowed) are computed from zeros and not stored: operands, residual and output are addressed as buffers
 //     that end with the last row.
 #pragma once
 #include "gemm_kernel.h"
 
 namespace ibert {
+
+// A residual's requantization in 32 bits: DY(r) = (r m + rnd) >> s for every INT8 r, |m| < 2^23 -- the multiplier without its low eight
+// bits, where that changes none of the 256 values (ok).
+struct ResShort {
+    int32_t m, rnd, s, ok;
+};
+inline ResShort residual_short(const GemmArgs& g)
+{
+    if (!g.R) return ResShort{0, 0, 0, 1};
+    const int32_t s = g.res_s - 8;
+    if (s < 1 || s > 30) return ResShort{0, 0, 0, 0};
+    const int64_t m = ((int64_t)g.res_m + 128) >> 8;
+    if (m <= -(1 << 23) || m >= (1 << 23)) return ResShort{0, 0, 0, 0};
+    const int64_t rnd = (int64_t)1 << (s - 1);
+    int bad = 0;
+    for (int r = -128; r < 128; ++r) bad |= ((r * m + rnd) >> s) != (((int64_t)r * g.res_m + g.res_rnd) >> g.res_s);
+    return ResShort{(int32_t)m, (int32_t)rnd, s, !bad};
+}
 
 struct StreamArgs {
     const int8_t* A;
@@ -53,6 +80,7 @@ struct StreamArgs {
     int32_t out_clamp;
     int32_t res_m, res_s, res_fast;
     int64_t res_rnd;
+    ResShort res_short;        // see residual_short
     int32_t k_fast;            // K * 127^2 < 2^30
     int32_t gelu_fast, gelu_lut_lo, gelu_lut_n;
     GeluConst gelu;
@@ -80,9 +108,27 @@ template <int BM, int BN, int NW, bool OUT_I8, bool GELU>
 struct StreamLayout {
     static constexpr int STAGE = (BM + BN) * 128;
     static constexpr int PAR = 2 * STAGE;                          // two buffers of 3 x BN constants
-    static constexpr int LUT = PAR + 2 * 3 * BN * 4;
+    static constexpr int TURN = PAR + 2 * 3 * BN * 4;              // rows on their way out, see `turn`
+    static constexpr int TURN_WAVE = BN % 128 == 0 ? (OUT_I8 ? 1280 : 2560) : 3584;     // bytes per wavefront
+    static constexpr int LUT = TURN + NW * TURN_WAVE;
     static constexpr int ROOM = 163840 - LUT;                      // for the GELU table
 };
+
+// The channel of its wavefront's tile that lane r of 16 holds in block column i.  An MFMA block is 16 rows of W, and which ones is free: chosen
+// so, a lane's channels are neighbours over the block columns: four in the first 64, two in 32 further ones.
+template <int FN>
+__host__ __device__ constexpr int lane_channel(int i, int r)
+{
+    return i < 4 ? 4 * r + i : 64 + 2 * r + (i - 4);
+}
+
+// Two values as 16 bits each, saturated, and not below `low`.
+__device__ __forceinline__ uint32_t pack2_i16_above(int32_t a, int32_t b, int16_t low)
+{
+    typedef short v2s __attribute__((ext_vector_type(2)));
+    const v2s v = __builtin_elementwise_max(__builtin_amdgcn_cvt_pk_i16(a, b), v2s{low, low});
+    return __builtin_bit_cast(uint32_t, v);
+}
 
 // OUT_I8: INT8 output (no residual), with GELU if GELU; else INT16 output with or without residual.
 template <int BM, int BN, int NW, bool OUT_I8, bool GELU>
@@ -90,17 +136,17 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
 {
     using SL = StreamLayout<BM, BN, NW, OUT_I8, GELU>;
     static_assert(!GELU || OUT_I8, "the GELU epilogue writes INT8");
-    constexpr int NT = 64 * NW, WC = NW / 2;                       // wavefronts in two rows of WC
-    constexpr int WM = BM / 2, WN = BN / WC, FM = WM / 16, FN = WN / 16;
-    constexpr int FMH = FM / 2, FN0 = (FN + 1) / 2, FN1 = FN / 2;  // MFMA blocks: A top and A bottom, W first and W second
+    constexpr int NT = 64 * NW, WR = BN % 128 == 0 ? 2 : 4, WC = NW / WR;     // wavefronts in WR rows of WC
+    constexpr int WM = BM / WR, WN = BN / WC, FM = WM / 16, FN = WN / 16;
+    constexpr int FMH = FM / 2, FN0 = FN / 4 * 2 + FN % 4, FN1 = FN - FN0;    // MFMA blocks: A top and A bottom, W first and W second
     // 1 KB requests (8 rows x 128 bytes) per wavefront and region: A top, A bottom, W first, W second
-    constexpr int QA = FMH * 2 * 2 / NW, QW0 = FN0 * 2 * WC / NW, QW1 = FN1 * 2 * WC / NW;
+    constexpr int QA = FMH * 2 * WR / NW, QW0 = FN0 * 2 * WC / NW, QW1 = FN1 * 2 * WC / NW;
     constexpr int N0 = QA + QW0, N1 = QW1 + QA;                    // requested together: group 0 (A top, W first), group 1
-    static_assert(FM % 2 == 0 && FN >= 2 && FN <= 4 && FMH * 4 % NW == 0 && FN0 * 2 * WC % NW == 0 && FN1 * 2 * WC % NW == 0, "tile shape");
+    static_assert(FM % 2 == 0 && (FN == 4 || FN == 6) && FMH * 2 * WR % NW == 0 && FN0 * 2 * WC % NW == 0 && FN1 * 2 * WC % NW == 0, "tile shape");
     extern __shared__ __attribute__((aligned(16))) int8_t lds[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm0 = (wave & 1) * WM, wn0 = (wave >> 1) * WN;
+    const int wm0 = wave % WR * WM, wn0 = wave / WR * WN;
     const int frow = lane & 15, fch = lane >> 4;
 
     // ---- the workgroup's tiles ------------------------------------------------------------------
@@ -131,12 +177,18 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
     auto first_row = [&](int nb, int rows) { return wave / nb * rows + wave % nb * 8; };
     constexpr int SA = NW / (FMH * 2) * WM, SW0 = NW / (FN0 * 2) * WN, SW1 = NW / (FN1 * 2) * WN;     // rows from request to request
     const int pa = first_row(FMH * 2, WM), pw0 = first_row(FN0 * 2, WN), pw1 = first_row(FN1 * 2, WN) + FN0 * 16;
+    // Rows of W go into LDS in the order that gives every lane neighbouring channels in the end: row 16 i + q of a wavefront's
+    // tile there is its channel lane_channel(i, q).
+    auto w_row = [&](int p) {                                      // tile row of W that belongs in row p of the stage's W part
+        const int w = p / WN, r = p - w * WN, q = (r & 8) + r8;
+        return w * WN + lane_channel<FN>(r >> 4, q);
+    };
     uint32_t va[2][QA];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int q = 0; q < QA; ++q) va[h][q] = (uint32_t)(pa + h * (WM / 2) + q * SA + r8) * (uint32_t)g.lda + chunk;
-    const uint32_t vw0 = (uint32_t)(pw0 + r8) * (uint32_t)g.ldw + chunk, vw1 = (uint32_t)(pw1 + r8) * (uint32_t)g.ldw + chunk;
+    const uint32_t vw0 = (uint32_t)w_row(pw0) * (uint32_t)g.ldw + chunk, vw1 = (uint32_t)w_row(pw1) * (uint32_t)g.ldw + chunk;
     const uint32_t sw0 = (uint32_t)(SW0 * g.ldw), sw1 = (uint32_t)(SW1 * g.ldw);
     static_assert(QW0 <= 2 && QW1 <= 2, "scalar offsets of the W requests");
     v4i da, dw;                                                    // request stream: descriptors of its tile's operands
@@ -204,8 +256,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
                     }
             } else {
                 int32_t* p = reinterpret_cast<int32_t*>(lds + SL::PAR + par_buf * 3 * BN * 4) + a * BN;
-                const int32_t fill = a == 0 ? 0 : (a == 1 ? g.dy_m : g.dy_s);
-                for (int c = tid; c < BN; c += NT) p[c] = fill;
+                int32_t fill = a == 0 ? 0 : (a == 1 ? g.dy_m : g.dy_s), c0 = tid;
+                asm volatile("" : "+s"(fill), "+v"(c0));           // (made here each time: no register for them in the loop)
+                for (int c = c0; c < BN; c += NT) p[c] = fill;
             }
         }
     };
@@ -269,7 +322,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
                 for (int j = 0; j < FMH; ++j) {
                     between((sl * NI + i) * FMH + j);
                     __builtin_amdgcn_sched_barrier(0);
-                    acc[i0 + i][j0 + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xw[i][sl], xa[j][sl], acc[i0 + i][j0 + j], 0, 0, 0);
+                    acc[i0 + i][j0 + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa[j][sl], xw[i][sl], acc[i0 + i][j0 + j], 0, 0, 0);
                 }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -324,7 +377,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
     };
 
     bool first = true;
-    const int8_t* const lut = lds + SL::LUT;
     const uint32_t lut_lds = lds0 + (uint32_t)SL::LUT;
     using R1 = std::integral_constant<int, 1>;
     using R2 = std::integral_constant<int, 2>;
@@ -342,7 +394,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         for (uint32_t kt = 128; kt < kbytes; kt += 128) step(R1{}, true);
 
         // ---- epilogue ---------------------------------------------------------------------------
-        // acc[i][j][e] = C[m0 + wm0 + 16 j + frow][n0 + wn0 + 16 i + 4 fch + e]
+        // acc[i][j][e] = C[m0 + wm0 + 16 j + 4 u + e][n0 + wn0 + lane_channel(i, r16)]
+        // (the lane's own index again: what follows from it is made here and not kept in registers through the loop)
+        int el = lane;
+        asm volatile("" : "+v"(el));
+        const int r16 = el & 15, u = el >> 4;
         const int32_t* par = reinterpret_cast<const int32_t*>(lds + SL::PAR + par_buf * 3 * BN * 4);
         // (what only the epilogue needs of the arguments is fetched here: kept in scalar registers through the loop it
         // would spill them)
@@ -356,170 +412,213 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         const int last = ga->M - 1 - m0;
         // Output and residual are buffers that end with the last row: lanes past it load zeros and store nothing.
         const int rows = last < BM ? last : BM - 1;                // (whole rows of them before the last one's BN columns)
-        const uint32_t row0 = (uint32_t)(wm0 + frow);
-        // Residual: 16 bytes of a row per lane, then the same transposition as for the stores (an involution) hands
-        // every lane the four channels it holds accumulators of.
+        // Residual: the lane's own channels, as the stores have them.
         typedef unsigned v2u __attribute__((ext_vector_type(2)));
+        typedef unsigned v3u __attribute__((ext_vector_type(3)));
         typedef unsigned v4u __attribute__((ext_vector_type(4)));
-        auto transpose4 = [](uint32_t& r0, uint32_t& r1, uint32_t& r2, uint32_t& r3) {
-            v2u t = __builtin_amdgcn_permlane32_swap(r0, r2, false, false); r0 = t.x; r2 = t.y;
-            t = __builtin_amdgcn_permlane32_swap(r1, r3, false, false); r1 = t.x; r3 = t.y;
-            t = __builtin_amdgcn_permlane16_swap(r0, r1, false, false); r0 = t.x; r1 = t.y;
-            t = __builtin_amdgcn_permlane16_swap(r2, r3, false, false); r2 = t.x; r3 = t.y;
-        };
         const bool has_res = !OUT_I8 && ga->R != nullptr;
-        constexpr int JH = OUT_I8 ? FM : FM / 2;                   // rows finished together, see below
-        v4i rt[2][OUT_I8 ? 1 : JH];
-        auto load_residual = [&](auto half_tag) {
-            constexpr int H = decltype(half_tag)::value;
+        constexpr uint32_t ES = OUT_I8 ? 1 : 2;
+        // Rows between lanes and memory: 16 bytes a lane, neighbouring lanes on neighbouring bytes.  (An instruction whose neighbouring lanes
+        // are in different rows takes the address unit 3.3 (stores) to 4.5 times as long: 45 against 14 cycles for 1 KB to L2, 95 against
+        // 20 from it.)  A unit of 16 or 32 rows goes through the wavefront's own part of LDS, whose instructions are executed in order.
+        // CP: pieces of 16 bytes in a row of the wavefront's columns; PITCH: bytes of a row there, such that the four rows of an
+        // access by token (16 lanes each) fall into different banks; lane l moves pieces 64 k + l of a unit, k = 0 .. MV - 1.
+        int8_t* const turn = lds + SL::TURN + wave * SL::TURN_WAVE;
+        struct Rows {
+            int cp, pitch, unit, mv;                               // unit: rows of blocks in it
+        };
+        constexpr Rows RO = OUT_I8 ? (FN == 4 ? Rows{4, 80, 1, 1} : Rows{6, 112, 2, 3}) : (FN == 4 ? Rows{8, 160, 1, 2} : Rows{12, 224, 1, 3});
+        constexpr Rows RR = FN == 4 ? Rows{4, 80, 1, 1} : Rows{6, 112, 2, 3};          // residual
+        static_assert(16 * RO.unit * RO.pitch <= SL::TURN_WAVE && (OUT_I8 || 16 * RR.unit * RR.pitch <= SL::TURN_WAVE), "place to turn rows");
+        static_assert(16 * RO.unit * RO.cp == 64 * RO.mv && FM % RO.unit == 0 && FM % RR.unit == 0, "whole units");
+        auto moved_row = [&](const Rows& r, int k) { return (64 * k + el) / r.cp; };
+        auto moved_at = [&](const Rows& r, int k) { return moved_row(r, k) * r.pitch + (64 * k + el) % r.cp * 16; };
+        auto fence = []() { __builtin_amdgcn_wave_barrier(); };
+        // Residual: units of rows AHEAD of their use, as they are moved.
+        constexpr int AHEAD = FN == 4 ? 4 : 2;
+        v4u rt[OUT_I8 ? 1 : AHEAD][RR.mv];
+        const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(ga->R + (int64_t)m0 * ga->ldr + n0), 0,
+                                                          has_res ? (int)((uint32_t)rows * (uint32_t)ga->ldr + BN) : 0, 0x00020000);
+        auto load_residual = [&](int unit) {
 #pragma unroll
-            for (int j = 0; j < (OUT_I8 ? 1 : JH); ++j) rt[H][j] = v4i{0, 0, 0, 0};
-            if (!OUT_I8 && has_res) {
-                const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(ga->R + (int64_t)m0 * ga->ldr + n0), 0,
-                                                                  (int)((uint32_t)rows * (uint32_t)ga->ldr + BN), 0x00020000);
-#pragma unroll
-                for (int j = 0; j < JH; ++j)
-                    rt[H][j] = __builtin_amdgcn_raw_buffer_load_b128(rb, (int)((row0 + 16 * (H * JH + j)) * (uint32_t)ga->ldr +
-                                                                               (uint32_t)(wn0 + (fch < FN ? fch : 0) * 16)), 0, 0);
-            }
+            for (int k = 0; k < RR.mv; ++k)
+                rt[OUT_I8 ? 0 : unit % AHEAD][k] = __builtin_amdgcn_raw_buffer_load_b128(
+                    rb, (wm0 + moved_row(RR, k)) * ga->ldr + wn0 + (64 * k + el) % RR.cp * 16, unit * RR.unit * 16 * ga->ldr, 0);
         };
         // Fast form: every shift in [33, 62], every |bias| and K * 127^2 below 2^30, the residual shift in [8, 62] (see gemm_kernel.h),
         // and a GELU table.
-        bool fast, fold;
+        bool fast, fold, tall;
         {
-            int badc = 0, bigs = 0;
+            int badc = 0, bigs = 0, lows = 0;
 #pragma unroll
             for (int c = 0; c < BN; c += 64) {
-                const int32_t pb = par[c + lane], ps = par[2 * BN + c + lane];
+                const int32_t pb = par[c + el], ps = par[2 * BN + c + el];
                 const int32_t ab = pb < 0 ? -pb : pb;
                 badc |= (ps < 33 || ps > 62 || ab < 0 || ab >= (1 << 30)) ? 1 : 0;
                 bigs |= ps > 43 ? 1 : 0;
+                lows |= ps < 40 ? 1 : 0;
             }
             fast = __builtin_amdgcn_ballot_w64(badc != 0) == 0 && ga->res_fast && ga->k_fast && (!GELU || ga->gelu_lut_n > 0);
             fold = __builtin_amdgcn_ballot_w64(bigs != 0) == 0;
+            tall = __builtin_amdgcn_ballot_w64(lows != 0) == 0;
         }
-        const int32_t lut_hi = ga->gelu_lut_n - 1;
+        const int32_t lut_lo = ga->gelu_lut_lo, lut_hi = ga->gelu_lut_n - 1;
         const int32_t clamp_lo = -ga->out_clamp, clamp_hi = ga->out_clamp;
-        constexpr uint32_t ES = OUT_I8 ? 1 : 2;
         const auto cb = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>(ga->C) + ((int64_t)m0 * ga->ldc + n0) * ES, 0,
                                                           (int)(((uint32_t)rows * (uint32_t)ga->ldc + BN) * ES), 0x00020000);
-        if (ga->path_word && m0 == 0 && n0 == 0 && tid == 0)
+        if (ga->path_word && m0 == 0 && n0 == 0 && wave + el == 0)
             *ga->path_word = !fast ? IBERT_EPILOGUE_STAGED : (GELU ? IBERT_EPILOGUE_DIRECT_GELU_TABLE : IBERT_EPILOGUE_DIRECT);
-        // INT16: the rows of the wavefront in two halves, which keeps the packed results (two dwords a group) and the residual
-        // within the registers that the operands have left; the second half's residual is asked for in the middle of the first.
-        auto finish_rows = [&](auto jh_tag) {
-            constexpr int jh = decltype(jh_tag)::value;
-            uint32_t pq[OUT_I8 ? 1 : 2][JH][4];                    // packed results by block column i
-#pragma unroll
-            for (int h = 0; h < (OUT_I8 ? 1 : 2); ++h)
-#pragma unroll
-                for (int j = 0; j < JH; ++j)
-#pragma unroll
-                    for (int i = FN; i < 4; ++i) pq[h][j][i] = 0u;
-            uint32_t rr[OUT_I8 ? 1 : JH][4];
+        if (fast) {
             if constexpr (!OUT_I8) {
 #pragma unroll
-                for (int j = 0; j < JH; ++j) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) rr[j][e] = (uint32_t)rt[jh / JH][j][e];
-                    transpose4(rr[j][0], rr[j][1], rr[j][2], rr[j][3]);
-                }
+                for (int unit = 0; unit < AHEAD && unit * RR.unit < FM; ++unit) load_residual(unit);
             }
-            auto put = [&](int i, int j, const int32_t (&o)[4]) {
-                if constexpr (OUT_I8) {
-                    pq[0][j][i] = pack4_perm(o[0], o[1], o[2], o[3]);
-                } else {
-                    pq[0][j][i] = __builtin_amdgcn_perm((uint32_t)o[1], (uint32_t)o[0], 0x05040100u);
-                    pq[OUT_I8 ? 0 : 1][j][i] = __builtin_amdgcn_perm((uint32_t)o[3], (uint32_t)o[2], 0x05040100u);
-                }
-            };
-            // RES: with residual; LUT: GELU from the table; FOLD: its address folded into the requantization constant (gemm_kernel.h)
-            auto finish_fast = [&](auto res_tag, auto lut_tag, auto fold_tag) {
-                constexpr bool RES = decltype(res_tag)::value, LUT = decltype(lut_tag)::value, FOLD = decltype(fold_tag)::value;
+            // constants of the lane's channels: c0 = bias m + 2^(s-1) (gemm_kernel.h); `low` further bits of the value are kept
+            int64_t c0[FN];
+            int32_t mm[FN], sh[FN];
+            auto constants = [&](int low, int32_t off, bool use_off) {
 #pragma unroll
                 for (int i = 0; i < FN; ++i) {
-                    const int cl = wn0 + 16 * i + 4 * fch;
-                    const v4i bb = *reinterpret_cast<const v4i*>(par + cl);
-                    const v4i mm = *reinterpret_cast<const v4i*>(par + BN + cl);
-                    const v4i ss = *reinterpret_cast<const v4i*>(par + 2 * BN + cl);
-                    int64_t cc[4];
-                    int32_t sh[4];
+                    const int c = wn0 + lane_channel<FN>(i, r16);
+                    const int32_t b = par[c], s = par[2 * BN + c];
+                    mm[i] = par[BN + c];
+                    c0[i] = (int64_t)b * mm[i] + ((int64_t)1 << ((s - 1) & 63));
+                    if (use_off) c0[i] -= (int64_t)off << (s & 63);
+                    sh[i] = (s - 32 - low) & 31;
+                }
+            };
+            auto value = [&](int i, int n) { return (int32_t)(((int64_t)acc[i][n >> 2][n & 3] * mm[i] + c0[i]) >> 32) >> sh[i]; };
+            // Token n of the lane: row 16 (n / 4) + 4 u + n % 4 of the wavefront's tile.  Its results go to LDS; when a unit is complete it is read
+            // back as it is moved, and stored while the next one is being made.  Before the first store this wavefront's requests have all
+            // landed (HOLD units give them time), so that the waits of the next tile's first step, which would count stores among
+            // the loads, can be left out.
+            constexpr int UNITS = FM / RO.unit, HOLD = UNITS >= 8 && OUT_I8 ? 4 : 2;
+            v4u mv[UNITS][RO.mv];
+            auto store = [&](int unit) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        cc[e] = (int64_t)bb[e] * mm[e] + ((int64_t)1 << ((ss[e] - 1) & 63));
-                        if (FOLD) cc[e] -= (int64_t)(ga->gelu_lut_lo - (int32_t)lut_lds) << (ss[e] & 63);
-                        sh[e] = (ss[e] - 32) & 31;
-                    }
+                for (int k = 0; k < RO.mv; ++k)
+                    // (the unit's rows in the lane's offset: with a scalar offset register, and then only, the compiler puts no wait state behind
+                    // a store whose registers the next instruction overwrites, and on this chip stores of 16 bytes need one there too --
+                    // the last quarter of the lanes stored what came after)
+                    __builtin_amdgcn_raw_buffer_store_b128(mv[unit][k], cb, ((wm0 + moved_row(RO, k)) * ga->ldc + wn0) * (int)ES + (64 * k + el) % RO.cp * 16 +
+                                                                                unit * RO.unit * 16 * ga->ldc * (int)ES, 0, 0);
+            };
+            auto put = [&](int n, uint32_t w0, uint32_t w1, uint32_t w2) {     // INT8: w0 and half of w2; INT16: w0, w1 and w2
+                int8_t* const row = turn + (16 * (n / 4 % RO.unit) + 4 * u + n % 4) * RO.pitch;
+                if (n % (4 * RO.unit) == 0) fence();
+                if constexpr (OUT_I8) {
+                    *reinterpret_cast<uint32_t*>(row + 4 * r16) = w0;
+                    if (FN == 6) *reinterpret_cast<uint16_t*>(row + 64 + 2 * r16) = (uint16_t)w2;
+                } else {
+                    *reinterpret_cast<v2u*>(row + 8 * r16) = v2u{w0, w1};
+                    if (FN == 6) *reinterpret_cast<uint32_t*>(row + 128 + 4 * r16) = w2;
+                }
+                if ((n + 1) % (4 * RO.unit) == 0) {
+                    const int unit = n / (4 * RO.unit);
+                    fence();
 #pragma unroll
-                    for (int j = 0; j < JH; ++j) {
-                        int32_t o[4];
+                    for (int k = 0; k < RO.mv; ++k) mv[unit][k] = *reinterpret_cast<const v4u*>(turn + moved_at(RO, k));
+                    if (unit + 1 == HOLD) __builtin_amdgcn_s_waitcnt(vm(0));
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int64_t p = (int64_t)acc[i][jh + j][e] * mm[e] + cc[e];
-                            int32_t v = (int32_t)(p >> 32) >> sh[e];
-                            if (RES) {
-                                const int32_t r8 = (int32_t)(int8_t)(rr[OUT_I8 ? 0 : j][i] >> (8 * e));
-                                v += (int32_t)(((int64_t)r8 * ga->res_m + ga->res_rnd) >> ga->res_s);
-                            }
-                            if (FOLD) {
-                                typedef const __attribute__((address_space(3))) uint8_t* lds_bytes;
-                                o[e] = *(lds_bytes)(uintptr_t)(uint32_t)med3_i32(v, (int32_t)lut_lds, (int32_t)lut_lds + lut_hi);
-                            } else if (LUT) {
-                                o[e] = lut[med3_i32(v - ga->gelu_lut_lo, 0, lut_hi)];
-                            } else {
-                                o[e] = med3_i32(v, clamp_lo, clamp_hi);
-                            }
-                        }
-                        put(i, j, o);
-                        // (two rows at a time, table reads a block column at a time: bounds the live registers)
-                        if (j % 2 == 1 && !LUT) __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (RES && jh == 0 && i == FN / 2) load_residual(std::integral_constant<int, 1>{});
-                    __builtin_amdgcn_sched_barrier(0);
+                    for (int x = unit + 1 == HOLD ? 0 : unit - 1; x < unit; ++x)
+                        if (unit + 1 >= HOLD) store(x);
                 }
             };
             using T = std::true_type;
             using F = std::false_type;
+            constexpr int TOKENS = 4 * FM;
             if constexpr (GELU) {
-                if (fold) finish_fast(F{}, T{}, T{}); else finish_fast(F{}, T{}, F{});
-            } else if constexpr (OUT_I8) {
-                finish_fast(F{}, F{}, F{});
-            } else {
-                finish_fast(T{}, F{}, F{});                        // (no residual: zeros)
-            }
-            // A lane holds 4 channels of one token per block column and the four lanes that share the token (16 apart) 16 consecutive
-            // ones; transposing the 4 x 4 arrangement (lane group x block column) gives lane group b the 16 channels of block
-            // column b: one 16-byte store per token (INT8; INT16: below), 16 rows of 64 consecutive bytes per instruction.
-            // Before the first store this wavefront's requests have all landed (they are at least half a step old), so that the
-            // waits of the next tile's first step, which would count stores among the loads, can be left out.
-            if (jh == 0) __builtin_amdgcn_s_waitcnt(vm(0));
-            __builtin_amdgcn_sched_barrier(0);
+                // Table reads stay outstanding while the next values are made: a token is packed LAG tokens after its reads were
+                // issued.  FOLD: the table's address is folded into the requantization constant (gemm_kernel.h)
+                constexpr int LAG = 12 / FN;                       // (a wait can leave at most 15 reads outstanding)
+                const int32_t lo = (int32_t)lut_lds;
+                int32_t by[TOKENS][FN];
+                auto pack = [&](int n) {
+                    put(n, pack4_perm(by[n][0], by[n][1], by[n][2], by[n][3]), 0u, FN == 6 ? __builtin_amdgcn_perm(by[n][FN - 1], by[n][FN - 2], 0x0c0c0400u) : 0u);
+                };
+                auto finish = [&](auto fold_tag) {
+                    constexpr bool FOLD = decltype(fold_tag)::value;
+                    typedef const __attribute__((address_space(3))) uint8_t* lds_bytes;
+                    constants(0, lut_lo - lo, FOLD);
 #pragma unroll
-            for (int j = 0; j < JH; ++j) {
-                const uint32_t off = ((row0 + 16 * (jh + j)) * (uint32_t)ga->ldc + (uint32_t)(wn0 + 16 / ES * fch)) * ES;
-                if constexpr (OUT_I8) {
-                    transpose4(pq[0][j][0], pq[0][j][1], pq[0][j][2], pq[0][j][3]);
-                    if (fch < FN) __builtin_amdgcn_raw_buffer_store_b128(v4u{pq[0][j][0], pq[0][j][1], pq[0][j][2], pq[0][j][3]}, cb, (int)off, 0, 0);
-                } else {
-                    // two block columns are 64 bytes of a row: lane group u takes bytes 16 u .. +15, which are the dword pairs of
-                    // column u / 2 from the groups 2 (u % 2) and the next -- the same two swaps
-                    constexpr int H = OUT_I8 ? 0 : 1;
+                    for (int n = 0; n < TOKENS; ++n) {
 #pragma unroll
-                    for (int p = 0; p < FN; p += 2) {
-                        v2u t = __builtin_amdgcn_permlane32_swap(pq[0][j][p], pq[0][j][p + 1], false, false);
-                        t = __builtin_amdgcn_permlane16_swap(t.x, t.y, false, false);
-                        v2u u = __builtin_amdgcn_permlane32_swap(pq[H][j][p], pq[H][j][p + 1], false, false);
-                        u = __builtin_amdgcn_permlane16_swap(u.x, u.y, false, false);
-                        if (p + 1 < FN || fch < 2)
-                            __builtin_amdgcn_raw_buffer_store_b128(v4u{t.x, u.x, t.y, u.y}, cb, (int)(off + 32 * p), 0, 0);
+                        for (int i = 0; i < FN; ++i) by[n][i] = *(lds_bytes)(uintptr_t)(uint32_t)med3_i32(FOLD ? value(i, n) : value(i, n) - (lut_lo - lo), lo, lo + lut_hi);
+                        if (n >= LAG) pack(n - LAG);
+                        __builtin_amdgcn_sched_barrier(0);
                     }
-                }
+#pragma unroll
+                    for (int n = TOKENS - LAG; n < TOKENS; ++n) pack(n);
+                };
+                if (fold) finish(T{}); else finish(F{});
+            } else if constexpr (OUT_I8) {
+                // TALL, every shift at least 40: shifted by eight less, a value keeps its fraction in the low byte of 16 bits, where
+                // packing two of them saturates to [-128, 128): what is left of the clamp to +-127 is half an instruction a value.
+                auto finish = [&](auto tall_tag) {
+                    constexpr bool TALL = decltype(tall_tag)::value;
+                    constants(TALL ? 8 : 0, 0, false);
+#pragma unroll
+                    for (int n = 0; n < TOKENS; ++n) {
+                        int32_t o[FN];
+#pragma unroll
+                        for (int i = 0; i < FN; ++i) o[i] = value(i, n);
+                        if constexpr (TALL) {
+                            const uint32_t a = pack2_i16_above(o[0], o[1], -127 * 256), b = pack2_i16_above(o[2], o[3], -127 * 256);
+                            const uint32_t c = FN == 6 ? pack2_i16_above(o[FN - 2], o[FN - 1], -127 * 256) : 0u;
+                            put(n, __builtin_amdgcn_perm(b, a, 0x07050301u), 0u, __builtin_amdgcn_perm(c, c, 0x0c0c0301u));
+                        } else {
+#pragma unroll
+                            for (int i = 0; i < FN; ++i) o[i] = med3_i32(o[i], clamp_lo, clamp_hi);
+                            put(n, pack4_perm(o[0], o[1], o[2], o[3]), 0u, __builtin_amdgcn_perm((uint32_t)o[FN - 1], (uint32_t)o[FN - 2], 0x0c0c0400u));
+                        }
+                        if (n % 2 == 1) __builtin_amdgcn_sched_barrier(0);     // (bounds the live registers)
+                    }
+                };
+                if (tall && clamp_hi == 127) finish(T{}); else finish(F{});
+            } else {
+                // SHORT: the residual's product fits 32 bits (residual_short) and the clamp is that of the type.  (No residual: zeros.)
+                auto finish = [&](auto short_tag) {
+                    constexpr bool SHORT = decltype(short_tag)::value;
+                    const int32_t r_m = ga->res_short.m, r_rnd = ga->res_short.rnd, r_s = ga->res_short.s;
+                    constants(0, 0, false);
+#pragma unroll
+                    for (int n0_ = 0; n0_ < TOKENS; n0_ += 4 * RR.unit) {
+                        uint32_t r4[4 * RR.unit], r2[4 * RR.unit];
+                        const int ru = n0_ / (4 * RR.unit);
+                        fence();
+#pragma unroll
+                        for (int k = 0; k < RR.mv; ++k) *reinterpret_cast<v4u*>(turn + moved_at(RR, k)) = rt[ru % AHEAD][k];
+                        fence();
+#pragma unroll
+                        for (int t = 0; t < 4 * RR.unit; ++t) {
+                            const int8_t* row = turn + (16 * (t / 4) + 4 * u + t % 4) * RR.pitch;
+                            r4[t] = *reinterpret_cast<const uint32_t*>(row + 4 * r16);
+                            r2[t] = FN == 6 ? *reinterpret_cast<const uint16_t*>(row + 64 + 2 * r16) : 0u;
+                        }
+                        if ((ru + AHEAD) * RR.unit < FM) load_residual(ru + AHEAD);
+#pragma unroll
+                        for (int t = 0; t < 4 * RR.unit; ++t) {
+                            const int n = n0_ + t;
+                            int32_t o[FN];
+                            uint32_t w[3] = {0u, 0u, 0u};
+#pragma unroll
+                            for (int i = 0; i < FN; ++i) {
+                                o[i] = value(i, n);
+                                const int32_t r8 = (int32_t)(int8_t)((i < 4 ? r4[t] : r2[t]) >> (8 * (i & 3)));
+                                if (SHORT) o[i] += smad24(r8, r_m, r_rnd) >> r_s;
+                                else o[i] = med3_i32(o[i] + (int32_t)(((int64_t)r8 * ga->res_m + ga->res_rnd) >> ga->res_s), clamp_lo, clamp_hi);
+                            }
+#pragma unroll
+                            for (int i = 0; i < FN; i += 2)
+                                w[i >> 1] = SHORT ? pack2_i16_above(o[i], o[i + 1], -32767) : __builtin_amdgcn_perm((uint32_t)o[i + 1], (uint32_t)o[i], 0x05040100u);
+                            put(n, w[0], w[1], w[2]);
+                            if (n % 2 == 1 || !SHORT) __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                };
+                if (ga->res_short.ok && clamp_hi == 32767) finish(T{}); else finish(F{});
             }
-        };
-        if (fast) {
-            load_residual(std::integral_constant<int, 0>{});
-            finish_rows(std::integral_constant<int, 0>{});
-            if constexpr (JH < FM) finish_rows(std::integral_constant<int, JH>{});
+            store(UNITS - 1);
         } else {
             // Any constants: 64-bit arithmetic in a rolled loop, 16 rows of each row of wavefronts at a time through LDS, where the
             // next tile's first steps had arrived -- they are requested again afterwards.  (Unrolled over the accumulators like
@@ -536,14 +635,19 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
                     if (k == j) {
 #pragma unroll
                         for (int i = 0; i < FN; ++i)
-                            *reinterpret_cast<v4i*>(st + ((wave & 1) * 16 + frow) * SP + wn0 + 16 * i + 4 * fch) = acc[i][k];
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) st[(wave % WR * 16 + 4 * u + e) * SP + wn0 + 16 * i + r16] = acc[i][k][e];
                     }
                 __syncthreads();
 #pragma unroll 1
-                for (int q = tid; q < 32 * G4; q += NT) {
+                for (int q = wave * 64 + el; q < 16 * WR * G4; q += NT) {
                     const int r = q / G4, c = (q - r * G4) * 4, row = (r >> 4) * WM + 16 * j + (r & 15);
                     if (row > last) continue;
-                    const v4i a4 = *reinterpret_cast<const v4i*>(st + r * SP + c);
+                    // (columns by block column: four channels are 16 apart, two pairs of the last 32 a pair and the next)
+                    const int cw = c % WN, c0 = cw < 64 ? c - cw + cw / 4 : c - cw + 64 + (cw - 64) / 2;
+                    v4i a4;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) a4[e] = st[r * SP + c0 + (cw < 64 ? 16 * e : 16 * (e & 1) + (e >> 1))];
                     uint32_t r4 = 0;
                     if (has_res) r4 = *reinterpret_cast<const uint32_t*>(ga->R + (int64_t)(m0 + row) * ga->ldr + n0 + c);
                     int32_t o[4];
@@ -618,6 +722,7 @@ int launch_stream(GemmArgs& g, bool i8, hipStream_t stream)
     stream_deal(s, g, BM, BN);
     s.per_channel = g.per_channel; s.dy_m = g.dy_m; s.dy_s = g.dy_s; s.out_clamp = g.out_clamp;
     s.res_m = g.res_m; s.res_s = g.res_s; s.res_fast = g.res_fast; s.res_rnd = g.res_rnd;
+    s.res_short = residual_short(g);
     s.k_fast = (int64_t)g.K * 16129 < (1 << 30);
     s.gelu_fast = g.gelu_fast; s.gelu_lut_lo = g.gelu_lut_lo; s.gelu_lut_n = 0; s.gelu = g.gelu;
     s.path_word = g.path_word;

@@ -265,6 +265,60 @@ def test_gemm_persistent_tiles_constants(G, cfg, bn, kind, constants):
     _eq(got.astype(np.int64), want.astype(np.int64), "persistent gemm, constants")
 
 
+# (clamp, shift, residual): on both sides of the forms of the persistent tiles' epilogue -- INT8 with every shift from 40 on and the type's own
+# clamp, or not; INT16 with the type's own clamp and a residual whose multiplier may lose its low eight bits, or not.  The last but one
+# product is a tie, 127 * 2^30 / 2^31 = 63.5, that the low bits decide; residual shifts from 8 to 62
+@pytest.mark.parametrize("cfg,bn", [(23, 256), (24, 192)])
+@pytest.mark.parametrize("clamp,shift,res", [(127, 39, None), (127, 40, None), (100, 41, None), (127, 62, None), (32767, 35, (1352745605, 33)),
+                                             (32767, 35, (-1352745605, 33)), (2000, 35, (1352745605, 33)), (32767, 36, (1073741823, 31)),
+                                             (32767, 36, (1073741825, 31)), (32767, 34, (1717986918, 8)), (32767, 34, (1717986918, 23)),
+                                             (32767, 34, (1717986918, 39)), (32767, 34, (1717986918, 62))])
+def test_gemm_persistent_tiles_forms_of_the_epilogue(G, cfg, bn, clamp, shift, res):
+    # ragged rows in the last tile, more than one tile for a workgroup; values in and beyond the clamp
+    from paper_2101_01321_amd import binding as B
+    M, N, K = 256 * 90 + 17, 3 * bn, 128
+    rng = np.random.default_rng(shift + clamp)
+    A, W = (rng.integers(-127, 128, size=(n, K), dtype=np.int8) for n in (M, N))
+    bias = rng.integers(-50000, 50000, size=N, dtype=np.int32)
+    mult = rng.integers(2 ** 30, 2 ** 31, size=N, dtype=np.int64).astype(np.int32)
+    shifts = (shift + rng.integers(0, 2, size=N) * (shift < 62)).astype(np.int32)
+    R = None if res is None else rng.integers(-127, 128, size=(M, N), dtype=np.int8)
+    kw = dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K, ldw=K, ldc=N, ldr=N, per_channel=1, residual_dy=res or (0, 0),
+              out_dtype=I8 if res is None else I16, out_clamp=clamp)
+    B.lib().ibert_gemm_config_override(cfg)
+    try:
+        G.say("persistent gemm cfg %d clamp %d shift %d residual %s" % (cfg, clamp, shift, res))
+        got = G.gemm(kw, A, W, bias, mult, shifts, R, out_elems=M * N)
+    finally:
+        B.lib().ibert_gemm_config_override(-1)
+    assert B.lib().ibert_last_kernel().decode().startswith(G.kernel_of(cfg))
+    spec = GemmSpec(M, N, K, per_channel=1, out_dtype=I8 if res is None else I32, out_clamp=clamp, res_dy=res or (0, 0))
+    _eq(got.astype(np.int64), oracle.gemm_requant(spec, A, W, bias, mult, shifts, R).reshape(-1).astype(np.int64), "persistent gemm, forms")
+
+
+@pytest.mark.parametrize("bn", [256, 192])
+def test_gemm_gelu_table_larger_than_the_persistent_tiles_have_room_for(G, bn):
+    # an output scale of 2.5 at an input scale of 2^-6: saturated from 127 * 2.5 * 64 = 20320 on
+    from paper_2101_01321_amd import binding as B
+    M, N, K = 256 * 90, 4 * bn, 128
+    rng = np.random.default_rng(bn)
+    A, W = (rng.integers(-127, 128, size=(n, K), dtype=np.int8) for n in (M, N))
+    mult = rng.integers(2 ** 30, 2 ** 31, size=N, dtype=np.int64).astype(np.int32)
+    shifts = np.full(N, 33, np.int32)
+    gp, op = B.ibert_gelu_params_from_scale(2.0 ** -6, 2.5), P.gelu_params(2.0 ** -6, 2.5)
+    kw = dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K, ldw=K, ldc=N, ldr=N, per_channel=1)
+    want = oracle.gelu(oracle.gemm_requant(GemmSpec(M, N, K, per_channel=1, out_dtype=I32, out_clamp=gp.q_max), A, W, None, mult, shifts, None).reshape(-1), op)
+    for cfg in (-1, 23 if bn == 256 else 24):
+        B.lib().ibert_gemm_config_override(cfg)
+        try:
+            G.say("GELU with a large table, cfg %d bn %d" % (cfg, bn))
+            got = G.gemm_gelu(dict(kw, out_dtype=I8, out_clamp=5), A, W, None, mult, shifts, gp, M * N)[0]
+        finally:
+            B.lib().ibert_gemm_config_override(-1)
+        assert B.lib().ibert_last_kernel().decode().startswith("gemm_stream_kernel") == (cfg >= 0)
+        _eq(got.astype(np.int64), want.astype(np.int64), "GELU with a large table")
+
+
 @pytest.mark.parametrize("cfg,bn", [(23, 256), (24, 192)])
 @pytest.mark.parametrize("kind", ["i8", "i16", "i16res", "gelu"])
 @pytest.mark.parametrize("cols,shift", [(3, 40), (9, 40), (3, 30)])
