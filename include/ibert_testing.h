@@ -41,10 +41,11 @@ enum {
 };
 void ibert_gemm_epilogue_record(uint32_t* device_word);
 
-/* How the one-kernel attention (Alg. 3 between its two MatMuls) holds K_h and V_h for 385 <= seq <= 512: *shared = 1 where a launch of
+/* How the one-kernel attention (Alg. 3 between its two MatMuls) holds K_h and V_h for 385 <= seq <= 512 (forms 3 and 4 from 321 on): *shared = 1 where a launch of
  * `workgroups` (batch x heads x ceil(seq / 64)) has them take turns in one LDS buffer, 0 where each has its own; *fit_two, *fit_one =
  * workgroups that a compute unit holds at once with two buffers and with one.  form: 0 any constants, 1 and 2 the faster
- * forms (scores' shift at least 32, and below).  Asks the device. */
+ * forms (scores' shift at least 32, and below), 3 and 4 those with a table of the exponent (scores' shift up to 33, and above; fit_* with the
+ * largest table).  Asks the device. */
 int ibert_attention_buffers(int32_t seq, int32_t form, int64_t workgroups, int32_t* shared, int32_t* fit_two, int32_t* fit_one);
 
 /* What the XCDs read of W [N, K] (dense rows, K a multiple of 128, N * K of 1024) when this MatMul runs with all operands aligned, and

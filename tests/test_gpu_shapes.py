@@ -72,6 +72,41 @@ def test_attention_shares_a_buffer_only_where_more_workgroups_fit(G, L, form):
     assert _buffers(L, form, 512)[0] == 0
 
 
+@pytest.mark.parametrize("L,form", [(321, 3), (384, 4), (385, 3), (448, 4), (449, 3), (512, 4)])
+def test_attention_with_a_table_shares_a_buffer_only_where_more_workgroups_fit(G, L, form):
+    shared, two, one = _buffers(L, form, 513)
+    assert two == 2 and one > two and shared, (shared, two, one)
+    assert _buffers(L, form, 512)[0] == 0
+
+
+# The table of the exponent: shifts on both sides of 33, the smallest one and the largest; multipliers on both sides of what the 32-bit product holds
+# (5000 and 4900 at 23); 11 to 16 bits of the exponent and, at 2^-8, more than the table takes; one entry a step and none for some
+@pytest.mark.parametrize("S,k,sdy", [(2.0 ** -6, 7, (37581, 23)), (2.0 ** -6, 7, (5000, 23)), (2.0 ** -6, 7, (4900, 23)), (2.0 ** -6, 7, (1187698534, 33)),
+                                     (2.0 ** -6, 7, (1187698534, 34)), (2.0 ** -6, 6, (2147483647, 45)), (2.0 ** -6, 7, (2000000011, 26)), (2.0 ** -4, 7, (1187698534, 30)),
+                                     (2.0 ** -7, 7, (1187698534, 27)), (2.0 ** -7, 7, (1518500250, 35)), (2.0 ** -8, 7, (1187698534, 26)), (2.0 ** -8, 7, (1518500250, 34))])
+@pytest.mark.parametrize("B_,nh,L", [(2, 3, 67), (43, 3, 128), (43, 2, 190)])         # 12, 258 and 258 workgroups
+def test_attention_exponent_from_a_table(G, S, k, sdy, B_, nh, L):
+    from paper_2101_01321_amd import binding as B
+    H, cdy = 64 * nh, (1073741824, 30 + k)
+    rng = np.random.default_rng(L)
+    x = sdy[0] / 2.0 ** sdy[1] * S                           # of one unit of an accumulator: logits of some units, and rows of the largest products
+    qkv = np.clip(np.rint(rng.normal(0, min(60.0, max(1.0, (0.4 / x) ** 0.5)), size=(B_ * L, 3 * H))), -128, 127).astype(np.int8)
+    qkv[L - 2] = -128
+    qkv[L - 1, H:2 * H] = 127
+    sp, op = B.ibert_softmax_params_from_scale(S, L, k), P.softmax_params(S, k)
+    G.say("attention, table, B=%d heads=%d L=%d S=%g k=%d s=%s" % (B_, nh, L, S, k, sdy))
+    got = G.attention(qkv, B_, L, H, nh, sdy, sp, cdy)
+    for b in (0, B_ - 1):
+        part = qkv[b * L:(b + 1) * L]
+        _eq(got[b * L:(b + 1) * L], _attention_oracle(part, 1, L, H, nh, sdy, op, cdy), "attention, sequence %d" % b)
+    lens = np.full(B_, 65, np.int32)
+    lens[-1] = 3
+    masked = G.attention(qkv, B_, L, H, nh, sdy, sp, cdy, key_lens=lens)
+    for b, n in ((0, 65), (B_ - 1, 3)):
+        part = qkv[b * L:b * L + n]
+        _eq(masked[b * L:b * L + n], _attention_oracle(part, 1, n, H, nh, sdy, op, cdy), "masked attention, sequence %d" % b)
+
+
 # 504 to 539 workgroups, on both sides of the switch at 512; lengths at, before and behind the ends of key blocks
 @pytest.mark.parametrize("B_,nh,L,many", [(8, 9, 447, 0), (8, 8, 449, 0), (11, 7, 385, 1), (11, 7, 447, 1), (11, 7, 448, 1), (13, 5, 449, 1),
                                           (13, 5, 511, 1), (13, 5, 512, 1)])
