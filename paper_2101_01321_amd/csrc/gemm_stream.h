@@ -265,12 +265,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
     constexpr auto vm = [](int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); };
 
     v4i acc[FN][FM];
-    auto clear = [&]() {
-#pragma unroll
-        for (int i = 0; i < FN; ++i)
-#pragma unroll
-            for (int j = 0; j < FM; ++j) acc[i][j] = v4i{0, 0, 0, 0};
-    };
     // operand reads: block rows are multiples of 16, so the swizzle depends on frow only; slice sl of the step
     // (the second slice is four chunks on: the address with bit 6 flipped)
     const int rd0 = frow * 128 + ((fch ^ ((frow >> 1) & 7)) << 4);
@@ -311,9 +305,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
     // The MFMAs of one quadrant: W blocks i0 .. i0 + NI - 1 (operands xw) by A blocks j0 .. j0 + FMH - 1 (operands xa), slice by
-    // slice; `between(idx)` issues what goes in front of MFMA idx (`sched_barrier` pins that order).
-    auto quadrant = [&](auto& xw, auto ni_tag, int i0, v4i (&xa)[FMH][2], int j0, auto&& between) {
+    // slice; `between(idx)` issues what goes in front of MFMA idx (`sched_barrier` pins that order).  A tile's first step adds to zero.
+    auto quadrant = [&](auto& xw, auto ni_tag, int i0, v4i (&xa)[FMH][2], int j0, auto zero_tag, auto&& between) {
         constexpr int NI = decltype(ni_tag)::value;
+        constexpr bool ZERO = decltype(zero_tag)::value;
 #pragma unroll
         for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
@@ -322,7 +317,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
                 for (int j = 0; j < FMH; ++j) {
                     between((sl * NI + i) * FMH + j);
                     __builtin_amdgcn_sched_barrier(0);
-                    acc[i0 + i][j0 + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa[j][sl], xw[i][sl], acc[i0 + i][j0 + j], 0, 0, 0);
+                    acc[i0 + i][j0 + j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa[j][sl], xw[i][sl], ZERO && sl == 0 ? v4i{0, 0, 0, 0} : acc[i0 + i][j0 + j], 0, 0, 0);
                 }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -330,11 +325,12 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
     using NI1 = std::integral_constant<int, FN1>;
     constexpr int M0 = 2 * FN0 * FMH, M1 = 2 * FN1 * FMH;          // MFMAs of the two kinds of quadrant
     static_assert(2 * FN1 <= M0 && 2 * FMH <= M1 && 2 * FMH <= M0 && 2 * FN0 <= M1, "one operand read per MFMA at most");
-    // One K step.  REQ 1: each half requests its group for the step after next.  REQ 2: nothing in the first half (a wavefront may
+    // One K step.  REQ 2 is the first one of a tile.  REQ 1: each half requests its group for the step after next.  REQ 2: nothing in the first half (a wavefront may
     // still be in the epilogue of the last tile, with the first operands of this step to read), both groups in the second.
     // wait: whether the next step has to be waited for.
     auto step = [&](auto req_tag, bool wait) {
         constexpr int REQ = decltype(req_tag)::value;
+        using Z = std::integral_constant<bool, REQ == 2>;
         const int nst = SL::STAGE - stage;
         // request r of n over the MFMAs [0, M0 + M1) of a half step
         auto ask = [&](int h, int n, int idx) {
@@ -342,11 +338,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
             for (int r = 0; r < N0 + N1; ++r)
                 if (r < n && idx == (2 * r + 1) * (M0 + M1) / (2 * n)) request_one(REQ == 2 ? (r < N0 ? 0 : 1) : h, REQ == 2 && r >= N0 ? r - N0 : r);
         };
-        quadrant(w0, NI0{}, 0, at, 0, [&](int idx) {
+        quadrant(w0, NI0{}, 0, at, 0, Z{}, [&](int idx) {
             if (idx < 2 * FN1) read_w1(stage, idx);
             if (REQ == 1) ask(0, N0, idx);
         });
-        quadrant(w1, NI1{}, FN0, at, 0, [&](int idx) {
+        quadrant(w1, NI1{}, FN0, at, 0, Z{}, [&](int idx) {
             if (idx < 2 * FMH) read_a(ab, stage, 1, idx);
             if (REQ == 1) ask(0, N0, M0 + idx);
         });
@@ -354,19 +350,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
             // group 0 of the next step has landed when only younger requests are outstanding: group 1 of that step and (made in
             // this half) group 0 of the one after
             __builtin_amdgcn_s_waitcnt(vm(REQ == 1 ? N1 + N0 : N1));
-        } else if (REQ == 2 && koff == 0) {
-            // A tile of one step has no later step whose wait covers the constants requested at its head; behind them nothing has
-            // been requested yet (counting would not do: the last tile's stores stand in the queue before them).  The requests
-            // are two steps ahead here, at step 2 of nk: koff is 0 for one step always, for two where the wait does no harm, and
-            // for none with more.
-            __builtin_amdgcn_s_waitcnt(vm(0));
         }
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        quadrant(w0, NI0{}, 0, ab, FMH, [&](int idx) {
+        quadrant(w0, NI0{}, 0, ab, FMH, Z{}, [&](int idx) {
             if (idx < 2 * FMH) read_a(at, nst, 0, idx);
             ask(1, REQ == 2 ? N0 + N1 : N1, idx);
         });
-        quadrant(w1, NI1{}, FN0, ab, FMH, [&](int idx) {
+        quadrant(w1, NI1{}, FN0, ab, FMH, Z{}, [&](int idx) {
             if (idx < 2 * FN0) read_w0(nst, idx);
             ask(1, REQ == 2 ? N0 + N1 : N1, M0 + idx);
         });
@@ -381,16 +371,20 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
     using R1 = std::integral_constant<int, 1>;
     using R2 = std::integral_constant<int, 2>;
     for (;;) {
-        if (!first) request_constants(n0);
-        clear();
 #pragma unroll
         for (int q = 0; q < 2 * FMH; ++q) read_a(at, stage, 0, q);
 #pragma unroll
         for (int q = 0; q < 2 * FN0; ++q) read_w0(stage, q);
-        // (the first two steps of a tile that follows another were waited for before that one's stores, see below; its constants,
-        // requested just now, are covered by the first wait of its second step, which leaves only younger requests outstanding --
-        // a tile of one step waits for them by itself)
+        // (the first two steps of a tile that follows another were waited for before that one's stores, see below)
         step(R2{}, first);
+        // The constants of the next tile, into the buffer that the tile before this one left: every epilogue waits for all that has been requested.
+        // (At that tile's head they stood behind the stores: 600 cycles of every wavefront.)
+        const int par_own = par_buf;
+        if (lt + g.per_xcd < count) {
+            int next_m0, next_n0;
+            tile_at(lt + g.per_xcd, next_m0, next_n0);
+            request_constants(next_n0);
+        }
         for (uint32_t kt = 128; kt < kbytes; kt += 128) step(R1{}, true);
 
         // ---- epilogue ---------------------------------------------------------------------------
@@ -399,7 +393,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         int el = lane;
         asm volatile("" : "+v"(el));
         const int r16 = el & 15, u = el >> 4;
-        const int32_t* par = reinterpret_cast<const int32_t*>(lds + SL::PAR + par_buf * 3 * BN * 4);
+        const int32_t* par = reinterpret_cast<const int32_t*>(lds + SL::PAR + par_own * 3 * BN * 4);
         // (what only the epilogue needs of the arguments is fetched here: kept in scalar registers through the loop it
         // would spill them)
         typedef const __attribute__((address_space(4))) StreamArgs* kernel_args;
@@ -445,22 +439,23 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
                 rt[OUT_I8 ? 0 : unit % AHEAD][k] = __builtin_amdgcn_raw_buffer_load_b128(
                     rb, (wm0 + moved_row(RR, k)) * ga->ldr + wn0 + (64 * k + el) % RR.cp * 16, unit * RR.unit * 16 * ga->ldr, 0);
         };
-        // Fast form: every shift in [33, 62], every |bias| and K * 127^2 below 2^30, the residual shift in [8, 62] (see gemm_kernel.h),
+        // Fast form: every shift in [33, 62], every |bias| and K * 127^2 below 2^30 (|acc + bias| stays below 2^31), the residual shift in [8, 62] (see gemm_kernel.h),
         // and a GELU table.
         bool fast, fold, tall;
         {
-            int badc = 0, bigs = 0, lows = 0;
+            // (|bias| below 2^30 or bias = -2^30: the two highest bits are equal)
+            int32_t lo = par[2 * BN + el], hi = lo, pb = par[el], big = pb ^ (pb << 1);
 #pragma unroll
-            for (int c = 0; c < BN; c += 64) {
-                const int32_t pb = par[c + el], ps = par[2 * BN + c + el];
-                const int32_t ab = pb < 0 ? -pb : pb;
-                badc |= (ps < 33 || ps > 62 || ab < 0 || ab >= (1 << 30)) ? 1 : 0;
-                bigs |= ps > 43 ? 1 : 0;
-                lows |= ps < 40 ? 1 : 0;
+            for (int c = 64; c < BN; c += 64) {
+                const int32_t ps = par[2 * BN + c + el];
+                lo = lo < ps ? lo : ps;
+                hi = hi > ps ? hi : ps;
+                pb = par[c + el];
+                big |= pb ^ (pb << 1);
             }
-            fast = __builtin_amdgcn_ballot_w64(badc != 0) == 0 && ga->res_fast && ga->k_fast && (!GELU || ga->gelu_lut_n > 0);
-            fold = __builtin_amdgcn_ballot_w64(bigs != 0) == 0;
-            tall = __builtin_amdgcn_ballot_w64(lows != 0) == 0;
+            fast = __builtin_amdgcn_ballot_w64(big < 0 || lo < 33 || hi > 62) == 0 && ga->res_fast && ga->k_fast && (!GELU || ga->gelu_lut_n > 0);
+            fold = __builtin_amdgcn_ballot_w64(hi > 43) == 0;
+            tall = __builtin_amdgcn_ballot_w64(lo < 40) == 0;
         }
         const int32_t lut_lo = ga->gelu_lut_lo, lut_hi = ga->gelu_lut_n - 1;
         const int32_t clamp_lo = -ga->out_clamp, clamp_hi = ga->out_clamp;
