@@ -26,6 +26,12 @@ namespace ibert {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 
+// A residual's requantization in 32 bits: DY(r) = (r m + rnd) >> s for every INT8 r, |m| < 2^23 -- the multiplier without its low eight
+// bits, where that changes none of the 256 values (ok).
+struct ResShort {
+    int32_t m, rnd, s, ok;
+};
+
 struct GemmArgs {
     const int8_t* A;
     const int8_t* W;
@@ -49,6 +55,7 @@ struct GemmArgs {
     int32_t c16;       // the INT32 kernels store 16-bit elements (IBERT_I16: |value| <= out_clamp <= 32767)
     int32_t res_fast;  // residual absent, or its shift is in [8, 62]: its requantized value fits 32 bits
     int64_t res_rnd;   // 2^(res_s - 1), or 0 when res_s == 0
+    ResShort res_short;    // (direct-to-LDS and persistent tiles)
     int32_t xcd_chunk; // tiles per XCD when the grid divides by 8, else 0 (no remap)
     int32_t xcd_xn;    // >= 1: each XCD works on a block of the tile grid, xcd_xn (a power of two) blocks side by side
     int32_t xcd_xs;    // log2(xcd_xn)
@@ -58,6 +65,27 @@ struct GemmArgs {
     GeluConst gelu;    // GELU epilogue: constants (the clamp before it is out_clamp = q_max)
     uint32_t* path_word;   // tests only (may be null): workgroup 0 records which epilogue form it ran
 };
+
+inline ResShort residual_short(const GemmArgs& g)
+{
+    if (!g.R) return ResShort{0, 0, 0, 1};
+    const int32_t s = g.res_s - 8;
+    if (s < 1 || s > 30) return ResShort{0, 0, 0, 0};
+    const int64_t m = ((int64_t)g.res_m + 128) >> 8;
+    if (m <= -(1 << 23) || m >= (1 << 23)) return ResShort{0, 0, 0, 0};
+    const int64_t rnd = (int64_t)1 << (s - 1);
+    int bad = 0;
+    for (int r = -128; r < 128; ++r) bad |= ((r * m + rnd) >> s) != (((int64_t)r * g.res_m + g.res_rnd) >> g.res_s);
+    return ResShort{(int32_t)m, (int32_t)rnd, s, !bad};
+}
+
+// Two values as 16 bits each, saturated, and not below `low`.
+__device__ __forceinline__ uint32_t pack2_i16_above(int32_t a, int32_t b, int16_t low)
+{
+    typedef short v2s __attribute__((ext_vector_type(2)));
+    const v2s v = __builtin_elementwise_max(__builtin_amdgcn_cvt_pk_i16(a, b), v2s{low, low});
+    return __builtin_bit_cast(uint32_t, v);
+}
 
 // Requantize one accumulator and finish the output value (before the store).
 __device__ __forceinline__ int32_t finish(int32_t acc, int32_t m, int32_t s, bool has_res, int32_t res,
@@ -179,6 +207,12 @@ __host__ __device__ __forceinline__ void mfma_tile(const GemmArgs& g, unsigned b
 // request the loop of the 128x96 tile runs in three quarters of its time); a wavefront of their own takes that wait
 // instead.  They join every barrier of the loop and end before the epilogue (a barrier waits for the surviving
 // wavefronts only).
+//
+// Per-channel constants of a direct-to-LDS tile behind its stages: bias, mult and shift as they are, and 16 bytes a channel of what the
+// epilogue makes of them (see `made`).
+template <int BN>
+constexpr int par_bytes() { return ((3 * BN * 4 + 255) & ~255) + 16 * BN; }
+
 template <int BM, int BN, int BK, int RING, bool OUT_I8, int KMODE, bool TW = false, bool DMA = false, bool GELU = false,
           int NW = 4, int NLD = 0>
 __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs g)
@@ -373,7 +407,10 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
     }
     // (direct-to-LDS kernels: the constants live in LDS behind the stages, requested before the loop starts, see below)
     int32_t* const par_early = reinterpret_cast<int32_t*>(lds + EL::LDS_BYTES);
-    constexpr int PAR_BYTES = (3 * BN * 4 + 255) & ~255;
+    constexpr int PAR_BYTES = par_bytes<BN>();
+    // Behind them what the epilogue makes of a channel's constants: multiplier, shift - 32, and the 64-bit addend.
+    v4i* const made = reinterpret_cast<v4i*>(lds + EL::LDS_BYTES + PAR_BYTES - 16 * BN);
+    const int32_t gelu_lut_at = (int32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)lds + EL::LDS_BYTES + PAR_BYTES;
     bool fast_early = false, fold_early = false;
 
     if constexpr (DMA) {
@@ -565,16 +602,32 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             // The constants have landed with the first stage.  Every wavefront looks at all BN channels itself and decides
             // whether they allow the register-direct epilogue (see "Fast path" below): the same answer in all of
             // them without another barrier, and nothing but the epilogue itself is left to do after the loop.
-            int badc = 0, bigs = 0;
-            for (int c = lane; c < BN; c += 64) {
+            // (|bias| below 2^30, or bias = -2^30, which is as good: the two highest bits are equal)
+            int32_t lo = 63, hi = 0, big = 0;
+#pragma unroll
+            for (int c0 = 0; c0 < BN; c0 += 64) {
+                const int c = BN % 64 == 0 || c0 + 64 <= BN ? c0 + lane : c0 + (lane & 31);      // (the last 32 columns twice)
                 const int32_t pbc = par_early[c], psc = par_early[2 * BN + c];
-                const int32_t ab = pbc < 0 ? -pbc : pbc;
-                badc |= (psc < 33 || psc > 62 || ab < 0 || ab >= (1 << 30)) ? 1 : 0;
-                bigs |= psc > 43 ? 1 : 0;
+                lo = lo < psc ? lo : psc;
+                hi = hi > psc ? hi : psc;
+                big |= pbc ^ (pbc << 1);
             }
-            fast_early = __builtin_amdgcn_ballot_w64(badc != 0) == 0 && g.res_fast && (int64_t)g.K * 16129 < (1 << 30);
-            fold_early = __builtin_amdgcn_ballot_w64(bigs != 0) == 0;  // every shift at most 43
+            static_assert(BN % 32 == 0, "columns in halves of a wavefront");
+            fast_early = __builtin_amdgcn_ballot_w64(big < 0 || lo < 33 || hi > 62) == 0 && g.res_fast && (int64_t)g.K * 16129 < (1 << 30);
+            fold_early = __builtin_amdgcn_ballot_w64(hi > 43) == 0;    // every shift at most 43
         }
+        // What the epilogue makes of a channel's constants, one channel a thread, before the barrier of the first step, where there is mostly a
+        // wait for the second step's tiles: made by every lane of the epilogue for its own channels this was a quarter of its instructions.
+        // With it, with the residual's product in 32 bits and a saturating pack, us before / after: 128x96 with loaders [4096,768] INT16 + residual
+        // x K 768 8.95 / 8.57, x K 3072 16.9 / 16.7, [488,3072] x K 768 + GELU 7.73 / 7.45; 128x128 [4096,1024] + residual x K 1024 11.1 / 10.7.
+        auto make_constants = [&]() {
+            if (tid < BN) {
+                const int32_t b = par_early[tid], m = par_early[BN + tid], s = par_early[2 * BN + tid];
+                int64_t cc = (int64_t)b * m + ((int64_t)1 << ((s - 1) & 63));
+                if (GELU && fold_early && g.gelu_lut_n > 0) cc -= (int64_t)(g.gelu_lut_lo - gelu_lut_at) << (s & 63);
+                made[tid] = v4i{m, (s - 32) & 31, (int32_t)(uint32_t)cc, (int32_t)(cc >> 32)};
+            }
+        };
         // One K step.  Phase 1: slice 0 (fragments already in registers) while slice 1 is read.  Then this
         // wavefront's share of step kt+1 has landed and its reads of stage `buf` are done; after the barrier
         // that holds for the whole workgroup, so `buf` may be refilled and the next stage read.  Phase 2:
@@ -590,6 +643,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             else
                 phase(xa0, wb0, xa1, wb1, buf, 1, std::true_type{}, kt - 1 + NSTG, pbuf, asker && kt >= 1 && kt - 1 + NSTG < nk,
                       std::integral_constant<int, QH>{}, std::integral_constant<int, NL>{});
+            if (kt == 0) make_constants();
             // steps requested after kt+1 so far: kt+2 .. min(kt+RING-1, nk-1)
             const int hi = kt + NSTG - 1 < nk - 1 ? kt + NSTG - 1 : nk - 1;
             if (NLD == 0 || asker) wait_landed(hi - (kt + 1));
@@ -841,17 +895,20 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
     // byte read per value.  (Byte loads into register halves would pack four values with one instruction, but with
     // ECC on the register file they clear the other half instead of keeping it.)
     auto finish_direct = [&](auto res_tag, auto gf_tag, auto lut_tag, auto sm_tag, auto es_tag, auto fold_tag) {
-        constexpr bool RES = decltype(res_tag)::value, GF = decltype(gf_tag)::value, LUT = decltype(lut_tag)::value;
+        constexpr int RES = decltype(res_tag)::value;              // 2: the residual's product in 32 bits, the clamp that of the type
+        constexpr bool GF = decltype(gf_tag)::value, LUT = decltype(lut_tag)::value;
         constexpr int SM = decltype(sm_tag)::value, ES = decltype(es_tag)::value;
         constexpr bool FOLD = decltype(fold_tag)::value;
         static_assert(!FOLD || (LUT && ES == 1 && !RES), "folding belongs to the table form");
         static_assert((ES == 1) == OUT_I8, "INT8 kernels store bytes");
+        static_assert(!FOLD || DMA, "the table's address is in the constants that direct-to-LDS kernels make");
+        static_assert(RES != 2 || ES == 2, "a clamp that packing does: 16 bits");
         const int8_t* const lut = lds + EL::LDS_BYTES + PAR_BYTES;
-        const uint32_t lut_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)lds + (uint32_t)(EL::LDS_BYTES + PAR_BYTES);
+        const uint32_t lut_lds = (uint32_t)gelu_lut_at;
         const int32_t lut_hi = g.gelu_lut_n - 1;
         constexpr int SPB = BN + 16;                               // staged INT8 rows: 16-byte pieces, padded by one
         auto ost_at = [&](int row, int col) { return row * SPB + col; };
-        constexpr int SPH = 2 * BN + 8;                            // int16 rows: 8-byte pieces, padded by one
+        constexpr int SPH = 2 * BN + 8;                            // int16 rows: 8-byte pieces, padded by one (16-byte pieces: the same time)
         static_assert(SM == 0 || ES != 2 || BM * SPH <= 32 * JC * SP * 4, "the 16-bit staging tile ends where the constants begin");
         static_assert(SM != 1 || ES != 1 || BM * SPB <= 32 * JC * SP * 4, "the INT8 staging tile fits in front of the constants");
         static_assert(SM != 1 || !LUT, "GELU tiles do not leave through LDS");
@@ -878,16 +935,26 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
 #pragma clang loop unroll(full)
         for (int i = 0; i < FN; ++i) {
             const int cl = wn0 + 16 * i + 4 * fch;
-            const v4i bb = *reinterpret_cast<const v4i*>(par + cl);
-            const v4i mm = *reinterpret_cast<const v4i*>(par + BN + cl);
-            const v4i ss = *reinterpret_cast<const v4i*>(par + 2 * BN + cl);
             int64_t cc[4];
-            int32_t sh[4];
+            int32_t mm[4], sh[4];
+            if constexpr (DMA) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                cc[e] = (int64_t)bb[e] * mm[e] + ((int64_t)1 << ((ss[e] - 1) & 63));
-                if (FOLD) cc[e] -= (int64_t)(g.gelu_lut_lo - (int32_t)lut_lds) << (ss[e] & 63);
-                sh[e] = (ss[e] - 32) & 31;
+                for (int e = 0; e < 4; ++e) {
+                    const v4i c = made[cl + e];
+                    mm[e] = c[0];
+                    sh[e] = c[1];
+                    cc[e] = (int64_t)(((uint64_t)(uint32_t)c[3] << 32) | (uint32_t)c[2]);
+                }
+            } else {
+                const v4i bb = *reinterpret_cast<const v4i*>(par + cl);
+                const v4i m4 = *reinterpret_cast<const v4i*>(par + BN + cl);
+                const v4i ss = *reinterpret_cast<const v4i*>(par + 2 * BN + cl);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    mm[e] = m4[e];
+                    sh[e] = (ss[e] - 32) & 31;
+                    cc[e] = (int64_t)bb[e] * m4[e] + ((int64_t)1 << ((ss[e] - 1) & 63));
+                }
             }
             uint32_t pk[FM];
             if constexpr (FOLD) {
@@ -925,7 +992,12 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
                     int32_t v = (int32_t)(p >> 32) >> sh[e];
                     if (RES) {
                         const int32_t r8 = (int32_t)(int8_t)(pk[j] >> (8 * e));
-                        v += (int32_t)(((int64_t)r8 * g.res_m + g.res_rnd) >> g.res_s);
+                        if (RES == 2) v += smad24(r8, g.res_short.m, g.res_short.rnd) >> g.res_short.s;
+                        else v += (int32_t)(((int64_t)r8 * g.res_m + g.res_rnd) >> g.res_s);
+                    }
+                    if (RES == 2) {
+                        o[j][e] = v;
+                        continue;
                     }
                     if (LUT) {
                         // (the table covers [lo, lo + n) inside [-q_max, q_max] and the function is constant beyond its
@@ -952,7 +1024,8 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
                     else if (SM == 1) *reinterpret_cast<uint32_t*>(ostage + ost_at(row, colb)) = pk4;
                     else *reinterpret_cast<uint32_t*>(cp) = pk4;
                 } else if (ES == 2) {
-                    const uint2 pk2 = uint2{pack2_i16(o[j][0], o[j][1]), pack2_i16(o[j][2], o[j][3])};
+                    const uint2 pk2 = RES == 2 ? uint2{pack2_i16_above(o[j][0], o[j][1], -32767), pack2_i16_above(o[j][2], o[j][3], -32767)}
+                                               : uint2{pack2_i16(o[j][0], o[j][1]), pack2_i16(o[j][2], o[j][3])};
                     if (SM == 1) *reinterpret_cast<uint2*>(ostage + row * SPH + colb * 2) = pk2;
                     else *reinterpret_cast<uint2*>(cp) = pk2;
                 } else {
@@ -1031,9 +1104,11 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         // (GELU excludes a residual; without a table -- it did not fit, or the parameters are unusual -- the
         // arithmetic form runs, with the choice between its two variants made per value)
         if constexpr (GELU) {
-            if (g.gelu_lut_n > 0) {
-                if (fold_early) { if (g.c_vec16) finish_direct(F{}, F{}, T{}, I2{}, I1{}, T{}); else finish_direct(F{}, F{}, T{}, I0{}, I1{}, T{}); }
-                else { if (g.c_vec16) finish_direct(F{}, F{}, T{}, I2{}, I1{}, F{}); else finish_direct(F{}, F{}, T{}, I0{}, I1{}, F{}); }
+            if (DMA && g.gelu_lut_n > 0) {                         // (register-ring kernels are launched without a table)
+                if constexpr (DMA) {
+                    if (fold_early) { if (g.c_vec16) finish_direct(F{}, F{}, T{}, I2{}, I1{}, T{}); else finish_direct(F{}, F{}, T{}, I0{}, I1{}, T{}); }
+                    else { if (g.c_vec16) finish_direct(F{}, F{}, T{}, I2{}, I1{}, F{}); else finish_direct(F{}, F{}, T{}, I0{}, I1{}, F{}); }
+                }
             } else {
                 if (g.c_vec16) finish_direct(F{}, F{}, F{}, I2{}, I1{}, F{}); else finish_direct(F{}, F{}, F{}, I0{}, I1{}, F{});
             }
@@ -1047,8 +1122,11 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             }
         } else {
             if (g.c16) {
-                if constexpr (OST16) { if (R) finish_direct(T{}, F{}, F{}, I1{}, I2{}, F{}); else finish_direct(F{}, F{}, F{}, I1{}, I2{}, F{}); }
-                else { if (R) finish_direct(T{}, F{}, F{}, I0{}, I2{}, F{}); else finish_direct(F{}, F{}, F{}, I0{}, I2{}, F{}); }
+                if constexpr (OST16) {
+                    if (R && g.res_short.ok && clamp_hi == 32767) finish_direct(I2{}, F{}, F{}, I1{}, I2{}, F{});
+                    else if (R) finish_direct(T{}, F{}, F{}, I1{}, I2{}, F{});
+                    else finish_direct(F{}, F{}, F{}, I1{}, I2{}, F{});
+                } else { if (R) finish_direct(T{}, F{}, F{}, I0{}, I2{}, F{}); else finish_direct(F{}, F{}, F{}, I0{}, I2{}, F{}); }
             } else {
                 if (R) finish_direct(T{}, F{}, F{}, I0{}, I4{}, F{}); else finish_direct(F{}, F{}, F{}, I0{}, I4{}, F{});
             }
@@ -1128,9 +1206,10 @@ int launch_mfma(GemmArgs& g, bool i8, hipStream_t stream)
     constexpr size_t lds_tile = EpiLayout<BM, BN, BK, (DMA ? RING : 2)>::LDS_BYTES;
     static_assert(lds_tile <= 163840, "LDS budget");
     // (direct-to-LDS kernels keep the per-channel constants behind the stages)
-    constexpr size_t par_bytes = DMA ? (size_t)((3 * BN * 4 + 255) & ~255) : 0;
-    static_assert(lds_tile + par_bytes <= 163840, "LDS budget");
-    size_t lds_bytes = lds_tile + par_bytes;
+    constexpr size_t lds_par = DMA ? (size_t)par_bytes<BN>() : 0;
+    static_assert(lds_tile + lds_par <= 163840, "LDS budget");
+    size_t lds_bytes = lds_tile + lds_par;
+    g.res_short = DMA && !i8 ? residual_short(g) : ResShort{0, 0, 0, 0};
     if (GELU) {
         // the GELU table rides behind them if it fits the CU's 160 KB (and, for tiles that share a CU,
         // stays small enough not to cost a resident workgroup)

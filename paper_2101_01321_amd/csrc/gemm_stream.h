@@ -44,24 +44,6 @@
 
 namespace ibert {
 
-// A residual's requantization in 32 bits: DY(r) = (r m + rnd) >> s for every INT8 r, |m| < 2^23 -- the multiplier without its low eight
-// bits, where that changes none of the 256 values (ok).
-struct ResShort {
-    int32_t m, rnd, s, ok;
-};
-inline ResShort residual_short(const GemmArgs& g)
-{
-    if (!g.R) return ResShort{0, 0, 0, 1};
-    const int32_t s = g.res_s - 8;
-    if (s < 1 || s > 30) return ResShort{0, 0, 0, 0};
-    const int64_t m = ((int64_t)g.res_m + 128) >> 8;
-    if (m <= -(1 << 23) || m >= (1 << 23)) return ResShort{0, 0, 0, 0};
-    const int64_t rnd = (int64_t)1 << (s - 1);
-    int bad = 0;
-    for (int r = -128; r < 128; ++r) bad |= ((r * m + rnd) >> s) != (((int64_t)r * g.res_m + g.res_rnd) >> g.res_s);
-    return ResShort{(int32_t)m, (int32_t)rnd, s, !bad};
-}
-
 struct StreamArgs {
     const int8_t* A;
     const int8_t* W;
@@ -120,14 +102,6 @@ template <int FN>
 __host__ __device__ constexpr int lane_channel(int i, int r)
 {
     return i < 4 ? 4 * r + i : 64 + 2 * r + (i - 4);
-}
-
-// Two values as 16 bits each, saturated, and not below `low`.
-__device__ __forceinline__ uint32_t pack2_i16_above(int32_t a, int32_t b, int16_t low)
-{
-    typedef short v2s __attribute__((ext_vector_type(2)));
-    const v2s v = __builtin_elementwise_max(__builtin_amdgcn_cvt_pk_i16(a, b), v2s{low, low});
-    return __builtin_bit_cast(uint32_t, v);
 }
 
 // OUT_I8: INT8 output (no residual), with GELU if GELU; else INT16 output with or without residual.

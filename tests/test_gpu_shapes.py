@@ -331,6 +331,34 @@ def test_gemm_persistent_tiles_forms_of_the_epilogue(G, cfg, bn, clamp, shift, r
     _eq(got.astype(np.int64), oracle.gemm_requant(spec, A, W, bias, mult, shifts, R).reshape(-1).astype(np.int64), "persistent gemm, forms")
 
 
+# Constants made once a tile, one to three steps before they are used; residuals whose product fits 32 bits and (a
+# multiplier that rounds to 2^23, a shift of 8) does not, and 16-bit results that packing saturates or a smaller clamp does.
+@pytest.mark.parametrize("cfg,bn", [(7, 128), (9, 96), (13, 192), (14, 128), (17, 96), (18, 96), (19, 128), (21, 96), (22, 128)])
+@pytest.mark.parametrize("res,clamp", [(None, 32767), ((1717986816, 23), 32767), ((1717986816, 24), 30011), ((2147483647, 31), 32767), ((40000, 8), 32767),
+                                       ((2147483392, 38), 32767)])
+@pytest.mark.parametrize("K,shift", [(128, 33), (256, 40), (384, 62)])
+def test_gemm_direct_tiles_16_bit_epilogue(G, cfg, bn, res, clamp, K, shift):
+    from paper_2101_01321_amd import binding as B
+    M, N = 256 + 77, 2 * bn
+    rng = np.random.default_rng(cfg + K)
+    A, W = (rng.integers(-128, 128, size=(n, K), dtype=np.int8) for n in (M, N))
+    A[5], W[3] = -128, -128
+    bias = rng.integers(-(1 << 29), 1 << 29, size=N, dtype=np.int32) if shift > 40 else rng.integers(-50000, 50000, size=N, dtype=np.int32)
+    mult = (rng.integers(2 ** 28, 2 ** 31, size=N, dtype=np.int64) * rng.choice([-1, 1], size=N)).astype(np.int32)
+    shifts = np.clip(shift + np.arange(N) % 3 - 1, 33, 62).astype(np.int32)
+    R = None if res is None else rng.integers(-128, 128, size=(M, N), dtype=np.int8)
+    kw = dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K, ldw=K, ldc=N, ldr=N, per_channel=1, out_dtype=I16, out_clamp=clamp)
+    B.lib().ibert_gemm_config_override(cfg)
+    try:
+        G.say("16-bit epilogue cfg %d K=%d shift=%d res=%s clamp=%d" % (cfg, K, shift, res, clamp))
+        got = G.gemm(dict(kw, residual_dy=res or (1, 0)), A, W, bias, mult, shifts, R, out_elems=M * N)
+    finally:
+        B.lib().ibert_gemm_config_override(-1)
+    assert B.lib().ibert_last_kernel().decode().startswith(G.kernel_of(cfg))
+    spec = GemmSpec(M, N, K, per_channel=1, dy=(1, 0), out_dtype=I32, out_clamp=clamp, res_dy=res or (1, 0))
+    _eq(got.astype(np.int64), oracle.gemm_requant(spec, A, W, bias, mult, shifts, R).reshape(-1).astype(np.int64), "16-bit epilogue")
+
+
 @pytest.mark.parametrize("bn", [256, 192])
 def test_gemm_gelu_table_larger_than_the_persistent_tiles_have_room_for(G, bn):
     # an output scale of 2.5 at an input scale of 2^-6: saturated from 127 * 2.5 * 64 = 20320 on
