@@ -191,10 +191,10 @@ static uint32_t blocks_of(int32_t n, int b) { return ((uint32_t)n + (uint32_t)b 
 // again[] the extra cost of a tile that has to wait for a place (0 where share is 1).  (Tiles of gemm_few.h: n from its own
 // dealing of tiles to XCDs, and a share that depends on K.)  The coefficients are least-squares fits to 640 problems timed
 // on MI355X (K 128 to 8192, N 128 to 4096, 1 to 32768 rows, W changing from call to call), for 16-bit outputs with a
-// residual (32-bit ones use them too), INT8 outputs and GELU outputs; the fits were within 4 to 13 % (r.m.s.).  On problems that
-// no fit has seen (N 96 to 4352, K 128 to 4096, 1 to 32768 rows) the choice by the present table takes 0.5 % longer on average
-// than the best of all configurations with 145 without GELU, at worst 16 % ([884,1664] x K 256 + residual 6.4 against 5.5 us), and
-// 0.3 % with 260 with GELU, at worst 12 %.  Thresholds on tile counts, which the table replaced, took 16 % longer on average.
+// residual (32-bit ones use them too), INT8 outputs and GELU outputs; the fits were within 4 to 13 % (r.m.s.).  On 135 problems that
+// no fit has seen (N 192 to 4096, K 128 to 4096, 400 to 32768 rows) the choice by the present table takes 1.2 (16-bit with residual), 1.2 (INT8) and
+// 2.0 % (GELU) longer on average than the best of all configurations, at worst 19 % ([1024,3072] x K 1024 + GELU 10.4 against 8.8 us).
+// Thresholds on tile counts, which the table replaced, took 16 % longer on average.
 // Some lines they could not draw: [4096,1024] x K 4096 to 4096 rows more, 52 -> 40 us at 8192 rows; 2741 rows of [768] x K 3072
 // 25.1 -> 14.5 us (the last tile row is ragged); a second round of large tiles that would be nearly empty, [5120,1024] x K 1024
 // 19.7 -> 13.3 us.

@@ -33,6 +33,11 @@
 //     41.9, 35.6 / 32.0, 76.7 / 71.3, 104 / 101, 134 / 130.  Tried and not kept: the next tile's first operands held in registers over
 //     the epilogue, so that requests go on in its first half step (they queue behind the stores: 176 k -> 199 k cycles); a barrier at a tile's
 //     head in place of that (equal).
+//   * A 256x192 INT8 tile of K 768 took 18.8 thousand cycles (stamps): first step 2.1, five more 9.7 (7.7 of MFMA), clearing accumulators and requesting
+//     constants 0.7, head of the epilogue 1.1, values and stores 2.8 for the first wavefront of a SIMD, 4.7 for the second; 256x256 + GELU 25.8: 2.5, 12.5, 1.1,
+//     1.5, 6.3 / 7.6.  What stands between loop and values is gone or shorter since: the first step's MFMAs add to zero, constants are requested a
+//     tile ahead (at a tile's head they stood behind the stores), the tests of the head are minima and maxima.  us: [32768,3072] x K 1024 INT8 104.5 ->
+//     101.0, [32768,4096] x K 1024 + GELU 141.1 -> 137.3, [32768,768] x K 768 INT16 + residual 33.1 -> 32.4 (a card that power binds).
 //   * Measured against one workgroup per tile, us, W cold, when it came: [32768,4096] x K 1024 with GELU 212 -> 142, [15311,3072] x K 768
 //     with GELU 115 -> 45 (any M: tiles may be ragged), [32768,1024] x K 1024 + residual 62 -> 44.
 //   * The vector registers must hold everything: with one of them spilled the loop takes 1.6 times as long, even where no scratch is

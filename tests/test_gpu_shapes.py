@@ -386,8 +386,8 @@ def test_gemm_gelu_table_larger_than_the_persistent_tiles_have_room_for(G, bn):
 @pytest.mark.parametrize("kind", ["i8", "i16", "i16res", "gelu"])
 @pytest.mark.parametrize("cols,shift", [(3, 40), (9, 40), (3, 30)])
 def test_gemm_persistent_tiles_of_one_step(G, cfg, bn, kind, cols, shift):
-    # K 128: a tile is a single K step, so the constants of its columns, requested at its head, have that step alone to arrive
-    # in.  More than four tiles for every workgroup, in another tile column each time (3 and 9 do not divide the 32
+    # K 128: a tile is a single K step, so the constants of the next tile's columns, requested behind it, have the epilogue alone to
+    # arrive in.  More than four tiles for every workgroup, in another tile column each time (3 and 9 do not divide the 32
     # workgroups of an XCD), and constants that differ from column to column by far more than an output step.  The rows
     # repeat after 509 (which no tile edge does), so that the oracle's work stays small.
     import torch
