@@ -415,8 +415,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         auto load_residual = [&](int unit) {
 #pragma unroll
             for (int k = 0; k < RR.mv; ++k)
+                // (the unit's rows in the lane's offset: a scalar offset is documented as no part of the buffer's range check, so rows past M would pass it)
                 rt[OUT_I8 ? 0 : unit % AHEAD][k] = __builtin_amdgcn_raw_buffer_load_b128(
-                    rb, (wm0 + moved_row(RR, k)) * ga->ldr + wn0 + (64 * k + el) % RR.cp * 16, unit * RR.unit * 16 * ga->ldr, 0);
+                    rb, (wm0 + unit * RR.unit * 16 + moved_row(RR, k)) * ga->ldr + wn0 + (64 * k + el) % RR.cp * 16, 0, 0);
         };
         // Fast form: every shift in [33, 62], every |bias| and K * 127^2 below 2^30 (|acc + bias| stays below 2^31), the residual shift in [8, 62] (see gemm_kernel.h),
         // and a GELU table.

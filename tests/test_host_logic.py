@@ -432,3 +432,30 @@ def test_weights_read_ahead_for_every_tile():
 def test_gelu_tile_chosen_is_the_fastest_measured(M, N, K, config):
     # problems at which the configuration named was the fastest of all on the device, most by 4 to 17 % before the next
     assert _weight_plan(M, N, K, "gelu")[0][0] == config
+
+
+# ------------------------------------------------------------------------------------------- buffers that end with the last row
+def test_rows_of_the_persistent_tiles_are_checked_whole_against_the_buffers_end(tmp_path):
+    # Output and residual are buffers that end with the last row, so that lanes past it neither load nor store.  The range check takes the
+    # lane's offset alone: with a part of the row in the scalar offset, lanes past M would pass it.  Looked up in the built code: all that
+    # moves between such a buffer and registers has no scalar offset.  (Operands go to LDS, with the K step as the scalar offset:
+    # their rows past M fail on the lane's offset.)
+    import os
+    import re
+    import shutil
+    import subprocess
+    from paper_2101_01321_amd import build
+    tool = "/opt/rocm/llvm/bin/llvm-objdump"
+    if not os.path.exists(tool):
+        pytest.skip("no disassembler")
+    so = shutil.copy(build.LIB, tmp_path)
+    subprocess.run([tool, "--offloading", so], check=True, capture_output=True, cwd=tmp_path)
+    seen = {"buffer_load": 0, "buffer_store": 0}
+    for part in sorted(tmp_path.glob("*gfx950")):
+        text = subprocess.run([tool, "-d", "--no-show-raw-insn", str(part)], check=True, capture_output=True, text=True).stdout
+        for line in re.findall(r"^\s+(buffer_(?:load|store)_dword.*)$", text, re.M):
+            if " lds" in line:
+                continue
+            seen[line[:line.index("_dword")]] += 1
+            assert re.match(r"buffer_\w+ v\S+, v\d+, s\[[0-9:]+\], 0 offen", line), line
+    assert seen["buffer_load"] >= 8 and seen["buffer_store"] >= 32, seen
