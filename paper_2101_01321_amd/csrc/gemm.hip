@@ -255,8 +255,8 @@ static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb
             if (w.first[0] == 0 || (f.direct && !dma_ok(d, f.bn))) continue;
             if (c.config == 23 && !stream_ok<256, 256, 8>(g, i8)) continue;
             if (c.config == 24 && !stream_ok<256, 192, 8>(g, i8)) continue;
-            // (a GELU table of more than 16 KB, which takes an output scale above 2 at an input scale of 2^-6, finds no room beside the
-            // persistent tiles; the others hold up to 46 KB)
+            // (a GELU table of more than 26 thousand entries beside 256x256, 44 beside 256x192, which take output scales above 3 at an input
+            // scale of 2^-6, finds no room beside the persistent tiles)
             if (gelu && (c.config == 23 ? g.gelu_lut_n > StreamLayout<256, 256, 8, true, true>::ROOM
                                         : c.config == 24 && g.gelu_lut_n > StreamLayout<256, 192, 8, true, true>::ROOM)) continue;
             const int64_t k = d.K / 128;

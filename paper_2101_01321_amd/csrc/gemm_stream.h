@@ -26,7 +26,7 @@
 //     against 1.75 to 1.95; [32768,3072] x K 1024 105 -> 80 us).  A loop of nothing but the step's MFMAs sustains 4.05 POP/s on random
 //     operands, with its LDS reads 3.5, with its requests 3.0 -- 1425 ns a step, about what a step takes here.
 //   * An epilogue is what the address unit, then the ALU, make of it.  Rows leave and residuals come with neighbouring lanes on neighbouring
-//     bytes, through LDS (see `turn`), one unit of rows at a time while the next is being made; the MFMA's first operand are the rows of
+//     bytes, through LDS (see `turn`; with GELU as they are), one unit of rows at a time while the next is being made; the MFMA's first operand are the rows of
 //     A, so that a lane has the same few channels for all its tokens and their constants are made once.  Cycles of a launch, thousands, with
 //     lane swaps in place of LDS and stores that left together at the end / as it is: [32768,1024] x K 1024 INT16 + residual 84.0 / 73.5,
 //     [32768,768] x K 768 63 / 56.5, x K 3072 133 / 125, [32768,3072] x K 1024 INT8 175 / 166, [32768,4096] x K 1024 + GELU 250 / 237; us: 45.3 /
@@ -96,7 +96,7 @@ struct StreamLayout {
     static constexpr int STAGE = (BM + BN) * 128;
     static constexpr int PAR = 2 * STAGE;                          // two buffers of 3 x BN constants
     static constexpr int TURN = PAR + 2 * 3 * BN * 4;              // rows on their way out, see `turn`
-    static constexpr int TURN_WAVE = BN % 128 == 0 ? (OUT_I8 ? 1280 : 2560) : 3584;     // bytes per wavefront
+    static constexpr int TURN_WAVE = GELU ? 0 : BN % 128 == 0 ? (OUT_I8 ? 1280 : 2560) : 3584;     // bytes per wavefront
     static constexpr int LUT = TURN + NW * TURN_WAVE;
     static constexpr int ROOM = 163840 - LUT;                      // for the GELU table
 };
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
         };
         constexpr Rows RO = OUT_I8 ? (FN == 4 ? Rows{4, 80, 1, 1} : Rows{6, 112, 2, 3}) : (FN == 4 ? Rows{8, 160, 1, 2} : Rows{12, 224, 1, 3});
         constexpr Rows RR = FN == 4 ? Rows{4, 80, 1, 1} : Rows{6, 112, 2, 3};          // residual
-        static_assert(16 * RO.unit * RO.pitch <= SL::TURN_WAVE && (OUT_I8 || 16 * RR.unit * RR.pitch <= SL::TURN_WAVE), "place to turn rows");
+        static_assert(GELU || (16 * RO.unit * RO.pitch <= SL::TURN_WAVE && (OUT_I8 || 16 * RR.unit * RR.pitch <= SL::TURN_WAVE)), "place to turn rows");
         static_assert(16 * RO.unit * RO.cp == 64 * RO.mv && FM % RO.unit == 0 && FM % RR.unit == 0, "whole units");
         auto moved_row = [&](const Rows& r, int k) { return (64 * k + el) / r.cp; };
         auto moved_at = [&](const Rows& r, int k) { return moved_row(r, k) * r.pitch + (64 * k + el) % r.cp * 16; };
@@ -508,8 +508,24 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
                 constexpr int LAG = 12 / FN;                       // (a wait can leave at most 15 reads outstanding)
                 const int32_t lo = (int32_t)lut_lds;
                 int32_t by[TOKENS][FN];
+                // Tokens are stored as they are packed, four bytes a lane (and two): neighbouring lanes are on neighbouring bytes of four rows as it
+                // is.  With the rows turned in LDS first the time was the same ([32768,4096] x K 1024 131.8 / 131.1 us, [4096,3072] x K 768 16.4 / 16.3),
+                // and what that takes of LDS is room of the table: one of 20 thousand entries found none on 256x256 then, 140 -> 282 us.
+                constexpr int HELD = HOLD * 4 * RO.unit;           // (tokens, see HOLD)
+                uint32_t w4[TOKENS], w2[TOKENS];
+                const int corner = (wm0 + 4 * u) * ga->ldc + wn0;
+                auto store_token = [&](int n) {
+                    const int at = corner + (16 * (n / 4) + n % 4) * ga->ldc;
+                    __builtin_amdgcn_raw_buffer_store_b32(w4[n], cb, at + 4 * r16, 0, 0);
+                    if (FN == 6) __builtin_amdgcn_raw_buffer_store_b16((uint16_t)w2[n], cb, at + 64 + 2 * r16, 0, 0);
+                };
                 auto pack = [&](int n) {
-                    put(n, pack4_perm(by[n][0], by[n][1], by[n][2], by[n][3]), 0u, FN == 6 ? __builtin_amdgcn_perm(by[n][FN - 1], by[n][FN - 2], 0x0c0c0400u) : 0u);
+                    w4[n] = pack4_perm(by[n][0], by[n][1], by[n][2], by[n][3]);
+                    w2[n] = FN == 6 ? __builtin_amdgcn_perm(by[n][FN - 1], by[n][FN - 2], 0x0c0c0400u) : 0u;
+                    if (n + 1 == HELD) __builtin_amdgcn_s_waitcnt(vm(0));
+#pragma unroll
+                    for (int x = n + 1 == HELD ? 0 : n; x <= n; ++x)
+                        if (n + 1 >= HELD) store_token(x);
                 };
                 auto finish = [&](auto fold_tag) {
                     constexpr bool FOLD = decltype(fold_tag)::value;
@@ -593,7 +609,7 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
                 };
                 if (ga->res_short.ok && clamp_hi == 32767) finish(T{}); else finish(F{});
             }
-            store(UNITS - 1);
+            if constexpr (!GELU) store(UNITS - 1);
         } else {
             // Any constants: 64-bit arithmetic in a rolled loop, 16 rows of each row of wavefronts at a time through LDS, where the
             // next tile's first steps had arrived -- they are requested again afterwards.  (Unrolled over the accumulators like

@@ -359,26 +359,35 @@ def test_gemm_direct_tiles_16_bit_epilogue(G, cfg, bn, res, clamp, K, shift):
     _eq(got.astype(np.int64), oracle.gemm_requant(spec, A, W, bias, mult, shifts, R).reshape(-1).astype(np.int64), "16-bit epilogue")
 
 
-@pytest.mark.parametrize("bn", [256, 192])
-def test_gemm_gelu_table_larger_than_the_persistent_tiles_have_room_for(G, bn):
-    # an output scale of 2.5 at an input scale of 2^-6: saturated from 127 * 2.5 * 64 = 20320 on
+# Output scales and the length of the table that they take: a usual one, one of 20 thousand entries, the largest that 256x256 (26624) and 256x192 (44544)
+# have room for and one or two more; saturated from 127 S_out / S_in on
+@pytest.mark.parametrize("bn,S,S_out,fits", [(256, 2.0 ** -6, 0.7, 1), (256, 2.0 ** -6, 2.5, 1), (256, 2.0 ** -6, 3.2685, 1), (256, 2.0 ** -6, 3.2688, 0),
+                                             (192, 2.0 ** -6, 2.5, 1), (192, 2.0 ** -5, 10.9846, 1), (192, 2.0 ** -5, 10.9848, 0)])
+def test_gemm_gelu_table_larger_than_the_persistent_tiles_have_room_for(G, bn, S, S_out, fits):
+    import torch
     from paper_2101_01321_amd import binding as B
-    M, N, K = 256 * 90, 4 * bn, 128
+    M, N, K = 256 * 90 - 7, 4 * bn, 128
     rng = np.random.default_rng(bn)
     A, W = (rng.integers(-127, 128, size=(n, K), dtype=np.int8) for n in (M, N))
     mult = rng.integers(2 ** 30, 2 ** 31, size=N, dtype=np.int64).astype(np.int32)
     shifts = np.full(N, 33, np.int32)
-    gp, op = B.ibert_gelu_params_from_scale(2.0 ** -6, 2.5), P.gelu_params(2.0 ** -6, 2.5)
+    gp, op = B.ibert_gelu_params_from_scale(S, S_out), P.gelu_params(S, S_out)
     kw = dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K, ldw=K, ldc=N, ldr=N, per_channel=1)
     want = oracle.gelu(oracle.gemm_requant(GemmSpec(M, N, K, per_channel=1, out_dtype=I32, out_clamp=gp.q_max), A, W, None, mult, shifts, None).reshape(-1), op)
+    word = torch.zeros(1, dtype=torch.int32, device=G.DEV)
     for cfg in (-1, 23 if bn == 256 else 24):
         B.lib().ibert_gemm_config_override(cfg)
+        B.ibert_gemm_epilogue_record(word)
         try:
-            G.say("GELU with a large table, cfg %d bn %d" % (cfg, bn))
+            G.say("GELU with a large table, cfg %d bn %d S_out %g" % (cfg, bn, S_out))
             got = G.gemm_gelu(dict(kw, out_dtype=I8, out_clamp=5), A, W, None, mult, shifts, gp, M * N)[0]
         finally:
+            B.ibert_gemm_epilogue_record(None)
             B.lib().ibert_gemm_config_override(-1)
-        assert B.lib().ibert_last_kernel().decode().startswith("gemm_stream_kernel") == (cfg >= 0)
+        # chosen where its table fits; forced on one that does not, it computes GELU value by value
+        assert B.lib().ibert_last_kernel().decode().startswith("gemm_stream_kernel") == bool(fits or cfg >= 0)
+        if fits or cfg >= 0:
+            assert int(word.item()) == (B.EPILOGUE_DIRECT_GELU_TABLE if fits else B.EPILOGUE_STAGED)
         _eq(got.astype(np.int64), want.astype(np.int64), "GELU with a large table")
 
 
