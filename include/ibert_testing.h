@@ -52,9 +52,12 @@ int ibert_attention_buffers(int32_t seq, int32_t form, int64_t workgroups, int32
  * what each reads ahead when an encoder plans for it.  plan: the tile configuration chosen, then rows and xs: XCD x is to have the row
  * blocks (j << xs) + x % 2^xs of `rows` rows each.  readers[n] (N bytes, zeroed by the caller): bit x is set where a workgroup on XCD x
  * multiplies row n, by the kernel's own dealing of tiles.  ahead[x * N K / 1024 + i] (8 N K / 1024 bytes, zeroed): how often XCD x reads
- * the i-th KB ahead, by the attention kernel's own arithmetic (nothing of a W above 32 MB).  gelu: with the GELU epilogue.
- * IBERT_ERR_NOT_IMPLEMENTED: nothing is planned for such operands; IBERT_ERR_SHAPE: a read past the end of W.  Host only. */
+ * the i-th KB ahead, by the attention kernel's own arithmetic (nothing of a W above 32 MB).  gelu: with the GELU epilogue,
+ * at an input scale of 2^-6 and an output scale of 8 / 127.  IBERT_ERR_NOT_IMPLEMENTED: nothing is planned for such operands; IBERT_ERR_SHAPE: a read past the end of W.  Host only. */
 int ibert_gemm_weight_plan(const ibert_gemm_desc* desc, int32_t gelu, int32_t plan[3], uint8_t* readers, uint8_t* ahead);
+
+/* The same with the GELU epilogue at these parameters, whose table some tiles have no room for. */
+int ibert_gemm_gelu_weight_plan(const ibert_gemm_desc* desc, const ibert_gelu_params* gelu, int32_t plan[3], uint8_t* readers, uint8_t* ahead);
 
 #ifdef __cplusplus
 }

@@ -101,6 +101,7 @@ SIGNATURES = {
     "ibert_gemm_xcd_blocks": (None, [C.c_int32]),
     "ibert_attention_buffers": (C.c_int, [C.c_int32, C.c_int32, C.c_int64] + 3 * [C.POINTER(C.c_int32)]),
     "ibert_gemm_weight_plan": (C.c_int, [C.POINTER(GemmDesc), C.c_int32, C.POINTER(C.c_int32), _P, _P]),
+    "ibert_gemm_gelu_weight_plan": (C.c_int, [C.POINTER(GemmDesc), C.POINTER(GeluParams), C.POINTER(C.c_int32), _P, _P]),
     "ibert_last_kernel": (C.c_char_p, []),
     "ibert_gemm_i8_gelu": (C.c_int, [C.POINTER(GemmDesc)] + [_P] * 5 + [C.POINTER(GeluParams)] + [_P] * 3),
     "ibert_isqrt_i": (C.c_int, [_P, _P, C.c_int64, C.c_int32, _P]),

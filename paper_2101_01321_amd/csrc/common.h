@@ -195,9 +195,9 @@ struct ReadAhead {
 int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias,
                 const int32_t* mult, const int32_t* shift, const int8_t* residual, void* C,
                 hipStream_t stream, const ibert_gelu_params* gelu = nullptr);
-// How launch_gemm will share W (gelu: with the GELU epilogue).
+// How launch_gemm will share W (gelu: with the GELU epilogue, whose table decides on the tile too).
 GemmPlan plan_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias, const int32_t* mult,
-                   const int32_t* shift, const int8_t* residual, const void* C, bool gelu);
+                   const int32_t* shift, const int8_t* residual, const void* C, const ibert_gelu_params* gelu);
 int launch_gemm_gelu(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias,
                      const int32_t* mult, const int32_t* shift, const ibert_gelu_params& gelu, int8_t* C,
                      int32_t* scratch, hipStream_t stream);

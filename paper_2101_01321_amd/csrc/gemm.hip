@@ -327,6 +327,14 @@ static GemmArgs gemm_args(const ibert_gemm_desc& d, const int8_t* A, const int8_
     return g;
 }
 
+// With the GELU epilogue.
+static void gelu_args(GemmArgs& g, const ibert_gelu_params& p)
+{
+    g.gelu = GeluConst{p.q_b, p.q_c, p.q_1, p.q_max, p.out.m, p.out.s};
+    g.gelu_fast = gelu_fast_ok(p) ? 1 : 0;
+    gelu_table_range(p, &g.gelu_lut_lo, &g.gelu_lut_n);
+}
+
 // Rows whose 16-byte chunks are aligned, W as [N,K].
 static bool rows_aligned(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W)
 {
@@ -335,12 +343,13 @@ static bool rows_aligned(const ibert_gemm_desc& d, const int8_t* A, const int8_t
 }
 
 GemmPlan plan_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, const int32_t* bias, const int32_t* mult,
-                   const int32_t* shift, const int8_t* residual, const void* C, bool gelu)
+                   const int32_t* shift, const int8_t* residual, const void* C, const ibert_gelu_params* gelu)
 {
     GemmPlan p;
     if (d.batch_outer != 1 || d.batch_inner != 1 || d.M < 1 || d.N < 1 || d.ldw != d.K || d.K % 128 != 0 || !rows_aligned(d, A, W)) return p;
     GemmArgs g = gemm_args(d, A, W, bias, mult, shift, residual, const_cast<void*>(C));
-    const int cfg = choose_config(d, g, 1, gelu);
+    if (gelu) gelu_args(g, *gelu);
+    const int cfg = choose_config(d, g, 1, gelu != nullptr);
     const GemmConfig& f = kConfigs[cfg];
     if (d.N % f.bn != 0) return p;
     if (cfg >= 25) {
@@ -364,7 +373,7 @@ GemmPlan plan_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, c
 }
 
 // For tests, see ibert_testing.h.
-static int weight_plan(const ibert_gemm_desc& d, bool gelu, int32_t out[3], uint8_t* readers, uint8_t* ahead)
+static int weight_plan(const ibert_gemm_desc& d, const ibert_gelu_params* gelu, int32_t out[3], uint8_t* readers, uint8_t* ahead)
 {
     alignas(16) static const int32_t any[4] = {};                  // (an aligned address; nothing is read)
     int8_t* const p = reinterpret_cast<int8_t*>(const_cast<int32_t*>(any));
@@ -372,7 +381,8 @@ static int weight_plan(const ibert_gemm_desc& d, bool gelu, int32_t out[3], uint
     const GemmPlan plan = plan_gemm(d, p, p, any, any, any, residual, p, gelu);
     if (plan.rows < 1) return IBERT_ERR_NOT_IMPLEMENTED;
     GemmArgs g = gemm_args(d, p, p, any, any, any, residual, p);
-    const int cfg = choose_config(d, g, 1, gelu);
+    if (gelu) gelu_args(g, *gelu);
+    const int cfg = choose_config(d, g, 1, gelu != nullptr);
     const GemmConfig& f = kConfigs[cfg];
     out[0] = cfg; out[1] = plan.rows; out[2] = plan.xs;
     auto reads = [&](int xcd, int tm, int tn) {
@@ -435,9 +445,7 @@ int launch_gemm(const ibert_gemm_desc& d, const int8_t* A, const int8_t* W, cons
     const bool i8 = d.out_dtype == IBERT_I8;
     if (gelu) {
         if (!i8 || residual || d.out_clamp != gelu->q_max) return IBERT_ERR_NOT_IMPLEMENTED;
-        g.gelu = GeluConst{gelu->q_b, gelu->q_c, gelu->q_1, gelu->q_max, gelu->out.m, gelu->out.s};
-        g.gelu_fast = gelu_fast_ok(*gelu) ? 1 : 0;
-        gelu_table_range(*gelu, &g.gelu_lut_lo, &g.gelu_lut_n);
+        gelu_args(g, *gelu);
     }
     const bool fast = rows_aligned(d, A, W);
     if (gelu && !(fast && d.K % 16 == 0)) return IBERT_ERR_NOT_IMPLEMENTED;
@@ -570,7 +578,16 @@ extern "C" const char* ibert_last_kernel(void) { return ibert::g_last_kernel; }
 extern "C" int ibert_gemm_weight_plan(const ibert_gemm_desc* desc, int32_t gelu, int32_t plan[3], uint8_t* readers, uint8_t* ahead)
 {
     if (!desc || !plan || !readers || !ahead) return IBERT_ERR_NULL;
-    return ibert::weight_plan(*desc, gelu != 0, plan, readers, ahead);
+    ibert_gelu_params usual;
+    const int rc = ibert_gelu_params_from_scale(1.0 / 64, 8.0 / 127, &usual);
+    return rc ? rc : ibert::weight_plan(*desc, gelu ? &usual : nullptr, plan, readers, ahead);
+}
+
+extern "C" int ibert_gemm_gelu_weight_plan(const ibert_gemm_desc* desc, const ibert_gelu_params* gelu, int32_t plan[3], uint8_t* readers, uint8_t* ahead)
+{
+    if (!desc || !gelu || !plan || !readers || !ahead) return IBERT_ERR_NULL;
+    const int rc = ibert::check_gelu(*gelu);
+    return rc ? rc : ibert::weight_plan(*desc, gelu, plan, readers, ahead);
 }
 
 extern "C" void ibert_gemm_xcd_blocks(int32_t on) { ibert::g_xcd_blocks = on != 0; }

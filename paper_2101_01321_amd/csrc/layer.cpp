@@ -175,19 +175,20 @@ static ibert_gemm_desc projection(int64_t T, int64_t N, int64_t K, int32_t out_d
 
 // How the MatMuls of a layer share their weights among the XCDs.  The layers of a call have one shape: made once a call, as a
 // forward of few tokens is bound by what the host does (a forward of Base, host, us: 220 without plans, 232 with twelve, 219 with one
-// and the choice of a tile in half its time).
+// and the choice of a tile in half its time).  The GELU parameters are those of the first layer: a layer whose table is so much larger that another
+// tile is chosen for it has its weights brought nearer, but not to the XCDs that read them.
 struct LayerPlan {
     GemmPlan o, up, down, qkv;
-    LayerPlan(const ibert_layer_weights& w, const int8_t* x, int8_t* y, int64_t T, int64_t H, int64_t F, char* ws, const ibert_layer_workspace_layout& lo)
+    LayerPlan(const ibert_layer_weights& w, const ibert_gelu_params& gelu, const int8_t* x, int8_t* y, int64_t T, int64_t H, int64_t F, char* ws, const ibert_layer_workspace_layout& lo)
     {
         auto plan = [&](int64_t N, int64_t K, int32_t dtype, const void* in, const int8_t* wt, const int32_t* bias, const int32_t* m,
-                        const int32_t* s, const void* res, const void* out, bool gelu) {
-            return plan_gemm(projection(T, N, K, dtype, 127), (const int8_t*)in, wt, bias, m, s, (const int8_t*)res, out, gelu);
+                        const int32_t* s, const void* res, const void* out, const ibert_gelu_params* with = nullptr) {
+            return plan_gemm(projection(T, N, K, dtype, 127), (const int8_t*)in, wt, bias, m, s, (const int8_t*)res, out, with);
         };
-        o = plan(H, H, IBERT_I16, ws + lo.ctx, w.w_o, w.b_o, w.m_o, w.s_o, x, ws + lo.r1, false);
-        up = plan(F, H, IBERT_I8, ws + lo.h1, w.w_1, w.b_1, w.m_1, w.s_1, nullptr, ws + lo.g, true);
-        down = plan(H, F, IBERT_I16, ws + lo.g, w.w_2, w.b_2, w.m_2, w.s_2, ws + lo.h1, ws + lo.r2, false);
-        qkv = plan(3 * H, H, IBERT_I8, y, w.w_qkv, w.b_qkv, w.m_qkv, w.s_qkv, nullptr, ws + lo.qkv, false);
+        o = plan(H, H, IBERT_I16, ws + lo.ctx, w.w_o, w.b_o, w.m_o, w.s_o, x, ws + lo.r1);
+        up = plan(F, H, IBERT_I8, ws + lo.h1, w.w_1, w.b_1, w.m_1, w.s_1, nullptr, ws + lo.g, &gelu);
+        down = plan(H, F, IBERT_I16, ws + lo.g, w.w_2, w.b_2, w.m_2, w.s_2, ws + lo.h1, ws + lo.r2);
+        qkv = plan(3 * H, H, IBERT_I8, y, w.w_qkv, w.b_qkv, w.m_qkv, w.s_qkv, nullptr, ws + lo.qkv);
     }
 };
 
@@ -532,7 +533,7 @@ int ibert_encoder_masked_i(const ibert_layer_weights* weights, const ibert_layer
     int8_t* pp[2] = {reinterpret_cast<int8_t*>(ws + lo.total), reinterpret_cast<int8_t*>(ws + lo.total + act)};
     const int8_t* in = x;
     std::optional<ibert::LayerPlan> plan;
-    if (n_layers > 1) plan.emplace(weights[0], x, pp[0], (int64_t)batch * seq, hidden, ffn, ws, lo);
+    if (n_layers > 1) plan.emplace(weights[0], quant[0].gelu, x, pp[0], (int64_t)batch * seq, hidden, ffn, ws, lo);
     for (int32_t l = 0; l < n_layers; ++l) {
         int8_t* out = (l == n_layers - 1) ? y : pp[l & 1];
         rc = ibert::run_layer(weights[l], plan ? &*plan : nullptr, l + 1 < n_layers ? weights + l + 1 : nullptr, quant[l], in, out, batch, seq, hidden, heads, ffn, key_lens, ws, lo, false,

@@ -361,19 +361,22 @@ def test_shift_and_subtract_square_root_recipe_is_exact():
 
 
 # ------------------------------------------------------------------------------------------- weights read ahead
-def _weight_plan(M, N, K, kind):
+def _weight_plan(M, N, K, kind, gelu=None):
     d = B.GemmDesc()
     for k, v in dict(M=M, N=N, K=K, batch_outer=1, batch_inner=1, lda=K, ldw=K, ldc=N, ldr=N, per_channel=1,
                      out_dtype=B.I16 if kind == "i16res" else B.I8, out_clamp=127).items():
         setattr(d, k, v)
     plan, readers, ahead = (C.c_int32 * 3)(), np.zeros(N, np.uint8), np.zeros((8, N * K // 1024), np.uint8)
-    rc = B.lib().ibert_gemm_weight_plan(C.byref(d), kind == "gelu", plan, readers.ctypes.data, ahead.ctypes.data)
+    if gelu is None:
+        rc = B.lib().ibert_gemm_weight_plan(C.byref(d), kind == "gelu", plan, readers.ctypes.data, ahead.ctypes.data)
+    else:
+        rc = B.lib().ibert_gemm_gelu_weight_plan(C.byref(d), C.byref(gelu), plan, readers.ctypes.data, ahead.ctypes.data)
     assert rc == 0, (M, N, K, kind, rc)                       # (a read past the end of W is an error)
     return list(plan), readers, ahead
 
 
-def _check_weight_plan(M, N, K, kind):
-    (config, rows, xs), readers, ahead = _weight_plan(M, N, K, kind)
+def _check_weight_plan(M, N, K, kind, gelu=None):
+    (config, rows, xs), readers, ahead = _weight_plan(M, N, K, kind, gelu)
     case = (M, N, K, kind, config, rows, xs)
     assert readers.all() and N % rows == 0, case
     assert ahead.max() == 1 and ahead.any(axis=0).all(), case            # all of W, nothing twice by one XCD
@@ -398,6 +401,16 @@ def test_weights_read_ahead_are_those_the_kernels_read(H, F):
         for N, K, kind in ((3 * H, H, "i8"), (H, H, "i16res"), (F, H, "gelu"), (H, F, "i16res")):
             seen.add(_check_weight_plan(M, N, K, kind))
     assert len(seen) > 4, seen
+
+
+# (the same parameters as in the test of the table's room on the device: what is planned is what is launched)
+@pytest.mark.parametrize("bn,S,S_out,fits", [(256, 2.0 ** -6, 0.7, 1), (256, 2.0 ** -6, 3.2685, 1), (256, 2.0 ** -6, 3.2688, 0),
+                                             (192, 2.0 ** -6, 2.5, 1), (192, 2.0 ** -5, 10.9846, 1), (192, 2.0 ** -5, 10.9848, 0)])
+def test_weights_read_ahead_follow_the_gelu_table(bn, S, S_out, fits):
+    # a table that finds no room beside the persistent tiles sends the MatMul to another tile, which shares its weights in another way
+    gp = B.ibert_gelu_params_from_scale(S, S_out)
+    config = _check_weight_plan(256 * 90 - 7, 4 * bn, 128, "gelu", gp)
+    assert (config in (23, 24)) == bool(fits), config
 
 
 @pytest.mark.parametrize("N,K,kind,read", [(32768, 1024, "gelu", 1), (32768 + 128, 1024, "gelu", 0), (1024, 32768, "i16res", 1),
