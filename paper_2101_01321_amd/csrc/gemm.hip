@@ -255,10 +255,11 @@ static int choose_config(const ibert_gemm_desc& d, const GemmArgs& g, int64_t nb
             if (w.first[0] == 0 || (f.direct && !dma_ok(d, f.bn))) continue;
             if (c.config == 23 && !stream_ok<256, 256, 8>(g, i8)) continue;
             if (c.config == 24 && !stream_ok<256, 192, 8>(g, i8)) continue;
-            // (a GELU table of more than 26 thousand entries beside 256x256, 44 beside 256x192, which take output scales above 3 at an input
-            // scale of 2^-6, finds no room beside the persistent tiles)
-            if (gelu && (c.config == 23 ? g.gelu_lut_n > StreamLayout<256, 256, 8, true, true>::ROOM
-                                        : c.config == 24 && g.gelu_lut_n > StreamLayout<256, 192, 8, true, true>::ROOM)) continue;
+            // Without a table the persistent tiles compute GELU in their 64-bit epilogue, the others in the direct one, and are ahead, us: no table
+            // (an input scale of 2^-9) [32768,4096] x K 1024 356 / 262, [4096,3072] x K 768 36.3 / 21.4; no room for it (more than 26
+            // thousand entries beside 256x256, 44 beside 256x192: output scales above 3 at an input scale of 2^-6) [32768,4096] x K 1024 354 / 331.
+            if (gelu && (c.config == 23 || c.config == 24) &&
+                (g.gelu_lut_n == 0 || g.gelu_lut_n > (c.config == 23 ? StreamLayout<256, 256, 8, true, true>::ROOM : StreamLayout<256, 192, 8, true, true>::ROOM))) continue;
             const int64_t k = d.K / 128;
             const int64_t one = w.first[0] + w.first[1] * k;            // (the other terms only add to it)
             if (best >= 0 && one >= best_t) continue;

@@ -362,7 +362,8 @@ def test_gemm_direct_tiles_16_bit_epilogue(G, cfg, bn, res, clamp, K, shift):
 # Output scales and the length of the table that they take: a usual one, one of 20 thousand entries, the largest that 256x256 (26624) and 256x192 (44544)
 # have room for and one or two more; saturated from 127 S_out / S_in on
 @pytest.mark.parametrize("bn,S,S_out,fits", [(256, 2.0 ** -6, 0.7, 1), (256, 2.0 ** -6, 2.5, 1), (256, 2.0 ** -6, 3.2685, 1), (256, 2.0 ** -6, 3.2688, 0),
-                                             (192, 2.0 ** -6, 2.5, 1), (192, 2.0 ** -5, 10.9846, 1), (192, 2.0 ** -5, 10.9848, 0)])
+                                             (192, 2.0 ** -6, 2.5, 1), (192, 2.0 ** -5, 10.9846, 1), (192, 2.0 ** -5, 10.9848, 0),
+                                             (256, 2.0 ** -9, 0.06, 0), (192, 2.0 ** -9, 0.06, 0)])                   # no table at all
 def test_gemm_gelu_table_larger_than_the_persistent_tiles_have_room_for(G, bn, S, S_out, fits):
     import torch
     from paper_2101_01321_amd import binding as B

@@ -405,7 +405,8 @@ def test_weights_read_ahead_are_those_the_kernels_read(H, F):
 
 # (the same parameters as in the test of the table's room on the device: what is planned is what is launched)
 @pytest.mark.parametrize("bn,S,S_out,fits", [(256, 2.0 ** -6, 0.7, 1), (256, 2.0 ** -6, 3.2685, 1), (256, 2.0 ** -6, 3.2688, 0),
-                                             (192, 2.0 ** -6, 2.5, 1), (192, 2.0 ** -5, 10.9846, 1), (192, 2.0 ** -5, 10.9848, 0)])
+                                             (192, 2.0 ** -6, 2.5, 1), (192, 2.0 ** -5, 10.9846, 1), (192, 2.0 ** -5, 10.9848, 0),
+                                             (256, 2.0 ** -9, 0.06, 0), (192, 2.0 ** -9, 0.06, 0)])                   # no table at all
 def test_weights_read_ahead_follow_the_gelu_table(bn, S, S_out, fits):
     # a table that finds no room beside the persistent tiles sends the MatMul to another tile, which shares its weights in another way
     gp = B.ibert_gelu_params_from_scale(S, S_out)
