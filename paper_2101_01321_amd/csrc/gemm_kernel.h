@@ -55,7 +55,7 @@ struct GemmArgs {
     int32_t c16;       // the INT32 kernels store 16-bit elements (IBERT_I16: |value| <= out_clamp <= 32767)
     int32_t res_fast;  // residual absent, or its shift is in [8, 62]: its requantized value fits 32 bits
     int64_t res_rnd;   // 2^(res_s - 1), or 0 when res_s == 0
-    ResShort res_short;    // (direct-to-LDS and persistent tiles)
+    ResShort res_short;    // (direct-to-LDS tiles of eight wavefronts and persistent ones, 16-bit output)
     int32_t xcd_chunk; // tiles per XCD when the grid divides by 8, else 0 (no remap)
     int32_t xcd_xn;    // >= 1: each XCD works on a block of the tile grid, xcd_xn (a power of two) blocks side by side
     int32_t xcd_xs;    // log2(xcd_xn)
@@ -1209,7 +1209,8 @@ int launch_mfma(GemmArgs& g, bool i8, hipStream_t stream)
     constexpr size_t lds_par = DMA ? (size_t)par_bytes<BN>() : 0;
     static_assert(lds_tile + lds_par <= 163840, "LDS budget");
     size_t lds_bytes = lds_tile + lds_par;
-    g.res_short = DMA && !i8 ? residual_short(g) : ResShort{0, 0, 0, 0};
+    // (256 products, 0.2 us of the host: only for the kernels that read it)
+    g.res_short = DMA && NW == 8 && g.c16 && g.out_clamp == 32767 ? residual_short(g) : ResShort{0, 0, 0, 0};
     if (GELU) {
         // the GELU table rides behind them if it fits the CU's 160 KB (and, for tiles that share a CU,
         // stays small enough not to cost a resident workgroup)

@@ -713,7 +713,7 @@ int launch_stream(GemmArgs& g, bool i8, hipStream_t stream)
     stream_deal(s, g, BM, BN);
     s.per_channel = g.per_channel; s.dy_m = g.dy_m; s.dy_s = g.dy_s; s.out_clamp = g.out_clamp;
     s.res_m = g.res_m; s.res_s = g.res_s; s.res_fast = g.res_fast; s.res_rnd = g.res_rnd;
-    s.res_short = residual_short(g);
+    s.res_short = g.c16 && g.out_clamp == 32767 ? residual_short(g) : ResShort{0, 0, 0, 0};
     s.k_fast = (int64_t)g.K * 16129 < (1 << 30);
     s.gelu_fast = g.gelu_fast; s.gelu_lut_lo = g.gelu_lut_lo; s.gelu_lut_n = 0; s.gelu = g.gelu;
     s.path_word = g.path_word;
