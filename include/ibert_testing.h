@@ -41,11 +41,15 @@ enum {
 };
 void ibert_gemm_epilogue_record(uint32_t* device_word);
 
+/* The form in which the one-kernel attention computes with these parameters in a launch of `workgroups` (batch x heads x ceil(seq / 64)) that
+ * stores neither scores nor probabilities: 0 any constants, 1 and 2 faster ones (scores' shift at least 32, and below), 3 and 4 those with a
+ * table of the exponent (scores' shift up to 33, and above).  Host only. */
+int ibert_attention_form(const ibert_dyadic* scores_dy, const ibert_softmax_params* softmax, const ibert_dyadic* ctx_dy, int64_t workgroups, int32_t* form);
+
 /* How the one-kernel attention (Alg. 3 between its two MatMuls) holds K_h and V_h for 385 <= seq <= 512 (forms 3 and 4 from 321 on): *shared = 1 where a launch of
  * `workgroups` (batch x heads x ceil(seq / 64)) has them take turns in one LDS buffer, 0 where each has its own; *fit_two, *fit_one =
- * workgroups that a compute unit holds at once with two buffers and with one.  form: 0 any constants, 1 and 2 the faster
- * forms (scores' shift at least 32, and below), 3 and 4 those with a table of the exponent (scores' shift up to 33, and above; fit_* with the
- * largest table).  Asks the device. */
+ * workgroups that a compute unit holds at once with two buffers and with one.  form: see ibert_attention_form (3 and 4:
+ * fit_* with the largest table).  Asks the device. */
 int ibert_attention_buffers(int32_t seq, int32_t form, int64_t workgroups, int32_t* shared, int32_t* fit_two, int32_t* fit_one);
 
 /* What the XCDs read of W [N, K] (dense rows, K a multiple of 128, N * K of 1024) when this MatMul runs with all operands aligned, and

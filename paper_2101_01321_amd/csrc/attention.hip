@@ -490,6 +490,15 @@ static bool exp_table(const ibert_softmax_params& sp, int32_t m, int32_t s, int6
     return true;
 }
 
+// FORM of a launch that stores neither scores nor probabilities (see the kernel): accumulators are at most 64*128^2 = 2^20 (scores) and
+// 512*127*128 < 2^23 (context).
+static int attention_form(const ibert_softmax_params& sp, const ibert_dyadic& scores, const ibert_dyadic& ctx, int64_t blocks, ExpTable* t)
+{
+    if (!softmax_fast_ok(sp) || scores.m <= 0 || scores.s < 21 || scores.s > 45 || ctx.s < 23 || ctx.s > 62) return 0;
+    if (exp_table(sp, scores.m, scores.s, blocks, t)) return scores.s <= 33 ? 3 : 4;
+    return scores.s >= 32 ? 1 : 2;
+}
+
 template <int NKB>
 static int launch_attention_l(const AttentionArgs& a, int64_t blocks, int form, hipStream_t stream)
 {
@@ -545,10 +554,8 @@ int launch_attention(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq,
     a.z_c = (int32_t)(M * (uint32_t)sp.q_b);
     a.key_lens = key_lens;
     a.scores = scores; a.probs = probs;
-    // FORM 1, 2 (see the kernel): accumulators are at most 64*128^2 = 2^20 (scores) and 512*127*128 < 2^23 (context)
-    const bool fast = softmax_fast_ok(sp) && a.s_m > 0 && a.s_s >= 21 && a.s_s <= 45 && a.c_s >= 23 && a.c_s <= 62 && !scores && !probs;
     a.t = ExpTable{0, 0, 0};
-    const int form = !fast ? 0 : (exp_table(sp, a.s_m, a.s_s, blocks, &a.t) ? (a.s_s <= 33 ? 3 : 4) : (a.s_s >= 32 ? 1 : 2));
+    const int form = scores || probs ? 0 : attention_form(sp, scores_dy, ctx_dy, blocks, &a.t);
     int rc;
     switch ((seq + 63) / 64) {
         case 1: rc = launch_attention_l<1>(a, blocks, form, stream); break;
@@ -578,6 +585,14 @@ static int attention_occupancy(int32_t* two, int32_t* one)
 }
 
 }  // namespace ibert
+
+extern "C" int ibert_attention_form(const ibert_dyadic* scores_dy, const ibert_softmax_params* softmax, const ibert_dyadic* ctx_dy, int64_t workgroups, int32_t* form)
+{
+    if (!scores_dy || !softmax || !ctx_dy || !form) return IBERT_ERR_NULL;
+    ibert::ExpTable t;
+    *form = ibert::attention_form(*softmax, *scores_dy, *ctx_dy, workgroups, &t);
+    return IBERT_OK;
+}
 
 extern "C" int ibert_attention_buffers(int32_t seq, int32_t form, int64_t workgroups, int32_t* shared, int32_t* fit_two, int32_t* fit_one)
 {

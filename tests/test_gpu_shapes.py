@@ -18,18 +18,28 @@ def _qkv(B_, L, H, seed):
     return qkv
 
 
+def _attention_form(sdy, sp, cdy, workgroups):
+    import ctypes as C
+    from paper_2101_01321_amd import binding as B
+    form = C.c_int32()
+    assert B.lib().ibert_attention_form(C.byref(B.Dyadic(*sdy)), C.byref(sp), C.byref(B.Dyadic(*cdy)), workgroups, C.byref(form)) == 0
+    return form.value
+
+
 # ------------------------------------------------------------------------------------------- attention, any length
 @pytest.mark.parametrize("L", [1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 191, 192, 193, 251, 255, 257, 319, 321, 384, 385, 447, 449,
                                511, 512])
-@pytest.mark.parametrize("S,k,sdy", [(2.0 ** -6, 7, (1518500250, 36)), (2.0 ** -6, 7, (1187698534, 28)),
-                                     (2.0 ** -4, 5, (1518500250, 36)),        # q_ln2 = 11, fewer output bits
-                                     (2.0 ** -6, 7, (-1518500250, 36))])      # a negative multiplier: the general form
-def test_attention_any_length(G, L, S, k, sdy):
+@pytest.mark.parametrize("S,k,sdy,form", [(2.0 ** -6, 7, (1518500250, 36), 4), (2.0 ** -6, 7, (1187698534, 28), 3),
+                                          (2.0 ** -4, 5, (1518500250, 36), 4),        # q_ln2 = 11, fewer output bits
+                                          (2.0 ** -8, 7, (1518500250, 36), 1), (2.0 ** -8, 7, (1187698534, 28), 2),   # an exponent of 18 bits: no table
+                                          (2.0 ** -6, 7, (-1518500250, 36), 0)])      # a negative multiplier: the general form
+def test_attention_any_length(G, L, S, k, sdy, form):
     from paper_2101_01321_amd import binding as B
     B_, nh = 2, 3
     H, cdy = 64 * nh, (1073741824, 37 if k == 7 else 35)
     qkv = _qkv(B_, L, H, L)
     sp, op = B.ibert_softmax_params_from_scale(S, L, k), P.softmax_params(S, k)
+    assert _attention_form(sdy, sp, cdy, B_ * nh * -(-L // 64)) == form
     G.say("attention L=%d S=%g k=%d s=%s" % (L, S, k, sdy))
     want = _attention_oracle(qkv, B_, L, H, nh, sdy, op, cdy)
     _eq(G.attention(qkv, B_, L, H, nh, sdy, sp, cdy), want, "attention L=%d" % L)
@@ -80,12 +90,14 @@ def test_attention_with_a_table_shares_a_buffer_only_where_more_workgroups_fit(G
 
 
 # The table of the exponent: shifts on both sides of 33, the smallest one and the largest; multipliers on both sides of what the 32-bit product holds
-# (5000 and 4900 at 23); 11 to 16 bits of the exponent and, at 2^-8, more than the table takes; one entry a step and none for some
-@pytest.mark.parametrize("S,k,sdy", [(2.0 ** -6, 7, (37581, 23)), (2.0 ** -6, 7, (5000, 23)), (2.0 ** -6, 7, (4900, 23)), (2.0 ** -6, 7, (1187698534, 33)),
-                                     (2.0 ** -6, 7, (1187698534, 34)), (2.0 ** -6, 6, (2147483647, 45)), (2.0 ** -6, 7, (2000000011, 26)), (2.0 ** -4, 7, (1187698534, 30)),
-                                     (2.0 ** -7, 7, (1187698534, 27)), (2.0 ** -7, 7, (1518500250, 35)), (2.0 ** -8, 7, (1187698534, 26)), (2.0 ** -8, 7, (1518500250, 34))])
+# (5000 and 4900 at 23); 11 to 16 bits of the exponent and, at 2^-8, more than the table takes; one entry a step and none for some; at 2^-7 a table from 257
+# workgroups on (form: with up to 256 and with more)
+@pytest.mark.parametrize("S,k,sdy,form", [(2.0 ** -6, 7, (37581, 23), (3, 3)), (2.0 ** -6, 7, (5000, 23), (3, 3)), (2.0 ** -6, 7, (4900, 23), (2, 2)),
+                                          (2.0 ** -6, 7, (1187698534, 33), (3, 3)), (2.0 ** -6, 7, (1187698534, 34), (4, 4)), (2.0 ** -6, 6, (2147483647, 45), (4, 4)),
+                                          (2.0 ** -6, 7, (2000000011, 26), (3, 3)), (2.0 ** -4, 7, (1187698534, 30), (3, 3)), (2.0 ** -7, 7, (1187698534, 27), (2, 3)),
+                                          (2.0 ** -7, 7, (1518500250, 35), (1, 4)), (2.0 ** -8, 7, (1187698534, 26), (2, 2)), (2.0 ** -8, 7, (1518500250, 34), (1, 1))])
 @pytest.mark.parametrize("B_,nh,L", [(2, 3, 67), (43, 3, 128), (43, 2, 190)])         # 12, 258 and 258 workgroups
-def test_attention_exponent_from_a_table(G, S, k, sdy, B_, nh, L):
+def test_attention_exponent_from_a_table(G, S, k, sdy, form, B_, nh, L):
     from paper_2101_01321_amd import binding as B
     H, cdy = 64 * nh, (1073741824, 30 + k)
     rng = np.random.default_rng(L)
@@ -94,6 +106,8 @@ def test_attention_exponent_from_a_table(G, S, k, sdy, B_, nh, L):
     qkv[L - 2] = -128
     qkv[L - 1, H:2 * H] = 127
     sp, op = B.ibert_softmax_params_from_scale(S, L, k), P.softmax_params(S, k)
+    workgroups = B_ * nh * -(-L // 64)
+    assert _attention_form(sdy, sp, cdy, workgroups) == form[workgroups > 256]
     G.say("attention, table, B=%d heads=%d L=%d S=%g k=%d s=%s" % (B_, nh, L, S, k, sdy))
     got = G.attention(qkv, B_, L, H, nh, sdy, sp, cdy)
     for b in (0, B_ - 1):
@@ -110,18 +124,19 @@ def test_attention_exponent_from_a_table(G, S, k, sdy, B_, nh, L):
 # 504 to 539 workgroups, on both sides of the switch at 512; lengths at, before and behind the ends of key blocks
 @pytest.mark.parametrize("B_,nh,L,many", [(8, 9, 447, 0), (8, 8, 449, 0), (11, 7, 385, 1), (11, 7, 447, 1), (11, 7, 448, 1), (13, 5, 449, 1),
                                           (13, 5, 511, 1), (13, 5, 512, 1)])
-@pytest.mark.parametrize("sdy", [(1518500250, 36), (1187698534, 28), (-1518500250, 36)])
-def test_attention_keys_and_values_in_one_buffer(G, B_, nh, L, many, sdy):
+@pytest.mark.parametrize("S,sdy,form", [(2.0 ** -6, (1518500250, 36), 4), (2.0 ** -6, (1187698534, 28), 3), (2.0 ** -8, (1518500250, 36), 1),
+                                        (2.0 ** -8, (1187698534, 28), 2), (2.0 ** -6, (-1518500250, 36), 0)])
+def test_attention_keys_and_values_in_one_buffer(G, B_, nh, L, many, S, sdy, form):
     # long sequences of more workgroups than find a place at once: V_h takes the place of K_h in LDS where that makes room for more; also
     # with masked blocks of keys, down to a single key, against the oracle on the last sequence
     from paper_2101_01321_amd import binding as B
     H, cdy = 64 * nh, (1073741824, 37)
-    workgroups, form = B_ * nh * -(-L // 64), 0 if sdy[0] < 0 else (1 if sdy[1] >= 32 else 2)
-    assert (workgroups > 512) == bool(many)
-    assert _buffers(L, form, workgroups)[0] == (many and not (form == 0 and L > 448))
+    workgroups = B_ * nh * -(-L // 64)
     qkv = _qkv(B_, L, H, L + nh)
-    sp, op = B.ibert_softmax_params_from_scale(2.0 ** -6, L, 7), P.softmax_params(2.0 ** -6, 7)
-    G.say("attention, one buffer, B=%d heads=%d L=%d s=%s" % (B_, nh, L, sdy))
+    sp, op = B.ibert_softmax_params_from_scale(S, L, 7), P.softmax_params(S, 7)
+    assert (workgroups > 512) == bool(many) and _attention_form(sdy, sp, cdy, workgroups) == form
+    assert _buffers(L, form, workgroups)[0] == (many and not (form == 0 and L > 448))
+    G.say("attention, one buffer, B=%d heads=%d L=%d S=%g s=%s" % (B_, nh, L, S, sdy))
     got = G.attention(qkv, B_, L, H, nh, sdy, sp, cdy)
     last = qkv[(B_ - 1) * L:]
     _eq(got[(B_ - 1) * L:], _attention_oracle(last, 1, L, H, nh, sdy, op, cdy), "attention, last sequence")
