@@ -121,8 +121,8 @@ def test_attention_exponent_from_a_table(G, S, k, sdy, form, B_, nh, L):
         _eq(masked[b * L:b * L + n], _attention_oracle(part, 1, n, H, nh, sdy, op, cdy), "masked attention, sequence %d" % b)
 
 
-# 504 to 539 workgroups, on both sides of the switch at 512; lengths at, before and behind the ends of key blocks
-@pytest.mark.parametrize("B_,nh,L,many", [(8, 9, 447, 0), (8, 8, 449, 0), (11, 7, 385, 1), (11, 7, 447, 1), (11, 7, 448, 1), (13, 5, 449, 1),
+# 504 to 546 workgroups, on both sides of the switch at 512; lengths at, before and behind the ends of key blocks
+@pytest.mark.parametrize("B_,nh,L,many", [(12, 7, 321, 0), (12, 7, 384, 0), (13, 7, 321, 1), (43, 2, 383, 1), (13, 7, 384, 1), (8, 9, 447, 0), (8, 8, 449, 0), (11, 7, 385, 1), (11, 7, 447, 1), (11, 7, 448, 1), (13, 5, 449, 1),
                                           (13, 5, 511, 1), (13, 5, 512, 1)])
 @pytest.mark.parametrize("S,sdy,form", [(2.0 ** -6, (1518500250, 36), 4), (2.0 ** -6, (1187698534, 28), 3), (2.0 ** -8, (1518500250, 36), 1),
                                         (2.0 ** -8, (1187698534, 28), 2), (2.0 ** -6, (-1518500250, 36), 0)])
@@ -135,7 +135,8 @@ def test_attention_keys_and_values_in_one_buffer(G, B_, nh, L, many, S, sdy, for
     qkv = _qkv(B_, L, H, L + nh)
     sp, op = B.ibert_softmax_params_from_scale(S, L, 7), P.softmax_params(S, 7)
     assert (workgroups > 512) == bool(many) and _attention_form(sdy, sp, cdy, workgroups) == form
-    assert _buffers(L, form, workgroups)[0] == (many and not (form == 0 and L > 448))
+    if L > 384 or form >= 3:                                 # (six key blocks: only with a table)
+        assert _buffers(L, form, workgroups)[0] == (many and not (form == 0 and L > 448))
     G.say("attention, one buffer, B=%d heads=%d L=%d S=%g s=%s" % (B_, nh, L, S, sdy))
     got = G.attention(qkv, B_, L, H, nh, sdy, sp, cdy)
     last = qkv[(B_ - 1) * L:]
