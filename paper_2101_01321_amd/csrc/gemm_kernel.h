@@ -209,9 +209,13 @@ __host__ __device__ __forceinline__ void mfma_tile(const GemmArgs& g, unsigned b
 // wavefronts only).
 //
 // Per-channel constants of a direct-to-LDS tile behind its stages: bias, mult and shift as they are, and 16 bytes a channel of what the
-// epilogue makes of them (see `made`).
-template <int BN>
-constexpr int par_bytes() { return ((3 * BN * 4 + 255) & ~255) + 16 * BN; }
+// epilogue makes of them (see `made`).  Tiles of 64 rows have no such part: up to three of them share a compute unit and its waits, and a lane's constants
+// serve few tokens, so the detour costs more than it saves, us with it / made lane by lane: 64x128 [8704,512] x K 512 INT16 9.57 / 9.44, INT8
+// 7.08 / 6.95, [2048,2304] x K 768 INT16 11.9 / 11.5, 64x96 10.62 / 10.30, INT8 8.19 / 8.16, three stages [1200,2304] x K 768 INT16 + residual 7.90 / 7.77.
+template <int BM>
+constexpr bool made_constants() { return BM >= 128; }
+template <int BM, int BN>
+constexpr int par_bytes() { return ((3 * BN * 4 + 255) & ~255) + (made_constants<BM>() ? 16 * BN : 0); }
 
 template <int BM, int BN, int BK, int RING, bool OUT_I8, int KMODE, bool TW = false, bool DMA = false, bool GELU = false,
           int NW = 4, int NLD = 0>
@@ -407,7 +411,8 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
     }
     // (direct-to-LDS kernels: the constants live in LDS behind the stages, requested before the loop starts, see below)
     int32_t* const par_early = reinterpret_cast<int32_t*>(lds + EL::LDS_BYTES);
-    constexpr int PAR_BYTES = par_bytes<BN>();
+    constexpr int PAR_BYTES = par_bytes<BM, BN>();
+    constexpr bool MADE = DMA && made_constants<BM>();
     // Behind them what the epilogue makes of a channel's constants: multiplier, shift - 32, and the 64-bit addend.
     v4i* const made = reinterpret_cast<v4i*>(lds + EL::LDS_BYTES + PAR_BYTES - 16 * BN);
     const int32_t gelu_lut_at = (int32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)lds + EL::LDS_BYTES + PAR_BYTES;
@@ -621,7 +626,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         // With it, with the residual's product in 32 bits and a saturating pack, us before / after: 128x96 with loaders [4096,768] INT16 + residual
         // x K 768 8.95 / 8.57, x K 3072 16.9 / 16.7, [488,3072] x K 768 + GELU 7.73 / 7.45; 128x128 [4096,1024] + residual x K 1024 11.1 / 10.7.
         auto make_constants = [&]() {
-            if (tid < BN) {
+            if (MADE && tid < BN) {
                 const int32_t b = par_early[tid], m = par_early[BN + tid], s = par_early[2 * BN + tid];
                 int64_t cc = (int64_t)b * m + ((int64_t)1 << ((s - 1) & 63));
                 if (GELU && fold_early && g.gelu_lut_n > 0) cc -= (int64_t)(g.gelu_lut_lo - gelu_lut_at) << (s & 63);
@@ -901,7 +906,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
         constexpr bool FOLD = decltype(fold_tag)::value;
         static_assert(!FOLD || (LUT && ES == 1 && !RES), "folding belongs to the table form");
         static_assert((ES == 1) == OUT_I8, "INT8 kernels store bytes");
-        static_assert(!FOLD || DMA, "the table's address is in the constants that direct-to-LDS kernels make");
+        static_assert(!FOLD || MADE, "the table's address is in the constants that one thread a channel makes");
         static_assert(RES != 2 || ES == 2, "a clamp that packing does: 16 bits");
         const int8_t* const lut = lds + EL::LDS_BYTES + PAR_BYTES;
         const uint32_t lut_lds = (uint32_t)gelu_lut_at;
@@ -937,7 +942,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
             const int cl = wn0 + 16 * i + 4 * fch;
             int64_t cc[4];
             int32_t mm[4], sh[4];
-            if constexpr (DMA) {
+            if constexpr (MADE) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const v4i c = made[cl + e];
@@ -1206,7 +1211,7 @@ int launch_mfma(GemmArgs& g, bool i8, hipStream_t stream)
     constexpr size_t lds_tile = EpiLayout<BM, BN, BK, (DMA ? RING : 2)>::LDS_BYTES;
     static_assert(lds_tile <= 163840, "LDS budget");
     // (direct-to-LDS kernels keep the per-channel constants behind the stages)
-    constexpr size_t lds_par = DMA ? (size_t)par_bytes<BN>() : 0;
+    constexpr size_t lds_par = DMA ? (size_t)par_bytes<BM, BN>() : 0;
     static_assert(lds_tile + lds_par <= 163840, "LDS budget");
     size_t lds_bytes = lds_tile + lds_par;
     // (256 products, 0.2 us of the host: only for the kernels that read it)
