@@ -413,7 +413,7 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
     int32_t* const par_early = reinterpret_cast<int32_t*>(lds + EL::LDS_BYTES);
     constexpr int PAR_BYTES = par_bytes<BM, BN>();
     constexpr bool MADE = DMA && made_constants<BM>();
-    // Behind them what the epilogue makes of a channel's constants: multiplier, shift - 32, and the 64-bit addend.
+    // Behind them (MADE) what the epilogue makes of a channel's constants: multiplier, shift - 32, and the 64-bit addend.
     v4i* const made = reinterpret_cast<v4i*>(lds + EL::LDS_BYTES + PAR_BYTES - 16 * BN);
     const int32_t gelu_lut_at = (int32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)lds + EL::LDS_BYTES + PAR_BYTES;
     bool fast_early = false, fold_early = false;

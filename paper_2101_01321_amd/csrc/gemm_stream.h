@@ -26,8 +26,9 @@
 //     against 1.75 to 1.95; [32768,3072] x K 1024 105 -> 80 us).  A loop of nothing but the step's MFMAs sustains 4.05 POP/s on random
 //     operands, with its LDS reads 3.5, with its requests 3.0 -- 1425 ns a step, about what a step takes here.
 //   * An epilogue is what the address unit, then the ALU, make of it.  Rows leave and residuals come with neighbouring lanes on neighbouring
-//     bytes, through LDS (see `turn`; with GELU as they are), one unit of rows at a time while the next is being made; the MFMA's first operand are the rows of
-//     A, so that a lane has the same few channels for all its tokens and their constants are made once.  Cycles of a launch, thousands, with
+//     bytes, through LDS (see `turn`; with GELU as they are), one unit of rows at a time while the next is being made (not 256x192 INT8 and GELU: what is
+//     stored before their last value would wait for all requests, see HOLD, so everything leaves behind it); the MFMA's first operand are
+//     the rows of A, so that a lane has the same few channels for all its tokens and their constants are made once.  Cycles of a launch, thousands, with
 //     lane swaps in place of LDS and stores that left together at the end / as it is: [32768,1024] x K 1024 INT16 + residual 84.0 / 73.5,
 //     [32768,768] x K 768 63 / 56.5, x K 3072 133 / 125, [32768,3072] x K 1024 INT8 175 / 166, [32768,4096] x K 1024 + GELU 250 / 237; us: 45.3 /
 //     41.9, 35.6 / 32.0, 76.7 / 71.3, 104 / 101, 134 / 130.  Tried and not kept: the next tile's first operands held in registers over
@@ -41,7 +42,7 @@
 //   * Measured against one workgroup per tile, us, W cold, when it came: [32768,4096] x K 1024 with GELU 212 -> 142, [15311,3072] x K 768
 //     with GELU 115 -> 45 (any M: tiles may be ragged), [32768,1024] x K 1024 + residual 62 -> 44.
 //   * The vector registers must hold everything: with one of them spilled the loop takes 1.6 times as long, even where no scratch is
-//     touched.  None is (225 at most of 256x192, 239 of 256x256): what an epilogue derives from the lane's index is made there.
+//     touched.  None is (224 at most of 256x192, 239 of 256x256): what an epilogue derives from the lane's index is made there.
 //   * Rows past M (any M is allowed) are computed from zeros and not stored: operands, residual and output are addressed as buffers
 //     that end with the last row.
 #pragma once
@@ -95,7 +96,7 @@ template <int BM, int BN, int NW, bool OUT_I8, bool GELU>
 struct StreamLayout {
     static constexpr int STAGE = (BM + BN) * 128;
     static constexpr int PAR = 2 * STAGE;                          // two buffers of 3 x BN constants
-    static constexpr int TURN = PAR + 2 * 3 * BN * 4;              // rows on their way out, see `turn`
+    static constexpr int TURN = PAR + 2 * 3 * BN * 4;              // rows on their way out, see `turn` (none with GELU)
     static constexpr int TURN_WAVE = GELU ? 0 : BN % 128 == 0 ? (OUT_I8 ? 1280 : 2560) : 3584;     // bytes per wavefront
     static constexpr int LUT = TURN + NW * TURN_WAVE;
     static constexpr int ROOM = 163840 - LUT;                      // for the GELU table
@@ -465,8 +466,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
             auto value = [&](int i, int n) { return (int32_t)(((int64_t)acc[i][n >> 2][n & 3] * mm[i] + c0[i]) >> 32) >> sh[i]; };
             // Token n of the lane: row 16 (n / 4) + 4 u + n % 4 of the wavefront's tile.  Its results go to LDS; when a unit is complete it is read
             // back as it is moved, and stored while the next one is being made.  Before the first store this wavefront's requests have all
-            // landed (HOLD units give them time), so that the waits of the next tile's first step, which would count stores among
-            // the loads, can be left out.
+            // landed (HOLD units give them time; both there are of a 256x192 INT8 or GELU tile), so that the waits of the next tile's first step, which
+            // would count stores among the loads, can be left out.
             constexpr int UNITS = FM / RO.unit, HOLD = UNITS >= 8 && OUT_I8 ? 4 : 2;
             v4u mv[UNITS][RO.mv];
             auto store = [&](int unit) {
