@@ -292,11 +292,13 @@ typedef struct {
  *   - steps 2, 3 and 4 as one kernel where ibert_attention_i can do so (profile records: one, numbered 2); the workspace
  *     regions scores and probs are then left untouched, except that a single-layer call with a workspace stores them for
  *     every seq that is not a multiple of 128;
+ *   - step 1 in that kernel too (profile records: one, numbered 1) where heads are 64 wide, sequences short and that is the faster way; the
+ *     region qkv is then left untouched, except by a single-layer call with a workspace;
  *   - r1 / r2, which are clamped to 16 bits by definition, stored as int16 [T, hidden] (IBERT_I16) at the start of their
  *     workspace regions and read by ibert_layernorm_i16: the two kernels move half the bytes. */
 enum {
     IBERT_ROUTE_SEPARATE_GELU = 1,        /* step 7 writes f1 (int32), step 8 is a kernel of its own        */
-    IBERT_ROUTE_SEPARATE_ATTENTION = 2,   /* steps 2, 3, 4 as three kernels through scores and probs        */
+    IBERT_ROUTE_SEPARATE_ATTENTION = 2,   /* steps 1, 2, 3, 4 as four kernels through qkv, scores and probs */
     IBERT_ROUTE_I32_LN_INPUT = 4          /* r1 / r2 stored as int32, steps 6 / 10 run ibert_layernorm_i     */
 };
 

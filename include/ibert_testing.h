@@ -52,6 +52,15 @@ int ibert_attention_form(const ibert_dyadic* scores_dy, const ibert_softmax_para
  * fit_* with the largest table).  Asks the device. */
 int ibert_attention_buffers(int32_t seq, int32_t form, int64_t workgroups, int32_t* shared, int32_t* fit_two, int32_t* fit_one);
 
+/* Steps 1 to 4 of a layer as one kernel: 0 never; a tile (1000 wavefronts + 100 MFMA rows of one + 10 sequences + stages, one of those ibert_qkv_attention_plan names)
+ * wherever its rows hold a sequence and the parameters allow it; negative where it is the faster way (the default).  Process-wide, not thread-safe. */
+void ibert_qkv_attention_override(int32_t tile);
+
+/* How that kernel deals a layer of heads of 64: *tile as above; IBERT_ERR_NOT_IMPLEMENTED where the choice is to run the steps apart.  places[batch * heads] (zeroed): how often a
+ * (sequence, head) is worked on.  readers[3 * heads] (zeroed): bit x is set where XCD x multiplies the head's rows of W_q, W_k, W_v.  ahead[x * 3 H H / 1024 + i] (zeroed): how
+ * often XCD x reads the i-th KB of W_qkv ahead when an encoder plans for it (H = 64 heads).  Host only. */
+int ibert_qkv_attention_plan(int32_t batch, int32_t seq, int32_t heads, int32_t* tile, uint8_t* places, uint8_t* readers, uint8_t* ahead);
+
 /* What the XCDs read of W [N, K] (dense rows, K a multiple of 128, N * K of 1024) when this MatMul runs with all operands aligned, and
  * what each reads ahead when an encoder plans for it.  plan: the tile configuration chosen, then rows and xs: XCD x is to have the row
  * blocks (j << xs) + x % 2^xs of `rows` rows each.  readers[n] (N bytes, zeroed by the caller): bit x is set where a workgroup on XCD x

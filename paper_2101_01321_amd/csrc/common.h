@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cstdio>
+
 #include "ibert.h"
 
 namespace ibert {
@@ -145,6 +147,13 @@ inline uint32_t udiv_magic(int32_t d) { return d == 1 ? 0u : (uint32_t)(((uint64
 // Name of the kernel family chosen by the most recent launch_* call (for the optional profile).
 extern const char* g_last_kernel;
 
+// A kernel's name as a profiler shows it, for static objects: made once, also where several threads launch first together.
+struct KernelName {
+    char text[96];
+    template <typename... A>
+    KernelName(const char* format, A... a) { std::snprintf(text, sizeof text, format, a...); }
+};
+
 // How the XCDs will share the weights of a MatMul (gemm.hip: plan_gemm): XCD x works on the row blocks (j << xs) + x % 2^xs,
 // j = 0, 1 ..., of `rows` rows each (rows 0: no such plan).
 struct GemmPlan {
@@ -156,7 +165,7 @@ struct GemmPlan {
 // us, 24 (12 from FFN 32768 on) layers of hidden 1024, without W_1 and W_2 / with them, 128 tokens and 4096: FFN 16384 (16 MB each)
 // 1057 / 1023, 4677 / 4488; 32768 (32 MB) 676 / 698, 4000 / 3800; 65536 (64 MB) 1080 / 1232, 7540 / 7650.
 struct ReadAhead {
-    static constexpr int MOST = 4;
+    static constexpr int MOST = 6;
     static constexpr int64_t MOST_BYTES = 32 << 20;      // of a matrix
     struct Part {
         const int8_t* p;
@@ -208,6 +217,14 @@ int launch_attention(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq,
                      ibert_dyadic scores_dy, const ibert_softmax_params& sp, ibert_dyadic ctx_dy, hipStream_t stream,
                      const int32_t* key_lens = nullptr, int32_t* scores = nullptr, int8_t* probs = nullptr,
                      const ReadAhead* ahead = nullptr);
+// Steps 1 to 4 as one kernel (qkv_attention.hip): is there one for this problem, and is it the faster way?
+bool qkv_attention_ok(const int8_t* x, const int8_t* w, const int8_t* ctx, int32_t batch, int32_t seq, int32_t hidden, int32_t heads, const ibert_dyadic& scores_dy,
+                      const ibert_softmax_params& sp, const ibert_dyadic& ctx_dy);
+int launch_qkv_attention(const int8_t* x, const int8_t* w, const int32_t* bias, const int32_t* mult, const int32_t* shift, int8_t* qkv, int8_t* ctx, int32_t batch,
+                         int32_t seq, int32_t hidden, int32_t heads, const ibert_dyadic& scores_dy, const ibert_softmax_params& sp, const ibert_dyadic& ctx_dy,
+                         const int32_t* key_lens, const ReadAhead* ahead, hipStream_t stream);
+// Its W_qkv among what is read ahead.
+void qkv_attention_ahead(ReadAhead& ahead, const int8_t* w, int32_t batch, int32_t seq, int32_t hidden, int32_t heads);
 // key_lens (device, optional): row r keeps its first key_lens[r / rows_per_len] columns
 int launch_softmax(const int32_t* x, void* y, int64_t rows, int32_t cols, int64_t ldx, int64_t ldy,
                    const ibert_softmax_params& p, hipStream_t stream, const int32_t* key_lens = nullptr,

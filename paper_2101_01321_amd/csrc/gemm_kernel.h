@@ -15,7 +15,6 @@
 //   * Four wavefronts per workgroup, or eight (two per SIMD) for the big INT8 tiles.
 // Generic path (unaligned operands): one output element per lane, byte loads.
 #pragma once
-#include <cstdio>
 #include <type_traits>
 
 #include "common.h"
@@ -1156,13 +1155,6 @@ __global__ __launch_bounds__(64 * (NW + NLD)) void gemm_nt_mfma_kernel(GemmArgs 
 // Launchers.  Each tile configuration is instantiated in exactly one translation unit (gemm_inst_*.hip, which list
 // their configurations in gemm_instances_*.inc); gemm.hip sees them as extern templates.
 // ---------------------------------------------------------------------------------------------
-// A kernel's name as a profiler shows it, for static objects: made once, also where several threads launch first together.
-struct KernelName {
-    char text[96];
-    template <typename... A>
-    KernelName(const char* format, A... a) { std::snprintf(text, sizeof text, format, a...); }
-};
-
 bool xcd_blocks_enabled();       // (gemm.hip: a switch for A/B measurements, on by default)
 
 // How one problem's tile grid is dealt to the XCDs in blocks: log2 of the blocks side by side, -1 where it does not divide.

@@ -238,13 +238,7 @@ static int run_layer(const ibert_layer_weights& w, const LayerPlan* plan, const 
         prof_after(stream, (STEP_) + 1, 0.0, (half ? 3.0 : 5.0) * T * H);                                    \
     } while (0)
 
-    // 1: QKV projection, one GEMM with N = 3H
-    d = projection(T, 3 * H, H, IBERT_I8, 127);
-    prof_before(stream);
-    RUN_GEMM(x, w.w_qkv, w.b_qkv, w.m_qkv, w.s_qkv, nullptr, qkv);
-    prof_after(stream, 1, 2.0 * T * 3 * H * H, gemm_bytes(T, 3 * H, H, 1, 1, false, true));
-
-    // 2-4: attention scores, Softmax, context
+    // 1-4: QKV projection, one GEMM with N = 3H; attention scores, Softmax, context
     // The attention works on its registers for most of its time and leaves memory idle: it also brings nearer the weights of the
     // MatMuls up to the next attention, which come from HBM otherwise -- a model's weights are more than the caches hold, or other
     // work has been there since (MatMul on weights from HBM against weights in L2, us: [128,768] x K 3072 5.2 / 4.1, [4096,768] x
@@ -252,16 +246,35 @@ static int run_layer(const ibert_layer_weights& w, const LayerPlan* plan, const 
     // 1236 / 1182, Base b32 900 / 849, b61 s251 2243 / 2132, 32768 tokens the same.  A program that runs one Base model and nothing else
     // finds its 85 MB in the memory-side cache from forward to forward and gains little: b1 314 / 312, b8 s61 413 / 409, b32 837 / 834.  (So
     // does a layer called by itself, in a program that cycles through few of them: 177 tokens 27.7 without, 27.9 with.)
+    const bool fuse_qkv = fuse_attention && (!keep || attention_whole_blocks(seq)) &&
+                          qkv_attention_ok(x, w.w_qkv, ctx, batch, seq, hidden, heads, q.scores_dy, q.softmax, q.ctx_dy);
     ReadAhead ahead;
     if (plan && fuse_attention && fuse_gelu && half) {
         ahead.add(w.w_o, H, H, plan->o);
         ahead.add(w.w_1, F, H, plan->up);
         ahead.add(w.w_2, H, F, plan->down);
-        if (next) ahead.add(next->w_qkv, 3 * H, H, plan->qkv);
+        if (next && fuse_qkv) qkv_attention_ahead(ahead, next->w_qkv, batch, seq, hidden, heads);
+        else if (next) ahead.add(next->w_qkv, 3 * H, H, plan->qkv);
     }
-    rc = run_attention(qkv, scores, probs, ctx, B, L, H, nh, q.scores_dy, q.softmax, q.ctx_dy, key_lens,
-                       fuse_attention, keep, stream, ahead.n ? &ahead : nullptr);
-    if (rc) return rc;
+    if (fuse_qkv) {
+        // 1-4 in one kernel; qkv is stored only where the caller may look at it
+        prof_before(stream);
+        rc = launch_qkv_attention(x, w.w_qkv, w.b_qkv, w.m_qkv, w.s_qkv, keep ? qkv : nullptr, ctx, batch, seq, hidden, heads, q.scores_dy, q.softmax, q.ctx_dy,
+                                  key_lens, ahead.n ? &ahead : nullptr, stream);
+        if (rc) return rc;
+        prof_after(stream, 1, 2.0 * T * 3 * H * H + 4.0 * B * nh * L * L * dh, T * 2.0 * H + 3.0 * H * (H + 12));
+    } else {
+        // 1: QKV projection, one GEMM with N = 3H
+        d = projection(T, 3 * H, H, IBERT_I8, 127);
+        prof_before(stream);
+        RUN_GEMM(x, w.w_qkv, w.b_qkv, w.m_qkv, w.s_qkv, nullptr, qkv);
+        prof_after(stream, 1, 2.0 * T * 3 * H * H, gemm_bytes(T, 3 * H, H, 1, 1, false, true));
+
+        // 2-4: attention scores, Softmax, context
+        rc = run_attention(qkv, scores, probs, ctx, B, L, H, nh, q.scores_dy, q.softmax, q.ctx_dy, key_lens,
+                           fuse_attention, keep, stream, ahead.n ? &ahead : nullptr);
+        if (rc) return rc;
+    }
 
     // 5: output projection + residual x, INT32 at the LayerNorm input scale
     d = projection(T, H, H, IBERT_I32, 32767);

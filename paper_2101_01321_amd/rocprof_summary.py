@@ -32,6 +32,8 @@ def short(name):
 
 def step_of(name):
     """Which step of the layer a kernel name belongs to (for the reader; from the template arguments)."""
+    if name.startswith("qkv_attention"):
+        return "S1-4"
     if name.startswith("attention"):
         return "S2-4"
     if name.startswith("softmax"):

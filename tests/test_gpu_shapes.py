@@ -691,3 +691,115 @@ def test_encoder_reads_ahead_weights_at_odd_addresses(G):
     got = model.forward(x)
     torch.cuda.synchronize()
     _eq(got.cpu().numpy(), want.cpu().numpy(), "weights at odd addresses")
+
+
+# ------------------------------------------------------------------------------------------- QKV projection and attention as one kernel
+def _qkv_layer(G, heads, B_, L, lens=None, edit=None):
+    """One layer of 64 x heads channels: weights and quantization (edit: changes made to both sides), input, masks."""
+    import torch
+    from paper_2101_01321_amd import binding as B
+    cfg = synth.EncoderConfig("qkv", 64 * heads, heads, 128, L, B_, 1)
+    x_q, S_x, _ = synth.input_activations(cfg)
+    model = G.DeviceModel(cfg, S_x)
+    w, q = P.layer_params(synth.layer_raw(cfg, 0), model.scales[0], cfg.hidden, heads)
+    if edit:
+        edit(model, w, q)
+    x = G.to_dev(x_q)
+    key_lens = None if lens is None else G.to_dev(np.asarray(lens, np.int32))
+
+    def run(tile):
+        B.lib().ibert_qkv_attention_override(tile)
+        try:
+            model.ws.fill_(0x55)
+            y = model.layer_forward(0, x, key_lens)
+            torch.cuda.synchronize()
+            # a layer call that stores scores (any length but 128 and 256) runs the steps apart; the encoder call of one layer stores no qkv
+            model.ws.fill_(0x55)
+            z = model.forward(x, key_lens)
+            torch.cuda.synchronize()
+            got = model.intermediates(r_half=True)
+            assert (got["qkv"] == 0x55).all(), "steps 1 to 4 did not run as one kernel"
+            return y.cpu().numpy(), z.cpu().numpy(), got
+        finally:
+            B.lib().ibert_qkv_attention_override(-1)
+    return cfg, x_q, w, q, run
+
+
+def _qkv_tiles(L):
+    r = -(-L // 32)
+    if L > 128:
+        return [16313, 16412] if L <= 192 else [16412]
+    return [8012 + 100 * r, 8014 + 100 * r, 8412, 8414] + ([8222, 8442] if L <= 32 else []) + ([8422] if L <= 64 else [])
+
+
+# rows at, before and behind the ends of the tiles; groups that are not full; one K step, an odd number of them, more than there are stages
+@pytest.mark.parametrize("heads", [2, 6, 10])
+@pytest.mark.parametrize("L", [1, 16, 31, 32, 33, 63, 64, 65, 96, 97, 127, 128, 129, 192, 193, 255, 256])
+def test_qkv_attention_every_tile(G, heads, L):
+    import torch
+    B_ = 5 if L <= 128 else 2
+    cfg, x_q, w, q, run = _qkv_layer(G, heads, B_, L)
+    want, inter = oracle.encoder_layer(w, q, x_q, B_, L, cfg.hidden, heads, cfg.ffn, dump=True)
+    for tile in _qkv_tiles(L):
+        G.say("qkv + attention, tile %d, heads=%d L=%d" % (tile, heads, L))
+        y, z, got = run(tile)
+        _eq(got["ctx"], inter["ctx"], "tile %d ctx" % tile)
+        _eq(y, want, "tile %d layer" % tile)
+        _eq(z, want, "tile %d encoder" % tile)
+
+
+@pytest.mark.parametrize("tile,L", [(8112, 20), (8442, 30), (8222, 32), (8422, 61), (8312, 70), (8412, 128), (8414, 100), (16313, 150), (16412, 251)])
+def test_qkv_attention_masked(G, tile, L):
+    lens = [L, 1, (L + 1) // 2, max(1, L - 1), min(L, 64)]
+    cfg, x_q, w, q, run = _qkv_layer(G, 4, 5, L, lens)
+    want = oracle.encoder_layer(w, q, x_q, 5, L, cfg.hidden, 4, cfg.ffn, key_lens=np.asarray(lens, np.int32))
+    G.say("qkv + attention, masked, tile %d L=%d" % (tile, L))
+    y, z, _ = run(tile)
+    _eq(z, want, "masked, tile %d" % tile)
+    _eq(y, want, "masked, tile %d, one layer" % tile)
+
+
+def test_qkv_attention_stores_qkv_for_a_single_layer(G):
+    # a layer call with a workspace leaves Q, K and V there, as the MatMul by itself stores them
+    from paper_2101_01321_amd import binding as B
+    import torch
+    cfg = synth.EncoderConfig("qkv", 256, 4, 128, 128, 3, 1)
+    x_q, S_x, _ = synth.input_activations(cfg)
+    model = G.DeviceModel(cfg, S_x)
+    w, q = P.layer_params(synth.layer_raw(cfg, 0), model.scales[0], cfg.hidden, cfg.heads)
+    want, inter = oracle.encoder_layer(w, q, x_q, 3, 128, 256, 4, 128, dump=True)
+    for tile in (8412, 8414, 16412):
+        B.lib().ibert_qkv_attention_override(tile)
+        try:
+            model.ws.fill_(0x55)
+            G.say("qkv stored, tile %d" % tile)
+            model.layer_forward(0, G.to_dev(x_q))
+            torch.cuda.synchronize()
+        finally:
+            B.lib().ibert_qkv_attention_override(-1)
+        got = model.intermediates(r_half=True)
+        _eq(got["qkv"], inter["qkv"], "tile %d qkv" % tile)
+        _eq(got["ctx"], inter["ctx"], "tile %d ctx" % tile)
+
+
+# which arithmetic a matrix's channels take: every shift at least 40, at least 33, any; biases at the ends of 2^30 and beyond; sums that saturate
+@pytest.mark.parametrize("shift,mult,bias", [(40, 1 << 30, 0), (47, 2147483647, (1 << 30) - 1), (44, -2147483647, -(1 << 30)), (39, 1 << 30, 5), (33, 3, 1 << 20),
+                                             (32, 1, 1000), (0, 1, -3), (62, 2147483647, 1 << 29), (45, 2147483647, 1 << 30), (40, 2147483647, -(1 << 30) - 1)])
+@pytest.mark.parametrize("tile", [8212, 8414])
+def test_qkv_attention_any_constants(G, shift, mult, bias, tile):
+    import torch
+
+    def edit(model, w, q):
+        # the constants go to one matrix (K) whole and to single channels of the others' halves; the device's arrays are changed in place
+        H = 256
+        for name, value in (("m_qkv", mult), ("s_qkv", shift), ("b_qkv", bias)):
+            host = w[name]
+            host[H:2 * H] = value
+            host[5] = value
+            t = model.layers[0].tensors[name]
+            t.copy_(torch.from_numpy(np.ascontiguousarray(host)).to(t.device))
+    cfg, x_q, w, q, run = _qkv_layer(G, 4, 3, 61, edit=edit)
+    want, inter = oracle.encoder_layer(w, q, x_q, 3, 61, 256, 4, cfg.ffn, dump=True)
+    G.say("qkv + attention, shift %d mult %d bias %d tile %d" % (shift, mult, bias, tile))
+    y, z, _ = run(tile)
+    _eq(z, want, "shift %d mult %d bias %d" % (shift, mult, bias))

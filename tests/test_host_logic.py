@@ -448,6 +448,50 @@ def test_gelu_tile_chosen_is_the_fastest_measured(M, N, K, config):
     assert _weight_plan(M, N, K, "gelu")[0][0] == config
 
 
+# ------------------------------------------------------------------------------------------- QKV projection and attention as one kernel
+def _qkv_plan(batch, seq, heads):
+    H = 64 * heads
+    tile, places, readers, ahead = C.c_int32(), np.zeros((batch, heads), np.uint8), np.zeros((3, heads), np.uint8), np.zeros((8, 3 * H * H // 1024), np.uint8)
+    rc = B.lib().ibert_qkv_attention_plan(batch, seq, heads, C.byref(tile), places.ctypes.data, readers.ctypes.data, ahead.ctypes.data)
+    return rc, tile.value, places, readers, ahead
+
+
+@pytest.mark.parametrize("heads", [2, 4, 6, 10, 12, 14, 16, 24])
+def test_qkv_attention_deals_every_head_once_and_reads_its_weights_ahead(heads):
+    H, tiles = 64 * heads, set()
+    try:
+        for forced in (None, 8112, 8222, 8442, 8422, 8414, 16313, 16412):
+            for batch in (1, 2, 3, 5, 8, 11, 16, 21, 32, 43, 61, 64, 97, 128, 250):
+                for seq in (1, 17, 32, 33, 61, 64, 90, 100, 128, 129, 192, 193, 256):
+                    B.lib().ibert_qkv_attention_override(-1 if forced is None else forced)
+                    rc, tile, places, readers, ahead = _qkv_plan(batch, seq, heads)
+                    case = (batch, seq, heads, tile, rc)
+                    if rc == -7:
+                        assert forced is None, case
+                        continue
+                    assert rc == 0, case                                   # (a place or a read outside is an error)
+                    tiles.add(tile)
+                    assert (places == 1).all() and readers.all(), case
+                    assert ahead.max() == 1 and ahead.any(axis=0).all(), case
+                    copies = ahead.sum(axis=0)
+                    if (copies == 1).all():
+                        continue                                           # once, by any XCD
+                    by_kb = np.bitwise_or.reduce(ahead << np.arange(8, dtype=np.uint8)[:, None], axis=0)
+                    kb_of_head = by_kb.reshape(3, heads, H * 64 // 1024)   # (64 rows of H bytes)
+                    assert not (readers[:, :, None] & ~kb_of_head).any(), case
+    finally:
+        B.lib().ibert_qkv_attention_override(-1)
+    assert len(tiles) >= 7, tiles
+
+
+@pytest.mark.parametrize("batch,seq,heads,tile", [(8, 61, 12, 8214), (32, 128, 12, 8412), (32, 128, 16, 8412), (1, 128, 4, 8414), (1, 128, 12, 0), (3, 59, 12, 0), (8, 128, 12, 0), (256, 128, 16, 0),
+                                                  (4, 256, 16, 0), (16, 256, 16, 16412), (16, 150, 12, 16313), (61, 251, 12, 0), (128, 64, 12, 8422), (43, 32, 12, 8222), (128, 32, 12, 8442),
+                                                  (512, 40, 16, 0), (1024, 16, 12, 0)])
+def test_qkv_attention_is_chosen_where_it_was_the_faster_way(batch, seq, heads, tile):
+    rc, got, *_ = _qkv_plan(batch, seq, heads)
+    assert (got if rc == 0 else 0) == tile
+
+
 # ------------------------------------------------------------------------------------------- buffers that end with the last row
 def test_rows_of_the_persistent_tiles_are_checked_whole_against_the_buffers_end(tmp_path):
     # Output and residual are buffers that end with the last row, so that lanes past it neither load nor store.  The range check takes the
