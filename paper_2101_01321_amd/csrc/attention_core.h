@@ -89,9 +89,11 @@ __device__ __forceinline__ void read_ahead(uint32_t lds0, int wave, int lane, in
 #else
     kernel_args ga = nullptr;
 #endif
-    const int wgs = ga->ahead_wgs >> 3;                    // of an XCD
-#pragma unroll
-    for (int r = 0; r < ReadAhead::MOST; ++r) {
+    const int wgs = ga->ahead_wgs >> 3, parts = ga->ahead.n;       // (of an XCD)
+    // (Rolled: the attention's own code, which every launch fetches, is that much nearer.  Unrolled for up to six parts against this, forwards, us: Base 2 x 512
+    // 538.8 / 526.4, 1 x 512 474.2 / 466.7, Large 4 x 256 1208 / 1178.)
+#pragma unroll 1
+    for (int r = 0; r < parts; ++r) {
         const auto& q = ga->ahead.part[r];
         const int s = ReadAhead::share(x, q.xs), total = ReadAhead::count(s, q.kb, q.blocks, q.xs);
         for (int k = first * NW + wave; k < total; k += NW * wgs) {
