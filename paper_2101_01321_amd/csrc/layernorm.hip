@@ -213,6 +213,101 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_rows_kernel(LayerNormArg
     else finish(std::false_type{});
 }
 
+// Many int16 rows of 256 NCH columns, four to a wavefront, all 64 lanes on each (aligned as ALIGNED above, shift at least 8).  Bound: ALU issue, then HBM.
+// What the kernel above repeats in every lane of a row is done for R rows at once here: sums are reduced with the rows folded into the lanes (each exchange leaves
+// a lane half of the rows), after which 64 / R lanes hold a row's and work out its mean, variance, root and factor, which go back to all lanes as scalars.
+// A value costs half a maximum, half a product for the sum, half for the squares and half an addition for their two-part sum, then a difference, a product, a shift, a
+// multiply-add, a shift, and 1.25 instructions of packing that saturates.  175 instructions a row of 768 instead of 240.  us, rows just written, the kernel above / this (moving as many bytes
+// takes 2.2, 4.4, 12.2 and 15.7): [4096,768] 4.08 / 3.66, [15311,768] 9.25 / 8.13, [32768,768] 16.4 / 14.5, [32768,1024] 21.8 / 17.9; from beyond the caches the same to 5 % shorter.
+// Tried and not kept: two and eight rows ([15311,768] 8.6, 8.4), wavefronts that go on to further rows, requested ahead (8.3 to 9.4: twice the registers), int32 rows
+// ([15311,768] 10.5 / 11.6: twice the bytes held).
+template <int NCH>
+__global__ __launch_bounds__(LN_THREADS) void layernorm_many_kernel(LayerNormArgs a)
+{
+    constexpr int R = 4;
+    typedef short v2s __attribute__((ext_vector_type(2)));
+    typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    asm volatile("" :: "s"(a.x), "s"(a.y), "s"(a.rows), "s"(a.C), "s"(a.ldx), "s"(a.ldy), "s"(a.gamma_q), "s"(a.beta_q), "s"(a.shift),
+                 "s"(a.magic_c));
+    const int64_t row0 = ((int64_t)blockIdx.x * (LN_THREADS / 64) + wave) * R;
+    if (row0 >= a.rows) return;
+    v2u v[R][NCH];                                         // pairs of values
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t row = row0 + r < a.rows ? row0 + r : a.rows - 1;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) v[r][c] = *reinterpret_cast<const v2u*>(reinterpret_cast<const int16_t*>(a.x) + row * a.ldx + c * 256 + lane * 4);
+    }
+    const int32_t rnd = 1 << (a.shift - 1);
+    int4 gm[NCH], bt[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        gm[c] = *reinterpret_cast<const int4*>(a.gamma_q + c * 256 + lane * 4);
+        bt[c] = *reinterpret_cast<const int4*>(a.beta_q + c * 256 + lane * 4);
+    }
+
+    // clamped to +-32767; sum, and sum of squares in two parts (see above)
+    int32_t sum[R], lo[R], hi[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        sum[r] = lo[r] = hi[r] = 0;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            uint32_t sq = 0;                               // four squares of at most 32767^2: below 2^32
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t t = v[r][c][h];             // (a copy: of an element itself the bit cast takes element 0)
+                const v2s w = __builtin_elementwise_max(__builtin_bit_cast(v2s, t), v2s{-32767, -32767});
+                v[r][c][h] = __builtin_bit_cast(uint32_t, w);
+                sum[r] = __builtin_amdgcn_sdot2(w, v2s{1, 1}, sum[r], false);
+                sq = (uint32_t)__builtin_amdgcn_sdot2(w, w, (int32_t)sq, false);
+            }
+            lo[r] += (int32_t)(sq & 0xffffu);
+            hi[r] += (int32_t)(sq >> 16);
+        }
+    }
+    // t[r] of all lanes -> the total of row lane / (64 / R)
+    auto fold = [&](int32_t (&t)[R]) {
+        int32_t u[R / 2];
+#pragma unroll
+        for (int r = 0; r < R / 2; ++r) {
+            const auto e = __builtin_amdgcn_permlane32_swap((uint32_t)t[r], (uint32_t)t[r + R / 2], false, false);
+            u[r] = (int32_t)(e[0] + e[1]);
+        }
+        const auto e = __builtin_amdgcn_permlane16_swap((uint32_t)u[0], (uint32_t)u[R / 2 - 1], false, false);
+        return group_sum_i32<16>((int32_t)(e[0] + e[1]));
+    };
+    const int32_t s = fold(sum), s_lo = fold(lo), s_hi = fold(hi);
+    const uint64_t sq = (uint64_t)(uint32_t)s_lo + ((uint64_t)(uint32_t)s_hi << 16);
+    const uint32_t Cu = 256 * NCH;
+    const int32_t mu = ln_row_mean(s, Cu, a.magic_c);
+    const uint32_t var = ln_row_variance((uint64_t)((int64_t)sq - 2 * (int64_t)mu * s + (int64_t)Cu * ((int64_t)mu * mu)), Cu, a.magic_c);
+    const int32_t f = ln_factor_of_sigma(isqrt_floor_rowwise<64 / R>(var, lane & (64 / R - 1)));
+
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (row0 + r >= a.rows) break;
+        const int32_t mu_r = __builtin_amdgcn_readlane(mu, r * (64 / R)), f_r = __builtin_amdgcn_readlane(f, r * (64 / R));
+        int8_t* const y = a.y + (row0 + r) * a.ldy;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int32_t g[4] = {gm[c].x, gm[c].y, gm[c].z, gm[c].w}, b[4] = {bt[c].x, bt[c].y, bt[c].z, bt[c].w};
+            int32_t o[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int32_t d = (int32_t)(int16_t)(v[r][c][e >> 1] >> (16 * (e & 1))) - mu_r;      // |d| < 2^17
+                const int32_t n = (int32_t)((uint32_t)d * (uint32_t)f_r) >> 14;                     // |d f| < 2^30
+                o[e] = smad24(n, g[e], b[e] + rnd) >> (a.shift - 8);                                // the result and eight more bits
+            }
+            auto two = [](int32_t p, int32_t q) {
+                return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(v2s, __builtin_amdgcn_cvt_pk_i16(p, q)), v2s{-127 * 256, -127 * 256}));
+            };
+            *reinterpret_cast<uint32_t*>(y + c * 256 + lane * 4) = __builtin_amdgcn_perm(two(o[2], o[3]), two(o[0], o[1]), 0x07050301u);
+        }
+    }
+}
+
 // Alg. 4's integer square root on its own.  METHOD 0: a value per lane.  METHOD 1-3: the LPR = 64, 32, 16 lanes of a
 // group take the group's values one after the other, all lanes working on one value, as the row kernel does with its
 // one variance per row.
@@ -311,6 +406,19 @@ int launch_layernorm16(const int16_t* x, int8_t* y, int64_t rows, int32_t C, int
     const bool al = aligned(x, 8) && ldx % 4 == 0 && aligned(y, 4) && ldy % 4 == 0 && C % 4 == 0 &&
                     aligned(gamma_q, 16) && aligned(beta_q, 16);
     // (wide chunks pay from about 8192 rows on: [32768,768] 19.3 -> 17.2 us; a few hundred rows lose half a microsecond)
+    // From 4096 rows on (2741 rows of 768 3.5 us with either), in forwards, us, without / with: Base 32 x 128 745.6 / 737.3, Large 32 x 128 1856.8 / 1845.5, 256 x 128 10069 /
+    // 10015.  Not 768 columns from 8192 rows on: there wide chunks have their 16 bytes a lane, which this kernel has not, and rows come from beyond the L2s: 61 x 251
+    // 1838 / 1849, 64 x 512 4022 / 4026.
+    if (al && rows >= 4096 && shift >= 8 && (C == 512 || C == 1024 || (C == 768 && rows < 8192))) {
+        const int64_t blocks = (rows + 4 * (LN_THREADS / 64) - 1) / (4 * (LN_THREADS / 64));
+        const dim3 grid((unsigned)blocks), block(LN_THREADS);
+        if (C == 512) hipLaunchKernelGGL(layernorm_many_kernel<2>, grid, block, 0, stream, a);
+        else if (C == 768) hipLaunchKernelGGL(layernorm_many_kernel<3>, grid, block, 0, stream, a);
+        else hipLaunchKernelGGL(layernorm_many_kernel<4>, grid, block, 0, stream, a);
+        IBERT_LAUNCH_CHECK("layernorm kernel");
+        g_last_kernel = "layernorm_many_kernel";
+        return IBERT_OK;
+    }
     const bool wide = rows >= 8192 && al && aligned(x, 16) && ldx % 8 == 0 && aligned(y, 8) && ldy % 8 == 0 && C % 8 == 0;
     return dispatch_rows(a, al, true, wide, stream);
 }

@@ -179,6 +179,30 @@ def test_layernorm_matches_oracle(G, C, rows):
         assert np.all(got[:, C:] == 77)
 
 
+@pytest.mark.parametrize("C", [512, 768, 1024])
+@pytest.mark.parametrize("rows", [4095, 4096, 4097, 4111, 8191, 8192])
+def test_layernorm_many_int16_rows(G, C, rows):
+    # four rows to a wavefront: both sides of the switch, rows that leave a group or a workgroup unfilled, the least shift it takes and the one before, and what
+    # 16 bits hold that the clamp does not
+    from paper_2101_01321_amd import binding as B
+    x, S, gamma, beta = synth.layernorm_inputs(rows, C, seed=rows + C)
+    x[::5] *= 40
+    x = np.clip(x, -32767, 32767)
+    x[0], x[1], x[2], x[-1] = 123, 0, -32768, -32768
+    x[3] = np.where(np.arange(C) % 2, 32767, -32768)
+    x[4] = np.where(np.arange(C) == C - 1, 1, 0)
+    x[-2] = 32767
+    gq, bq, s = B.ibert_layernorm_params_from_float(gamma, beta, 5.0 / 127)
+    for shift in (s, 8, 7):
+        G.say("layernorm int16 [%d,%d] shift %d" % (rows, C, shift))
+        got = G.layernorm(x, gq, bq, shift, ldx=C + 8, ldy=C + 16, half=True)
+        _eq(got[:, :C], oracle.layernorm(x, gq, bq, shift), "layernorm int16 [%d,%d] shift %d" % (rows, C, shift))
+        assert np.all(got[:, C:] == 77)
+        if shift == s:
+            want = b"layernorm_many_kernel" if rows >= 4096 and (C != 768 or rows < 8192) else b"layernorm_rows_kernel"
+            assert B.lib().ibert_last_kernel() == want
+
+
 def test_layernorm_full_shape_and_small_sigma(G):
     from paper_2101_01321_amd import binding as B
     x, S, gamma, beta = synth.layernorm_inputs(4096, 768)   # configs[1]
