@@ -213,18 +213,19 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_rows_kernel(LayerNormArg
     else finish(std::false_type{});
 }
 
-// Many int16 rows of 256 NCH columns, four to a wavefront, all 64 lanes on each (aligned as ALIGNED above, shift at least 8).  Bound: ALU issue, then HBM.
-// What the kernel above repeats in every lane of a row is done for R rows at once here: sums are reduced with the rows folded into the lanes (each exchange leaves
+// int16 rows of 256 NCH columns, R of them to a wavefront, all 64 lanes on each (aligned as ALIGNED above, shift at least 8).  Bound: ALU issue, then HBM; few rows: latency.
+// What the kernel above repeats in every lane of a row is done for R = 4 rows at once here: sums are reduced with the rows folded into the lanes (each exchange leaves
 // a lane half of the rows), after which 64 / R lanes hold a row's and work out its mean, variance, root and factor, which go back to all lanes as scalars.
 // A value costs half a maximum, half a product for the sum, half for the squares and half an addition for their two-part sum, then a difference, a product, a shift, a
 // multiply-add, a shift, and 1.25 instructions of packing that saturates.  175 instructions a row of 768 instead of 240.  us, rows just written, the kernel above / this (moving as many bytes
 // takes 2.2, 4.4, 12.2 and 15.7): [4096,768] 4.08 / 3.66, [15311,768] 9.25 / 8.13, [32768,768] 16.4 / 14.5, [32768,1024] 21.8 / 17.9; from beyond the caches the same to 5 % shorter.
+// R = 1, where four rows would leave SIMDs without a wavefront, is the shorter chain alone: [128,768] 2.43 / 2.38, [1024,1024] 2.70 / 2.64, [2741,768] 3.48 / 3.31.
 // Tried and not kept: two and eight rows ([15311,768] 8.6, 8.4), wavefronts that go on to further rows, requested ahead (8.3 to 9.4: twice the registers), int32 rows
 // ([15311,768] 10.5 / 11.6: twice the bytes held).
-template <int NCH>
+template <int NCH, int R>
 __global__ __launch_bounds__(LN_THREADS) void layernorm_many_kernel(LayerNormArgs a)
 {
-    constexpr int R = 4;
+    static_assert(R == 1 || R == 4, "rows of a wavefront");
     typedef short v2s __attribute__((ext_vector_type(2)));
     typedef uint32_t v2u __attribute__((ext_vector_type(2)));
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -269,14 +270,18 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_many_kernel(LayerNormArg
     }
     // t[r] of all lanes -> the total of row lane / (64 / R)
     auto fold = [&](int32_t (&t)[R]) {
-        int32_t u[R / 2];
+        if constexpr (R == 1) {
+            return group_sum_i32<64>(t[0]);
+        } else {
+            int32_t u[2];
 #pragma unroll
-        for (int r = 0; r < R / 2; ++r) {
-            const auto e = __builtin_amdgcn_permlane32_swap((uint32_t)t[r], (uint32_t)t[r + R / 2], false, false);
-            u[r] = (int32_t)(e[0] + e[1]);
+            for (int r = 0; r < 2; ++r) {
+                const auto e = __builtin_amdgcn_permlane32_swap((uint32_t)t[r], (uint32_t)t[r + 2], false, false);
+                u[r] = (int32_t)(e[0] + e[1]);
+            }
+            const auto e = __builtin_amdgcn_permlane16_swap((uint32_t)u[0], (uint32_t)u[1], false, false);
+            return group_sum_i32<16>((int32_t)(e[0] + e[1]));
         }
-        const auto e = __builtin_amdgcn_permlane16_swap((uint32_t)u[0], (uint32_t)u[R / 2 - 1], false, false);
-        return group_sum_i32<16>((int32_t)(e[0] + e[1]));
     };
     const int32_t s = fold(sum), s_lo = fold(lo), s_hi = fold(hi);
     const uint64_t sq = (uint64_t)(uint32_t)s_lo + ((uint64_t)(uint32_t)s_hi << 16);
@@ -405,20 +410,28 @@ int launch_layernorm16(const int16_t* x, int8_t* y, int64_t rows, int32_t C, int
     LayerNormArgs a{reinterpret_cast<const int32_t*>(x), y, rows, C, ldx, ldy, gamma_q, beta_q, shift, ln_magic_for(C), EmbedArgs{}};
     const bool al = aligned(x, 8) && ldx % 4 == 0 && aligned(y, 4) && ldy % 4 == 0 && C % 4 == 0 &&
                     aligned(gamma_q, 16) && aligned(beta_q, 16);
-    // (wide chunks pay from about 8192 rows on: [32768,768] 19.3 -> 17.2 us; a few hundred rows lose half a microsecond)
-    // From 4096 rows on (2741 rows of 768 3.5 us with either), in forwards, us, without / with: Base 32 x 128 745.6 / 737.3, Large 32 x 128 1856.8 / 1845.5, 256 x 128 10069 /
-    // 10015.  Not 768 columns from 8192 rows on: there wide chunks have their 16 bytes a lane, which this kernel has not, and rows come from beyond the L2s: 61 x 251
+    // Rows of whole chunks of 256 columns: four to a wavefront from 4096 on, in forwards, us, without / with: Base 32 x 128 745.6 / 737.3, Large 32 x 128 1856.8 / 1845.5,
+    // 256 x 128 10069 / 10015.  One below ([2741,768] 3.5 with four, 3.3 with one): Base 1 x 128 310.1 / 309.1, 8 x 61 408.9 / 407.2, Large 4 x 256 1222 / 1209.
+    // Not 768 columns from 8192 rows on: there wide chunks have their 16 bytes a lane, which this kernel has not, and rows come from beyond the L2s: 61 x 251
     // 1838 / 1849, 64 x 512 4022 / 4026.
-    if (al && rows >= 4096 && shift >= 8 && (C == 512 || C == 1024 || (C == 768 && rows < 8192))) {
-        const int64_t blocks = (rows + 4 * (LN_THREADS / 64) - 1) / (4 * (LN_THREADS / 64));
-        const dim3 grid((unsigned)blocks), block(LN_THREADS);
-        if (C == 512) hipLaunchKernelGGL(layernorm_many_kernel<2>, grid, block, 0, stream, a);
-        else if (C == 768) hipLaunchKernelGGL(layernorm_many_kernel<3>, grid, block, 0, stream, a);
-        else hipLaunchKernelGGL(layernorm_many_kernel<4>, grid, block, 0, stream, a);
+    if (al && shift >= 8 && (C == 512 || C == 1024 || (C == 768 && rows < 8192))) {
+        const int R = rows >= 4096 ? 4 : 1;
+        const int64_t blocks = (rows + R * (LN_THREADS / 64) - 1) / (R * (LN_THREADS / 64));
+#define IBERT_LN_MANY(NCH_, R_) hipLaunchKernelGGL((layernorm_many_kernel<NCH_, R_>), dim3((unsigned)blocks), dim3(LN_THREADS), 0, stream, a)
+        switch (10 * (C / 256) + R) {
+            case 24: IBERT_LN_MANY(2, 4); break;
+            case 34: IBERT_LN_MANY(3, 4); break;
+            case 44: IBERT_LN_MANY(4, 4); break;
+            case 21: IBERT_LN_MANY(2, 1); break;
+            case 31: IBERT_LN_MANY(3, 1); break;
+            default: IBERT_LN_MANY(4, 1); break;
+        }
+#undef IBERT_LN_MANY
         IBERT_LAUNCH_CHECK("layernorm kernel");
         g_last_kernel = "layernorm_many_kernel";
         return IBERT_OK;
     }
+    // (wide chunks pay from about 8192 rows on: [32768,768] 19.3 -> 17.2 us; a few hundred rows lose half a microsecond)
     const bool wide = rows >= 8192 && al && aligned(x, 16) && ldx % 8 == 0 && aligned(y, 8) && ldy % 8 == 0 && C % 8 == 0;
     return dispatch_rows(a, al, true, wide, stream);
 }
