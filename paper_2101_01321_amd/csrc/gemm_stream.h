@@ -26,8 +26,7 @@
 //     against 1.75 to 1.95; [32768,3072] x K 1024 105 -> 80 us).  A loop of nothing but the step's MFMAs sustains 4.05 POP/s on random
 //     operands, with its LDS reads 3.5, with its requests 3.0 -- 1425 ns a step, about what a step takes here.
 //   * An epilogue is what the address unit, then the ALU, make of it.  Rows leave and residuals come with neighbouring lanes on neighbouring
-//     bytes, through LDS (see `turn`; with GELU as they are), one unit of rows at a time while the next is being made (not 256x192 INT8 and GELU: what is
-//     stored before their last value would wait for all requests, see HOLD, so everything leaves behind it); the MFMA's first operand are
+//     bytes, through LDS (see `turn`; with GELU as they are), one unit of rows at a time while the next is being made; the MFMA's first operand are
 //     the rows of A, so that a lane has the same few channels for all its tokens and their constants are made once.  Cycles of a launch, thousands, with
 //     lane swaps in place of LDS and stores that left together at the end / as it is: [32768,1024] x K 1024 INT16 + residual 84.0 / 73.5,
 //     [32768,768] x K 768 63 / 56.5, x K 3072 133 / 125, [32768,3072] x K 1024 INT8 175 / 166, [32768,4096] x K 1024 + GELU 250 / 237; us: 45.3 /
@@ -466,9 +465,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
             auto value = [&](int i, int n) { return (int32_t)(((int64_t)acc[i][n >> 2][n & 3] * mm[i] + c0[i]) >> 32) >> sh[i]; };
             // Token n of the lane: row 16 (n / 4) + 4 u + n % 4 of the wavefront's tile.  Its results go to LDS; when a unit is complete it is read
             // back as it is moved, and stored while the next one is being made.  Before the first store this wavefront's requests have all
-            // landed (HOLD units give them time; both there are of a 256x192 INT8 or GELU tile), so that the waits of the next tile's first step, which
+            // landed (HOLD units give them time, of 256x192 INT8 and GELU tiles the first of two: with everything stored behind the last value [32768,3072] x K 1024
+            // INT8 101.7 us, as it is 98.3, [15311,3072] x K 768 + GELU 44.9 / 43.2, forward of Base 32 x 128 779.1 / 771.0), so that the waits of the next tile's first step, which
             // would count stores among the loads, can be left out.
-            constexpr int UNITS = FM / RO.unit, HOLD = UNITS >= 8 && OUT_I8 ? 4 : 2;
+            constexpr int UNITS = FM / RO.unit, HOLD = UNITS == 2 ? 1 : UNITS >= 8 && OUT_I8 ? 4 : 2;
+            constexpr bool SOON = UNITS == 2;                      // its first unit is stored four tokens into the second, when it has come back from LDS
             v4u mv[UNITS][RO.mv];
             auto store = [&](int unit) {
 #pragma unroll
@@ -497,8 +498,9 @@ __global__ __launch_bounds__(64 * NW) void gemm_stream_kernel(StreamArgs g)
                     if (unit + 1 == HOLD) __builtin_amdgcn_s_waitcnt(vm(0));
 #pragma unroll
                     for (int x = unit + 1 == HOLD ? 0 : unit - 1; x < unit; ++x)
-                        if (unit + 1 >= HOLD) store(x);
+                        if (unit + 1 >= HOLD && !SOON) store(x);
                 }
+                if (SOON && n == 4 * RO.unit + 3) store(0);
             };
             using T = std::true_type;
             using F = std::false_type;
