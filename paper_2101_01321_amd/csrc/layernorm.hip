@@ -219,7 +219,7 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_rows_kernel(LayerNormArg
 // A value costs half a maximum, half a product for the sum, half for the squares and half an addition for their two-part sum, then a difference, a product, a shift, a
 // multiply-add, a shift, and 1.25 instructions of packing that saturates.  175 instructions a row of 768 instead of 240.  us, rows just written, the kernel above / this (moving as many bytes
 // takes 2.2, 4.4, 12.2 and 15.7): [4096,768] 4.08 / 3.66, [15311,768] 9.25 / 8.13, [32768,768] 16.4 / 14.5, [32768,1024] 21.8 / 17.9; from beyond the caches the same to 5 % shorter.
-// R = 1, where four rows would leave SIMDs without a wavefront, is the shorter chain alone: [128,768] 2.43 / 2.38, [1024,1024] 2.70 / 2.64, [2741,768] 3.48 / 3.31.
+// R = 1, where four rows would leave SIMDs without a wavefront or some with one more than others, is the shorter chain alone: [128,768] 2.43 / 2.38, [1024,1024] 2.70 / 2.64, [2741,768] 3.48 / 3.31.
 // Tried and not kept: two and eight rows ([15311,768] 8.6, 8.4), wavefronts that go on to further rows, requested ahead (8.3 to 9.4: twice the registers), int32 rows
 // ([15311,768] 10.5 / 11.6: twice the bytes held).
 template <int NCH, int R>
@@ -410,12 +410,19 @@ int launch_layernorm16(const int16_t* x, int8_t* y, int64_t rows, int32_t C, int
     LayerNormArgs a{reinterpret_cast<const int32_t*>(x), y, rows, C, ldx, ldy, gamma_q, beta_q, shift, ln_magic_for(C), EmbedArgs{}};
     const bool al = aligned(x, 8) && ldx % 4 == 0 && aligned(y, 4) && ldy % 4 == 0 && C % 4 == 0 &&
                     aligned(gamma_q, 16) && aligned(beta_q, 16);
-    // Rows of whole chunks of 256 columns: four to a wavefront from 4096 on, in forwards, us, without / with: Base 32 x 128 745.6 / 737.3, Large 32 x 128 1856.8 / 1845.5,
-    // 256 x 128 10069 / 10015.  One below ([2741,768] 3.5 with four, 3.3 with one): Base 1 x 128 310.1 / 309.1, 8 x 61 408.9 / 407.2, Large 4 x 256 1222 / 1209.
-    // Not 768 columns from 8192 rows on: there wide chunks have their 16 bytes a lane, which this kernel has not, and rows come from beyond the L2s: 61 x 251
-    // 1838 / 1849, 64 x 512 4022 / 4026.
-    if (al && shift >= 8 && (C == 512 || C == 1024 || (C == 768 && rows < 8192))) {
-        const int R = rows >= 4096 ? 4 : 1;
+    // Rows of whole chunks of 256 columns.  Four rows to a wavefront make few, long workgroups, all of them on the chip at once, so that the compute units
+    // with one more than others set the time: taken where these workgroups fill 7/8 of their rounds of 256 units, one row to a wavefront otherwise.  us, rows just
+    // written, layernorm_rows_kernel / one / four: C 768 at 3500 rows 4.38 / 4.19 / 4.14, 4096 4.57 / 4.38 / 4.35, 4300 4.96 / 4.72 / 5.26, 6000 5.54 / 5.34 / 5.56, 8191 6.0 / 6.6 / 6.1;
+    // C 512, from 5/8 on, as a round of short rows does not last as long, at 5000 rows 4.69 / 4.57 / 4.69, 6000 5.06 / 5.06 / 4.80, 9000 6.56 / 6.49 / 5.91;
+    // C 1024, whose rows last longer, at 4096 4.99 / 4.46 / 4.97, 4300 5.38 / 4.90 / 6.16, 8192 7.56 / 6.83 / 7.19, 12288 10.2 / 10.1 / 9.5, 13300 10.4 / 10.6 / 10.9,
+    // 15311 11.6 / 11.9 / 11.3, 32768 20.2 / 19.6 / 17.6.  From 8192 rows on wide chunks have their 16 bytes a lane, which this kernel has not, and rows come from beyond the L2s: 768
+    // columns keep them (forwards of Base 61 x 251 1838 / 1849 with four, 64 x 512 4022 / 4026), 1024 where four do not fill their rounds.
+    constexpr int64_t UNITS = 256, TWO_ROUNDS = 2 * UNITS * 4 * (LN_THREADS / 64);       // (8192 rows)
+    const int64_t fours = (rows + 4 * (LN_THREADS / 64) - 1) / (4 * (LN_THREADS / 64)), rounds = (fours + UNITS - 1) / UNITS;
+    const bool filled = fours >= rounds * (C == 512 ? UNITS * 5 / 8 : UNITS * 7 / 8);
+    const bool many = C == 512 || (C == 768 && rows < TWO_ROUNDS) || (C == 1024 && (rows <= TWO_ROUNDS || filled));
+    if (al && shift >= 8 && many) {
+        const int R = filled && (C != 1024 || rows > TWO_ROUNDS) ? 4 : 1;
         const int64_t blocks = (rows + R * (LN_THREADS / 64) - 1) / (R * (LN_THREADS / 64));
 #define IBERT_LN_MANY(NCH_, R_) hipLaunchKernelGGL((layernorm_many_kernel<NCH_, R_>), dim3((unsigned)blocks), dim3(LN_THREADS), 0, stream, a)
         switch (10 * (C / 256) + R) {
