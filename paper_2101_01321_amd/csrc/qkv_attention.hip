@@ -345,6 +345,8 @@ static QkvTile qkv_tile(int32_t batch, int32_t seq, int32_t heads)
 //     32 x 16 90.9 / 82.1.  A head of two or three K steps takes little longer than a launch (a layer of 256 with 4 heads, one sequence of 128, called by itself: 26.5 / 23.8).
 //   * More tokens of a wider model: the persistent MatMul streams, while here the path from L2 bounds the loop (more bytes a product), 256 x 16, L = 128 forwards
 //     of 24 layers 10.0 / 10.2 ms; 64 x 16 3.37 / 3.24.  With 768 channels 256 x 12 311.6 / 296.3.
+//   * 512 workgroups have a place at once, and a few more begin anew behind them, which costs a wide head (more K steps) most: forwards of 24 layers, ms, 32 x 16, L = 128 1.99 / 1.82,
+//     33 x 16 2.71 / 2.78, 39 x 16 2.79 / 2.85, 44 x 16 3.04 / 2.91, 48 x 16 3.11 / 3.00, 52 x 16 3.27 / 3.24; 12 layers of 768 43 x 12 1.106 / 1.100, 48 x 12 1.119 / 1.113.
 //   * Rows past the end of a sequence are multiplied too: 512 x 12, L = 40 195.0 / 197.9, L = 16 113.6 / 109.6, but 1024 x 12 173.4 / 178.2; 512 x 16, L = 40 308.6 / 340.6.
 //   * More than 128 tokens take all of a unit, so that whole rounds of units count: 16 x 16, L = 256 95.1 / 86.1, 21 x 12 88.1 / 82.3, L = 192 69.7 / 66.0; 11 x 12, L = 150 50.9 /
 //     51.0; 24 x 12, L = 192 75.3 / 79.6.
@@ -353,7 +355,7 @@ static bool qkv_faster(int32_t batch, int32_t seq, int32_t heads)
     const int64_t n = (int64_t)batch * heads;
     if (n > 512 && 4 * seq < 3 * qkv_tile(batch, seq, heads).rows()) return false;
     if (seq > 128) return n >= 160 && n <= 256;
-    if (heads > 12 && n > 1024) return false;
+    if (heads > 12 && (n > 1024 || (seq > 64 && n > 512 && n < 704))) return false;
     return n >= (seq > 64 ? 128 : 96) || heads <= 6;
 }
 

@@ -486,7 +486,7 @@ def test_qkv_attention_deals_every_head_once_and_reads_its_weights_ahead(heads):
 
 @pytest.mark.parametrize("batch,seq,heads,tile", [(8, 61, 12, 8214), (32, 128, 12, 8412), (32, 128, 16, 8412), (1, 128, 4, 8414), (1, 128, 12, 0), (3, 59, 12, 0), (8, 128, 12, 0), (256, 128, 16, 0),
                                                   (4, 256, 16, 0), (16, 256, 16, 16412), (16, 150, 12, 16313), (61, 251, 12, 0), (128, 64, 12, 8422), (43, 32, 12, 8222), (128, 32, 12, 8442),
-                                                  (512, 40, 16, 0), (1024, 16, 12, 0)])
+                                                  (512, 40, 16, 0), (1024, 16, 12, 0), (33, 128, 16, 0), (43, 128, 16, 0), (44, 128, 16, 8412), (43, 128, 12, 8412), (33, 64, 16, 8422)])
 def test_qkv_attention_is_chosen_where_it_was_the_faster_way(batch, seq, heads, tile):
     rc, got, *_ = _qkv_plan(batch, seq, heads)
     assert (got if rc == 0 else 0) == tile
