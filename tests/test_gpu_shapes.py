@@ -803,3 +803,135 @@ def test_qkv_attention_any_constants(G, shift, mult, bias, tile):
     G.say("qkv + attention, shift %d mult %d bias %d tile %d" % (shift, mult, bias, tile))
     y, z, _ = run(tile)
     _eq(z, want, "shift %d mult %d bias %d" % (shift, mult, bias))
+
+
+def _set_constants(kind):
+    """An edit for _qkv_layer: the constants of a kind, on both sides."""
+    import torch
+    import qkv_constants as QC
+
+    def edit(model, w, q):
+        QC.deal(w, model.cfg.hidden, kind)
+        for name in ("m_qkv", "s_qkv", "b_qkv"):
+            t = model.layers[0].tensors[name]
+            t.copy_(torch.from_numpy(np.ascontiguousarray(w[name], dtype=np.int32)).to(t.device))
+    return edit
+
+
+# (128 tokens: a layer call with a workspace stores what the kernel made of the constants, in Q, K and V)
+@pytest.mark.parametrize("kind", ["tall", "fast", "slow", "bias", "mixed"])
+@pytest.mark.parametrize("tile", [8412, 8414, 16313, 16412])
+def test_qkv_attention_constants_in_q_k_and_v(G, kind, tile):
+    import torch
+    from paper_2101_01321_amd import binding as B
+    import qkv_constants as QC
+    heads, B_, L = 4, 2, 128
+    cfg, x_q, S_x, w, q = QC.layer(heads, B_, L)
+    model = G.DeviceModel(cfg, S_x)
+    _set_constants(kind)(model, w, q)
+    want, inter = oracle.encoder_layer(w, q, x_q, B_, L, cfg.hidden, heads, cfg.ffn, dump=True)
+    G.say("qkv + attention, %s constants, tile %d" % (kind, tile))
+    B.lib().ibert_qkv_attention_override(tile)
+    try:
+        y = model.layer_forward(0, G.to_dev(x_q))
+        torch.cuda.synchronize()
+    finally:
+        B.lib().ibert_qkv_attention_override(-1)
+    got = model.intermediates(r_half=True)
+    for name in ("qkv", "ctx"):
+        _eq(got[name], inter[name], "%s, tile %d, %s" % (kind, tile, name))
+    _eq(y.cpu().numpy(), want, "%s, tile %d" % (kind, tile))
+
+
+# (several sequences to a workgroup, rows of half a key block, tiles that no layer call stores Q, K and V of: in V, which the context shows)
+@pytest.mark.parametrize("kind", ["values tall", "values fast", "values slow", "values bias"])
+@pytest.mark.parametrize("tile,L", [(8112, 29), (8114, 32), (8212, 61), (8214, 64), (8222, 32), (8442, 30), (8422, 61), (8312, 96), (8314, 70)])
+def test_qkv_attention_constants_in_v(G, kind, tile, L):
+    cfg, x_q, w, q, run = _qkv_layer(G, 4, 5, L, edit=_set_constants(kind))
+    want, inter = oracle.encoder_layer(w, q, x_q, 5, L, cfg.hidden, 4, cfg.ffn, dump=True)
+    G.say("qkv + attention, %s constants, tile %d L=%d" % (kind, tile, L))
+    y, z, got = run(tile)
+    _eq(got["ctx"], inter["ctx"], "%s, tile %d, ctx" % (kind, tile))
+    _eq(z, want, "%s, tile %d" % (kind, tile))
+
+
+def _scores(sdy, S, cdy):
+    """An edit for _qkv_layer: the attention's constants, on both sides."""
+    from paper_2101_01321_amd import binding as B
+
+    def edit(model, w, q):
+        q.scores_m, q.scores_s = sdy
+        q.ctx_m, q.ctx_s = cdy
+        q.softmax = P.softmax_params(S, 7)
+        for quant in (model.layers[0].quant, model.quant[0]):
+            quant.scores_dy, quant.ctx_dy = B.Dyadic(*sdy), B.Dyadic(*cdy)
+            quant.softmax = B.ibert_softmax_params_from_scale(S, model.cfg.seq, 7)
+    return edit
+
+
+def _kernels(run):
+    """(step, kernel) of what run() launches in layers."""
+    from paper_2101_01321_amd import binding as B
+    B.ibert_profile_begin(64)
+    try:
+        run()
+    finally:
+        records = B.ibert_profile_end(64)
+    return [(r[0], r[4]) for r in records]
+
+
+# every instantiation of the form for scores shifts from 34 on, and beside it the other one; context shifts on both sides of 32; masks past both ends of a sequence
+@pytest.mark.parametrize("tile,L", [(8112, 20), (8212, 64), (8312, 70), (8412, 128), (8114, 32), (8214, 33), (8314, 96), (8414, 100), (8222, 32), (8422, 61), (8442, 30),
+                                    (16313, 150), (16412, 251)])
+@pytest.mark.parametrize("sdy,form", [((1518500250, 36), 4), ((1187698534, 34), 4), ((1187698534, 33), 3), ((1187698534, 28), 3)])
+def test_qkv_attention_both_forms(G, tile, L, sdy, form):
+    import torch
+    from paper_2101_01321_amd import binding as B
+    B_, heads, S = 5 if L <= 128 else 2, 2, 2.0 ** -6
+    for cdy in ((1073741824, 37), (8388608, 30)):
+        assert _attention_form(sdy, B.ibert_softmax_params_from_scale(S, L, 7), cdy, B_ * heads * -(-L // 64)) == form
+        cfg, x_q, w, q, run = _qkv_layer(G, heads, B_, L, edit=_scores(sdy, S, cdy))
+        want, inter = oracle.encoder_layer(w, q, x_q, B_, L, cfg.hidden, heads, cfg.ffn, dump=True)
+        G.say("qkv + attention, form %d, tile %d L=%d s=%s c=%s" % (form, tile, L, sdy, cdy))
+        out = []
+        ran = [k for step, k in _kernels(lambda: out.extend(run(tile))) if step == 1 and k.startswith("qkv_attention")]
+        digits = str(tile)
+        name = "qkv_attention_kernel<%s, %s, %s, %d, %s>" % (digits[:-3], digits[-3], digits[-2], form, digits[-1])
+        assert ran and all(k == name for k in ran), (ran, name)
+        _eq(out[2]["ctx"], inter["ctx"], "form %d, tile %d, ctx" % (form, tile))
+        _eq(out[1], want, "form %d, tile %d" % (form, tile))
+        lens = [L, 1, (L + 1) // 2, max(1, L - 1), min(L, 64)][:B_]
+        given = [L + 7, 0, (L + 1) // 2, max(1, L - 1), min(L, 64)][:B_]       # (taken as the nearest length there is)
+        cfg, x_q, w, q, run = _qkv_layer(G, heads, B_, L, given, edit=_scores(sdy, S, cdy))
+        want = oracle.encoder_layer(w, q, x_q, B_, L, cfg.hidden, heads, cfg.ffn, key_lens=np.asarray(lens, np.int32))
+        _eq(run(tile)[1], want, "masked, form %d, tile %d" % (form, tile))
+
+
+# constants that the attention has no table of the exponent for: the steps run apart, also where a tile is asked for
+@pytest.mark.parametrize("S,sdy,form", [(2.0 ** -8, (1518500250, 36), 1), (2.0 ** -8, (1187698534, 28), 2), (2.0 ** -6, (-1518500250, 36), 0), (2.0 ** -6, (1518500250, 46), 0)])
+@pytest.mark.parametrize("tile,L", [(8412, 128), (8222, 30), (16412, 200)])
+def test_qkv_attention_without_a_table_runs_apart(G, S, sdy, form, tile, L):
+    import torch
+    from paper_2101_01321_amd import binding as B
+    import qkv_constants as QC
+    B_, heads, cdy = 2, 4, (1073741824, 37)
+    assert _attention_form(sdy, B.ibert_softmax_params_from_scale(S, L, 7), cdy, B_ * heads * -(-L // 64)) == form
+    cfg, x_q, S_x, w, q = QC.layer(heads, B_, L)
+    model = G.DeviceModel(cfg, S_x)
+    _scores(sdy, S, cdy)(model, w, q)
+    want, inter = oracle.encoder_layer(w, q, x_q, B_, L, cfg.hidden, heads, cfg.ffn, dump=True)
+    x = G.to_dev(x_q)
+    G.say("qkv and attention apart, form %d, tile %d L=%d" % (form, tile, L))
+    B.lib().ibert_qkv_attention_override(tile)
+    try:
+        model.ws.fill_(0x55)
+        out = []
+        kernels = _kernels(lambda: out.append(model.forward(x)))
+        torch.cuda.synchronize()
+    finally:
+        B.lib().ibert_qkv_attention_override(-1)
+    assert not any(k.startswith("qkv_attention") for _, k in kernels), kernels
+    got = model.intermediates(r_half=True)
+    _eq(got["qkv"], inter["qkv"], "form %d, qkv" % form)
+    _eq(got["ctx"], inter["ctx"], "form %d, ctx" % form)
+    _eq(out[0].cpu().numpy(), want, "form %d" % form)

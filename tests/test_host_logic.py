@@ -492,6 +492,31 @@ def test_qkv_attention_is_chosen_where_it_was_the_faster_way(batch, seq, heads, 
     assert (got if rc == 0 else 0) == tile
 
 
+@pytest.mark.parametrize("kind", ["tall", "fast", "slow", "bias", "mixed"])
+def test_qkv_constants_show_a_wrong_requantization(kind):
+    # what the GPU tests of the joined kernel feed it: results vary in every channel that is meant to, and each of the mistakes that a requantization may
+    # have (rounding left out, half a unit too much, a clamp at -128, no clamp, a wrapped sum) changes some
+    import qkv_constants as QC
+    heads, B_, L = 4, 2, 128
+    cfg, x, _, w, q = QC.layer(heads, B_, L)
+    vary = QC.deal(w, cfg.hidden, kind)
+    _, inter = oracle.encoder_layer(w, q, x, B_, L, cfg.hidden, heads, cfg.ffn, dump=True)
+    qkv = inter["qkv"]
+    assert (qkv.min(axis=0) < qkv.max(axis=0))[vary].all()
+    acc = x.reshape(B_ * L, -1).astype(np.int64) @ w["w_qkv"].astype(np.int64).T.reshape(cfg.hidden, -1)
+    assert np.abs(acc).max() < 1 << 23
+    total, m, sh = acc + w["b_qkv"].astype(np.int64), w["m_qkv"].astype(np.int64), w["s_qkv"].astype(np.int64)
+    half = np.where(sh > 0, np.int64(1) << np.maximum(sh - 1, 0), 0)
+
+    def requantized(t=total, add=half, lo=-127, hi=127):
+        return np.clip((t * m + add) >> sh, lo, hi)
+    assert np.array_equal(requantized(), qkv)
+    for name, wrong in (("rounding left out", requantized(add=0 * half)), ("one more", requantized(add=half + (np.int64(1) << np.maximum(sh - 8, 0)))), ("clamp", requantized(lo=-128)),
+                        ("wrapped byte", requantized(lo=-(1 << 62), hi=1 << 62).astype(np.int8)), ("wrapped sum", requantized(t=((total + (1 << 30)) % (1 << 31)) - (1 << 30)))):
+        if name != "wrapped sum" or kind == "bias":
+            assert (wrong != qkv).any(), name
+
+
 # ------------------------------------------------------------------------------------------- buffers that end with the last row
 def test_rows_of_the_persistent_tiles_are_checked_whole_against_the_buffers_end(tmp_path):
     # Output and residual are buffers that end with the last row, so that lanes past it neither load nor store.  The range check takes the
