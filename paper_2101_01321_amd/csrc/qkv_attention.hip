@@ -34,7 +34,6 @@ struct QkvAttentionArgs {
     int32_t batch, nk;             // nk: K steps (K / 128)
     int32_t xs, cols, groups;      // see qkv_attention_place
     uint32_t cols_magic;           // see udiv_fix
-    int32_t k_fast;                // K * 127^2 < 2^30
 };
 
 constexpr int QA_COLS = 192;
@@ -219,7 +218,7 @@ __global__ __launch_bounds__(64 * NW, 4) void qkv_attention_kernel(QkvAttentionA
 
     // ---- requantization into LDS ---------------------------------------------------------------
     // A wavefront's columns are of two matrices at most; their multipliers and shifts go to LDS, and how they can be computed with as the least of both.
-    // FAST (gemm_kernel.h): every shift in [33, 62], every |bias| and K * 127^2 below 2^30: |sum| is below 2^31.  TALL: and every shift at least 40, which those of
+    // FAST (gemm_kernel.h): every shift in [33, 62], every |bias| below 2^30: |sum| is below 2^31, as K * 128^2 is below 2^30 too.  TALL: and every shift at least 40, which those of
     // these matrices mostly are.  With w = floor(sum m / 2^(s - 8)), the high half of a product shifted, the result is floor((w + 128) / 256): 16 bits of w hold all that the clamp
     // leaves, so packing two saturates, the 128 is added to both (saturating) and the high bytes are the result: 3.75 instructions a value, with a 64-bit
     // multiply-add 4.75 slots.
@@ -234,7 +233,7 @@ __global__ __launch_bounds__(64 * NW, 4) void qkv_attention_kernel(QkvAttentionA
     make_exp_table(a, lds0 + QL::TABLE, tid, 64 * NW);
     __syncthreads();
     const int m0 = par[2 * QA_COLS + (wc >> 6)], m1 = par[2 * QA_COLS + ((wc + 32) >> 6)];
-    const int mode = __builtin_amdgcn_ballot_w64(big < 0) != 0 || !g.k_fast ? (int)SLOW : __builtin_amdgcn_readfirstlane(m0 < m1 ? m0 : m1);
+    const int mode = __builtin_amdgcn_ballot_w64(big < 0) != 0 ? (int)SLOW : __builtin_amdgcn_readfirstlane(m0 < m1 ? m0 : m1);
     auto requantize = [&](auto&& pack) {
 #pragma unroll
         for (int i = 0; i < FN; ++i) {
@@ -359,10 +358,14 @@ static bool qkv_faster(int32_t batch, int32_t seq, int32_t heads)
     return n >= (seq > 64 ? 128 : 96) || heads <= 6;
 }
 
+// (Buffers of W_qkv below 2 GiB, and sums of products below 2^30, which the kernel's fast requantizations take for granted.)
+constexpr int32_t QA_MAX_HIDDEN = 1 << 13;
+static_assert((int64_t)QA_MAX_HIDDEN * 128 * 128 < (1 << 30) && (int64_t)3 * QA_MAX_HIDDEN * QA_MAX_HIDDEN < 0x7fffffff, "widths");
+
 bool qkv_attention_ok(const int8_t* x, const int8_t* w, const int8_t* ctx, int32_t batch, int32_t seq, int32_t hidden, int32_t heads, const ibert_dyadic& scores_dy,
                       const ibert_softmax_params& sp, const ibert_dyadic& ctx_dy)
 {
-    if (seq > 256 || hidden != heads * ATT_DH || hidden % 128 != 0 || hidden > (1 << 13) || (int64_t)batch * heads > (1 << 24) || !aligned(x, 16) || !aligned(w, 16) ||
+    if (seq > 256 || hidden != heads * ATT_DH || hidden % 128 != 0 || hidden > QA_MAX_HIDDEN || (int64_t)batch * heads > (1 << 24) || !aligned(x, 16) || !aligned(w, 16) ||
         !aligned(ctx, 4))
         return false;
     if (g_qkv_override == 0 || (g_qkv_override < 0 && !qkv_faster(batch, seq, heads)) || seq > qkv_tile(batch, seq, heads).rows()) return false;
@@ -417,7 +420,6 @@ int launch_qkv_attention(const int8_t* x, const int8_t* w, const int32_t* bias, 
     if (form < 3 || seq > t.rows()) return IBERT_ERR_NOT_IMPLEMENTED;
     g.x = x; g.w = w; g.bias = bias; g.mult = mult; g.shift = shift; g.qkv = qkv;
     g.batch = batch; g.nk = hidden / 128;
-    g.k_fast = (int64_t)hidden * 16129 < (1 << 30);
     switch (t.code()) {
 #define IBERT_QA_TILE(NW_, FM_, S_, ST_) case 1000 * NW_ + 100 * FM_ + 10 * S_ + ST_: return launch_tile<NW_, FM_, S_, ST_>(g, form, stream);
         IBERT_QA_TILE(8, 1, 1, 2) IBERT_QA_TILE(8, 2, 1, 2) IBERT_QA_TILE(8, 3, 1, 2) IBERT_QA_TILE(8, 4, 1, 2)
