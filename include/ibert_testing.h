@@ -52,6 +52,10 @@ int ibert_attention_form(const ibert_dyadic* scores_dy, const ibert_softmax_para
  * fit_* with the largest table).  Asks the device. */
 int ibert_attention_buffers(int32_t seq, int32_t form, int64_t workgroups, int32_t* shared, int32_t* fit_two, int32_t* fit_one);
 
+/* How ibert_layernorm_i16 takes `rows` aligned rows: *rows_of_wavefront = 1 or 4 rows to a wavefront of layernorm_many_kernel, 0 where it is
+ * layernorm_rows_kernel.  (The name that ibert_last_kernel() gives is the same for 1 and 4.)  Host only. */
+int ibert_layernorm_i16_plan(int64_t rows, int32_t C, int32_t shift, int32_t* rows_of_wavefront);
+
 /* Steps 1 to 4 of a layer as one kernel: 0 never; a tile (1000 wavefronts + 100 MFMA rows of one + 10 sequences + stages, one of those ibert_qkv_attention_plan names)
  * wherever its rows hold a sequence and the parameters allow it; negative where it is the faster way (the default).  Process-wide, not thread-safe. */
 void ibert_qkv_attention_override(int32_t tile);

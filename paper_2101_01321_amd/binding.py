@@ -101,6 +101,7 @@ SIGNATURES = {
     "ibert_gemm_xcd_blocks": (None, [C.c_int32]),
     "ibert_attention_form": (C.c_int, [C.POINTER(Dyadic), C.POINTER(SoftmaxParams), C.POINTER(Dyadic), C.c_int64, C.POINTER(C.c_int32)]),
     "ibert_attention_buffers": (C.c_int, [C.c_int32, C.c_int32, C.c_int64] + 3 * [C.POINTER(C.c_int32)]),
+    "ibert_layernorm_i16_plan": (C.c_int, [C.c_int64, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]),
     "ibert_qkv_attention_override": (None, [C.c_int32]),
     "ibert_qkv_attention_plan": (C.c_int, [C.c_int32] * 3 + [C.POINTER(C.c_int32), _P, _P, _P]),
     "ibert_gemm_weight_plan": (C.c_int, [C.POINTER(GemmDesc), C.c_int32, C.POINTER(C.c_int32), _P, _P]),

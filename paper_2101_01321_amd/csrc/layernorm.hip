@@ -213,15 +213,17 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_rows_kernel(LayerNormArg
     else finish(std::false_type{});
 }
 
-// int16 rows of 256 NCH columns, R of them to a wavefront, all 64 lanes on each (aligned as ALIGNED above, shift at least 8).  Bound: ALU issue, then HBM; few rows: latency.
+// int16 rows of 256 NCH columns, R of them to a wavefront, all 64 lanes on each (aligned as ALIGNED above, shift at least 8).  Bound: few rows, up to a wavefront a SIMD (4096 rows at R = 4):
+// latency, the chain from the loads over the sums to the factor -- with 175 instead of 240 instructions a row a launch of 4096 rows of 768 keeps the vector ALU busy 32 instead of 56 % of its
+// cycles and takes as long (4.52 / 4.55 us).  Many rows: memory; moving as many bytes as 32768 rows of 768 takes 12.2 us, this 15.3 to 15.6, layernorm_rows_kernel 16.7; of 1024 15.7, 20.1, 21.4 (inside
+// whole forwards; all figures at rows_of_wavefront).
 // What the kernel above repeats in every lane of a row is done for R = 4 rows at once here: sums are reduced with the rows folded into the lanes (each exchange leaves
 // a lane half of the rows), after which 64 / R lanes hold a row's and work out its mean, variance, root and factor, which go back to all lanes as scalars.
 // A value costs half a maximum, half a product for the sum, half for the squares and half an addition for their two-part sum, then a difference, a product, a shift, a
-// multiply-add, a shift, and 1.25 instructions of packing that saturates.  175 instructions a row of 768 instead of 240.  us, rows just written, the kernel above / this (moving as many bytes
-// takes 2.2, 4.4, 12.2 and 15.7): [4096,768] 4.08 / 3.66, [15311,768] 9.25 / 8.13, [32768,768] 16.4 / 14.5, [32768,1024] 21.8 / 17.9; from beyond the caches the same to 5 % shorter.
-// R = 1, where four rows would leave SIMDs without a wavefront or some with one more than others, is the shorter chain alone: [128,768] 2.43 / 2.38, [1024,1024] 2.70 / 2.64, [2741,768] 3.48 / 3.31.
-// Tried and not kept: two and eight rows ([15311,768] 8.6, 8.4), wavefronts that go on to further rows, requested ahead (8.3 to 9.4: twice the registers), int32 rows
-// ([15311,768] 10.5 / 11.6: twice the bytes held).
+// multiply-add, a shift, and 1.25 instructions of packing that saturates.
+// R = 1, where four rows would leave SIMDs without a wavefront or some with one more than others, is the shorter chain alone.
+// Tried and not kept, by itself on 15311 rows of 768 just written, where R = 4 takes 8.13 us: two and eight rows (8.6, 8.4), wavefronts that go on to further rows, requested ahead (8.3 to 9.4: twice
+// the registers), int32 rows (10.5 / 11.6: twice the bytes held).
 template <int NCH, int R>
 __global__ __launch_bounds__(LN_THREADS) void layernorm_many_kernel(LayerNormArgs a)
 {
@@ -401,6 +403,25 @@ int launch_layernorm(const int32_t* x, int8_t* y, int64_t rows, int32_t C, int64
     return dispatch_rows(a, al, false, false, stream);
 }
 
+// Which kernel for int16 rows that are aligned?  Rows of a wavefront of layernorm_many_kernel: 1 or 4; 0: layernorm_rows_kernel.
+// Rows of whole chunks of 256 columns.  Four rows to a wavefront make few, long workgroups, all of them on the chip at once, so that the compute units
+// with one more than others set the time: taken where these workgroups fill 7/8 of their rounds of 256 units, one row to a wavefront otherwise.
+// us a launch inside whole forwards, layernorm_rows_kernel / one / four: C 768 at 40 rows 2.95 / 2.91 / 3.33, 128 3.07 / 3.04 / 4.03, 488 3.11 / 3.04 / 3.97, 4096 4.55 / 4.50 / 4.52, 8192 5.97 / 6.21 /
+// 5.96, 15311 9.47 / 9.64 / 9.33, 32768 16.7 / 17.7 / 15.3 to 15.6; C 1024 at 1024 rows 3.33 / 3.28 / 4.07, 4096 5.37 / 5.38 / 5.37, 32768 21.4 / 23.0 / 20.1.  By itself, over and over on rows just
+// written: C 768 at 4300 rows 4.96 / 4.72 / 5.26, 6000 5.54 / 5.34 / 5.56; C 512, from 5/8 on, as a round of short rows does not last as long, at 5000 rows 4.69 / 4.57 / 4.69, 6000
+// 5.06 / 5.06 / 4.80, 9000 6.56 / 6.49 / 5.91; C 1024 at 4300 5.38 / 4.90 / 6.16, 8192 7.56 / 6.83 / 7.19, 12288 10.2 / 10.1 / 9.5, 13300 10.4 / 10.6 / 10.9.
+// From 8192 rows on wide chunks have their 16 bytes a lane, which this kernel has not: 1024 columns keep them where four rows do not fill their rounds.  768 columns keep them throughout, which the
+// figures above do not bear out where four rows fill their rounds: forwards, us, as it is / four, Base 64 x 128 1184 / 1175, 61 x 251 1927 / 1932, 256 x 128 3515 / 3484, 64 x 512 4296 / 4291.
+static int rows_of_wavefront(int64_t rows, int32_t C, int32_t shift)
+{
+    constexpr int64_t UNITS = 256, TWO_ROUNDS = 2 * UNITS * 4 * (LN_THREADS / 64);       // (8192 rows)
+    const int64_t fours = (rows + 4 * (LN_THREADS / 64) - 1) / (4 * (LN_THREADS / 64)), rounds = (fours + UNITS - 1) / UNITS;
+    const bool filled = fours >= rounds * (C == 512 ? UNITS * 5 / 8 : UNITS * 7 / 8);
+    const bool many = C == 512 || (C == 768 && rows < TWO_ROUNDS) || (C == 1024 && (rows <= TWO_ROUNDS || filled));
+    if (shift < 8 || !many) return 0;
+    return filled && (C != 1024 || rows > TWO_ROUNDS) ? 4 : 1;
+}
+
 // The same on int16 rows (the 16-bit form the MatMul can store its clamped LayerNorm input in).
 int launch_layernorm16(const int16_t* x, int8_t* y, int64_t rows, int32_t C, int64_t ldx, int64_t ldy,
                        const int32_t* gamma_q, const int32_t* beta_q, int32_t shift, hipStream_t stream)
@@ -410,19 +431,7 @@ int launch_layernorm16(const int16_t* x, int8_t* y, int64_t rows, int32_t C, int
     LayerNormArgs a{reinterpret_cast<const int32_t*>(x), y, rows, C, ldx, ldy, gamma_q, beta_q, shift, ln_magic_for(C), EmbedArgs{}};
     const bool al = aligned(x, 8) && ldx % 4 == 0 && aligned(y, 4) && ldy % 4 == 0 && C % 4 == 0 &&
                     aligned(gamma_q, 16) && aligned(beta_q, 16);
-    // Rows of whole chunks of 256 columns.  Four rows to a wavefront make few, long workgroups, all of them on the chip at once, so that the compute units
-    // with one more than others set the time: taken where these workgroups fill 7/8 of their rounds of 256 units, one row to a wavefront otherwise.  us, rows just
-    // written, layernorm_rows_kernel / one / four: C 768 at 3500 rows 4.38 / 4.19 / 4.14, 4096 4.57 / 4.38 / 4.35, 4300 4.96 / 4.72 / 5.26, 6000 5.54 / 5.34 / 5.56, 8191 6.0 / 6.6 / 6.1;
-    // C 512, from 5/8 on, as a round of short rows does not last as long, at 5000 rows 4.69 / 4.57 / 4.69, 6000 5.06 / 5.06 / 4.80, 9000 6.56 / 6.49 / 5.91;
-    // C 1024, whose rows last longer, at 4096 4.99 / 4.46 / 4.97, 4300 5.38 / 4.90 / 6.16, 8192 7.56 / 6.83 / 7.19, 12288 10.2 / 10.1 / 9.5, 13300 10.4 / 10.6 / 10.9,
-    // 15311 11.6 / 11.9 / 11.3, 32768 20.2 / 19.6 / 17.6.  From 8192 rows on wide chunks have their 16 bytes a lane, which this kernel has not, and rows come from beyond the L2s: 768
-    // columns keep them (forwards of Base 61 x 251 1838 / 1849 with four, 64 x 512 4022 / 4026), 1024 where four do not fill their rounds.
-    constexpr int64_t UNITS = 256, TWO_ROUNDS = 2 * UNITS * 4 * (LN_THREADS / 64);       // (8192 rows)
-    const int64_t fours = (rows + 4 * (LN_THREADS / 64) - 1) / (4 * (LN_THREADS / 64)), rounds = (fours + UNITS - 1) / UNITS;
-    const bool filled = fours >= rounds * (C == 512 ? UNITS * 5 / 8 : UNITS * 7 / 8);
-    const bool many = C == 512 || (C == 768 && rows < TWO_ROUNDS) || (C == 1024 && (rows <= TWO_ROUNDS || filled));
-    if (al && shift >= 8 && many) {
-        const int R = filled && (C != 1024 || rows > TWO_ROUNDS) ? 4 : 1;
+    if (const int R = al ? rows_of_wavefront(rows, C, shift) : 0) {
         const int64_t blocks = (rows + R * (LN_THREADS / 64) - 1) / (R * (LN_THREADS / 64));
 #define IBERT_LN_MANY(NCH_, R_) hipLaunchKernelGGL((layernorm_many_kernel<NCH_, R_>), dim3((unsigned)blocks), dim3(LN_THREADS), 0, stream, a)
         switch (10 * (C / 256) + R) {
@@ -515,4 +524,14 @@ extern "C" int ibert_embedding_i(const int32_t* ids, const int8_t* tok, const in
     if (!ids || !tok || !pos || !gamma_q || !beta_q || !y) return IBERT_ERR_NULL;
     return ibert::launch_embedding(ids, tok, pos, tokens, seq, hidden, vocab, *tok_dy, *pos_dy, gamma_q, beta_q, ln_shift, y,
                                    ldy, (hipStream_t)stream);
+}
+
+extern "C" int ibert_layernorm_i16_plan(int64_t rows, int32_t C, int32_t shift, int32_t* rows_of_wavefront)
+{
+    if (!rows_of_wavefront) return IBERT_ERR_NULL;
+    if (rows < 1 || rows > 0x7fffffffLL) return IBERT_ERR_SHAPE;
+    const int rc = ibert::check_layernorm(C, shift);
+    if (rc) return rc;
+    *rows_of_wavefront = ibert::rows_of_wavefront(rows, C, shift);
+    return IBERT_OK;
 }

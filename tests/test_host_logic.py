@@ -517,6 +517,18 @@ def test_qkv_constants_show_a_wrong_requantization(kind):
             assert (wrong != qkv).any(), name
 
 
+# rows to a wavefront: 16 rows make a workgroup of four, 256 of these a round
+@pytest.mark.parametrize("C_,rows,want", [(768, 1, 1), (768, 3568, 1), (768, 3569, 4), (768, 4096, 4), (768, 4097, 1), (768, 7152, 1), (768, 7153, 4), (768, 8191, 4), (768, 8192, 0),
+                                          (768, 32768, 0), (512, 2544, 1), (512, 2545, 4), (512, 4097, 1), (512, 5104, 1), (512, 5105, 4), (512, 8192, 4), (512, 8193, 4), (512, 32768, 4),
+                                          (1024, 4096, 1), (1024, 8192, 1), (1024, 8193, 0), (1024, 10736, 0), (1024, 10737, 4), (1024, 12288, 4), (1024, 12289, 0), (1024, 32768, 4),
+                                          (256, 4096, 0), (770, 4096, 0), (640, 4096, 0)])
+def test_layernorm_rows_of_a_wavefront(C_, rows, want):
+    got = C.c_int32(-1)
+    for shift, expect in ((14, want), (8, want), (7, 0)):
+        assert B.lib().ibert_layernorm_i16_plan(rows, C_, shift, C.byref(got)) == 0
+        assert got.value == expect, shift
+
+
 # ------------------------------------------------------------------------------------------- buffers that end with the last row
 def test_rows_of_the_persistent_tiles_are_checked_whole_against_the_buffers_end(tmp_path):
     # Output and residual are buffers that end with the last row, so that lanes past it neither load nor store.  The range check takes the
