@@ -56,7 +56,7 @@ __global__ __launch_bounds__(ATT_THREADS) void attention_kernel(AttentionArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if ((int)blockIdx.x >= a.blocks) {
         // (last, one for every unit: the attention's own are on their way by then, and a unit that has some runs these beside them)
-        read_ahead<ATT_THREADS / 64>((uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)att_lds, wave, lane, (int)blockIdx.x - a.blocks);
+        read_ahead<ATT_THREADS / 64, NKB == 1>((uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)att_lds, wave, lane, (int)blockIdx.x - a.blocks);
         return;
     }
     // Workgroups are dealt round-robin to the 8 XCDs.  The query blocks of a head read the same K and V,

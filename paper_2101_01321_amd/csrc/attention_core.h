@@ -76,7 +76,11 @@ __device__ __forceinline__ void make_exp_table(const AttentionArgs& a, uint32_t 
 
 // Workgroups behind the attention's own that read ahead (see ReadAhead), each for its own XCD: 1 KB a request into LDS that nobody reads.  NW:
 // wavefronts of a workgroup; index: of the workgroup among these.  The kernel's first argument is its AttentionArgs.
-template <int NW>
+// UNROLL: all parts of a layer whose steps run apart in one run of code, for attention over one key block.  It is over before a loop, which waits for each part's
+// arguments anew, has asked for its last part, so that the launch waits for those requests.  A loop otherwise: unrolled, its 4 KB stand between the kernel's head and the attention's own
+// code.  Forwards, us, loop / unrolled (a layout of the code alone may be worth 1.5 %): Large 1 x 16 560.6 / 550.9, 1 x 40 605.1 / 591.0, 1 x 64 612.8 / 599.1, 2 x 60 682.6 /
+// 666.7, 4 x 64 806.3 / 794.8, Base 1 x 40 270.7 / 271.5; two key blocks and more, Large 1 x 128 677.1 / 677.2, 4 x 256 1258 / 1273, Base 1 x 128 308.5 / 309.8, 1 x 512 460.2 / 463.9.
+template <int NW, bool UNROLL>
 __device__ __forceinline__ void read_ahead(uint32_t lds0, int wave, int lane, int index)
 {
     const int x = (int)blockIdx.x & 7, first = index >> 3;
@@ -89,11 +93,8 @@ __device__ __forceinline__ void read_ahead(uint32_t lds0, int wave, int lane, in
 #else
     kernel_args ga = nullptr;
 #endif
-    const int wgs = ga->ahead_wgs >> 3, parts = ga->ahead.n;       // (of an XCD)
-    // (Rolled: the attention's own code, which every launch fetches, is that much nearer.  Unrolled for up to six parts against this, forwards, us: Base 2 x 512
-    // 538.8 / 526.4, 1 x 512 474.2 / 466.7, Large 4 x 256 1208 / 1178.)
-#pragma unroll 1
-    for (int r = 0; r < parts; ++r) {
+    const int wgs = ga->ahead_wgs >> 3;                            // (of an XCD)
+    auto part = [&](int r) {
         const auto& q = ga->ahead.part[r];
         const int s = ReadAhead::share(x, q.xs), total = ReadAhead::count(s, q.kb, q.blocks, q.xs);
         for (int k = first * NW + wave; k < total; k += NW * wgs) {
@@ -101,6 +102,14 @@ __device__ __forceinline__ void read_ahead(uint32_t lds0, int wave, int lane, in
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                          :: "s"(dst), "v"((uint32_t)lane * 16u), "s"(src) : "memory", "m0");
         }
+    };
+    if constexpr (UNROLL) {
+#pragma unroll
+        for (int r = 0; r < ReadAhead::APART; ++r) part(r);        // (parts that are not used have no blocks)
+    } else {
+        const int parts = ga->ahead.n;
+#pragma unroll 1
+        for (int r = 0; r < parts; ++r) part(r);
     }
     __builtin_amdgcn_s_waitcnt(0x0f70);                    // (the LDS is given back only when nothing writes to it any more)
 }

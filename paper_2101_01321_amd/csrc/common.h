@@ -165,7 +165,7 @@ struct GemmPlan {
 // us, 24 (12 from FFN 32768 on) layers of hidden 1024, without W_1 and W_2 / with them, 128 tokens and 4096: FFN 16384 (16 MB each)
 // 1057 / 1023, 4677 / 4488; 32768 (32 MB) 676 / 698, 4000 / 3800; 65536 (64 MB) 1080 / 1232, 7540 / 7650.
 struct ReadAhead {
-    static constexpr int MOST = 6;
+    static constexpr int MOST = 6, APART = 4;            // matrices; of a layer whose steps run apart: W_o, W_1, W_2 and the next layer's W_qkv
     static constexpr int64_t MOST_BYTES = 32 << 20;      // of a matrix
     struct Part {
         const int8_t* p;

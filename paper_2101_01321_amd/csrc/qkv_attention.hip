@@ -74,7 +74,7 @@ __global__ __launch_bounds__(64 * NW, 4) void qkv_attention_kernel(QkvAttentionA
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int8_t*)qa_lds;
     if (__builtin_expect((int)blockIdx.x >= a.blocks, 0)) {
-        read_ahead<NW>(lds0, wave, lane, (int)blockIdx.x - a.blocks);
+        read_ahead<NW, false>(lds0, wave, lane, (int)blockIdx.x - a.blocks);
         return;
     }
     int group, h;
