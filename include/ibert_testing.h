@@ -62,8 +62,11 @@ void ibert_qkv_attention_override(int32_t tile);
 
 /* How that kernel deals a layer of heads of 64: *tile as above; IBERT_ERR_NOT_IMPLEMENTED where the choice is to run the steps apart.  places[batch * heads] (zeroed): how often a
  * (sequence, head) is worked on.  readers[3 * heads] (zeroed): bit x is set where XCD x multiplies the head's rows of W_q, W_k, W_v.  ahead[x * 3 H H / 1024 + i] (zeroed): how
- * often XCD x reads the i-th KB of W_qkv ahead when an encoder plans for it (H = 64 heads).  Host only. */
+ * often XCD x reads the i-th KB of W_qkv ahead when an encoder plans for it (H = 64 heads).  The choice is that for a layer called by itself.  Host only. */
 int ibert_qkv_attention_plan(int32_t batch, int32_t seq, int32_t heads, int32_t* tile, uint8_t* places, uint8_t* readers, uint8_t* ahead);
+
+/* The tile that a call of `layers` layers takes where the parameters allow that kernel, 0 where it runs the steps apart; no override.  Host only. */
+int ibert_qkv_attention_chosen(int32_t batch, int32_t seq, int32_t heads, int32_t layers, int32_t* tile);
 
 /* What the XCDs read of W [N, K] (dense rows, K a multiple of 128, N * K of 1024) when this MatMul runs with all operands aligned, and
  * what each reads ahead when an encoder plans for it.  plan: the tile configuration chosen, then rows and xs: XCD x is to have the row

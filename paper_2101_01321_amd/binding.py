@@ -104,6 +104,7 @@ SIGNATURES = {
     "ibert_layernorm_i16_plan": (C.c_int, [C.c_int64, C.c_int32, C.c_int32, C.POINTER(C.c_int32)]),
     "ibert_qkv_attention_override": (None, [C.c_int32]),
     "ibert_qkv_attention_plan": (C.c_int, [C.c_int32] * 3 + [C.POINTER(C.c_int32), _P, _P, _P]),
+    "ibert_qkv_attention_chosen": (C.c_int, [C.c_int32] * 4 + [C.POINTER(C.c_int32)]),
     "ibert_gemm_weight_plan": (C.c_int, [C.POINTER(GemmDesc), C.c_int32, C.POINTER(C.c_int32), _P, _P]),
     "ibert_gemm_gelu_weight_plan": (C.c_int, [C.POINTER(GemmDesc), C.POINTER(GeluParams), C.POINTER(C.c_int32), _P, _P]),
     "ibert_last_kernel": (C.c_char_p, []),

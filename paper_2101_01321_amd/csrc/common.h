@@ -217,9 +217,9 @@ int launch_attention(const int8_t* qkv, int8_t* ctx, int32_t batch, int32_t seq,
                      ibert_dyadic scores_dy, const ibert_softmax_params& sp, ibert_dyadic ctx_dy, hipStream_t stream,
                      const int32_t* key_lens = nullptr, int32_t* scores = nullptr, int8_t* probs = nullptr,
                      const ReadAhead* ahead = nullptr);
-// Steps 1 to 4 as one kernel (qkv_attention.hip): is there one for this problem, and is it the faster way?
+// Steps 1 to 4 as one kernel (qkv_attention.hip): is there one for this problem, and is it the faster way?  alone: for a layer called by itself.
 bool qkv_attention_ok(const int8_t* x, const int8_t* w, const int8_t* ctx, int32_t batch, int32_t seq, int32_t hidden, int32_t heads, const ibert_dyadic& scores_dy,
-                      const ibert_softmax_params& sp, const ibert_dyadic& ctx_dy);
+                      const ibert_softmax_params& sp, const ibert_dyadic& ctx_dy, bool alone);
 int launch_qkv_attention(const int8_t* x, const int8_t* w, const int32_t* bias, const int32_t* mult, const int32_t* shift, int8_t* qkv, int8_t* ctx, int32_t batch,
                          int32_t seq, int32_t hidden, int32_t heads, const ibert_dyadic& scores_dy, const ibert_softmax_params& sp, const ibert_dyadic& ctx_dy,
                          const int32_t* key_lens, const ReadAhead* ahead, hipStream_t stream);

@@ -247,7 +247,7 @@ static int run_layer(const ibert_layer_weights& w, const LayerPlan* plan, const 
     // finds its 85 MB in the memory-side cache from forward to forward and gains little: b1 314 / 312, b8 s61 413 / 409, b32 837 / 834.  (So
     // does a layer called by itself, in a program that cycles through few of them: 177 tokens 27.7 without, 27.9 with.)
     const bool fuse_qkv = fuse_attention && (!keep || attention_whole_blocks(seq)) &&
-                          qkv_attention_ok(x, w.w_qkv, ctx, batch, seq, hidden, heads, q.scores_dy, q.softmax, q.ctx_dy);
+                          qkv_attention_ok(x, w.w_qkv, ctx, batch, seq, hidden, heads, q.scores_dy, q.softmax, q.ctx_dy, plan == nullptr);
     ReadAhead ahead;
     if (plan && fuse_attention && fuse_gelu && half) {
         ahead.add(w.w_o, H, H, plan->o);

@@ -12,7 +12,7 @@
 //   * What bounds it: with two workgroups on a unit the path from L2 while they multiply (40 KB a step in 1600 to 1700 cycles for the two, 50 B/clk), then vector ALU issue.  Cycles,
 //     thousands, 128 rows, K 768, one workgroup on a unit / two: first step there 3.7 / 3.7, five more 6.9 / 7.1 to 9, requantization 2.4 / 3.3, attention 4.2 / 5.0 of 20 / 24 to 30.
 //     Launched apart the two kernels took those cycles, a launch (1.7 us), Q, K, V out and in, and two heads and tails.  Forwards, us: Base b32 811.6 -> 771.3, b8 s61 419.9 -> 410.7, Large
-//     32 x 128 2108 -> 1938; one layer of 256 channels, 4 heads, called by itself 26.5 -> 23.8.
+//     32 x 128 2108 -> 1938; one layer of 256 channels, 4 heads, called by itself 26.4 -> 23.3.
 //   * Tried and not kept: all operands of a step read before its MFMAs (a barrier more, reads and MFMAs one after the other: 1600 cycles a step by itself, 1340 as it is); requests by
 //     half of the wavefronts in front of the MFMAs and by the other half behind them (the same); wave priorities, workgroups of a unit out of step by a sleep (the same);
 //     sixteen wavefronts on two sequences of 128 (equal on one round of tiles, 2 to 4 % behind on more).
@@ -341,7 +341,12 @@ static QkvTile qkv_tile(int32_t batch, int32_t seq, int32_t heads)
 // Is it faster than the MatMul and the attention one after the other?  us a layer, those / this:
 //   * One workgroup multiplies a whole head, by itself on its unit for a long time where there are few: 4 x 12 heads, L = 64 31.3 / 30.7, L = 128 36.1 / 36.7; 1 x 12, L = 128
 //     26.9 / 30.1; 8 x 12, L = 64 35.4 / 34.2, L = 128 41.6 / 42.1; 11 x 12, L = 128 49.7 / 47.5, 16 x 12 52.4 / 48.4, 32 x 12 68.5 / 65.7, 64 x 12 109.5 / 99.2; 16 x 16 68.6 / 64.4,
-//     32 x 16 90.9 / 82.1.  A head of two or three K steps takes little longer than a launch (a layer of 256 with 4 heads, one sequence of 128, called by itself: 26.5 / 23.8).
+//     32 x 16 90.9 / 82.1.
+//   * A head of one to three K steps takes little longer than a launch.  A layer called by itself is ahead anywhere (us, graph and launches one by one: 2 heads 1 x 128 25.3 / 23.2 and 27.5 / 22.2, 4 heads
+//     25.7 / 24.3 and 28.7 / 22.7, 6 heads 27.0 / 26.5 and 28.1 / 23.2, 6 x 128 32.2 / 31.7 and 28.7 / 27.8).  In a forward of several layers the weights come from farther away, and up to eight sequences a
+//     workgroup waits for them longer than the launch takes, by the rows and K steps it has: us a forward of 12 layers, 2 heads 1 x 64 213.1 / 208.0, 1 x 96 224.0 / 225.8, 1 x 128 222.5 / 227.4, 8 x 128 249.3 /
+//     251.1, 9 x 128 258.2 / 258.2, 12 x 128 269.2 / 265.0; 4 heads 1 x 64 222.0 / 219.0, 1 x 65 229.6 / 234.4, 1 x 128 232.2 / 242.0, 8 x 128 306.7 / 314.3, 9 x 70 276.9 / 274.2, 10 x 128 334.8 / 330.6; 6 heads
+//     1 x 32 229.2 / 228.9, 3 x 33 241.8 / 254.0, 3 x 64 266.5 / 267.7, 1 x 128 257.2 / 273.9, 4 x 128 304.4 / 313.4, 8 x 100 342.1 / 345.2, 9 x 100 358.3 / 352.7, 16 x 128 432.3 / 416.6.
 //   * More tokens of a wider model: the persistent MatMul streams, while here the path from L2 bounds the loop (more bytes a product), 256 x 16, L = 128 forwards
 //     of 24 layers 10.0 / 10.2 ms; 64 x 16 3.37 / 3.24.  With 768 channels 256 x 12 311.6 / 296.3.
 //   * 512 workgroups have a place at once, and a few more begin anew behind them, which costs a wide head (more K steps) most: forwards of 24 layers, ms, 32 x 16, L = 128 1.99 / 1.82,
@@ -349,13 +354,14 @@ static QkvTile qkv_tile(int32_t batch, int32_t seq, int32_t heads)
 //   * Rows past the end of a sequence are multiplied too: 512 x 12, L = 40 195.0 / 197.9, L = 16 113.6 / 109.6, but 1024 x 12 173.4 / 178.2; 512 x 16, L = 40 308.6 / 340.6.
 //   * More than 128 tokens take all of a unit, so that whole rounds of units count: 16 x 16, L = 256 95.1 / 86.1, 21 x 12 88.1 / 82.3, L = 192 69.7 / 66.0; 11 x 12, L = 150 50.9 /
 //     51.0; 24 x 12, L = 192 75.3 / 79.6.
-static bool qkv_faster(int32_t batch, int32_t seq, int32_t heads)
+// alone: a layer called by itself.
+static bool qkv_faster(int32_t batch, int32_t seq, int32_t heads, bool alone)
 {
     const int64_t n = (int64_t)batch * heads;
     if (n > 512 && 4 * seq < 3 * qkv_tile(batch, seq, heads).rows()) return false;
     if (seq > 128) return n >= 160 && n <= 256;
     if (heads > 12 && (n > 1024 || (seq > 64 && n > 512 && n < 704))) return false;
-    return n >= (seq > 64 ? 128 : 96) || heads <= 6;
+    return n >= (seq > 64 ? 128 : 96) || (heads <= 6 && (alone || batch > 8 || seq + 16 * heads <= 128));
 }
 
 // (Buffers of W_qkv below 2 GiB, and sums of products below 2^30, which the kernel's fast requantizations take for granted.)
@@ -363,12 +369,12 @@ constexpr int32_t QA_MAX_HIDDEN = 1 << 13;
 static_assert((int64_t)QA_MAX_HIDDEN * 128 * 128 < (1 << 30) && (int64_t)3 * QA_MAX_HIDDEN * QA_MAX_HIDDEN < 0x7fffffff, "widths");
 
 bool qkv_attention_ok(const int8_t* x, const int8_t* w, const int8_t* ctx, int32_t batch, int32_t seq, int32_t hidden, int32_t heads, const ibert_dyadic& scores_dy,
-                      const ibert_softmax_params& sp, const ibert_dyadic& ctx_dy)
+                      const ibert_softmax_params& sp, const ibert_dyadic& ctx_dy, bool alone)
 {
     if (seq > 256 || hidden != heads * ATT_DH || hidden % 128 != 0 || hidden > QA_MAX_HIDDEN || (int64_t)batch * heads > (1 << 24) || !aligned(x, 16) || !aligned(w, 16) ||
         !aligned(ctx, 4))
         return false;
-    if (g_qkv_override == 0 || (g_qkv_override < 0 && !qkv_faster(batch, seq, heads)) || seq > qkv_tile(batch, seq, heads).rows()) return false;
+    if (g_qkv_override == 0 || (g_qkv_override < 0 && !qkv_faster(batch, seq, heads, alone)) || seq > qkv_tile(batch, seq, heads).rows()) return false;
     AttentionArgs a;
     return attention_args(a, nullptr, batch, seq, heads, scores_dy, sp, ctx_dy, nullptr, nullptr, false) >= 3;
 }
@@ -442,7 +448,7 @@ extern "C" int ibert_qkv_attention_plan(int32_t batch, int32_t seq, int32_t head
     if (batch < 1 || seq < 1 || seq > 256 || heads < 2 || heads % 2) return IBERT_ERR_SHAPE;
     const QkvTile t = qkv_tile(batch, seq, heads);
     *tile = t.code();
-    if (g_qkv_override < 0 && !qkv_faster(batch, seq, heads)) return IBERT_ERR_NOT_IMPLEMENTED;
+    if (g_qkv_override < 0 && !qkv_faster(batch, seq, heads, true)) return IBERT_ERR_NOT_IMPLEMENTED;
     QkvAttentionArgs g;
     g.att.heads = heads;
     const int64_t blocks = qkv_deal(g, batch, seq, heads, t.seqs);
@@ -469,5 +475,14 @@ extern "C" int ibert_qkv_attention_plan(int32_t batch, int32_t seq, int32_t head
             }
         }
     }
+    return IBERT_OK;
+}
+
+extern "C" int ibert_qkv_attention_chosen(int32_t batch, int32_t seq, int32_t heads, int32_t layers, int32_t* tile)
+{
+    using namespace ibert;
+    if (!tile) return IBERT_ERR_NULL;
+    if (batch < 1 || seq < 1 || heads < 2 || heads % 2 || layers < 1) return IBERT_ERR_SHAPE;
+    *tile = seq <= 256 && qkv_faster(batch, seq, heads, layers == 1) ? qkv_tile(batch, seq, heads).code() : 0;
     return IBERT_OK;
 }

@@ -517,6 +517,20 @@ def test_qkv_constants_show_a_wrong_requantization(kind):
             assert (wrong != qkv).any(), name
 
 
+# few heads: a layer by itself anywhere; in a forward of several, up to eight sequences only where rows and K steps are few
+@pytest.mark.parametrize("batch,seq,heads,tile", [(1, 96, 2, 8314), (1, 97, 2, 0), (8, 128, 2, 0), (9, 128, 2, 8414), (1, 64, 4, 8214), (1, 65, 4, 0), (1, 128, 4, 0), (8, 128, 4, 0), (9, 65, 4, 8314),
+                                                  (1, 32, 6, 8114), (1, 33, 6, 0), (8, 64, 6, 0), (9, 33, 6, 8214), (8, 61, 12, 8214), (32, 128, 12, 8412), (1, 128, 12, 0), (1, 257, 2, 0), (8, 200, 2, 0)])
+def test_qkv_attention_of_few_heads_in_a_forward_of_several_layers(batch, seq, heads, tile):
+    got = C.c_int32()
+    for layers in (2, 12):
+        assert B.lib().ibert_qkv_attention_chosen(batch, seq, heads, layers, C.byref(got)) == 0
+        assert got.value == tile, layers
+    assert B.lib().ibert_qkv_attention_chosen(batch, seq, heads, 1, C.byref(got)) == 0
+    rc, alone, *_ = _qkv_plan(batch, min(seq, 256), heads)
+    assert got.value == (alone if rc == 0 and seq <= 256 else 0)
+    assert not (heads <= 6 and seq <= 128) or got.value
+
+
 # rows to a wavefront: 16 rows make a workgroup of four, 256 of these a round
 @pytest.mark.parametrize("C_,rows,want", [(768, 1, 1), (768, 3568, 1), (768, 3569, 4), (768, 4096, 4), (768, 4097, 1), (768, 7152, 1), (768, 7153, 4), (768, 8191, 4), (768, 8192, 0),
                                           (768, 32768, 0), (512, 2544, 1), (512, 2545, 4), (512, 4097, 1), (512, 5104, 1), (512, 5105, 4), (512, 8192, 4), (512, 8193, 4), (512, 32768, 4),
