@@ -348,12 +348,16 @@ static QkvTile qkv_tile(int32_t batch, int32_t seq, int32_t heads)
 //     251.1, 9 x 128 258.2 / 258.2, 12 x 128 269.2 / 265.0; 4 heads 1 x 64 222.0 / 219.0, 1 x 65 229.6 / 234.4, 1 x 128 232.2 / 242.0, 8 x 128 306.7 / 314.3, 9 x 70 276.9 / 274.2, 10 x 128 334.8 / 330.6; 6 heads
 //     1 x 32 229.2 / 228.9, 3 x 33 241.8 / 254.0, 3 x 64 266.5 / 267.7, 1 x 128 257.2 / 273.9, 4 x 128 304.4 / 313.4, 8 x 100 342.1 / 345.2, 9 x 100 358.3 / 352.7, 16 x 128 432.3 / 416.6.
 //   * More tokens of a wider model: the persistent MatMul streams, while here the path from L2 bounds the loop (more bytes a product), 256 x 16, L = 128 forwards
-//     of 24 layers 10.0 / 10.2 ms; 64 x 16 3.37 / 3.24.  With 768 channels 256 x 12 311.6 / 296.3.
+//     of 24 layers 10.0 / 10.2 ms; 64 x 16 3.37 / 3.24.  With 768 channels 256 x 12 311.6 / 296.3.  (Between 1024 workgroups and 4096 the two are mostly equal: forwards of 8 layers, us, 72 x 16 1336 / 1320,
+//     80 x 16 1373 / 1351, 96 x 16 1486 / 1473, 128 x 16 1788 / 1783, 160 x 16 2453 / 2439, but 192 x 16 2815 / 2702: the line could lie higher.)
 //   * 512 workgroups have a place at once, and a few more begin anew behind them, which costs a wide head (more K steps) most: forwards of 24 layers, ms, 32 x 16, L = 128 1.99 / 1.82,
-//     33 x 16 2.71 / 2.78, 39 x 16 2.79 / 2.85, 44 x 16 3.04 / 2.91, 48 x 16 3.11 / 3.00, 52 x 16 3.27 / 3.24; 12 layers of 768 43 x 12 1.106 / 1.100, 48 x 12 1.119 / 1.113.
-//   * Rows past the end of a sequence are multiplied too: 512 x 12, L = 40 195.0 / 197.9, L = 16 113.6 / 109.6, but 1024 x 12 173.4 / 178.2; 512 x 16, L = 40 308.6 / 340.6.
+//     33 x 16 2.71 / 2.78, 39 x 16 2.79 / 2.85, 44 x 16 3.04 / 2.91, 48 x 16 3.11 / 3.00, 52 x 16 3.27 / 3.24; 12 layers of 768 43 x 12 1.106 / 1.100, 48 x 12 1.119 / 1.113.  Of 8 layers, us: 39 x 16 903 / 919,
+//     41 x 16 928 / 932, 42 x 16 920 / 917, 43 x 16 979 / 943: the kernel is ahead from 688 workgroups on, 16 before the line.
+//   * Rows past the end of a sequence are multiplied too: 512 x 12, L = 40 195.0 / 197.9, L = 16 113.6 / 109.6, but 1024 x 12 173.4 / 178.2; 512 x 16, L = 40 308.6 / 340.6.  Up to 512 (sequence, head) pairs, where tiles
+//     of 64 rows begin, it is even: forwards of 6 layers, us, 22 x 12, L = 33 231.9 / 232.9, 24 x 12 234.7 / 232.7, 42 x 12 280.7 / 270.4; 24 layers, 17 x 16 1035 / 1043, 20 x 16 1053 / 1052, 24 x 16 1069 / 1065.  (Short
+//     sequences of two or four heads beyond 512 would be ahead, 6 layers: 1000 x 2, L = 20 322 / 290, 700 x 2, L = 40 348 / 341, but 700 x 6 728 / 756.)
 //   * More than 128 tokens take all of a unit, so that whole rounds of units count: 16 x 16, L = 256 95.1 / 86.1, 21 x 12 88.1 / 82.3, L = 192 69.7 / 66.0; 11 x 12, L = 150 50.9 /
-//     51.0; 24 x 12, L = 192 75.3 / 79.6.
+//     51.0; 24 x 12, L = 192 75.3 / 79.6.  At 160 pairs, us a forward of 6 layers: 10 x 16, L = 129 375.6 / 377.4, L = 256 445.9 / 428.8; 20 x 8, L = 129 301.5 / 297.6; 40 x 4 270.3 / 273.9, L = 193 297.2 / 286.5.
 // alone: a layer called by itself.
 static bool qkv_faster(int32_t batch, int32_t seq, int32_t heads, bool alone)
 {
